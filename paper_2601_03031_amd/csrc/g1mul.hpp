@@ -4,7 +4,7 @@
 // (0 <= d0, d1 < 4) and one program of two doublings plus an addition per 2-bit window
 // (two doublings alone for a zero window).  Additions that meet equal x-coordinates
 // (H = 0) are resolved exactly: equal points are doubled, opposite points give the
-// identity.  The control code is shared by the device (DevCtx) and the host model (HostCtx).
+// identity.  The windows' programs run as one list of calls.  The control code is shared by the device (DevCtx) and the host model (HostCtx).
 #pragma once
 #include "slp.hpp"
 #include "glv.hpp"
@@ -87,31 +87,30 @@ __host__ __device__ inline bool mul_add(Ctx &c, const glv::Dec &dec, bool pinf, 
     }
     c.sync();
     c.run(slp::PROG_G1_TABLE, 0, 0, 0);
-    int w = (int)(dec.nbits + 1) / 2 - 1;
-    copy3(c, slp::G1_T_0, slp::G1_TB1_0 + 3 * ((int)glv::digit2(dec, (uint32_t)w) - 1));
-    for (w = w - 1; w >= 0; w--) {
-      uint32_t d = glv::digit2(dec, (uint32_t)w);
-      if (!d) {
-        if (!inf) c.run(slp::PROG_G1_DBL2, 0, 0, 0);
-        continue;
-      }
-      int tb = slp::G1_TB1_0 + 3 * ((int)d - 1);
-      if (inf) {
-        copy3(c, slp::G1_T_0, tb);
-        inf = false;
-        continue;
-      }
-      c.run(slp::PROG_G1_DBL2_ADD, 0, tb, 0);
+    const int W = (int)(dec.nbits + 1) / 2 - 1;  // windows below the top one, a call each
+    copy3(c, slp::G1_T_0, slp::G1_TB1_0 + 3 * ((int)glv::digit2(dec, (uint32_t)W) - 1));
+    for (int e = c.lane(); e < W; e += c.lanes()) {
+      const int d = (int)glv::digit2(dec, (uint32_t)(W - 1 - e));
+      c.cl[e] = d ? slp::call(slp::PROG_G1_DBL2_ADD, 0, slp::G1_TB1_0 + 3 * (d - 1), 0)
+                  : slp::call(slp::PROG_G1_DBL2, 0, 0, 0);
+    }
+    for (int e = 0; e < W;) {
+      e = c.run_list(e, W, slp::G1_H, 1);
+      if (e >= 0) break;
+      e = -e;  // stopped after call e - 1, whose H looked like zero
       bool dbl;
-      if (add_degenerate(c, dbl)) {
-        c.sync();
-        if (dbl) {
-          copy3(c, slp::G1_T_0, tb);
-          c.run(slp::PROG_G1_DBL, 0, 0, 0);
-        } else {
-          inf = true;
-        }
+      if (!add_degenerate(c, dbl)) continue;
+      c.sync();
+      const int tb = slp::call_y(c.cl[e - 1]);
+      if (dbl) {
+        copy3(c, slp::G1_T_0, tb);
+        c.run(slp::PROG_G1_DBL, 0, 0, 0);
+        continue;
       }
+      // T is the identity: the doublings do nothing until the next table entry
+      while (e < W && slp::call_is(c.cl[e], slp::PROG_G1_DBL2)) e++;
+      if (e == W) inf = true;
+      else copy3(c, slp::G1_T_0, slp::call_y(c.cl[e++]));
     }
   }
   if (has_a) add_affine(c, inf, abase, one);

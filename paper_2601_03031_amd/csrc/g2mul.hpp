@@ -2,8 +2,9 @@
 // k = sum_j k_j lam^j, the signed bases B_j = sign(k_j) psi^j(Q), a table of the 15
 // subset sums, and one doubling plus at most one table addition per bit of max |k_j|
 // (65 bits).  Additions that meet equal x-coordinates (H = 0) are resolved exactly:
-// equal points are doubled, opposite points give the identity.  The control code is
-// shared by the device (DevCtx, all lanes of the workgroup) and the host model (HostCtx).
+// equal points are doubled, opposite points give the identity.  The bits' programs run as one
+// list of calls.  The control code is shared by the device (DevCtx, all lanes of the workgroup)
+// and the host model (HostCtx).
 #pragma once
 #include "slp.hpp"
 #include "gls.hpp"
@@ -18,16 +19,10 @@ __host__ __device__ inline bool zero29(const f29 &x) {
   return t == 0;
 }
 
-// p - x for an almost-reduced x (result in (0, p])
+// -x (limbs are signed)
 __host__ __device__ inline f29 neg29(const f29 &x) {
-  f29 c = slp::canon29(x), o;
-  int64_t bw = 0;
-  for (int j = 0; j < 9; j++) {
-    int64_t v = (int64_t)slp::P29[j] - c.l[j] + bw;
-    o.l[j] = (uint32_t)v & SLP_M29;
-    bw = v >> 29;
-  }
-  o.l[9] = o.l[10] = o.l[11] = 0;
+  f29 o;
+  for (int j = 0; j < 12; j++) o.l[j] = 0u - x.l[j];
   return o;
 }
 
@@ -107,29 +102,28 @@ __host__ __device__ inline bool mul_add(Ctx &c, const gls::Dec &dec, bool qinf, 
     }
     c.sync();
     c.run(slp::PROG_G2_TABLE, 0, 0, 0);
-    int t = (int)dec.nbits - 1;
-    copy_slots(c, slp::G2_T_0, slp::G2_TB1_0 + 6 * ((int)gls::digit(dec, (uint32_t)t) - 1), 6);
-    for (t = t - 1; t >= 0; t--) {
-      if (!inf) c.run(slp::PROG_G2_DBL, 0, 0, 0);
-      uint32_t d = gls::digit(dec, (uint32_t)t);
-      if (!d) continue;
-      int tb = slp::G2_TB1_0 + 6 * ((int)d - 1);
-      if (inf) {
-        copy_slots(c, slp::G2_T_0, tb, 6);
-        inf = false;
+    const int n = (int)dec.nbits - 1;  // bits below the top one, a call each
+    copy_slots(c, slp::G2_T_0, slp::G2_TB1_0 + 6 * ((int)gls::digit(dec, (uint32_t)n) - 1), 6);
+    for (int e = c.lane(); e < n; e += c.lanes()) {
+      const int d = (int)gls::digit(dec, (uint32_t)(n - 1 - e));
+      c.cl[e] = d ? slp::call(slp::PROG_G2_DBL_ADD, 0, slp::G2_TB1_0 + 6 * (d - 1)) : slp::call(slp::PROG_G2_DBL);
+    }
+    for (int e = 0; e < n;) {
+      e = c.run_list(e, n, slp::G2_H_0, 2);
+      if (e >= 0) break;
+      e = -e;  // stopped after call e - 1, whose H looked like zero
+      bool dbl;
+      if (!add_degenerate(c, dbl)) continue;
+      c.sync();
+      if (dbl) {
+        copy_slots(c, slp::G2_T_0, slp::call_y(c.cl[e - 1]), 6);
+        c.run(slp::PROG_G2_DBL, 0, 0, 0);
         continue;
       }
-      c.run(slp::PROG_G2_ADD, 0, tb, 0);
-      bool dbl;
-      if (add_degenerate(c, dbl)) {
-        c.sync();
-        if (dbl) {
-          copy_slots(c, slp::G2_T_0, tb, 6);
-          c.run(slp::PROG_G2_DBL, 0, 0, 0);
-        } else {
-          inf = true;
-        }
-      }
+      // T is the identity: the doublings do nothing until the next table entry
+      while (e < n && slp::call_is(c.cl[e], slp::PROG_G2_DBL)) e++;
+      if (e == n) inf = true;
+      else copy_slots(c, slp::G2_T_0, slp::call_y(c.cl[e++]), 6);
     }
   }
   if (has_a) add_affine(c, inf, abase, one, zero);

@@ -1,18 +1,17 @@
 """Generate slp_progs.hpp: straight-line programs (SLPs) over F_p for the
-wave-cooperative engine in slp.hpp.
+workgroup-cooperative engine in slp.hpp.
 
 A program is a dataflow graph of base-field operations, produced by running the
 formulas of the BN254 tower, the twist and the pairing on tracer values.  The
-scheduler packs it into levels of at most 64 independent operations; one wavefront
-executes a level per step, lane t doing the t-th operation of the level.
-Operations:
-  MUL  dst = a * b                                  (Montgomery product)
-  LIN  dst = ka * a + sb * b + sc * c  (mod p)      ka in [-15, 15], sb, sc in {-1, 0, 1}
+scheduler packs it into levels of independent operations; a workgroup executes a level
+per step, a pair of lanes per operation (32 operations per wavefront).  Operations:
+  MUL  dst = (sum_i k_i x_i) (sum_i l_i y_i)        (Montgomery product; a lane per factor)
+  LIN  dst = sum_i k_i x_i  (mod p)                 (half of the terms per lane)
 Linear combinations are kept symbolic by the tracer and materialised only where a
 product or an output needs them, so chains of additions fuse into few LIN operations.
-Slots are 32-byte field elements in LDS.  An operand field holds a 3-bit segment and
-a 9-bit offset: segment 0 is absolute, segments 1..7 are bases the caller sets before
-running a relocatable program.
+Slots are field elements in LDS.  An operand names a 2-bit segment and a 9-bit offset:
+segment 0 is absolute, segments 1..3 are bases the caller sets before running a
+relocatable program.
 
 Programs:
   * Miller-loop bodies for the optimal ate pairing, software-pipelined: the T-chain
@@ -37,15 +36,15 @@ U = 0x44E992B44A6909F1
 P = 36 * U**4 + 36 * U**3 + 24 * U**2 + 6 * U + 1
 R = 36 * U**4 + 36 * U**3 + 18 * U**2 + 6 * U + 1
 RMONT = 1 << 256
-LANES = 64
+WAVE_OPS = 32          # operations of a level that one wavefront executes
 KMAX = 127
 
 OP_NOP, OP_MUL, OP_LIN = 0, 1, 2
 
 
 # ============================================================================ tracer
-ENC_NTERM = 16  # term positions of an encoded operation
-ENC_SIDE = 8    # a product's second factor starts at this term position
+LANE_TERMS = (2, 4, 6, 10, 14)  # terms that a lane sums (padded up to one of these; a record is
+                                # whole groups of four words, two of them head and chain)
 # Trace-time limits (set per program by build_all from TRACE_LIMITS): terms of a linear
 # operation and terms of one factor of a product
 NTERM = 16
@@ -656,6 +655,8 @@ def fe_programs():
         progs[name] = p
 
     mk("f12_mul", lambda X, Y: X.mul(Y), 2)
+    mk("f12_sqr", lambda X: X.sqr(), 1)
+    mk("f12_sqr_mul", lambda X, Y: X.sqr().mul(Y), 2)
     mk("f12_csqr", cyclo_sqr, 1)
     mk("f12_csqr_mul", lambda X, Y: cyclo_sqr(X).mul(Y), 2)
     # (the conjugate is the inverse in the cyclotomic subgroup: its sign changes fold into
@@ -950,6 +951,12 @@ def g2_programs():
     p = Prog("g2_dbl")
     jac_out(p, "T", j_dbl(jac_in(p, "T")))
     progs[p.name] = p
+    p = Prog("g2_dbl_add")
+    T, H, r = j_add(j_dbl(jac_in(p, "T")), jac_in(p, "A"))
+    jac_out(p, "T", T)
+    f2_out(p, "H", H)
+    f2_out(p, "RR", r)
+    progs[p.name] = p
     p = Prog("g2_add")
     T, H, r = j_add(jac_in(p, "T"), jac_in(p, "A"))
     jac_out(p, "T", T)
@@ -1067,40 +1074,97 @@ def operands(v):
     return ()
 
 
-# Cost of a level in cycles of the interpreter (one wavefront): a fixed part, a part per
-# group of four term positions loaded (the union over the level's operations) and the
-# Montgomery product of a level with products (measured on gfx950).
-LEVEL_BASE, LEVEL_GROUP, LEVEL_MUL = 880, 430, 1310
+# Cost of a level in ns of the interpreter (measured on gfx950): a fixed part, a part per
+# term of the longest lane record, the Montgomery product of a level with products.
+LEVEL_BASE, LEVEL_TERM, LEVEL_MUL = 240, 26, 410
 
 
-def op_groups(v):
-    """term groups an operation's encoding uses (see encode_op)"""
+def lane_terms(v):
+    """terms of an operation's longer lane record (before padding)"""
     if v[0] == "mul":
-        na, nb = len(v[1]), len(v[2])
-        return ((1 << -(-na // 4)) - 1) | (((1 << -(-nb // 4)) - 1) << 2)
-    return (1 << -(-len(v[1]) // 4)) - 1
+        return max(len(v[1]), len(v[2]))
+    return -(-len(v[1]) // 2)
+
+
+def pad_terms(n):
+    return next(t for t in LANE_TERMS if n <= t)
 
 
 def levels_cost(p, levels):
     c = 0
     for ops in levels:
-        gm = 0
-        mul = False
-        for i in ops:
-            gm |= op_groups(p.vals[i])
-            mul = mul or p.vals[i][0] == "mul"
-        c += LEVEL_BASE + LEVEL_GROUP * bin(gm).count("1") + (LEVEL_MUL if mul else 0)
+        t = max(pad_terms(lane_terms(p.vals[i])) for i in ops)
+        mul = any(p.vals[i][0] == "mul" for i in ops)
+        c += LEVEL_BASE + LEVEL_TERM * t + (LEVEL_MUL if mul else 0)
     return c
 
 
-def schedule(p, lanes=LANES):
-    """The cheaper of the two stage schedules below (as early / as late as possible)."""
-    a = schedule_phases(p, lanes, late=False)
-    b = schedule_phases(p, lanes, late=True)
-    return b if levels_cost(p, b[0]) <= levels_cost(p, a[0]) else a
+def schedule(p, lanes):
+    """The cheapest of the stage schedules below (as early / as late as possible) and the
+    list schedules."""
+    cand = [schedule_phases(p, lanes, late=False), schedule_phases(p, lanes, late=True)]
+    cand += [schedule_list(p, lanes, bias) for bias in (0, 100, 200, 300, -150)]
+    return min(cand, key=lambda c: levels_cost(p, c[0]))
 
 
-def schedule_phases(p, lanes=LANES, late=False):
+def schedule_list(p, lanes, bias=0):
+    """List scheduling by the longest remaining path (products and additions weighted by the
+    cost of their levels).  A level either runs every ready operation, or additions alone:
+    the latter when the additions lead the critical path and the products can wait for a
+    shorter level (bias shifts that choice)."""
+    vals = p.vals
+    n = len(vals)
+    live = [False] * n
+    stack = list(p.outputs.values())
+    while stack:
+        i = stack.pop()
+        if live[i]:
+            continue
+        live[i] = True
+        stack.extend(operands(vals[i]))
+    is_op = [live[i] and vals[i][0] in ("mul", "lin") for i in range(n)]
+    wl = LEVEL_BASE + 4 * LEVEL_TERM
+    wm = wl + LEVEL_MUL
+    h = [0] * n
+    users = [[] for _ in range(n)]
+    need = [0] * n
+    for i in range(n):
+        if is_op[i]:
+            for a in set(operands(vals[i])):
+                if is_op[a]:
+                    users[a].append(i)
+                    need[i] += 1
+    for i in reversed(range(n)):
+        if is_op[i]:
+            h[i] = (wm if vals[i][0] == "mul" else wl) + max([h[u] for u in users[i]] + [0])
+    ready = [i for i in range(n) if is_op[i] and need[i] == 0]
+    levels = []
+    level_of = [-1] * n
+    while ready:
+        muls = sorted((i for i in ready if vals[i][0] == "mul"), key=lambda i: (-h[i], i))
+        lins = sorted((i for i in ready if vals[i][0] == "lin"), key=lambda i: (-h[i], i))
+        hm = h[muls[0]] if muls else -1
+        hl = h[lins[0]] if lins else -1
+        if muls and (not lins or max(hm, hl - wl + wm) < max(hl, hm + wl) + bias):
+            pick = sorted(muls + lins, key=lambda i: (-h[i], i))[:lanes]
+        else:
+            pick = lins[:lanes]
+        if not pick:
+            pick = muls[:lanes]
+        L = len(levels)
+        levels.append(sorted(pick))
+        for i in pick:
+            level_of[i] = L
+        ready = [i for i in ready if level_of[i] < 0]
+        for i in pick:
+            for u in users[i]:
+                need[u] -= 1
+                if need[u] == 0:
+                    ready.append(u)
+    return levels, level_of, live
+
+
+def schedule_phases(p, lanes, late=False):
     """Stage scheduling: a product's stage is its multiplicative depth (products on the
     longest path from the inputs), so all products of one depth share one level (split
     only beyond the lane count).  Additions run in a phase between two product levels,
@@ -1174,10 +1238,12 @@ def schedule_phases(p, lanes=LANES, late=False):
     return levels, level_of, live
 
 
-def compile_prog(p, io_slot, const_slot, temp_base, temp_limit, lanes=LANES):
+def compile_prog(p, io_slot, const_slot, temp_base, temp_limit, lanes):
     """Schedule p and assign slots.  io_slot(name) gives the encoded slot of an input or
     output name (an output with the name of an input replaces it), const_slot(x) the slot
-    of a constant.  Returns (levels of encoded op tuples, highest temp slot used + 1)."""
+    of a constant.  Returns (levels of encoded op tuples, highest temp slot used + 1).
+    The wavefronts of a level run apart: an operation never writes a slot that an operation
+    of the same level reads."""
     levels, level_of, live = schedule(p, lanes)
     vals = p.vals
     n = len(vals)
@@ -1209,12 +1275,12 @@ def compile_prog(p, io_slot, const_slot, temp_base, temp_limit, lanes=LANES):
         L = level_of[i]
         keep = []
         for rl, s in busy:
-            (free if rl <= L else keep).append(s if rl <= L else (rl, s))
+            (free if rl < L else keep).append(s if rl < L else (rl, s))
         busy = keep
         names = outs.get(i, [])
         # write in place when this is the only output of the value and the slot's entry
         # value is not read after this level
-        if len(names) == 1 and held_read.get(io_slot(names[0]), -1) <= L:
+        if len(names) == 1 and held_read.get(io_slot(names[0]), -1) < L:
             slot[i] = io_slot(names[0])
             continue
         if not free:
@@ -1237,16 +1303,25 @@ def compile_prog(p, io_slot, const_slot, temp_base, temp_limit, lanes=LANES):
         for i in ops:
             v = vals[i]
             if v[0] == "mul":
-                za = (const_slot(0), 0)
-                ta = tuple((slot[k], c) for k, c in v[1]) + (za,) * (ENC_SIDE - len(v[1]))
-                row.append((OP_MUL, slot[i], ENC_SIDE, ta + tuple((slot[k], c) for k, c in v[2])))
+                row.append((OP_MUL, slot[i], len(v[1]), tuple((slot[k], c) for k, c in v[1] + v[2])))
             else:
                 row.append((OP_LIN, slot[i], len(v[1]), tuple((slot[k], c) for k, c in v[1])))
         enc.append(row)
+    # copies of inputs and constants share the last level, where its operations do not read
+    # their destinations; the others follow in a level of their own
+    early = [(nm, v) for nm, v in copies if level_of[v] < 0 and enc and held_read.get(io_slot(nm), -1) < nlev - 1]
+    early = early[:max(0, lanes - len(enc[-1]))] if enc else []
+    if early:
+        enc[-1] = enc[-1] + [(OP_LIN, io_slot(nm), 1, ((slot[v], 1),)) for nm, v in early]
+        copies = [c for c in copies if c not in early]
     if copies:
         row = [(OP_LIN, io_slot(nm), 1, ((slot[v], 1),)) for nm, v in copies]
         for k in range(0, len(row), lanes):
             enc.append(row[k:k + lanes])
+    for row in enc:
+        reads = set(s_ for op in row for s_, c in op[3] if c)
+        writes = [op[1] for op in row]
+        assert len(set(writes)) == len(writes) and not reads & set(writes), p.name
     return enc, used
 
 
@@ -1254,8 +1329,10 @@ def compile_prog(p, io_slot, const_slot, temp_base, temp_limit, lanes=LANES):
 class Kernel:
     """programs that share one LDS slot map: named state slots, constants, temps"""
 
-    def __init__(self, name, progs, state, segs=None, lanes=LANES):
+    def __init__(self, name, progs, state, segs=None, waves=2):
         self.name = name
+        self.waves = waves
+        lanes = WAVE_OPS * waves
         self.state = {nm: i for i, nm in enumerate(state)}
         self.segs = segs or {}
         consts = sorted(set(x for p in progs.values() for x in p.consts) | {0, 1})
@@ -1281,43 +1358,97 @@ class Kernel:
         return self.state[name]
 
 
-def encode_op(op):
-    """384-bit op: kind (2) | dst (12) | group mask (4) | 16 x (slot 12 | coefficient 8,
-    two's complement); a product multiplies the sum of terms [0, 8) by the sum of terms
-    [8, 16); unused terms have slot 0 and coefficient 0.  The mask has bit g set when
-    some operation of the level uses a term in positions 4g .. 4g + 3 (uniform over the
-    level)."""
-    kind, dst, gmask, terms = op
-    assert 0 <= dst < 4096 and len(terms) <= ENC_NTERM and 0 <= gmask < 16
-    # the interpreter adds 65536 p to each factor (or the sum): the scaled coefficient
-    # magnitudes must stay below 32768 so that the sum is positive (slots are below 2p)
+def encode_term(s, c):
+    """32-bit term: offset of the slot in its segment in 16-byte units (bits 0..10; a slot is
+    48 bytes), signed coefficient (bits 11..23), segment (bits 30..31)"""
+    assert 0 <= s < 2048 and -4096 <= c < 4096
+    return (3 * (s & 511)) | ((c & 0x1fff) << 11) | ((s >> 9) << 30)
+
+
+def lane_records(op):
+    """the two lanes' records of an operation: kind, destination (encoded as a term, the kind
+    in place of the coefficient) and the terms.  A product's first factor is scaled by 32,
+    which turns the radix-2^261 Montgomery product into the R = 2^256 one; a sum's terms are
+    dealt to both lanes."""
+    kind, dst, na, terms = op
     if kind == OP_MUL:
-        assert 32 * sum(abs(c) for _, c in terms[:ENC_SIDE]) < 32768 and sum(abs(c) for _, c in terms[ENC_SIDE:]) < 32768
+        A, B = [(s, 32 * c) for s, c in terms[:na]], list(terms[na:])
     else:
-        assert sum(abs(c) for _, c in terms) < 32768
-    x = kind | (dst << 2) | (gmask << 14)
-    for i, (s, c) in enumerate(terms):
-        assert 0 <= s < 4096 and -KMAX <= c <= KMAX
-        x |= ((s | ((c & 255) << 12)) << (18 + 20 * i))
-    return x
+        A, B = list(terms[0::2]), list(terms[1::2])
+    # columns and quotients of the interpreter are bounded for coefficient magnitudes that add up
+    # to less than 2^15
+    assert sum(abs(c) for _, c in A) < 32768 and sum(abs(c) for _, c in B) < 32768
+    head = encode_term(dst, kind)
+    return [[head] + [encode_term(s, c) for s, c in t] for t in (A, B)]
 
 
-def term_groups(op):
-    """bit g set when op has a nonzero coefficient in term positions 4g .. 4g + 3"""
-    m = 0
-    for i, (_, c) in enumerate(op[3]):
-        if c:
-            m |= 1 << (i // 4)
-    return m
+def level_blocks(row, waves):
+    """the operations of a level dealt to the wavefronts: products first (most terms first),
+    then the sums, those in wavefronts of their own while there are any; returns a list of
+    operations for each wavefront"""
+    def nt(op):
+        return max(op[2], len(op[3]) - op[2]) if op[0] == OP_MUL else -(-len(op[3]) // 2)
+    muls = sorted((op for op in row if op[0] == OP_MUL), key=nt, reverse=True)
+    lins = sorted((op for op in row if op[0] == OP_LIN), key=nt, reverse=True)
+    wm, wl = -(-len(muls) // WAVE_OPS), -(-len(lins) // WAVE_OPS)
+    out = [[] for _ in range(waves)]
+    if muls and lins and wm + wl <= waves:
+        for k, op in enumerate(muls):
+            out[k // WAVE_OPS].append(op)
+        for k, op in enumerate(lins):
+            out[wm + k // WAVE_OPS].append(op)
+    else:
+        for k, op in enumerate(muls + lins):
+            out[k // WAVE_OPS].append(op)
+    return out
 
 
-OP_WORDS = 6
+class OpTable:
+    """The wavefronts' operations of all levels ("blocks").  A block is a record per lane: head,
+    the descriptor of the wavefront's next level (0 at the program's end), the terms, padded to
+    groups of four words.  Groups lie 64 lanes apart (1 KB), so that a fetch is one 16-byte load
+    per group at fixed offsets; blocks of the same number of groups share a row of 64 lanes.
+    A block without operations still has one record, for the next descriptor.
+
+    A descriptor: bits 0..17 offset of the block in units of four words, 18 (in a call's first
+    descriptors) a checked addition, 19 / 20 / 21 / 22 more than 2 / 4 / 6 / 10 terms, 23 any
+    term or destination in segments 1..3, 24..29 operations, 30 any product, 31 any sum."""
+
+    def __init__(self):
+        self.words = [0] * 256       # row 0 is not used: no descriptor is 0
+        self.rows = {}               # groups -> [first word of the open row, lanes taken]
+
+    def add(self, ops, nxt):
+        recs = [r for op in ops for r in lane_records(op)] or [[0]]
+        T = pad_terms(max(len(r) - 1 for r in recs))
+        G = (T + 2 + 3) // 4
+        row = self.rows.get(G)
+        if row is None or row[1] + len(recs) > 64:
+            row = self.rows[G] = [len(self.words), 0]
+            self.words += [0] * (256 * G)
+        base = row[0] + 4 * row[1]
+        row[1] += len(recs)
+        for l, r in enumerate(recs):
+            r = [r[0], nxt] + r[1:] + [0] * (4 * G - 1 - len(r))
+            for g in range(G):
+                self.words[base + 256 * g + 4 * l:base + 256 * g + 4 * l + 4] = r[4 * g:4 * g + 4]
+        d = base // 4
+        assert base % 4 == 0 and d < 1 << 18 and len(ops) <= WAVE_OPS
+        d |= (T > 2) << 19 | (T > 4) << 20 | (T > 6) << 21 | (T > 10) << 22
+        d |= any(s_ >> 9 for op in ops for s_ in [op[1]] + [t[0] for t in op[3]]) << 23
+        d |= len(ops) << 24
+        d |= any(op[0] == OP_MUL for op in ops) << 30 | any(op[0] == OP_LIN for op in ops) << 31
+        return d
+
+    def finish(self):
+        self.words += [0] * (256 * 4)  # a fetch reads all 64 lanes of its rows
+        return self.words
 
 
-TRACE_LIMITS = ((8, 4), (12, 4), (16, 4), (8, 8), (12, 8), (16, 8))
+TRACE_LIMITS = tuple((nt, sd) for nt in (8, 12, 20, 28) for sd in (4, 6, 10, 14))
 
 
-def cheapest(make):
+def cheapest(make, waves):
     """trace every program under each (NTERM, SIDE) limit and keep, per program, the trace
     whose schedule costs least"""
     global NTERM, SIDE
@@ -1326,23 +1457,26 @@ def cheapest(make):
     for nt, sd in TRACE_LIMITS:
         NTERM, SIDE = nt, sd
         for nm, p in make().items():
-            c = levels_cost(p, schedule(p)[0])
+            c = levels_cost(p, schedule(p, WAVE_OPS * waves)[0])
             if nm not in best or c < best[nm][0]:
                 best[nm] = (c, p)
     NTERM, SIDE = saved
     return {nm: p for nm, (c, p) in best.items()}
 
 
+# wavefronts of a workgroup, by kernel family
+ML_WAVES, FE_WAVES, G2_WAVES, G1_WAVES = 2, 2, 2, 2
+
 _BUILT = []
 
 
 def build_all():
     if not _BUILT:
-        mk = Kernel("ml", cheapest(miller_programs), MILLER_STATE)
+        mk = Kernel("ml", cheapest(miller_programs, ML_WAVES), MILLER_STATE, waves=ML_WAVES)
         fe_state = ["t", "tinv"] + ["%s.%d" % (nm, k) for nm in ("nA", "nB", "nC", "n2") for k in (0, 1)]
-        fk = Kernel("fe", cheapest(fe_programs), fe_state, segs={"X": 1, "Y": 2, "D": 3})
-        gk = Kernel("g2", cheapest(g2_programs), G2_STATE, segs={"A": 2})
-        g1k = Kernel("g1", cheapest(g1_programs), G1_STATE, segs={"A": 2})
+        fk = Kernel("fe", cheapest(fe_programs, FE_WAVES), fe_state, segs={"X": 1, "Y": 2, "D": 3}, waves=FE_WAVES)
+        gk = Kernel("g2", cheapest(g2_programs, G2_WAVES), G2_STATE, segs={"A": 2}, waves=G2_WAVES)
+        g1k = Kernel("g1", cheapest(g1_programs, G1_WAVES), G1_STATE, segs={"A": 2}, waves=G1_WAVES)
         _BUILT.append((mk, fk, gk, g1k))
     return _BUILT[0]
 
@@ -1353,7 +1487,6 @@ def limbs(x):
 
 
 M29 = (1 << 29) - 1
-OFF_MULT = 65536          # offset multiple of p added to every linear combination
 
 
 def limbs29(x):
@@ -1365,13 +1498,12 @@ def emit_radix():
     o = []
     o.append("static constexpr uint32_t P29[9] = {%s};" % ", ".join("0x%08xu" % v for v in limbs29(P)))
     o.append("static constexpr uint32_t PINV29 = 0x%08xu;  // -p^{-1} mod 2^29" % ((-pow(P, -1, 1 << 29)) % (1 << 29)))
-    off = OFF_MULT * P
-    ol = [(off >> (29 * i)) & M29 for i in range(8)] + [off >> 232]
-    o.append("static constexpr int64_t OFF29[9] = {%s};  // %d p: limbs 0..7, then everything from bit 232" % (
-        ", ".join("%dll" % v for v in ol), OFF_MULT))
     assert P >> 232 < (1 << 29)
-    o.append("static constexpr double INVP232 = %r;  // 2^232 / p" % (float(2**232) / P))
+    o.append("static constexpr float INVP240 = %.9gf;  // 2^240 / p" % (float(2**240) / P))
     return o
+
+
+CHECKED = ("g1_dbl2_add", "g1_add", "g1_madd", "g2_dbl_add", "g2_add", "g2_madd")
 
 
 def emit(kernels):
@@ -1383,7 +1515,7 @@ def emit(kernels):
     w("namespace slp {")
     for line in emit_radix():
         w(line)
-    allops = []
+    table = OpTable()
     descs = []
     for k in kernels:
         w("// kernel %s: %d slots (%d state, %d constants)" % (k.name, k.nslots, len(k.state), len(k.consts)))
@@ -1391,29 +1523,31 @@ def emit(kernels):
         w("static constexpr int %s_NSLOT = %d;" % (k.name.upper(), k.nslots))
         w("static constexpr int %s_CBASE = %d;" % (k.name.upper(), k.cbase))
         w("static constexpr int %s_NCONST = %d;" % (k.name.upper(), len(k.consts)))
+        w("static constexpr int %s_WAVES = %d;" % (k.name.upper(), k.waves))
+        assert k.waves == 2
         for nm, s in k.state.items():
             w("static constexpr int %s_%s = %d;" % (k.name.upper(), nm.replace(".", "_"), s))
         for nm, enc in k.progs.items():
-            width = max(1, max(len(r) for r in enc))
-            descs.append((k.name, nm, len(allops), len(enc), width))
-            w("static constexpr int PROG_%s = %d;" % (nm.upper(), len(descs) - 1))
-            for row in enc:
-                # term groups in use by the level (products split their terms at ENC_SIDE)
-                gm = 0
-                for op in row:
-                    gm |= term_groups(op)
-                assert all(op[0] != OP_MUL or op[2] == ENC_SIDE for op in row)
-                allops += [encode_op((op[0], op[1], gm, op[3])) for op in row] + [0] * (width - len(row))
-    w("struct ProgDesc { uint32_t off; uint16_t nlev; uint16_t width; };")
-    w("__device__ const ProgDesc PROGS[%d] = {" % len(descs))
-    for kn, nm, off, nlev, width in descs:
-        w("  {%du, %du, %du},  // %s" % (off, nlev, width, nm))
+            nxt = [0] * k.waves
+            for row in reversed(enc):  # last level first: a level names the next one
+                for v, ops in enumerate(level_blocks(row, k.waves)):
+                    nxt[v] = table.add(ops, nxt[v])
+            w("static constexpr int PROG_%s = %d;" % (nm.upper(), len(descs)))
+            descs.append((nm, [d | (1 << 18 if nm in CHECKED else 0) for d in nxt]))
+    w("static constexpr int PROG_INV = 255;")
+    assert len(descs) < 255
+    w("// a program: descriptors of its first level, one per wavefront (bit 18: an addition that")
+    w("// reports equal x-coordinates in its H slots)")
+    w("struct ProgDesc { uint32_t d[2]; };")
+    w("static constexpr ProgDesc PROGS[%d] = {" % len(descs))
+    for nm, d in descs:
+        w("  {{0x%xu, 0x%xu}},  // %s" % (d[0], d[1], nm))
     w("};")
-    w("static constexpr int OP_WORDS = %d;" % OP_WORDS)
-    w("__device__ const uint64_t OPS[%d][%d] = {" % (len(allops), OP_WORDS))
-    for x in allops:
-        assert x >> (64 * OP_WORDS) == 0
-        w("  {%s}," % ", ".join("0x%xull" % ((x >> (64 * k)) & (2**64 - 1)) for k in range(OP_WORDS)))
+    w("static constexpr int LANE_TERMS_MAX = %d;" % max(LANE_TERMS))
+    words = table.finish()
+    w("__device__ const uint32_t OPS[%d] __attribute__((aligned(64))) = {" % len(words))
+    for k0 in range(0, len(words), 16):
+        w("  %s," % ", ".join("0x%xu" % x for x in words[k0:k0 + 16]))
     w("};")
     for k in kernels:
         w("__device__ const uint32_t %s_CONSTS[%d][9] = {" % (k.name.upper(), len(k.consts)))
@@ -1424,12 +1558,11 @@ def emit(kernels):
     seq = miller_sequence()
     w("static constexpr int ML_SEQ_LEN = %d;" % len(seq))
     w("__device__ const uint8_t ML_SEQ[%d][1] = {%s};" % (len(seq), ", ".join("{PROG_%s}" % s.upper() for s in seq)))
-    w("__device__ const uint8_t F12_MUL_CALL[1][4] = {{PROG_F12_MUL, 0, 1, 2}};")
     seqf, res_buf, nb = fe_sequence()
     w("static constexpr int FE_NBUF = %d;" % nb)
     w("static constexpr int FE_RESULT = %d;" % res_buf)
     w("static constexpr int FE_SEQ_LEN = %d;" % len(seqf))
-    w("static constexpr int PROG_INV = 255;")
+    w("static constexpr int FE_SEQ_INV = %d;  // the entry that stands for tinv = t^{-1}" % [c[0] for c in seqf].index("INV"))
     w("__device__ const uint8_t FE_SEQ[%d][4] = {" % len(seqf))
     for prog, X, Y, D in seqf:
         w("  {%s, %d, %d, %d}," % ("PROG_INV" if prog == "INV" else "PROG_%s" % prog.upper(), X, Y, D))

@@ -22,37 +22,45 @@ template <class Ctx> __host__ __device__ inline void copy12(Ctx &c, int dst, int
 }
 
 // g^k for g (cyclotomic) in buffer 0 and k given by its decomposition; returns the buffer
-// holding the result, or -1 when k = 0 (the result is 1)
+// holding the result, or -1 when k = 0 (the result is 1).  The signed Frobenius images, then
+// one list of calls: the 11 table products and a call per bit (a squaring, with a product
+// where the digit is not zero), the accumulator alternating between its two buffers.
 template <class Ctx> __host__ __device__ inline int pow_cyc(Ctx &c, const gls::Dec &dec, int fb) {
-  auto B = [fb](int b) { return fb + 12 * b; };
+  auto B = [fb](int b) { return (uint16_t)(fb + 12 * b); };
   if (dec.nbits == 0) return -1;
-  const int frob[4] = {-1, slp::PROG_F12_FROB1, slp::PROG_F12_FROB2, slp::PROG_F12_FROB3};
-  for (int j = 0; j < 4; j++) {
-    int src = 0;
-    if (j) {
-      c.run(frob[j], B(0), B(0), B(16));
-      src = 16;
-    }
-    if (dec.neg >> j & 1) c.run(slp::PROG_F12_CONJ, B(src), B(src), B(1 << j));
-    else copy12(c, B(1 << j), B(src));
-  }
-  for (int d = 3; d < 16; d++) {
-    int lo = d & -d;
-    if (d != lo) c.run(slp::PROG_F12_MUL, B(d - lo), B(lo), B(d));
-  }
-  int t = (int)dec.nbits - 1;
-  int acc = 16;
-  copy12(c, B(acc), B((int)gls::digit(dec, (uint32_t)t)));
-  for (t = t - 1; t >= 0; t--) {
-    c.run(slp::PROG_F12_CSQR, B(acc), B(acc), B(33 - acc));
-    acc = 33 - acc;
-    uint32_t d = gls::digit(dec, (uint32_t)t);
-    if (d) {
-      c.run(slp::PROG_F12_MUL, B(acc), B((int)d), B(33 - acc));
-      acc = 33 - acc;
+  const int n = (int)dec.nbits - 1;  // bits below the top one
+  const int top = (int)gls::digit(dec, (uint32_t)n);
+  if (c.lane() == 0) {
+    // image j to buffer 2^j; where k_j is negative by way of buffer 16, for the conjugate
+    int e = 0;
+    for (int j = 0; j < 4; j++) {
+      const bool neg = dec.neg >> j & 1;
+      const int dst = neg && j ? 16 : 1 << j;
+      if (j == 1) c.cl[e++] = slp::call(slp::PROG_F12_FROB1, B(0), B(0), B(dst));
+      if (j == 2) c.cl[e++] = slp::call(slp::PROG_F12_FROB2, B(0), B(0), B(dst));
+      if (j == 3) c.cl[e++] = slp::call(slp::PROG_F12_FROB3, B(0), B(0), B(dst));
+      if (neg) c.cl[e++] = slp::call(slp::PROG_F12_CONJ, B(j ? 16 : 0), B(j ? 16 : 0), B(1 << j));
     }
   }
-  return acc;
+  if (!(dec.neg & 1)) copy12(c, B(1), B(0));
+  c.sync();
+  c.run_list(0, 3 + __builtin_popcount(dec.neg & 15u), 0, 0);
+  const int HEAD = 11;
+  for (int e = c.lane(); e < HEAD + n; e += c.lanes()) {
+    if (e < HEAD) {
+      int d = e + 3;  // the e-th of 3, 5, 6, 7, 9, .. 15
+      d += d >= 4;
+      d += d >= 8;
+      const int lo = d & -d;
+      c.cl[e] = slp::call(slp::PROG_F12_MUL, B(d - lo), B(lo), B(d));
+    } else {
+      const int i = e - HEAD, d = (int)gls::digit(dec, (uint32_t)(n - 1 - i));
+      const int src = i == 0 ? top : 17 - (i & 1), dst = 16 + (i & 1);
+      c.cl[e] = d ? slp::call(slp::PROG_F12_CSQR_MUL, B(src), B(d), B(dst)) : slp::call(slp::PROG_F12_CSQR, B(src), B(src), B(dst));
+    }
+  }
+  c.run_list(0, HEAD + n, 0, 0);
+  return n == 0 ? top : 17 - (n & 1);
 }
 
 }  // namespace gtp

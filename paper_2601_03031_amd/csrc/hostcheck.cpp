@@ -282,8 +282,9 @@ API int hc_slp_f12(int op, const uint8_t *a, const uint8_t *b, uint8_t *out) {
 
 
 // radix-2^29 lane arithmetic on raw integers (big-endian 32 bytes, below 2p):
-// op 0: sum_i k_i x_i mod p (reduced to [0, 2p), then canonical); op 1: Montgomery
-// product a b 2^{-261} (canonical); op 2: the raw almost-reduced linear combination
+// ops 0 and 3: sum_i k_i x_i mod p (almost reduced, then canonical); op 1: Montgomery
+// product a b 2^{-261} (canonical); ops 2 and 4: the almost-reduced linear combination itself
+// plus p (it is signed, within p of zero)
 static fe rd_raw(const uint8_t *b) {
   fe a;
   for (int i = 0; i < 8; i++)
@@ -302,16 +303,15 @@ API int hc_slp_lane(int op, int n, const int *k, const uint8_t *xs, uint8_t *out
     wr_raw(out, slp::from29(r));
     return 0;
   }
-  // op 0/2: one offset (a product factor); op 3/4: twice the offset (a 16-term sum whose two
-  // halves each start at it, as the interpreter's linear combinations)
-  int64_t acc[9];
-  for (int j = 0; j < 9; j++) acc[j] = (op >= 3 ? 2 : 1) * slp::OFF29[j];
+  int64_t acc[9] = {};
   for (int i = 0; i < n; i++) {
     slp::f29 x = slp::to29(rd_raw(xs + 32 * i));
     for (int j = 0; j < 9; j++) acc[j] += (int64_t)k[i] * (int32_t)x.l[j];
   }
   slp::f29 r = slp::red29(acc);
-  wr_raw(out, slp::from29(op == 2 || op == 4 ? r : slp::canon29(r)));
+  if (op == 2 || op == 4)
+    for (int j = 0; j < 9; j++) r.l[j] += slp::P29[j];
+  wr_raw(out, slp::from29(op == 2 || op == 4 ? slp::norm29(r) : slp::canon29(r)));
   return 0;
 }
 
@@ -685,9 +685,10 @@ API int hc_gt_pow_cyc(const uint8_t *gb, const uint8_t *kb, uint8_t *out) {
 // one-lane inversion), 2 G2 psi images, 3 G2 table, 4 G2 doubling, 5 G2 addition,
 // 6 G2 mixed addition, 7 G2 to affine (norm + affine), 8 F_p12 product
 static uint64_t prog_muls(int prog) {
-  const slp::ProgDesc d = slp::PROGS[prog];
   uint64_t n = 0;
-  for (uint32_t i = 0; i < (uint32_t)d.nlev * d.width; i++) n += (slp::OPS[d.off + i][0] & 3) == 1;
+  for (int v = 0; v < 2; v++)
+    for (uint32_t d = slp::PROGS[prog].d[v]; d; d = slp::blk_word(slp::OPS, d, 0, 1))
+      for (int i = 0; i < slp::blk_ops(d); i++) n += slp::term_coef(slp::blk_word(slp::OPS, d, 2 * i, 0)) == 1;
   return n;
 }
 API uint64_t hc_engine_muls(int which) {

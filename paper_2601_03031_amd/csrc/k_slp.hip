@@ -1,5 +1,6 @@
-// Kernels on the wave-cooperative engine (slp.hpp): Miller loops, F_p12 product trees
-// and the final exponentiation, one 64-lane workgroup per pairing / product / element.
+// Kernels on the workgroup-cooperative engine (slp.hpp): Miller loops, F_p12 product trees,
+// the final exponentiation, scalar multiplications and powers, one workgroup of two wavefronts
+// per pairing / product / element.
 #include "kcommon.hpp"
 #include "slp.hpp"
 #include "g2mul.hpp"
@@ -7,9 +8,17 @@
 #include "g1mul.hpp"
 #include "oa_terms.hpp"
 
-#define SLP_T 64
-// slp::run_seq stages a call sequence of at most 256 calls in LDS
-static_assert(slp::ML_SEQ_LEN <= 256 && slp::FE_SEQ_LEN <= 256, "call sequence longer than its LDS copy");
+// every program family is scheduled for the same number of wavefronts, so that a kernel may
+// run several of them
+#define SLP_W 2
+#define SLP_T (64 * SLP_W)
+static_assert(slp::ML_WAVES == SLP_W && slp::FE_WAVES == SLP_W && slp::G1_WAVES == SLP_W && slp::G2_WAVES == SLP_W,
+              "programs scheduled for another workgroup size");
+static_assert(slp::ML_SEQ_LEN <= slp::MAX_CALLS && slp::FE_SEQ_LEN <= slp::MAX_CALLS, "call sequence longer than its LDS list");
+typedef slp::DevCtx<SLP_W> Ctx;
+typedef slp::DevCtx<SLP_W, true> CtxInline;  // for kernels with one place that runs calls
+// the call list of a workgroup in LDS
+#define CALL_LIST() __shared__ slp::Call calls_sh[slp::MAX_CALLS + 1]
 
 namespace {
 
@@ -32,7 +41,8 @@ __device__ __forceinline__ void load_consts(f29 *S, int base, const uint32_t (*C
 }
 
 // Miller loop of e(P, Q) into dst (12 coefficients); identity inputs give 1.
-__device__ void miller_one(f29 *S, const g1_aff *P, const g2_aff *Q, fp12 *dst) {
+__device__ __forceinline__ void miller_one(CtxInline c, const g1_aff *P, const g2_aff *Q, fp12 *dst) {
+  f29 *S = c.S;
   const int t = threadIdx.x;
   fe *out = reinterpret_cast<fe *>(dst);
   if (g1_inf(*P) || g2_inf(*Q)) {
@@ -45,45 +55,68 @@ __device__ void miller_one(f29 *S, const g1_aff *P, const g2_aff *Q, fp12 *dst) 
     S[slp::ML_xP + t] = slp::to29(q[t - 2]);  // xQ.0, xQ.1, yQ.0, yQ.1
   }
   load_consts<slp::ML_NCONST>(S, slp::ML_CBASE, slp::ML_CONSTS);
-  __syncthreads();
-  slp::run_seq<1>(S, slp::ML_SEQ, slp::ML_SEQ_LEN, 0, 0, 0);
+  for (int e = t; e < slp::ML_SEQ_LEN; e += SLP_T) c.cl[e] = slp::call(slp::ML_SEQ[e][0], 0, 0, 0);
+  c.run_list(0, slp::ML_SEQ_LEN, 0, 0);
   if (t < 12) out[t] = slp::from29(slp::canon29(S[slp::ML_f_0 + t]));
 }
 
 }  // namespace
 
 // out[i] = Miller(P[i sp], Q[i sq])
-__global__ void __launch_bounds__(SLP_T) ks_miller(const g1_aff *P, uint64_t sp, const g2_aff *Q, uint64_t sq, uint64_t n,
+__global__ void __launch_bounds__(SLP_T, 4) ks_miller(const g1_aff *P, uint64_t sp, const g2_aff *Q, uint64_t sq, uint64_t n,
                                                   fp12 *out) {
   __shared__ f29 S[slp::ML_NSLOT];
+  CALL_LIST();
   uint64_t i = blockIdx.x;
   if (i >= n) return;
-  miller_one(S, P + i * sp, Q + i * sq, out + i);
+  miller_one(CtxInline{S, calls_sh}, P + i * sp, Q + i * sq, out + i);
 }
 
 // side 0 (L) pairs A[h+i] with V[i], side 1 (R) A[i] with V[h+i]; F[(2k+side) K/2 + i]
-__global__ void __launch_bounds__(SLP_T) ks_oa_miller(const g1_aff *A, const g2_aff *V, uint64_t K, uint64_t nb, uint64_t h,
+__global__ void __launch_bounds__(SLP_T, 4) ks_oa_miller(const g1_aff *A, const g2_aff *V, uint64_t K, uint64_t nb, uint64_t h,
                                                      fp12 *F) {
   CHAIN_PRIORITY();
   __shared__ f29 S[slp::ML_NSLOT];
+  CALL_LIST();
   uint64_t id = blockIdx.x;
   if (id >= nb * 2 * h) return;
   uint64_t k = id / (2 * h), r = id % (2 * h), side = r / h, i = r % h;
   const g1_aff *P = A + (side ? k * K + i : k * K + h + i);
   const g2_aff *Q = V + (side ? k * K + h + i : k * K + i);
-  miller_one(S, P, Q, F + (k * 2 + side) * (K / 2) + i);
+  miller_one(CtxInline{S, calls_sh}, P, Q, F + (k * 2 + side) * (K / 2) + i);
+}
+
+// Of the n workgroups that meet at a counter, the last to arrive returns true (and resets it);
+// what the others wrote before is visible to it.  The fences are one lane's, between barriers:
+// each writes back or drops cache lines, and with both wavefronts issuing them a launch of 2^15
+// F_p12 products took 1.19 ms against 0.46 ms with one wavefront a workgroup.
+__device__ bool last_arrival(uint32_t *cnt, uint32_t n, uint32_t *flag) {
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    __threadfence();
+    const uint32_t old = atomicAdd(cnt, 1u);
+    if (old == n - 1) {
+      *cnt = 0;
+      __threadfence();
+    }
+    *flag = old == n - 1;
+  }
+  __syncthreads();
+  return *flag != 0;
 }
 
 #define FE_SLOTS (slp::FE_NSLOT + 12 * slp::FE_NBUF)
-#define FE_BUF(b) (slp::FE_NSLOT + 12 * (b))
+#define FE_BUF(b) ((uint16_t)(slp::FE_NSLOT + 12 * (b)))
 
 // Product of each segment data[g stride + 0 .. len) into data[g stride] in one launch: a
 // workgroup per pair of the first level; of two sibling nodes, the workgroup that finishes
 // second climbs to the parent (arrival counters as in k_jac_tree).
-__global__ void __launch_bounds__(SLP_T) ks_f12_tree(fp12 *data, uint64_t nseg, uint64_t stride, uint64_t len, uint32_t *cnt) {
+__global__ void __launch_bounds__(SLP_T, 4) ks_f12_tree(fp12 *data, uint64_t nseg, uint64_t stride, uint64_t len, uint32_t *cnt) {
   CHAIN_PRIORITY();
   __shared__ f29 S[slp::FE_NSLOT + 36];
   __shared__ uint32_t arrived;
+  CALL_LIST();
+  CtxInline cx{S, calls_sh};
   uint64_t per = (len + 1) / 2;
   uint64_t id = blockIdx.x;
   if (id >= nseg * per) return;
@@ -91,7 +124,6 @@ __global__ void __launch_bounds__(SLP_T) ks_f12_tree(fp12 *data, uint64_t nseg, 
   fp12 *seg = data + g * stride;
   uint32_t *c = cnt + g * tree_counters(len);
   const int t = threadIdx.x;
-  load_consts<slp::FE_NCONST>(S, slp::FE_CBASE, slp::FE_CONSTS);
   uint64_t s = 1, n = per, cb = 0;
   for (;;) {
     uint64_t a = 2 * s * q, b = a + s;
@@ -103,22 +135,13 @@ __global__ void __launch_bounds__(SLP_T) ks_f12_tree(fp12 *data, uint64_t nseg, 
         S[slp::FE_NSLOT + 12 + t] = slp::to29(db[t]);
       }
       __syncthreads();
-      slp::run_seq<4>(S, slp::F12_MUL_CALL, 1, slp::FE_NSLOT, 0, 0);
+      cx.run(slp::PROG_F12_MUL, FE_BUF(0), FE_BUF(1), FE_BUF(2));
       if (t < 12) da[t] = slp::from29(slp::canon29(S[slp::FE_NSLOT + 24 + t]));
     }
     if (n == 1) return;
     uint64_t nn = (n + 1) / 2, qp = q >> 1;
     if ((q ^ 1) < n) {
-      __threadfence();
-      __syncthreads();
-      if (t == 0) {
-        uint32_t old = atomicAdd(&c[cb + qp], 1u);
-        if (old) c[cb + qp] = 0;
-        arrived = old;
-      }
-      __syncthreads();
-      if (!arrived) return;
-      __threadfence();
+      if (!last_arrival(&c[cb + qp], 2, &arrived)) return;
     }
     cb += nn;
     q = qp;
@@ -127,52 +150,64 @@ __global__ void __launch_bounds__(SLP_T) ks_f12_tree(fp12 *data, uint64_t nseg, 
   }
 }
 
-// f^((p^12 - 1)/r), a workgroup per input; input s at in[s in_stride], output to
-// (s odd ? out1 : out0)[(s >> 1) ostride]
-__global__ void __launch_bounds__(SLP_T) ks_final_exp(const fp12 *in, uint64_t in_stride, uint64_t n, fp12 *out0, fp12 *out1,
-                                                     uint64_t ostride) {
-  CHAIN_PRIORITY();
-  __shared__ f29 S[FE_SLOTS];
-  uint64_t s = blockIdx.x;
-  if (s >= n) return;
+// final exponentiation of one F_p12 element on the engine
+__device__ __forceinline__ void fe_job(CtxInline c, const fp12 *in, fp12 *out) {
+  f29 *S = c.S;
   int t = threadIdx.x;
-  const fe *src = reinterpret_cast<const fe *>(in + s * in_stride);
+  const fe *src = reinterpret_cast<const fe *>(in);
   if (t < 12) S[FE_BUF(0) + t] = slp::to29(src[t]);
   load_consts<slp::FE_NCONST>(S, slp::FE_CBASE, slp::FE_CONSTS);
-  __syncthreads();
-  slp::run_seq<4>(S, slp::FE_SEQ, slp::FE_SEQ_LEN, slp::FE_NSLOT, slp::FE_t, slp::FE_tinv);
-  fp12 *o = (s & 1) ? out1 : out0;
-  fe *dst = reinterpret_cast<fe *>(o + (s >> 1) * ostride);
+  for (int e = t; e < slp::FE_SEQ_LEN; e += SLP_T) {
+    const uint8_t *q = slp::FE_SEQ[e];
+    if (e != slp::FE_SEQ_INV) c.cl[e] = slp::call(q[0], FE_BUF(q[1]), FE_BUF(q[2]), FE_BUF(q[3]));
+  }
+#pragma unroll 1
+  for (int first = 0; first < slp::FE_SEQ_LEN;) {
+    const int n = first ? slp::FE_SEQ_LEN : slp::FE_SEQ_INV;
+    c.run_list(first, n, 0, 0);
+    if (!first) c.invert(slp::FE_tinv, slp::FE_t);
+    first = n + 1;
+  }
+  fe *dst = reinterpret_cast<fe *>(out);
   if (t < 12) dst[t] = slp::from29(slp::canon29(S[FE_BUF(slp::FE_RESULT) + t]));
 }
 
+// f^((p^12 - 1)/r), a workgroup per input; input s at in[s in_stride], output to
+// (s odd ? out1 : out0)[(s >> 1) ostride]
+__global__ void __launch_bounds__(SLP_T, 4) ks_final_exp(const fp12 *in, uint64_t in_stride, uint64_t n, fp12 *out0, fp12 *out1,
+                                                     uint64_t ostride) {
+  CHAIN_PRIORITY();
+  __shared__ f29 S[FE_SLOTS];
+  CALL_LIST();
+  uint64_t s = blockIdx.x;
+  if (s >= n) return;
+  fe_job(CtxInline{S, calls_sh}, in + s * in_stride, ((s & 1) ? out1 : out0) + (s >> 1) * ostride);
+}
 
 // ---------------------------------------------------------------- G2 scalar multiplications
 #define G2_SLOTS (slp::G2_NSLOT + 4)
 #define G2_ABASE slp::G2_NSLOT
 
 // T (Jacobian, the identity when inf) to oaff
-__device__ void g2_store_aff(f29 *S, bool inf, g2_aff *oaff) {
+__device__ void g2_store_aff(Ctx c, bool inf, g2_aff *oaff) {
+  f29 *S = c.S;
   const int t = threadIdx.x;
   fe *o = reinterpret_cast<fe *>(oaff);
   if (inf) {
     if (t < 4) o[t] = fe_zero();
     return;
   }
-  slp::run1(S, slp::PROG_G2_NORM, 0, 0, 0);
-  {
-    fe ti = f_inv_uniform<FpP>(slp::from29(slp::canon29(S[slp::G2_t])), bn::P_R3);
-    if (t == 0) S[slp::G2_tinv] = slp::to29(ti);
-  }
-  __syncthreads();
-  slp::run1(S, slp::PROG_G2_AFF, 0, 0, 0);
+  c.run(slp::PROG_G2_NORM, 0, 0, 0);
+  c.invert(slp::G2_tinv, slp::G2_t);
+  c.run(slp::PROG_G2_AFF, 0, 0, 0);
   if (t < 4) o[t] = slp::from29(slp::canon29(S[slp::G2_ax_0 + t]));
 }
 
 // out = k Q + A on the engine (A optional); results written as affine (oaff) or Jacobian (ojac).
 // With lo >= 0 only bits [lo, lo + width) of the GLS split of k are applied (gls::chunk).
-__device__ void g2_job(f29 *S, gls::Dec *dec, const g2_aff *Q, const fe *k_mont, const g2_aff *A, g2_aff *oaff,
+__device__ void g2_job(Ctx c, gls::Dec *dec, const g2_aff *Q, const fe *k_mont, const g2_aff *A, g2_aff *oaff,
                        g2_jac *ojac, int lo = -1, int width = 0) {
+  f29 *S = c.S;
   const int t = threadIdx.x;
   if (t == 0) {
     fe kc = f_from_mont<FpR>(*k_mont);
@@ -185,7 +220,6 @@ __device__ void g2_job(f29 *S, gls::Dec *dec, const g2_aff *Q, const fe *k_mont,
   load_consts<slp::G2_NCONST>(S, slp::G2_CBASE, slp::G2_CONSTS);
   __syncthreads();
   bool qinf = g2_inf(*Q), has_a = A && !g2_inf(*A);
-  slp::DevCtx c{S};
   const f29 one = S[slp::G2_CBASE + 1], zero = S[slp::G2_CBASE];
   bool inf = g2m::mul_add(c, *dec, qinf, has_a, G2_ABASE, one, zero);
   if (ojac) {
@@ -193,42 +227,48 @@ __device__ void g2_job(f29 *S, gls::Dec *dec, const g2_aff *Q, const fe *k_mont,
     if (t < 6) o[t] = inf ? ((t == 0 || t == 2) ? f_one<FpP>() : fe_zero()) : slp::from29(slp::canon29(S[slp::G2_T_0 + t]));
     return;
   }
-  g2_store_aff(S, inf, oaff);
+  g2_store_aff(c, inf, oaff);
 }
 
 // Vout[i] = Vin[i] + x^{-1} Vin[h + i] for every batch k (Eq. folding); Vout may be Vin
-__global__ void __launch_bounds__(SLP_T) ks_oa_fold_g2(const g2_aff *Vin, g2_aff *Vout, const fe *Xinv, uint64_t K, uint64_t nb,
+__global__ void __launch_bounds__(SLP_T, 4) ks_oa_fold_g2(const g2_aff *Vin, g2_aff *Vout, const fe *Xinv, uint64_t K, uint64_t nb,
                                                       uint64_t h, uint32_t j, uint32_t lK) {
   __shared__ f29 S[G2_SLOTS];
+  CALL_LIST();
+  Ctx c{S, calls_sh};
   __shared__ gls::Dec dec;
   uint64_t id = blockIdx.x;
   if (id >= nb * h) return;
   uint64_t k = id / h, i = id % h;
-  g2_job(S, &dec, Vin + k * K + h + i, Xinv + k * lK + (j - 1), Vin + k * K + i, Vout + k * K + i, nullptr);
+  g2_job(c, &dec, Vin + k * K + h + i, Xinv + k * lK + (j - 1), Vin + k * K + i, Vout + k * K + i, nullptr);
 }
 
 // terms q_m h_m of the KZG proof of v_l with every multiplication split in four parts (bits
 // [16 p, 16 p + 16) of the GLS split, 17 for p = 3) on the multiples hm[3 m + p - 1] =
 // 2^{16 p} h_m made at setup: S2[4 id + p] (Jacobian) for term id = k (2K - 2) + m
-__global__ void __launch_bounds__(SLP_T) ks_kzg_terms_split(const g2_aff *h, const g2_aff *hm, const fe *Qc, uint64_t K,
+__global__ void __launch_bounds__(SLP_T, 4) ks_kzg_terms_split(const g2_aff *h, const g2_aff *hm, const fe *Qc, uint64_t K,
                                                            uint64_t nb, g2_jac *S2) {
   CHAIN_PRIORITY();
   __shared__ f29 S[G2_SLOTS];
+  CALL_LIST();
+  Ctx c{S, calls_sh};
   __shared__ gls::Dec dec;
   uint64_t n = 2 * K - 2;
   uint64_t id = blockIdx.x;
   if (id >= 4 * nb * n) return;
   uint64_t term = id >> 2, m = term % n;
   int part = (int)(id & 3);
-  g2_job(S, &dec, part ? hm + 3 * m + part - 1 : h + m, Qc + term, nullptr, nullptr, S2 + id, 16 * part,
+  g2_job(c, &dec, part ? hm + 3 * m + part - 1 : h + m, Qc + term, nullptr, nullptr, S2 + id, 16 * part,
          part < 3 ? 16 : 17);
 }
 
 // ---------------------------------------------------------------- G_T exponentiation
 // out[s] = in[s]^k_s (k in Montgomery F_r form), square-and-multiply with the engine's
 // F_p12 product (inputs need not lie in the cyclotomic subgroup)
-__global__ void __launch_bounds__(SLP_T) ks_gt_pow(const fp12 *in, const fe *k_mont, uint64_t n, fp12 *out) {
+__global__ void __launch_bounds__(SLP_T, 4) ks_gt_pow(const fp12 *in, const fe *k_mont, uint64_t n, fp12 *out) {
   __shared__ f29 S[slp::FE_NSLOT + 36];
+  CALL_LIST();
+  CtxInline c{S, calls_sh};
   __shared__ uint32_t kc[8];
   uint64_t s = blockIdx.x;
   if (s >= n) return;
@@ -249,18 +289,16 @@ __global__ void __launch_bounds__(SLP_T) ks_gt_pow(const fp12 *in, const fe *k_m
     if (t < 12) dst[t] = t == 0 ? f_one<FpP>() : fe_zero();
     return;
   }
-  // accumulator alternates between buffers 1 and 2; buffer 0 holds the base
-  if (t < 12) S[FE_BUF(1) + t] = S[FE_BUF(0) + t];
-  __syncthreads();
-  int acc = 1;
-  for (int b = top - 1; b >= 0; b--) {
-    slp::run1(S, slp::PROG_F12_MUL, FE_BUF(acc), FE_BUF(acc), FE_BUF(3 - acc));
-    acc = 3 - acc;
-    if ((kc[b >> 5] >> (b & 31)) & 1) {
-      slp::run1(S, slp::PROG_F12_MUL, FE_BUF(acc), FE_BUF(0), FE_BUF(3 - acc));
-      acc = 3 - acc;
-    }
+  // a call per bit below the top one (a squaring, with a product where the bit is set), the
+  // accumulator alternating between buffers 1 and 2; buffer 0 holds the base
+  for (int i = t; i < top; i += SLP_T) {
+    const int bit = top - 1 - i, src = i == 0 ? 0 : 2 - (i & 1), dst = 1 + (i & 1);
+    const bool one = kc[bit >> 5] >> (bit & 31) & 1;
+    c.cl[i] = one ? slp::call(slp::PROG_F12_SQR_MUL, FE_BUF(src), FE_BUF(0), FE_BUF(dst))
+                  : slp::call(slp::PROG_F12_SQR, FE_BUF(src), FE_BUF(src), FE_BUF(dst));
   }
+  if (top) c.run_list(0, top, 0, 0);
+  const int acc = top == 0 ? 0 : 2 - (top & 1);
   if (t < 12) dst[t] = slp::from29(slp::canon29(S[FE_BUF(acc) + t]));
 }
 
@@ -269,26 +307,24 @@ __global__ void __launch_bounds__(SLP_T) ks_gt_pow(const fp12 *in, const fe *k_m
 #define G1_ABASE slp::G1_NSLOT
 
 // T (Jacobian, the identity when inf) to oaff
-__device__ void g1_store_aff(f29 *S, bool inf, g1_aff *oaff) {
+__device__ void g1_store_aff(Ctx c, bool inf, g1_aff *oaff) {
+  f29 *S = c.S;
   const int t = threadIdx.x;
   fe *o = reinterpret_cast<fe *>(oaff);
   if (inf) {
     if (t < 2) o[t] = fe_zero();
     return;
   }
-  {
-    fe zi = f_inv_uniform<FpP>(slp::from29(slp::canon29(S[slp::G1_T_2])), bn::P_R3);
-    if (t == 0) S[slp::G1_tinv] = slp::to29(zi);
-  }
-  __syncthreads();
-  slp::run1(S, slp::PROG_G1_AFF, 0, 0, 0);
+  c.invert(slp::G1_tinv, slp::G1_T_2);
+  c.run(slp::PROG_G1_AFF, 0, 0, 0);
   if (t < 2) o[t] = slp::from29(slp::canon29(S[t ? slp::G1_ay : slp::G1_ax]));
 }
 
 // out = k P + A on the engine (A optional); results written as affine (oaff) or Jacobian (ojac).
 // With chunk >= 0 only that 32-bit part of the GLV split of k is applied (glv::chunk).
-__device__ void g1_job(f29 *S, glv::Dec *dec, const g1_aff *P, const fe *k_mont, const g1_aff *A, g1_aff *oaff,
+__device__ void g1_job(Ctx c, glv::Dec *dec, const g1_aff *P, const fe *k_mont, const g1_aff *A, g1_aff *oaff,
                        g1_jac *ojac, int chunk = -1) {
+  f29 *S = c.S;
   const int t = threadIdx.x;
   if (t == 0) {
     fe kc = f_from_mont<FpR>(*k_mont);
@@ -300,14 +336,13 @@ __device__ void g1_job(f29 *S, glv::Dec *dec, const g1_aff *P, const fe *k_mont,
   load_consts<slp::G1_NCONST>(S, slp::G1_CBASE, slp::G1_CONSTS);
   __syncthreads();
   bool pinf = g1_inf(*P), has_a = A && !g1_inf(*A);
-  slp::DevCtx c{S};
   bool inf = g1m::mul_add(c, *dec, pinf, has_a, G1_ABASE, S[slp::G1_CBASE + 1]);
   if (ojac) {
     fe *o = reinterpret_cast<fe *>(ojac);
     if (t < 3) o[t] = inf ? (t < 2 ? f_one<FpP>() : fe_zero()) : slp::from29(slp::canon29(S[slp::G1_T_0 + t]));
     return;
   }
-  g1_store_aff(S, inf, oaff);
+  g1_store_aff(c, inf, oaff);
 }
 
 // ---------------------------------------------------------------- group sums on the engine
@@ -316,11 +351,13 @@ __device__ void g1_job(f29 *S, glv::Dec *dec, const g1_aff *P, const fe *k_mont,
 // that finishes second climbs to the parent (arrival counters as in ks_f12_tree).  The
 // identity is any point with Z = 0; additions meeting equal x are resolved exactly.
 template <bool G2>
-__global__ void __launch_bounds__(SLP_T) ks_jac_tree(void *data, uint64_t nseg, uint64_t stride, uint64_t len, uint32_t *cnt) {
+__global__ void __launch_bounds__(SLP_T, 4) ks_jac_tree(void *data, uint64_t nseg, uint64_t stride, uint64_t len, uint32_t *cnt) {
   if (G2) CHAIN_PRIORITY();
   else AHEAD_PRIORITY();
   constexpr int NC = G2 ? 6 : 3;  // coordinates (F_p elements) per point
   __shared__ f29 S[G2 ? G2_SLOTS : G1_SLOTS];
+  CALL_LIST();
+  Ctx cx{S, calls_sh};
   __shared__ uint32_t arrived;
   uint64_t per = (len + 1) / 2;
   uint64_t id = blockIdx.x;
@@ -332,7 +369,6 @@ __global__ void __launch_bounds__(SLP_T) ks_jac_tree(void *data, uint64_t nseg, 
   const int T0 = G2 ? slp::G2_T_0 : slp::G1_T_0, A0 = G2 ? slp::G2_TB1_0 : slp::G1_TB1_0;
   if (G2) load_consts<slp::G2_NCONST>(S, slp::G2_CBASE, slp::G2_CONSTS);
   else load_consts<slp::G1_NCONST>(S, slp::G1_CBASE, slp::G1_CONSTS);
-  slp::DevCtx cx{S};
   uint64_t s = 1, n = per, cb = 0;
   for (;;) {
     uint64_t a = 2 * s * q, b = a + s;
@@ -356,16 +392,7 @@ __global__ void __launch_bounds__(SLP_T) ks_jac_tree(void *data, uint64_t nseg, 
     if (n == 1) return;
     uint64_t nn = (n + 1) / 2, qp = q >> 1;
     if ((q ^ 1) < n) {
-      __threadfence();
-      __syncthreads();
-      if (t == 0) {
-        uint32_t old = atomicAdd(&c[cb + qp], 1u);
-        if (old) c[cb + qp] = 0;
-        arrived = old;
-      }
-      __syncthreads();
-      if (!arrived) return;
-      __threadfence();
+      if (!last_arrival(&c[cb + qp], 2, &arrived)) return;
     }
     cb += nn;
     q = qp;
@@ -377,15 +404,17 @@ __global__ void __launch_bounds__(SLP_T) ks_jac_tree(void *data, uint64_t nseg, 
 // ---------------------------------------------------------------- Step 1 rounds, fused
 // Round-1 (direct) G1 terms on the engine: b_L[i] A_R[i] (side 0) and b_R[i] A_L[i] (side 1)
 // into S[(2k + side) (K / 2) + i] (Jacobian)
-__global__ void __launch_bounds__(SLP_T) ks_oa_g1terms(const g1_aff *A, const fe *B, uint64_t K, uint64_t nb, uint64_t h,
+__global__ void __launch_bounds__(SLP_T, 4) ks_oa_g1terms(const g1_aff *A, const fe *B, uint64_t K, uint64_t nb, uint64_t h,
                                                       g1_jac *Sout) {
   AHEAD_PRIORITY();
   __shared__ f29 S[G1_SLOTS];
+  CALL_LIST();
+  Ctx c{S, calls_sh};
   __shared__ glv::Dec d1;
   uint64_t id = blockIdx.x;
   if (id >= nb * 2 * h) return;
   uint64_t k = id / (2 * h), r = id % (2 * h), side = r / h, i = r % h;
-  g1_job(S, &d1, A + (side ? k * K + i : k * K + h + i), B + (side ? k * K + h + i : k * K + i), nullptr, nullptr,
+  g1_job(c, &d1, A + (side ? k * K + i : k * K + h + i), B + (side ? k * K + h + i : k * K + i), nullptr, nullptr,
          Sout + (k * 2 + side) * (K / 2) + i);
 }
 
@@ -394,11 +423,13 @@ template <int A_, int B_> struct imax { static constexpr int v = A_ > B_ ? A_ : 
 // The fold of round j (Eq. folding) for every batch: blocks [0, nb h) fold G1 and b,
 // blocks [nb h, 2 nb h) fold G2.  Aout[i] = Ain[i] + x Ain[h + i], Bout[i] = Bin[i] +
 // x^{-1} Bin[h + i], Vout[i] = Vin[i] + x^{-1} Vin[h + i].
-__global__ void __launch_bounds__(SLP_T) ks_oa_fold(const g1_aff *Ain, const fe *Bin, g1_aff *Aout, fe *Bout, const g2_aff *Vin,
+__global__ void __launch_bounds__(SLP_T, 4) ks_oa_fold(const g1_aff *Ain, const fe *Bin, g1_aff *Aout, fe *Bout, const g2_aff *Vin,
                                                    g2_aff *Vout, const fe *X, const fe *Xinv, uint64_t K, uint64_t nb,
                                                    uint64_t h, uint32_t j, uint32_t lK) {
   CHAIN_PRIORITY();
   __shared__ f29 S[imax<G1_SLOTS, G2_SLOTS>::v];
+  CALL_LIST();
+  Ctx c{S, calls_sh};
   __shared__ glv::Dec d1;
   __shared__ gls::Dec d2;
   uint64_t id = blockIdx.x;
@@ -407,34 +438,37 @@ __global__ void __launch_bounds__(SLP_T) ks_oa_fold(const g1_aff *Ain, const fe 
   if (g2) id -= nb * h;
   uint64_t k = id / h, i = id % h, slot = k * lK + (j - 1);
   if (g2) {
-    g2_job(S, &d2, Vin + k * K + h + i, Xinv + slot, Vin + k * K + i, Vout + k * K + i, nullptr);
+    g2_job(c, &d2, Vin + k * K + h + i, Xinv + slot, Vin + k * K + i, Vout + k * K + i, nullptr);
     return;
   }
   if (threadIdx.x == 32) Bout[k * K + i] = fr_add(Bin[k * K + i], fr_mul(Bin[k * K + h + i], Xinv[slot]));
-  g1_job(S, &d1, Ain + k * K + h + i, X + slot, Ain + k * K + i, Aout + k * K + i, nullptr);
+  g1_job(c, &d1, Ain + k * K + h + i, X + slot, Ain + k * K + i, Aout + k * K + i, nullptr);
 }
 
 // The next round's terms (oa_terms.hpp): the Miller loops into F[out], a workgroup per term
-__global__ void __launch_bounds__(SLP_T) ks_oa_pterms(const g1_aff *A, const g2_aff *V, uint64_t K, uint64_t nb, uint64_t q,
+__global__ void __launch_bounds__(SLP_T, 4) ks_oa_pterms(const g1_aff *A, const g2_aff *V, uint64_t K, uint64_t nb, uint64_t q,
                                                      fp12 *F) {
   CHAIN_PRIORITY();
   __shared__ f29 S[slp::ML_NSLOT];
+  CALL_LIST();
   uint64_t id = blockIdx.x;
   if (id >= nb * 8 * q) return;
   oat::Term tm = oat::term(id, K, nb, q);
-  miller_one(S, A + tm.a, V + tm.v, F + tm.out);
+  miller_one(CtxInline{S, calls_sh}, A + tm.a, V + tm.v, F + tm.out);
 }
 
 // The G1 terms b[v] A[a] of the next round into S1[out] (Jacobian), a workgroup per term
-__global__ void __launch_bounds__(SLP_T) ks_oa_g1terms_next(const g1_aff *A, const fe *B, uint64_t K, uint64_t nb, uint64_t q,
+__global__ void __launch_bounds__(SLP_T, 4) ks_oa_g1terms_next(const g1_aff *A, const fe *B, uint64_t K, uint64_t nb, uint64_t q,
                                                            g1_jac *S1) {
   AHEAD_PRIORITY();
   __shared__ f29 S[G1_SLOTS];
+  CALL_LIST();
+  Ctx c{S, calls_sh};
   __shared__ glv::Dec d1;
   uint64_t id = blockIdx.x;
   if (id >= nb * 8 * q) return;
   oat::Term tm = oat::term(id, K, nb, q);
-  g1_job(S, &d1, A + tm.a, B + tm.v, nullptr, nullptr, S1 + tm.out);
+  g1_job(c, &d1, A + tm.a, B + tm.v, nullptr, nullptr, S1 + tm.out);
 }
 
 // ---------------------------------------------------------------- cyclotomic G_T powers
@@ -443,9 +477,11 @@ __global__ void __launch_bounds__(SLP_T) ks_oa_g1terms_next(const g1_aff *A, con
 // ---------------------------------------------------------------- split multiplications
 // Multiples for the time-split multiplications: M[3 s + m - 1] = G[s]^{2^{16 m}} (cyclotomic
 // squarings), a workgroup per (s, m), m = 1, 2, 3
-__global__ void __launch_bounds__(SLP_T) ks_gt_sqr_mults(const fp12 *G, uint64_t n, fp12 *M) {
+__global__ void __launch_bounds__(SLP_T, 4) ks_gt_sqr_mults(const fp12 *G, uint64_t n, fp12 *M) {
   CHAIN_PRIORITY();
   __shared__ f29 S[slp::FE_NSLOT + 24];
+  CALL_LIST();
+  CtxInline c{S, calls_sh};
   uint64_t id = blockIdx.x;
   if (id >= 3 * n) return;
   uint64_t s = id / 3, m = id % 3 + 1;
@@ -454,13 +490,11 @@ __global__ void __launch_bounds__(SLP_T) ks_gt_sqr_mults(const fp12 *G, uint64_t
   if (t < 12) S[FE_BUF(0) + t] = slp::to29(src[t]);
   load_consts<slp::FE_NCONST>(S, slp::FE_CBASE, slp::FE_CONSTS);
   __syncthreads();
-  int b = 0;
-  for (int i = 0; i < 16 * (int)m; i++) {
-    slp::run1(S, slp::PROG_F12_CSQR, FE_BUF(b), FE_BUF(b), FE_BUF(1 - b));
-    b = 1 - b;
-  }
+  for (int e = t; e < 16 * (int)m; e += SLP_T)
+    c.cl[e] = slp::call(slp::PROG_F12_CSQR, FE_BUF(e & 1), FE_BUF(e & 1), FE_BUF(1 - (e & 1)));
+  c.run_list(0, 16 * (int)m, 0, 0);  // an even number of squarings: the result is in buffer 0
   fe *dst = reinterpret_cast<fe *>(M + 3 * s + m - 1);
-  if (t < 12) dst[t] = slp::from29(slp::canon29(S[FE_BUF(b) + t]));
+  if (t < 12) dst[t] = slp::from29(slp::canon29(S[FE_BUF(0) + t]));
 }
 
 // point s of a segmented list: P[(s / seg) segstride + s % seg]
@@ -468,88 +502,82 @@ __device__ __forceinline__ uint64_t seg_index(uint64_t s, uint64_t seg, uint64_t
   return (s / seg) * segstride + s % seg;
 }
 
+// prog n times on the same slots
+__device__ void repeat(Ctx c, int prog, int n) {
+  for (int e = threadIdx.x; e < n; e += SLP_T) c.cl[e] = slp::call(prog, 0, 0, 0);
+  c.run_list(0, n, 0, 0);
+}
+
 // 2^{32 m} P (affine) by 16 m double doublings on the engine
-__device__ void g1_dbl_mult(f29 *S, const g1_aff *P, int m, g1_aff *o) {
+__device__ void g1_dbl_mult(Ctx c, const g1_aff *P, int m, g1_aff *o) {
+  f29 *S = c.S;
   const int t = threadIdx.x;
   bool inf = g1_inf(*P);
   if (!inf) {
     load_consts<slp::G1_NCONST>(S, slp::G1_CBASE, slp::G1_CONSTS);
     if (t < 3) S[slp::G1_T_0 + t] = slp::to29(t == 2 ? f_one<FpP>() : t ? P->y : P->x);
-    __syncthreads();
-    for (int i = 0; i < 16 * m; i++) slp::run1(S, slp::PROG_G1_DBL2, 0, 0, 0);
+    repeat(c, slp::PROG_G1_DBL2, 16 * m);
   }
-  g1_store_aff(S, inf, o);
+  g1_store_aff(c, inf, o);
 }
 
 // 2^{16 m} Q (affine) by 16 m doublings on the engine
-__device__ void g2_dbl_mult(f29 *S, const g2_aff *Q, int m, g2_aff *o) {
+__device__ void g2_dbl_mult(Ctx c, const g2_aff *Q, int m, g2_aff *o) {
+  f29 *S = c.S;
   const int t = threadIdx.x;
   bool inf = g2_inf(*Q);
   if (!inf) {
     load_consts<slp::G2_NCONST>(S, slp::G2_CBASE, slp::G2_CONSTS);
     const fe *q = reinterpret_cast<const fe *>(Q);
     if (t < 6) S[slp::G2_T_0 + t] = t < 4 ? slp::to29(q[t]) : slp::to29(t == 4 ? f_one<FpP>() : fe_zero());
-    __syncthreads();
-    for (int i = 0; i < 16 * m; i++) slp::run1(S, slp::PROG_G2_DBL, 0, 0, 0);
+    repeat(c, slp::PROG_G2_DBL, 16 * m);
   }
-  g2_store_aff(S, inf, o);
+  g2_store_aff(c, inf, o);
 }
 
 // 2^{32 m} P (affine) for a Jacobian P (m = 0: P itself), on the engine
-__device__ void g1_jac_mult_aff(f29 *S, const g1_jac *P, int m, g1_aff *o) {
+__device__ void g1_jac_mult_aff(Ctx c, const g1_jac *P, int m, g1_aff *o) {
+  f29 *S = c.S;
   const int t = threadIdx.x;
   const fe *pj = reinterpret_cast<const fe *>(P);
   bool inf = fe_is_zero(pj[2]);
   if (!inf) {
     load_consts<slp::G1_NCONST>(S, slp::G1_CBASE, slp::G1_CONSTS);
     if (t < 3) S[slp::G1_T_0 + t] = slp::to29(pj[t]);
-    __syncthreads();
-    for (int i = 0; i < 16 * m; i++) slp::run1(S, slp::PROG_G1_DBL2, 0, 0, 0);
+    repeat(c, slp::PROG_G1_DBL2, 16 * m);
   }
-  g1_store_aff(S, inf, o);
+  g1_store_aff(c, inf, o);
 }
 
 // M[3 s + m - 1] = 2^{16 m} Q_s (affine), Q_s as in seg_index, a workgroup per (s, m), m = 1, 2, 3
-__global__ void __launch_bounds__(SLP_T) ks_g2_dbl_mults(const g2_aff *Q, uint64_t seg, uint64_t segstride, uint64_t n,
+__global__ void __launch_bounds__(SLP_T, 4) ks_g2_dbl_mults(const g2_aff *Q, uint64_t seg, uint64_t segstride, uint64_t n,
                                                         g2_aff *M) {
   __shared__ f29 S[G2_SLOTS];
+  CALL_LIST();
+  Ctx c{S, calls_sh};
   uint64_t id = blockIdx.x;
   if (id >= 3 * n) return;
   uint64_t s = id / 3, m = id % 3 + 1;
-  g2_dbl_mult(S, Q + seg_index(s, seg, segstride), (int)m, M + 3 * s + m - 1);
+  g2_dbl_mult(c, Q + seg_index(s, seg, segstride), (int)m, M + 3 * s + m - 1);
 }
 
 // the multiples of a round's arrays in one launch: blocks [0, 3 n1) M1[3 s + m - 1] =
 // 2^{32 m} P_s (G1, P_s at seg_index(s, seg1, segstride)), blocks [3 n1, 3 (n1 + n2))
 // M2[3 s + m - 1] = 2^{16 m} Q_s (G2, seg2)
-__global__ void __launch_bounds__(SLP_T) ks_fold_mults(const g1_aff *P, uint64_t seg1, uint64_t n1, const g2_aff *Q,
+__global__ void __launch_bounds__(SLP_T, 4) ks_fold_mults(const g1_aff *P, uint64_t seg1, uint64_t n1, const g2_aff *Q,
                                                       uint64_t seg2, uint64_t n2, uint64_t segstride, g1_aff *M1,
                                                       g2_aff *M2) {
   CHAIN_PRIORITY();
   __shared__ f29 S[imax<G1_SLOTS, G2_SLOTS>::v];
+  CALL_LIST();
+  Ctx c{S, calls_sh};
   uint64_t id = blockIdx.x;
   if (id >= 3 * (n1 + n2)) return;
   bool g2 = id >= 3 * n1;
   if (g2) id -= 3 * n1;
   uint64_t s = id / 3, m = id % 3 + 1;
-  if (g2) g2_dbl_mult(S, Q + seg_index(s, seg2, segstride), (int)m, M2 + 3 * s + m - 1);
-  else g1_dbl_mult(S, P + seg_index(s, seg1, segstride), (int)m, M1 + 3 * s + m - 1);
-}
-
-// of the four parts of one multiplication, the workgroup that finishes last returns true
-// (and resets the counter); partial results written before are visible to it
-__device__ bool last_of_four(uint32_t *cnt, uint32_t *flag) {
-  __threadfence();
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t old = atomicAdd(cnt, 1u);
-    if (old == 3) *cnt = 0;
-    *flag = old == 3;
-  }
-  __syncthreads();
-  bool last = *flag;
-  if (last) __threadfence();
-  return last;
+  if (g2) g2_dbl_mult(c, Q + seg_index(s, seg2, segstride), (int)m, M2 + 3 * s + m - 1);
+  else g1_dbl_mult(c, P + seg_index(s, seg1, segstride), (int)m, M1 + 3 * s + m - 1);
 }
 
 // The fold of round j with every multiplication split in four parts run in parallel (M1
@@ -561,13 +589,15 @@ __device__ bool last_of_four(uint32_t *cnt, uint32_t *flag) {
 // p = 3) of the GLS split into J2[4 s + p] (s = k h + i).  The last part to finish adds the
 // four partial results and A[i] (V[i]) and writes the affine result; part 0 of G1 also
 // folds b.  Same results as ks_oa_fold.
-__global__ void __launch_bounds__(SLP_T) ks_oa_fold_split(const g1_aff *Ain, const fe *Bin, g1_aff *Aout, fe *Bout,
+__global__ void __launch_bounds__(SLP_T, 4) ks_oa_fold_split(const g1_aff *Ain, const fe *Bin, g1_aff *Aout, fe *Bout,
                                                          const g2_aff *Vin, g2_aff *Vout, const fe *X, const fe *Xinv,
                                                          const g1_aff *M1, const g2_aff *M2, g1_jac *J1, g2_jac *J2,
                                                          uint32_t *cnt, uint64_t K, uint64_t nb, uint64_t h, uint32_t j,
                                                          uint32_t lK) {
   CHAIN_PRIORITY();
   __shared__ f29 S[imax<G1_SLOTS, G2_SLOTS>::v];
+  CALL_LIST();
+  Ctx c{S, calls_sh};
   __shared__ glv::Dec d1;
   __shared__ gls::Dec d2;
   __shared__ uint32_t flag;
@@ -578,12 +608,11 @@ __global__ void __launch_bounds__(SLP_T) ks_oa_fold_split(const g1_aff *Ain, con
   if (g2) id -= 4 * n;
   uint64_t s = id >> 2, k = s / h, i = s % h, slot = k * lK + (j - 1);
   int part = (int)(id & 3);
-  slp::DevCtx c{S};
   if (!g2) {
     if (part == 0 && t == 32) Bout[k * K + i] = fr_add(Bin[k * K + i], fr_mul(Bin[k * K + h + i], Xinv[slot]));
-    g1_job(S, &d1, part ? M1 + 3 * (k * 2 * h + h + i) + part - 1 : Ain + k * K + h + i, X + slot, nullptr, nullptr,
+    g1_job(c, &d1, part ? M1 + 3 * (k * 2 * h + h + i) + part - 1 : Ain + k * K + h + i, X + slot, nullptr, nullptr,
            J1 + 4 * s + part, part);
-    if (!last_of_four(cnt + s, &flag)) return;
+    if (!last_arrival(cnt + s, 4, &flag)) return;
     // sum of the parts (in the table slots) and A[i]
     const fe *pj = reinterpret_cast<const fe *>(J1 + 4 * s);
     if (t < 12) S[slp::G1_TB1_0 + t] = slp::to29(pj[t]);
@@ -593,12 +622,12 @@ __global__ void __launch_bounds__(SLP_T) ks_oa_fold_split(const g1_aff *Ain, con
     bool inf = true;
     for (int p = 0; p < 4; p++) g1m::add_jac(c, inf, slp::G1_TB1_0 + 3 * p, fe_is_zero(J1[4 * s + p].Z));
     if (!g1_inf(*A)) g1m::add_affine(c, inf, G1_ABASE, S[slp::G1_CBASE + 1]);
-    g1_store_aff(S, inf, Aout + k * K + i);
+    g1_store_aff(c, inf, Aout + k * K + i);
     return;
   }
-  g2_job(S, &d2, part ? M2 + 3 * s + part - 1 : Vin + k * K + h + i, Xinv + slot, nullptr, nullptr, J2 + 4 * s + part,
+  g2_job(c, &d2, part ? M2 + 3 * s + part - 1 : Vin + k * K + h + i, Xinv + slot, nullptr, nullptr, J2 + 4 * s + part,
          16 * part, part < 3 ? 16 : 17);
-  if (!last_of_four(cnt + n + s, &flag)) return;
+  if (!last_arrival(cnt + n + s, 4, &flag)) return;
   const fe *pj = reinterpret_cast<const fe *>(J2 + 4 * s);
   if (t < 24) S[slp::G2_TB1_0 + t] = slp::to29(pj[t]);
   const fe *a = reinterpret_cast<const fe *>(Vin + k * K + i);
@@ -610,17 +639,19 @@ __global__ void __launch_bounds__(SLP_T) ks_oa_fold_split(const g1_aff *Ain, con
     g2m::add_jac(c, inf, slp::G2_TB1_0 + 6 * p, fe_is_zero(Jp.Z.c0) && fe_is_zero(Jp.Z.c1));
   }
   if (!g2_inf(Vin[k * K + i])) g2m::add_affine(c, inf, G2_ABASE, S[slp::G2_CBASE + 1], S[slp::G2_CBASE]);
-  g2_store_aff(S, inf, Vout + k * K + i);
+  g2_store_aff(c, inf, Vout + k * K + i);
 }
 
 // The G1 terms b[v] A[a] of the next round (oa_terms.hpp, arrays of length 4q) with each
 // multiplication split in four parts: part p on the multiple M[3 (k 4q + a') + p - 1] =
 // 2^{32 p} A[k K + a'] (p > 0) with the p-th 32-bit chunk of the GLV split of b[v], into
 // J[4 term + p]; the last part to finish writes the sum to S1[out] (Jacobian)
-__global__ void __launch_bounds__(SLP_T) ks_oa_g1terms_split(const g1_aff *A, const fe *B, const g1_aff *M, uint64_t K,
+__global__ void __launch_bounds__(SLP_T, 4) ks_oa_g1terms_split(const g1_aff *A, const fe *B, const g1_aff *M, uint64_t K,
                                                             uint64_t nb, uint64_t q, g1_jac *J, uint32_t *cnt, g1_jac *S1) {
   AHEAD_PRIORITY();
   __shared__ f29 S[G1_SLOTS];
+  CALL_LIST();
+  Ctx c{S, calls_sh};
   __shared__ glv::Dec d1;
   __shared__ uint32_t flag;
   uint64_t id = blockIdx.x;
@@ -629,13 +660,12 @@ __global__ void __launch_bounds__(SLP_T) ks_oa_g1terms_split(const g1_aff *A, co
   uint64_t term = id >> 2, k = term / (8 * q);
   int part = (int)(id & 3);
   oat::Term tm = oat::term(term, K, nb, q);
-  g1_job(S, &d1, part ? M + 3 * (k * 4 * q + (tm.a - k * K)) + part - 1 : A + tm.a, B + tm.v, nullptr, nullptr,
+  g1_job(c, &d1, part ? M + 3 * (k * 4 * q + (tm.a - k * K)) + part - 1 : A + tm.a, B + tm.v, nullptr, nullptr,
          J + 4 * term + part, part);
-  if (!last_of_four(cnt + term, &flag)) return;
+  if (!last_arrival(cnt + term, 4, &flag)) return;
   const fe *pj = reinterpret_cast<const fe *>(J + 4 * term);
   if (t < 12) S[slp::G1_TB1_0 + t] = slp::to29(pj[t]);
   __syncthreads();
-  slp::DevCtx c{S};
   bool inf = true;
   for (int p = 0; p < 4; p++) g1m::add_jac(c, inf, slp::G1_TB1_0 + 3 * p, fe_is_zero(J[4 * term + p].Z));
   fe *o = reinterpret_cast<fe *>(S1 + tm.out);
@@ -649,11 +679,13 @@ __global__ void __launch_bounds__(SLP_T) ks_oa_g1terms_split(const g1_aff *A, co
 // restricted to bits [16 p, 16 p + 16) (17 bits for p = 3); blocks [16 nb, 32 nb):
 // PM[4 s + p] = chunk_p(k_s) (2^{32 p} PX1[s]) (Jacobian).  Multiples come from
 // ks_gt_sqr_mults and ks_g1_dbl_mults (PXm, PX1m).
-__global__ void __launch_bounds__(SLP_T) ks_oa_combine_split(const fp12 *PX, const fp12 *PXm, const g1_aff *PX1,
+__global__ void __launch_bounds__(SLP_T, 4) ks_oa_combine_split(const fp12 *PX, const fp12 *PXm, const g1_aff *PX1,
                                                             const g1_aff *PX1m, const fe *k_even, const fe *k_odd,
                                                             uint64_t kstride, uint64_t nb, fp12 *PE, g1_jac *PM) {
   CHAIN_PRIORITY();
   __shared__ f29 S[imax<GTP_SLOTS, G1_SLOTS>::v];
+  CALL_LIST();
+  Ctx c{S, calls_sh};
   __shared__ gls::Dec dec;
   __shared__ glv::Dec d1;
   uint64_t id = blockIdx.x;
@@ -665,7 +697,7 @@ __global__ void __launch_bounds__(SLP_T) ks_oa_combine_split(const fp12 *PX, con
   int part = (int)(id & 3);
   const fe *k = (s & 1 ? k_odd : k_even) + (s >> 2) * kstride;
   if (g1) {
-    g1_job(S, &d1, part ? PX1m + 3 * s + part - 1 : PX1 + s, k, nullptr, nullptr, PM + 4 * s + part, part);
+    g1_job(c, &d1, part ? PX1m + 3 * s + part - 1 : PX1 + s, k, nullptr, nullptr, PM + 4 * s + part, part);
     return;
   }
   if (t == 0) {
@@ -676,7 +708,6 @@ __global__ void __launch_bounds__(SLP_T) ks_oa_combine_split(const fp12 *PX, con
   if (t < 12) S[FE_BUF(0) + t] = slp::to29(src[t]);
   load_consts<slp::FE_NCONST>(S, slp::FE_CBASE, slp::FE_CONSTS);
   __syncthreads();
-  slp::DevCtx c{S};
   int r = gtp::pow_cyc(c, dec, slp::FE_NSLOT);
   fe *dst = reinterpret_cast<fe *>(PE + 4 * s + part);
   if (t < 12) dst[t] = r < 0 ? (t == 0 ? f_one<FpP>() : fe_zero()) : slp::from29(slp::canon29(S[FE_BUF(r) + t]));
@@ -686,10 +717,12 @@ __global__ void __launch_bounds__(SLP_T) ks_oa_combine_split(const fp12 *PX, con
 // (side ? R : L)[k lK] = U[2k + side] prod_{g in {2 side, 2 side + 1}, p < 4} P[4 (4k + g) + p]
 // (G_T, engine); blocks [2 nb, 4 nb): the G1 parts U1[2k + side] + sum of the 8 Jacobian
 // parts P1[4 (4k + 2 side) + i] (a tree over 8 lanes), affine, into L1 / R1.
-__global__ void __launch_bounds__(SLP_T) ks_oa_combine8(const fp12 *U, const fp12 *P, const g1_aff *U1, const g1_jac *P1,
+__global__ void __launch_bounds__(SLP_T, 4) ks_oa_combine8(const fp12 *U, const fp12 *P, const g1_aff *U1, const g1_jac *P1,
                                                        uint64_t nb, fp12 *L, fp12 *R, g1_aff *L1, g1_aff *R1, uint64_t lK) {
   CHAIN_PRIORITY();
-  __shared__ f29 S[slp::FE_NSLOT + 36];
+  __shared__ f29 S[slp::FE_NSLOT + 12 * 11];
+  CALL_LIST();
+  CtxInline c{S, calls_sh};
   uint64_t id = blockIdx.x;
   if (id >= 4 * nb) return;
   if (id >= 2 * nb) {
@@ -708,62 +741,48 @@ __global__ void __launch_bounds__(SLP_T) ks_oa_combine8(const fp12 *U, const fp1
   }
   uint64_t k = id / 2, side = id % 2;
   const int t = threadIdx.x;
-  const fe *u = reinterpret_cast<const fe *>(U + id);
-  if (t < 12) S[FE_BUF(0) + t] = slp::to29(u[t]);
+  // buffers 0 and 1 the product (alternating, U first), 2..9 the powers
+  const fe *u = reinterpret_cast<const fe *>(U + id), *pp = reinterpret_cast<const fe *>(P + 4 * (4 * k + 2 * side));
+  for (int i = t; i < 12 * 9; i += SLP_T) S[i < 12 ? FE_BUF(0) + i : FE_BUF(1) + i] = slp::to29(i < 12 ? u[i] : pp[i - 12]);
   load_consts<slp::FE_NCONST>(S, slp::FE_CBASE, slp::FE_CONSTS);
-  int acc = 0;
-  for (int i = 0; i < 8; i++) {
-    const fe *pi = reinterpret_cast<const fe *>(P + 4 * (4 * k + 2 * side) + i);
-    if (t < 12) S[FE_BUF(1) + t] = slp::to29(pi[t]);
-    __syncthreads();
-    slp::run1(S, slp::PROG_F12_MUL, FE_BUF(acc), FE_BUF(1), FE_BUF(2 - acc));
-    acc = 2 - acc;
-  }
+  if (t < 8) c.cl[t] = slp::call(slp::PROG_F12_MUL, FE_BUF(t & 1), FE_BUF(2 + t), FE_BUF(1 - (t & 1)));
+  c.run_list(0, 8, 0, 0);
   fe *dst = reinterpret_cast<fe *>((side ? R : L) + k * lK);
-  if (t < 12) dst[t] = slp::from29(slp::canon29(S[FE_BUF(acc) + t]));
+  if (t < 12) dst[t] = slp::from29(slp::canon29(S[FE_BUF(0) + t]));
 }
 
 // final exponentiations of two strided lists: job s < n0 takes in0[s st0] to out0[s], the
 // others in1[(s - n0) st1] to out1[s - n0]
-// final exponentiation of one F_p12 element on the engine
-__device__ void fe_job(f29 *S, const fp12 *in, fp12 *out) {
-  int t = threadIdx.x;
-  const fe *src = reinterpret_cast<const fe *>(in);
-  if (t < 12) S[FE_BUF(0) + t] = slp::to29(src[t]);
-  load_consts<slp::FE_NCONST>(S, slp::FE_CBASE, slp::FE_CONSTS);
-  __syncthreads();
-  slp::run_seq<4>(S, slp::FE_SEQ, slp::FE_SEQ_LEN, slp::FE_NSLOT, slp::FE_t, slp::FE_tinv);
-  fe *dst = reinterpret_cast<fe *>(out);
-  if (t < 12) dst[t] = slp::from29(slp::canon29(S[FE_BUF(slp::FE_RESULT) + t]));
-}
-
-__global__ void __launch_bounds__(SLP_T) ks_final_exp2(const fp12 *in0, uint64_t st0, uint64_t n0, fp12 *out0, const fp12 *in1,
+__global__ void __launch_bounds__(SLP_T, 4) ks_final_exp2(const fp12 *in0, uint64_t st0, uint64_t n0, fp12 *out0, const fp12 *in1,
                                                       uint64_t st1, uint64_t n1, fp12 *out1) {
   CHAIN_PRIORITY();
   __shared__ f29 S[FE_SLOTS];
+  CALL_LIST();
   uint64_t s = blockIdx.x;
   if (s >= n0 + n1) return;
-  fe_job(S, s < n0 ? in0 + s * st0 : in1 + (s - n0) * st1, s < n0 ? out0 + s : out1 + (s - n0));
+  fe_job(CtxInline{S, calls_sh}, s < n0 ? in0 + s * st0 : in1 + (s - n0) * st1, s < n0 ? out0 + s : out1 + (s - n0));
 }
 
 // The reduced G1 groups of the terms taken ahead (oa_terms.hpp, segment sums in PS) made
 // ready for the combine: blocks [0, 2 nb): U group (2k + side) to PU1 (affine); blocks
 // [2 nb, 18 nb): XY group s = 4k + g as PX1[s] (affine, m = 0) and PX1m[3 s + m - 1] =
 // 2^{32 m} PX1[s] (m = 1..3)
-__global__ void __launch_bounds__(SLP_T) ks_g1_finish(const g1_jac *PS, uint64_t nb, uint64_t q, g1_aff *PU1, g1_aff *PX1,
+__global__ void __launch_bounds__(SLP_T, 4) ks_g1_finish(const g1_jac *PS, uint64_t nb, uint64_t q, g1_aff *PU1, g1_aff *PX1,
                                                      g1_aff *PX1m) {
   AHEAD_PRIORITY();
   __shared__ f29 S[G1_SLOTS];
+  CALL_LIST();
+  Ctx c{S, calls_sh};
   uint64_t id = blockIdx.x;
   if (id >= 18 * nb) return;
   if (id < 2 * nb) {
-    g1_jac_mult_aff(S, PS + id * 2 * q, 0, PU1 + id);
+    g1_jac_mult_aff(c, PS + id * 2 * q, 0, PU1 + id);
     return;
   }
   id -= 2 * nb;
   uint64_t s = id >> 2;
   int m = (int)(id & 3);
-  g1_jac_mult_aff(S, PS + nb * 4 * q + s * q, m, m ? PX1m + 3 * s + m - 1 : PX1 + s);
+  g1_jac_mult_aff(c, PS + nb * 4 * q + s * q, m, m ? PX1m + 3 * s + m - 1 : PX1 + s);
 }
 
 namespace ks {

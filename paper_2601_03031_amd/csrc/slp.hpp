@@ -1,18 +1,20 @@
-// Wave-cooperative straight-line-program engine (device only, packed field layout).
+// Workgroup-cooperative straight-line-program engine (device only, packed field layout).
 //
-// One 64-lane workgroup (a single wavefront) runs a program generated by gen_slp.py:
-// a sequence of levels, each a set of at most 64 independent base-field operations
-// that the lanes execute together on field elements held in LDS slots.  An operation
-// (384 bits) is either
-//   LIN  dst = sum_i k_i x_i                      (up to 16 terms, |k_i| <= 127)
-//   MUL  dst = (sum_{i < 8} k_i x_i) (sum_{i >= 8} k_i x_i)
-// so additions feeding a product are folded into the product's lane.  Slots hold field
+// A workgroup of a few wavefronts runs programs generated by gen_slp.py: sequences of levels,
+// each a set of independent base-field operations on field elements held in LDS slots.  A pair
+// of lanes executes an operation, 32 operations a wavefront:
+//   MUL  dst = (sum_i k_i x_i) (sum_i l_i y_i)   each lane forms one factor, the lanes exchange
+//                                                them and form the product
+//   LIN  dst = sum_i k_i x_i                     each lane sums half of the terms
+// so additions feeding a product are folded into the product's lanes.  Slots hold field
 // elements as 9 limbs of 29 bits: every term and every partial product is one 32 x 32
-// multiply-add into a 64-bit column, with a single carry pass per result.  Within a level
-// every lane reads its operands before any lane writes (the loads precede the stores
-// in the wavefront's instruction stream) and the level ends in a barrier.  Slot fields
-// are 12 bits: 3-bit segment, 9-bit offset; segments 1..3 are relocated to the caller's
-// buffers X, Y and D.
+// multiply-add into a 64-bit column.  A level ends in a barrier; within a level no operation
+// writes a slot that another one reads, so the wavefronts need none in between.
+//
+// What bounds it: a level's time is the instruction stream of one wavefront (about 4 cycles an
+// instruction; the Montgomery product alone is 231 of them, 0.39 us), so a level is split
+// where it is free of dependences: the two factors of a product run on two lanes, a level's
+// operations on as many wavefronts (SIMDs) as it takes.
 #pragma once
 #include "field.hpp"
 #include "slp_progs.hpp"
@@ -21,7 +23,7 @@ namespace slp {
 
 // A slot: 9 limbs of 29 bits (little-endian, normalized), the same integer as the
 // 8 x 32-bit Montgomery form used elsewhere (R = 2^256); words 9..11 pad to 48 bytes.
-struct f29 {
+struct alignas(16) f29 {
   uint32_t l[12];
 };
 #define SLP_M29 0x1fffffffu
@@ -52,72 +54,108 @@ __host__ __device__ __forceinline__ fe from29(const f29 &x) {
   return r;
 }
 
-// Values in slots are kept in [0, 2p) ("almost reduced"); only kernel outputs are made
-// canonical.  A linear combination is accumulated in signed 64-bit columns that start at
-// the offset 65536 p (a product factor: |sum| < 2^15 2p, so V lies in (0, 2^17 p)) or at
-// twice that (the two halves of a 16-term sum, each started at the offset: V in (0, 2^18 p)).
+// Values in slots are signed and "almost reduced": |x| < 1.2 p, limbs 0..7 signed and below
+// 2^29 + 2^23 in magnitude ("loose"), the top limb signed.  Only kernel outputs are made
+// canonical.  So no offset is carried through the sums, a negation is the negated limbs, and
+// the carries of a sum are taken once, all columns side by side.
 //
-// red29: q = floor(V / p) is estimated in double precision from the top two columns.  Every
-// column is below 2^46 in magnitude, so the neglected columns move the estimate by less than
-// 2^-33, and the rounding of the sum (below 2^40 in units of 2^232) and of the product by
-// 2^232 / p by less than 2^-34 each: floor(estimate - 1e-9) is the true quotient or one less,
-// so V - q p lies in [0, 2p); one signed carry pass then normalises the limbs.
+// red29: V = sum c_j 2^{29 j} minus its rounded quotient by p.  The coefficient magnitudes of
+// a sum add up to less than 2^15, so every column is below 2^45 (V below 2^16 p).  The
+// quotient is estimated in single precision from the top column: the columns below it move V / p
+// by less than 0.021, the dropped low bits by 2^-13, the roundings by less than 0.01 for
+// quotients below 2^16.  The sum with 1.5 2^23 rounds it to the nearest integer, so
+// |V - q p| < 0.54 p.
+__host__ __device__ __forceinline__ int32_t neg_quotient29(int64_t top) {
+  const float magic = 12582912.0f;
+  const float f = __builtin_fmaf((float)(int32_t)(top >> 8), INVP240, magic);
+  return (int32_t)(0x4B400000u - __builtin_bit_cast(uint32_t, f));
+}
 __host__ __device__ __forceinline__ f29 red29(const int64_t *c) {
-  double vhat = (double)c[8] + (double)c[7] * 0x1p-29;
-  int32_t q = (int32_t)(vhat * INVP232 - 1e-9);   // below 2^18
+  const int32_t nq = neg_quotient29(c[8]);
+  f29 o;
+  int64_t v[8];
+#pragma unroll
+  for (int j = 0; j < 8; j++) v[j] = c[j] + (int64_t)nq * (int32_t)P29[j];
+  o.l[8] = (uint32_t)c[8] + (uint32_t)nq * P29[8] + (uint32_t)(v[7] >> 29);
+#pragma unroll
+  for (int j = 0; j < 8; j++) o.l[j] = ((uint32_t)v[j] & SLP_M29) + (j ? (uint32_t)(v[j - 1] >> 29) : 0u);
+  o.l[9] = o.l[10] = o.l[11] = 0;
+  return o;
+}
+
+// the same value with limbs 0..7 in [0, 2^29)
+__host__ __device__ __forceinline__ f29 norm29(const f29 &x) {
+  f29 o;
+  int32_t carry = 0;
+#pragma unroll
+  for (int j = 0; j < 8; j++) {
+    const int32_t v = (int32_t)x.l[j] + carry;
+    o.l[j] = (uint32_t)v & SLP_M29;
+    carry = v >> 29;
+  }
+  o.l[8] = x.l[8] + (uint32_t)carry;
+  o.l[9] = o.l[10] = o.l[11] = 0;
+  return o;
+}
+
+// canonical residue of an almost-reduced value: x + 2p lies in (0.8 p, 3.2 p), so p is taken
+// off three times where it fits
+__host__ __device__ __forceinline__ f29 canon29(const f29 &x) {
+  f29 y = x;
+#pragma unroll
+  for (int j = 0; j < 9; j++) y.l[j] += 2 * P29[j];
+  y = norm29(y);
+#pragma unroll
+  for (int k = 0; k < 3; k++) {
+    f29 d = y;
+#pragma unroll
+    for (int j = 0; j < 9; j++) d.l[j] -= P29[j];
+    d = norm29(d);
+    if ((int32_t)d.l[8] >= 0) y = d;
+  }
+  return y;
+}
+
+// keeps the instructions written before it ahead of those written after it
+#ifdef __HIP_DEVICE_COMPILE__
+#define SLP_ORDER() __builtin_amdgcn_sched_barrier(0)
+#else
+#define SLP_ORDER()
+#endif
+
+// Montgomery product with radix 2^29 over 9 limbs: a b 2^{-261} mod p for almost-reduced a and
+// b, result in (-0.01 p, 1.01 p) with limbs 0..7 in [0, 2^29).  Products go into signed 64-bit
+// columns without carries (each column stays below 2^62.5); the reduction clears one column at
+// a time.  The order is fixed row by row: a multiply-add that needs the one before it issues
+// after 8 cycles instead of 4, and left to itself the compiler sums each column in one
+// dependent chain to save registers (1512 cycles a product against 930 in this order).
+__host__ __device__ __forceinline__ f29 mont29(const f29 &a, const f29 &b) {
+  int64_t c[18];
+#pragma unroll
+  for (int k = 0; k < 18; k++) c[k] = 0;
+#pragma unroll
+  for (int j = 0; j < 9; j++) c[j] = (int64_t)(int32_t)a.l[0] * (int32_t)b.l[j];
+#pragma unroll
+  for (int k = 0; k < 9; k++) {
+    SLP_ORDER();
+    const uint32_t t = (uint32_t)c[k] * PINV29;
+    SLP_ORDER();
+    if (k < 8) {
+#pragma unroll
+      for (int j = 0; j < 9; j++) c[k + 1 + j] += (int64_t)(int32_t)a.l[k + 1] * (int32_t)b.l[j];
+    }
+    SLP_ORDER();
+    const int32_t m = (int32_t)(t & SLP_M29);
+#pragma unroll
+    for (int j = 0; j < 9; j++) c[k + j] += (int64_t)m * (int32_t)P29[j];
+    SLP_ORDER();
+    c[k + 1] += c[k] >> 29;
+  }
   f29 o;
   int64_t carry = 0;
 #pragma unroll
   for (int j = 0; j < 8; j++) {
-    int64_t v = c[j] + (int64_t)(-q) * (int32_t)P29[j] + carry;
-    o.l[j] = (uint32_t)v & SLP_M29;
-    carry = v >> 29;
-  }
-  o.l[8] = (uint32_t)(c[8] + (int64_t)(-q) * (int32_t)P29[8] + carry);
-  o.l[9] = o.l[10] = o.l[11] = 0;
-  return o;
-}
-
-// canonical residue of an almost-reduced value (below 2p)
-__host__ __device__ __forceinline__ f29 canon29(const f29 &x) {
-  uint32_t d[9];
-  int64_t bw = 0;
-#pragma unroll
-  for (int j = 0; j < 9; j++) {
-    int64_t v = (int64_t)x.l[j] - P29[j] + bw;
-    d[j] = (uint32_t)v & SLP_M29;
-    bw = v >> 29;
-  }
-  f29 o;
-#pragma unroll
-  for (int j = 0; j < 9; j++) o.l[j] = bw < 0 ? x.l[j] : d[j];
-  o.l[9] = o.l[10] = o.l[11] = 0;
-  return o;
-}
-
-// Montgomery product with radix 2^29 over 9 limbs: a b 2^{-261} mod p, for a, b < 2p,
-// result below 2p.  Products go into 64-bit columns without carries (each column stays
-// below 2^63); the reduction clears one column at a time.
-__host__ __device__ __forceinline__ f29 mont29(const f29 &a, const f29 &b) {
-  uint64_t c[18];
-#pragma unroll
-  for (int k = 0; k < 18; k++) c[k] = 0;
-#pragma unroll
-  for (int i = 0; i < 9; i++)
-#pragma unroll
-    for (int j = 0; j < 9; j++) c[i + j] += (uint64_t)a.l[i] * b.l[j];
-#pragma unroll
-  for (int k = 0; k < 9; k++) {
-    uint32_t m = ((uint32_t)c[k] * PINV29) & SLP_M29;
-#pragma unroll
-    for (int j = 0; j < 9; j++) c[k + j] += (uint64_t)m * P29[j];
-    c[k + 1] += c[k] >> 29;
-  }
-  f29 o;
-  uint64_t carry = 0;
-#pragma unroll
-  for (int j = 0; j < 8; j++) {
-    uint64_t v = c[9 + j] + carry;
+    const int64_t v = c[9 + j] + carry;
     o.l[j] = (uint32_t)v & SLP_M29;
     carry = v >> 29;
   }
@@ -126,257 +164,333 @@ __host__ __device__ __forceinline__ f29 mont29(const f29 &a, const f29 &b) {
   return o;
 }
 
-// 20-bit field at bit offset `bit` of the 384-bit operation (compile-time offsets); bits
-// above the field are left in place (every use below selects its bits)
-__host__ __device__ __forceinline__ uint32_t op_field(const uint64_t *w, int bit) {
-  int q = bit >> 6, s = bit & 63;
-  uint64_t v = w[q] >> s;
-  if (s > 44) v |= w[q + 1] << (64 - s);
-  return (uint32_t)v;
+// Segment bases in bytes packed 16 bits apiece: bits [16 s, 16 s + 16) hold the base of segment
+// s (segment 0 is absolute, so its base is 0).  Segments are 0..3.
+__host__ __device__ __forceinline__ uint64_t seg_bases(uint32_t bx, uint32_t by, uint32_t bd) {
+  return ((uint64_t)(bx * 48u) << 16) | ((uint64_t)(by * 48u) << 32) | ((uint64_t)(bd * 48u) << 48);
 }
 
-// Segment bases packed 16 bits apiece: bits [16 s, 16 s + 16) hold the base of segment s
-// (segment 0 is absolute, so its base is 0).  Segments are 0..3.
-__host__ __device__ __forceinline__ uint64_t seg_bases(int bx, int by, int bd) {
-  return ((uint64_t)(uint32_t)bx << 16) | ((uint64_t)(uint32_t)by << 32) | ((uint64_t)(uint32_t)bd << 48);
+// byte address of the slot that term t names: its segment's base is one shift of the packed
+// bases (bits 26..29 of a term are zero, so t >> 26 is 16 times the segment)
+__host__ __device__ __forceinline__ uint32_t term_addr(uint32_t t, uint64_t rel) {
+  return ((t & 0x7ffu) << 4) + ((uint32_t)(rel >> (t >> 26)) & 0xffffu);
 }
 
-// slot of a 12-bit slot field (bits 0..8 offset, 9..11 segment) of the raw field f: the
-// segment's base is one shift of the packed bases by 16 * segment
-__host__ __device__ __forceinline__ int slot_of(uint32_t f, uint64_t rel) {
-  const uint32_t sh = (f >> 5) & 0x30;
-  return (int)((uint32_t)(rel >> sh) & 0xffffu) + (int)(f & 511u);
+// signed 13-bit coefficient at bits 11..23 of a term
+__host__ __device__ __forceinline__ int term_coef(uint32_t t) { return (int)(t << 8) >> 19; }
+
+// a block descriptor's fields (gen_slp.py OpTable)
+static constexpr uint32_t BLK_OFF = (1u << 18) - 1, BLK_CHK = 1u << 18, BLK_T2 = 1u << 19, BLK_T4 = 1u << 20, BLK_T6 = 1u << 21,
+                          BLK_T10 = 1u << 22, BLK_SEG = 1u << 23, BLK_MUL = 1u << 30, BLK_LIN = 1u << 31;
+__host__ __device__ __forceinline__ int blk_ops(uint32_t d) { return (int)(d >> 24 & 63u); }
+__host__ __device__ __forceinline__ int blk_terms(uint32_t d) {
+  return d & BLK_T10 ? 14 : d & BLK_T6 ? 10 : d & BLK_T4 ? 6 : d & BLK_T2 ? 4 : 2;
+}
+// word i of lane l's record of the block
+__host__ __device__ __forceinline__ uint32_t blk_word(const uint32_t *ops, uint32_t d, int l, int i) {
+  return ops[4 * (d & BLK_OFF) + 256 * (i >> 2) + 4 * l + (i & 3)];
 }
 
-// signed 8-bit coefficient at bits 12..19 of the raw field f
-__host__ __device__ __forceinline__ int coef_of(uint32_t f) { return (int)(int8_t)(uint8_t)(f >> 12); }
-
-// Term groups used by the level of operation w (bit g: positions 4g .. 4g + 3): the
-// emitted mask is the same in every operation of a level; on the device it is read from
-// lane 0 (a level always starts at lane 0), so the group loop is uniform across the
-// wavefront.
-__host__ __device__ __forceinline__ int level_groups(const uint64_t *w) {
-#ifdef __HIP_DEVICE_COMPILE__
-  return __builtin_amdgcn_readfirstlane((int)(w[0] >> 14) & 15);
-#else
-  return (int)(w[0] >> 14) & 15;
-#endif
+// One call of a sequence: the program's first descriptors and the packed segment bases
+struct alignas(16) Call {
+  uint32_t d0, d1;
+  uint64_t rel;
+};
+__host__ __device__ __forceinline__ Call call(int prog, int x = 0, int y = 0, int d = 0) {
+  return Call{PROGS[prog].d[0], PROGS[prog].d[1], seg_bases(x, y, d)};
 }
+__host__ __device__ __forceinline__ bool call_is(const Call &c, int prog) { return c.d0 == PROGS[prog].d[0]; }
+__host__ __device__ __forceinline__ int call_y(const Call &c) { return (int)(c.rel >> 32 & 0xffffu) / 48; }
 
-// true if any active lane of the wavefront has `pred` (a single lane on the host)
-__host__ __device__ __forceinline__ bool any_lane(bool pred) {
-#ifdef __HIP_DEVICE_COMPILE__
-  return __ballot(pred) != 0;
-#else
-  return pred;
-#endif
-}
+static constexpr int MAX_CALLS = 256;
 
-// Evaluate one operation on the slots S (no write); returns its destination slot, or -1
-// for an empty lane.  A product scales its first factor's coefficients by 32, which turns
-// the radix-2^261 Montgomery product into the R = 2^256 one.
-// gmask: term groups used by any operation of the level (uniform)
-// (SP: a pointer to the slots; on the device an LDS-address-space pointer, so that every slot
-// access is a 32-bit LDS address with no generic-pointer checks)
-template <class SP>
-__host__ __device__ __forceinline__ int eval_op(SP S, const uint64_t *w, int gmask, int bx, int by, int bd, f29 &r) {
-  int kind = (int)(w[0] & 3);
-  if (!kind) return -1;
-  const int shift = kind == 1 ? 5 : 0;  // first factor's coefficients times 32
-  const uint64_t rel = seg_bases(bx, by, bd);
-  int64_t acc[9], accB[9];
-#pragma unroll
-  for (int j = 0; j < 9; j++) { acc[j] = OFF29[j]; accB[j] = OFF29[j]; }
-  // Terms are taken in groups of four (groups 0, 1: first factor of a product; 2, 3:
-  // second); within a group the loads are unconditional, so they issue back to back and
-  // their latencies overlap.  Unused positions hold slot 0 with coefficient 0.
-#pragma unroll
-  for (int g = 0; g < 4; g++) {
-    if (gmask >> g & 1) {
-      uint32_t x[4][9];
-      int k[4];
-#pragma unroll
-      for (int i = 0; i < 4; i++) {
-        uint32_t f = op_field(w, 18 + 20 * (4 * g + i));
-        const int c = coef_of(f);
-        k[i] = g < 2 ? (int)((uint32_t)c << shift) : c;
-        const int si = slot_of(f, rel);
-#pragma unroll
-        for (int j = 0; j < 9; j++) x[i][j] = S[si].l[j];
-      }
-      int64_t *ac = g < 2 ? acc : accB;
-#pragma unroll
-      for (int i = 0; i < 4; i++)
-#pragma unroll
-        for (int j = 0; j < 9; j++) ac[j] += (int64_t)k[i] * (int32_t)x[i][j];
-    }
-  }
-  if (kind == 1) {
-    r = mont29(red29(acc), red29(accB));
-  } else {  // the sum carries the offset twice
-#pragma unroll
-    for (int j = 0; j < 9; j++) acc[j] += accB[j];
-    r = red29(acc);
-  }
-  return slot_of((uint32_t)((w[0] >> 2) & 0xfff), rel);
+// whether an almost-reduced value may be congruent to 0, from its two low limbs alone (it is
+// then -p, 0 or p; another value passes with probability below 2^-56)
+__host__ __device__ __forceinline__ bool maybe_zero29(uint32_t l0, uint32_t l1) {
+  const uint64_t m = (1ull << 58) - 1;
+  const uint64_t v = ((uint64_t)(int64_t)(int32_t)l0 + ((uint64_t)l1 << 29)) & m, pv = (P29[0] + ((uint64_t)P29[1] << 29)) & m;
+  return v == 0 || v == pv || v == ((0 - pv) & m);
 }
 
 #ifdef __HIPCC__
 typedef __attribute__((address_space(3))) f29 lds_f29;
-__device__ __forceinline__ void put_slot(lds_f29 *SL, int i, const f29 &r) {
+typedef __attribute__((address_space(3))) Call lds_call;
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
+
+// the 9 limbs of the slot at an LDS address (slots are 16-byte aligned)
+__device__ __forceinline__ void get_slot(uint32_t addr, uint32_t *x) {
+  const lds_u32x4 *p = (const lds_u32x4 *)(uintptr_t)addr;
+  const u32x4 a = p[0], b = p[1];
+  x[8] = ((const lds_u32 *)p)[8];
 #pragma unroll
-  for (int j = 0; j < 12; j++) SL[i].l[j] = r.l[j];
+  for (int j = 0; j < 4; j++) {
+    x[j] = a[j];
+    x[4 + j] = b[j];
+  }
+}
+__device__ __forceinline__ void put_slot(uint32_t addr, const f29 &r) {
+  lds_u32x4 *p = (lds_u32x4 *)(uintptr_t)addr;
+  p[0] = u32x4{r.l[0], r.l[1], r.l[2], r.l[3]};
+  p[1] = u32x4{r.l[4], r.l[5], r.l[6], r.l[7]};
+  ((lds_u32 *)p)[8] = r.l[8];
 }
 
-// Run a sequence of program calls on the slots S.  calls[e] = {program, X, Y, D} (buffer
-// numbers, the absolute slot of buffer b being bufbase + 12 b); a program number of
-// PROG_INV replaces slot `inv_dst` by the inverse of slot `inv_src` (the binary GCD
-// inverse, computed on the scalar unit since the value is the same in all lanes).  The operations of the next level, also across calls,
-// are fetched one level ahead.  Must be called by all 64 lanes of the workgroup.
-template <int NCALL_FIELDS>
-__device__ __forceinline__ void run_seq(f29 *S, const uint8_t (*calls_g)[NCALL_FIELDS], int ncalls, int bufbase, int inv_src,
-                                        int inv_dst) {
-  const int lane = threadIdx.x;
-  lds_f29 *SL = (lds_f29 *)S;  // S is a __shared__ array of the calling kernel
-  // the call sequence in LDS: a byte read from global memory at a call boundary would wait
-  // for every load in flight, the operations fetched ahead included
-  __shared__ uint8_t calls_sh[256][NCALL_FIELDS];
-  for (int i = lane; i < ncalls * NCALL_FIELDS; i += 64)
-    calls_sh[i / NCALL_FIELDS][i % NCALL_FIELDS] = calls_g[i / NCALL_FIELDS][i % NCALL_FIELDS];
-  __syncthreads();
-  const uint8_t (*calls)[NCALL_FIELDS] = calls_sh;
-  // position of the next level to fetch, and the descriptor of its program (read once per
-  // call, so that a level's fetch is a single vector load)
-  int fe_call = 0, fe_lev = 0;
-  uint32_t f_row = 0, f_nlev = 0, f_width = 0;  // f_row: first operation of the level to fetch
-  // program numbers are the same in every lane: read through readfirstlane, so that the
-  // fetch position, the program descriptors and the level loop live in scalar registers
-  auto prog_at = [&](int e) { return __builtin_amdgcn_readfirstlane((int)calls[e][0]); };
-  auto next_call = [&]() {
-    while (fe_call < ncalls && prog_at(fe_call) == PROG_INV) fe_call++;
-    if (fe_call < ncalls) {
-      const ProgDesc d = PROGS[prog_at(fe_call)];
-      f_row = __builtin_amdgcn_readfirstlane(d.off);
-      f_nlev = __builtin_amdgcn_readfirstlane(d.nlev);
-      f_width = __builtin_amdgcn_readfirstlane(d.width);
-    }
-  };
-  next_call();
-  uint64_t nw[OP_WORDS] = {};
-  auto fetch = [&]() {
-    // a lane past the level's width gets kind 0 (no operation): eval_op reads nothing else
-    nw[0] = 0;
-    if (fe_call < ncalls) {
-      const uint32_t row = __builtin_amdgcn_readfirstlane(f_row);
-      if ((uint32_t)lane < f_width) {
-        const uint64_t *o = OPS[row + lane];
+// the other lane's value of a pair
+__device__ __forceinline__ uint32_t partner(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0xB1, 0xF, 0xF, true);  // quad_perm [1, 0, 3, 2]
+}
+
+// End of a level: the wavefront's slot writes are done, then the workgroup's.  (Operations
+// fetched ahead stay in flight: the barrier waits for LDS only.)
+template <int NW> __device__ __forceinline__ void level_sync() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  if (NW > 1) __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// base: the slots' LDS address; rel: the segment bases with it added
+template <int N, bool SEG>
+__device__ __forceinline__ void add_terms(uint32_t base, const uint32_t *w, uint64_t rel, int64_t *acc) {
+  uint32_t x[N][9];
 #pragma unroll
-        for (int q = 0; q < OP_WORDS; q++) nw[q] = o[q];
-      }
-      f_row = row + f_width;
-      if ((uint32_t)(fe_lev = __builtin_amdgcn_readfirstlane(fe_lev + 1)) == f_nlev) {
-        fe_lev = 0;
-        fe_call++;
-        next_call();
-      }
-    }
-  };
-  fetch();
-  for (int e = 0; e < ncalls; e++) {
-    const int prog = prog_at(e);
-    if (prog == PROG_INV) {
-      fe r = f_inv_uniform<FpP>(from29(canon29(S[inv_src])), bn::P_R3);
-      if (lane == 0) S[inv_dst] = to29(r);
-      __syncthreads();
-      continue;
-    }
-    int bx = 0, by = 0, bd = 0;
-    if (NCALL_FIELDS == 4) {
-      // the same in every lane: kept in scalar registers, so that the packed segment bases
-      // are scalar too
-      bx = __builtin_amdgcn_readfirstlane(bufbase + 12 * calls[e][1]);
-      by = __builtin_amdgcn_readfirstlane(bufbase + 12 * calls[e][NCALL_FIELDS == 4 ? 2 : 0]);
-      bd = __builtin_amdgcn_readfirstlane(bufbase + 12 * calls[e][NCALL_FIELDS == 4 ? 3 : 0]);
-    }
-    const ProgDesc pd = PROGS[prog];
-    for (int L = 0; L < pd.nlev; L++) {
-      uint64_t w[OP_WORDS];
+  for (int i = 0; i < N; i++) get_slot(SEG ? term_addr(w[i], rel) : ((w[i] & 0x7ffu) << 4) + base, x[i]);
 #pragma unroll
-      for (int q = 0; q < OP_WORDS; q++) w[q] = nw[q];
-      fetch();
-      f29 r;
-      int dst = eval_op(SL, w, level_groups(w), bx, by, bd, r);
-      if (dst >= 0) put_slot(SL, dst, r);
-      __syncthreads();
+  for (int i = 0; i < N; i++) {
+    const int k = term_coef(w[i]);
+    SLP_ORDER();
+#pragma unroll
+    for (int j = 0; j < 9; j++) acc[j] += (int64_t)k * (int32_t)x[i][j];
+  }
+  SLP_ORDER();
+}
+// the loads of up to six terms issue back to back, so that their latencies overlap; unused
+// terms name slot 0 with coefficient 0
+template <bool SEG>
+__device__ __forceinline__ void add_record(uint32_t base, uint32_t d, const uint32_t *w, uint64_t rel, int64_t *acc) {
+  if (!(d & BLK_T2)) {
+    add_terms<2, SEG>(base, w + 2, rel, acc);
+  } else if (!(d & BLK_T4)) {
+    add_terms<4, SEG>(base, w + 2, rel, acc);
+  } else {
+    add_terms<6, SEG>(base, w + 2, rel, acc);
+    if (d & BLK_T6) {
+      add_terms<4, SEG>(base, w + 8, rel, acc);
+      if (d & BLK_T10) add_terms<4, SEG>(base, w + 12, rel, acc);
     }
   }
 }
-#endif
 
-#ifdef __HIPCC__
-// Run one program (operations fetched one level ahead); all 64 lanes must call it.
-__device__ __forceinline__ void run1(f29 *S, int prog, int bx, int by, int bd) {
-  // the same in every lane; through readfirstlane they stay in scalar registers also where this
-  // runs in a called function (arguments arrive in vector registers), so that the descriptor is
-  // a scalar load and the level loop is uniform
-  prog = __builtin_amdgcn_readfirstlane(prog);
-  bx = __builtin_amdgcn_readfirstlane(bx);
-  by = __builtin_amdgcn_readfirstlane(by);
-  bd = __builtin_amdgcn_readfirstlane(bd);
-  const ProgDesc d = PROGS[prog];
-  const int lane = threadIdx.x;
-  lds_f29 *SL = (lds_f29 *)S;  // S is a __shared__ array of the calling kernel
-  uint64_t nw[OP_WORDS];
+// One wavefront's operations of a level (block descriptor d, this lane's record w); lanes past
+// the block's operations do not come here.
+__device__ __forceinline__ void run_block(uint32_t base, uint32_t d, const uint32_t *w, uint64_t rel) {
+  const bool mul = term_coef(w[0]) == 1;
+  const uint32_t dst = term_addr(w[0], rel);
+  int64_t acc[9];
 #pragma unroll
-  for (int q = 0; q < OP_WORDS; q++) nw[q] = lane < d.width ? OPS[d.off + lane][q] : 0;
-  for (int L = 0; L < d.nlev; L++) {
-    uint64_t w[OP_WORDS];
+  for (int j = 0; j < 9; j++) acc[j] = 0;
+  if (d & BLK_SEG) add_record<true>(base, d, w, rel, acc);
+  else add_record<false>(base, d, w, rel, acc);
+  f29 r = red29(acc);
+  if (d & BLK_LIN) {
+    if (!mul) {  // the sum of both lanes' halves
 #pragma unroll
-    for (int q = 0; q < OP_WORDS; q++) { w[q] = nw[q]; nw[q] = 0; }
-    if (L + 1 < d.nlev && lane < d.width) {
-      const uint64_t *o = OPS[d.off + (L + 1) * d.width + lane];
-#pragma unroll
-      for (int q = 0; q < OP_WORDS; q++) nw[q] = o[q];
+      for (int j = 0; j < 9; j++) r.l[j] += partner(r.l[j]);
     }
-    f29 r;
-    int dst = eval_op(SL, w, level_groups(w), bx, by, bd, r);
-    if (dst >= 0) put_slot(SL, dst, r);
+  }
+  if (d & BLK_MUL) {
+    f29 o;
+#pragma unroll
+    for (int j = 0; j < 9; j++) o.l[j] = partner(r.l[j]);
+    if (mul) r = mont29(r, o);
+  }
+  if (!(threadIdx.x & 1)) put_slot(dst, r);
+}
+
+// Runs the calls cl[0 .. n), n > 0 (LDS), on the slots at LDS address `base` with all
+// wavefronts of the workgroup.  After a call of a checked program the slots chk .. chk + nchk
+// (nchk = 1 or 2, 0 for no checks) are looked at: if all may be zero the run stops there and
+// returns the number of calls it ran, negated; otherwise it returns n.
+//
+// Records are fetched one level ahead, across calls too: a level's record names the next
+// level's block, the last one's is 0, and a call's entry (read from LDS a call ahead) names
+// the first.  The loop is written for the fewest scalar instructions, since one wavefront
+// issues about one instruction in four cycles whatever its kind.
+template <int NW> __device__ __forceinline__ int run_calls(uint32_t base, uint32_t list, int n, int chk, int nchk) {
+  static_assert(NW == 2, "a call entry holds two descriptors");
+  base = __builtin_amdgcn_readfirstlane(base);
+  list = __builtin_amdgcn_readfirstlane(list);
+  n = __builtin_amdgcn_readfirstlane(n);
+  chk = __builtin_amdgcn_readfirstlane(chk);
+  nchk = __builtin_amdgcn_readfirstlane(nchk);
+  const uint32_t lane = threadIdx.x & 63, half = lane >> 1;
+  const bool w1 = threadIdx.x >= 64;
+  const uint32_t end = list + 16u * n;
+  const uint64_t base4 = base * 0x0001000100010001ull;
+  const uint32_t chk_mask = nchk ? BLK_CHK : 0;
+  uint32_t n_ent = list;  // entry after the next level's call
+  u32x4 ahead = *(const lds_u32x4 *)(uintptr_t)list;
+  uint32_t nd = 0, n_chk = 0;  // the next level: descriptor, whether its call is a checked addition,
+  uint64_t n_rel = 0;          // segment bases
+  auto next_call = [&]() {
+    const u32x4 v = ahead;
+    n_ent += 16;
+    if (n_ent < end) ahead = *(const lds_u32x4 *)(uintptr_t)n_ent;
+    nd = __builtin_amdgcn_readfirstlane(w1 ? v[1] : v[0]);
+    n_chk = nd & chk_mask;
+    n_rel = base4 + (__builtin_amdgcn_readfirstlane(v[2]) | (uint64_t)__builtin_amdgcn_readfirstlane(v[3]) << 32);
+  };
+  // (all 64 lanes read, those past the block's operations to no effect; straight into the
+  // registers that the level reads, since a move of a loaded word here would wait for it)
+  auto load = [&](u32x4 *nw) {
+    const char *o = (const char *)OPS + (((nd & BLK_OFF) << 4) + (lane << 4));
+    nw[0] = *(const u32x4 *)o;
+    if (nd & BLK_T2) {
+      nw[1] = *(const u32x4 *)(o + 1024);
+      if (nd & BLK_T6) {
+        nw[2] = *(const u32x4 *)(o + 2048);
+        if (nd & BLK_T10) nw[3] = *(const u32x4 *)(o + 3072);
+      }
+    }
+  };
+  int ret = 0;
+  // one level from cw, the next fetched to nw; true at the end of the run
+  auto step = [&](const u32x4 *cw, u32x4 *nw) -> bool {
+    uint32_t w[LANE_TERMS_MAX + 2];
+#pragma unroll
+    for (int i = 0; i < LANE_TERMS_MAX + 2; i++) w[i] = cw[i >> 2][i & 3];
+    const uint32_t d = nd, c = n_chk;
+    const uint64_t rel = n_rel;
+    nd = __builtin_amdgcn_readfirstlane(w[1]);
+    const bool tail = nd == 0;
+    if (tail && n_ent < end) next_call();
+    if (nd) load(nw);
+    if (half < (uint32_t)blk_ops(d)) run_block(base, d, w, rel);
+    level_sync<NW>();
+    if (tail) {
+      if (c) {
+        bool z = true;
+        for (int i = 0; i < nchk; i++) {
+          const lds_u32 *p = (const lds_u32 *)(uintptr_t)(base + 48 * (chk + i));
+          z = z && maybe_zero29(p[0], p[1]);
+        }
+        if (__builtin_amdgcn_readfirstlane((int)z)) {
+          // calls run: the entries before n_ent, without the next level's
+          ret = -(int)((n_ent - list) / 16 - (nd ? 1 : 0));
+          return true;
+        }
+      }
+      if (!nd) {
+        ret = n;
+        return true;
+      }
+    }
+    return false;
+  };
+  u32x4 wa[4] = {}, wb[4] = {};
+  next_call();
+  load(wa);
+  while (!step(wa, wb) && !step(wb, wa)) {}
+  return ret;
+}
+
+// the same as a function: called, it saves and restores some sixty vector registers a lane in
+// scratch memory
+template <int NW> __device__ __noinline__ int run_calls_fn(uint32_t base, uint32_t list, int n, int chk, int nchk) {
+  return run_calls<NW>(base, list, n, chk, nchk);
+}
+
+// Device context for control code shared with the host model: the workgroup's slots and a list
+// of calls in LDS.  (cl: MAX_CALLS entries for lists and one more for single calls.)  A kernel
+// with one place that runs calls has the engine in line, one with several calls it: with the
+// call's scratch traffic a launch of 2^15 F_p12 products took 1.98 ms, in line it takes a
+// quarter of that.
+template <int NW, bool INLINE = false> struct DevCtx {
+  f29 *S;
+  Call *cl;
+  __device__ int lane() const { return threadIdx.x; }
+  __device__ int lanes() const { return 64 * NW; }
+  __device__ void sync() { __syncthreads(); }
+  // calls cl[first .. n); returns as run_calls, counted from the list's start
+  __device__ int run_list(int first, int n, int chk, int nchk) {
+    __syncthreads();
+    if (first >= n) return n;
+    const uint32_t base = (uint32_t)(uintptr_t)(lds_f29 *)S, list = (uint32_t)(uintptr_t)((lds_call *)cl + first);
+    const int r = INLINE ? run_calls<NW>(base, list, n - first, chk, nchk) : run_calls_fn<NW>(base, list, n - first, chk, nchk);
+    return r < 0 ? r - first : n;
+  }
+  // slot dst = the inverse of slot src (0 for 0), by the binary GCD on the scalar unit: the value
+  // is the same in all lanes
+  __device__ void invert(int dst, int src) {
+    __syncthreads();
+    const fe r = f_inv_uniform<FpP>(from29(canon29(S[src])), bn::P_R3);
+    if (threadIdx.x == 0) S[dst] = to29(r);
     __syncthreads();
   }
-}
-
-// device context for control code shared with the host model
-struct DevCtx {
-  f29 *S;
-  __device__ void run(int prog, int bx, int by, int bd) { run1(S, prog, bx, by, bd); }
-  __device__ void sync() { __syncthreads(); }
-  __device__ int lane() const { return threadIdx.x; }
-  __device__ int lanes() const { return 64; }
+  __device__ void run(int prog, int bx, int by, int bd) {
+    if (threadIdx.x == 0) cl[MAX_CALLS] = call(prog, bx, by, bd);
+    run_list(MAX_CALLS, MAX_CALLS + 1, 0, 0);
+  }
 };
 #endif
 
-// Host model of run(): every operation of a level reads before any writes.
-inline void run_host(f29 *S, int prog, int bx, int by, int bd) {
-  const ProgDesc d = PROGS[prog];
+// Host model: every operation of a level reads before any writes.
+inline void run_host(f29 *S, const Call &c) {
+  const uint64_t rel = c.rel;
   f29 r[64];
-  int dst[64];
-  for (int L = 0; L < d.nlev; L++) {
-    for (int lane = 0; lane < d.width; lane++) {
-      const uint64_t *op = OPS[d.off + L * d.width + lane];
-      dst[lane] = eval_op(S, op, level_groups(op), bx, by, bd, r[lane]);
+  uint32_t dst[64];
+  uint32_t d[2] = {c.d0, c.d1};
+  while (d[0]) {
+    int n = 0;
+    for (int v = 0; v < 2; v++) {
+      const int T = blk_terms(d[v]);
+      for (int i = 0; i < blk_ops(d[v]); i++, n++) {
+        int64_t acc[2][9];
+        for (int h = 0; h < 2; h++) {
+          for (int j = 0; j < 9; j++) acc[h][j] = 0;
+          for (int t = 0; t < T; t++) {
+            const uint32_t w = blk_word(OPS, d[v], 2 * i + h, 2 + t);
+            const f29 &x = S[term_addr(w, rel) / 48];
+            for (int j = 0; j < 9; j++) acc[h][j] += (int64_t)term_coef(w) * (int32_t)x.l[j];
+          }
+        }
+        const uint32_t head = blk_word(OPS, d[v], 2 * i, 0);
+        r[n] = red29(acc[0]);
+        const f29 o = red29(acc[1]);
+        if (term_coef(head) == 1) r[n] = mont29(r[n], o);
+        else
+          for (int j = 0; j < 9; j++) r[n].l[j] += o.l[j];
+        dst[n] = term_addr(head, rel) / 48;
+      }
+      d[v] = blk_word(OPS, d[v], 0, 1);
     }
-    for (int lane = 0; lane < d.width; lane++)
-      if (dst[lane] >= 0) S[dst[lane]] = r[lane];
+    for (int i = 0; i < n; i++) S[dst[i]] = r[i];
   }
 }
+
+inline void run_host(f29 *S, int prog, int bx, int by, int bd) { run_host(S, call(prog, bx, by, bd)); }
 
 struct HostCtx {
   f29 *S;
   int l = 0;
+  Call list[MAX_CALLS + 1];
+  Call *cl = list;
   void run(int prog, int bx, int by, int bd) { run_host(S, prog, bx, by, bd); }
   void sync() {}
   int lane() const { return l; }
   int lanes() const { return 1; }
+  int run_list(int first, int n, int chk, int nchk) {
+    for (int e = first; e < n; e++) {
+      run_host(S, cl[e]);
+      if (nchk && (cl[e].d0 & BLK_CHK)) {
+        bool z = true;
+        for (int i = 0; i < nchk; i++) z = z && maybe_zero29(S[chk + i].l[0], S[chk + i].l[1]);
+        if (z) return -(e + 1);
+      }
+    }
+    return n;
+  }
 };
 
 }  // namespace slp
