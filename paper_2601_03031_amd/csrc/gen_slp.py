@@ -9,19 +9,17 @@ per step, a pair of lanes per operation (32 operations per wavefront).  Operatio
   LIN  dst = sum_i k_i x_i  (mod p)                 (half of the terms per lane)
 Linear combinations are kept symbolic by the tracer and materialised only where a
 product or an output needs them, so chains of additions fuse into few LIN operations.
-Slots are field elements in LDS.  An operand names a 2-bit segment and a 9-bit offset:
+Slots are field elements in LDS.  An operand names a 2-bit segment and a 10-bit offset:
 segment 0 is absolute, segments 1..3 are bases the caller sets before running a
 relocatable program.
 
 Programs:
-  * Miller-loop bodies for the optimal ate pairing, software-pipelined: the T-chain
-    (doubling / addition of the twist point, with line coefficients) runs one step
-    ahead of the f-chain (squaring of the accumulator times the pending lines).  The
-    loop follows the non-adjacent form of 6u + 2; the closing additions use pi(Q)
-    and -pi^2(Q);
-  * F_p12 operations for the final exponentiation (relocatable: X in segment 1, Y in
-    segment 2, D in segment 3): product, Granger-Scott cyclotomic square, Frobenius
-    powers, conjugate, the norm down to F_p and the easy part from the inverse norm.
+  * the Miller loop of the optimal ate pairing, whole: the loop follows the non-adjacent form
+    of 6u + 2; the closing additions use pi(Q) and -pi^2(Q);
+  * the final exponentiation, whole but for its inversion in F_p;
+  * F_p12 operations (relocatable: X in segment 1, Y in segment 2, D in segment 3): product,
+    squarings, Frobenius powers, conjugate;
+  * G1 and G2 scalar multiplication steps.
 
 Run:  python gen_slp.py > slp_progs.hpp      (the build does this)
       python gen_slp.py --check              (run every program on random inputs
@@ -36,6 +34,7 @@ U = 0x44E992B44A6909F1
 P = 36 * U**4 + 36 * U**3 + 24 * U**2 + 6 * U + 1
 R = 36 * U**4 + 36 * U**3 + 18 * U**2 + 6 * U + 1
 RMONT = 1 << 256
+SEG_SHIFT = 10         # a slot field: segment | offset
 WAVE_OPS = 32          # operations of a level that one wavefront executes
 KMAX = 127
 
@@ -382,27 +381,27 @@ def frob12(f, e):
 
 # ============================================================================ pairing formulas
 def line_dbl(T, xP, yP):
-    """T = (X, Y, Z) homogeneous projective on y^2 = x^3 + b'.  Returns 2T (scaled by 4)
+    """T = (X, Y, Z, U) homogeneous projective on y^2 = x^3 + b' with U = 3 b' Z carried along, so
+    that 3 b' Z^2 = Z U is ready in the first product level.  Returns 2T (scaled by 4)
     and the tangent at T evaluated at P up to an F_p2 factor, as (l0, l1, l3) meaning
     l0 + l1 w + l3 w^3:  l0 = 2YZ yP, l1 = -3X^2 xP, l3 = Y^2 - 3b'Z^2."""
-    X, Y, Z = T
-    XX, YY, ZZ = X.sqr(), Y.sqr(), Z.sqr()
-    XY, YZ = X.mul(Y), Y.mul(Z)
-    F9 = ZZ.mul_const(B9)                  # 9 b' Z^2
-    E = ZZ.mul_const(B3)                   # 3 b' Z^2
-    X3 = XY.mul(YY - F9).scale(2)          # 2 XY (Y^2 - 9b'Z^2)
-    Y3 = (YY + F9).sqr() - E.sqr().scale(12)
+    X, Y, Z, U = T
+    XX, YY, E = X.sqr(), Y.sqr(), Z.mul(U)
+    XY, YZ, YU = X.mul(Y), Y.mul(Z), Y.mul(U)
+    X3 = XY.mul(YY - E.scale(3)).scale(2)  # 2 XY (Y^2 - 9b'Z^2)
+    Y3 = (YY + E.scale(3)).sqr() - E.sqr().scale(12)
     Z3 = YY.mul(YZ).scale(8)               # 8 Y^3 Z
+    U3 = YY.mul(YU).scale(8)
     l0 = YZ.scale(2).mul_fp(yP)
     l1 = XX.scale(-3).mul_fp(xP)
     l3 = YY - E
-    return (X3, Y3, Z3), (l0, l1, l3)
+    return (X3, Y3, Z3, U3), (l0, l1, l3)
 
 
 def line_add(T, Q, xP, yP):
-    """T projective, Q = (xQ, yQ) affine: T + Q and the line through T and Q at P:
+    """T projective as above, Q = (xQ, yQ) affine: T + Q and the line through T and Q at P:
     l0 = lam yP, l1 = -theta xP, l3 = theta xQ - lam yQ  (theta = Y - yQ Z, lam = X - xQ Z)."""
-    X, Y, Z = T
+    X, Y, Z, U = T
     xQ, yQ = Q
     th = Y - yQ.mul(Z)
     la = X - xQ.mul(Z)
@@ -412,12 +411,13 @@ def line_add(T, Q, xP, yP):
     G2 = X.mul(D)
     H2 = E2 + F2_ - G2.scale(2)
     X3 = la.mul(H2)
-    Y3 = th.mul(G2 - H2) - Y.mul(E2)
-    Z3 = Z.mul(E2)
+    Y3 = th.mul(G2 - H2) - Y.mul(la).mul(D)
+    Z3 = Z.mul(la).mul(D)
+    U3 = U.mul(la).mul(D)
     l0 = la.mul_fp(yP)
     l1 = (-th).mul_fp(xP)
     l3 = th.mul(xQ) - la.mul(yQ)
-    return (X3, Y3, Z3), (l0, l1, l3)
+    return (X3, Y3, Z3, U3), (l0, l1, l3)
 
 
 def line_to_f12(l):
@@ -530,121 +530,68 @@ def pt_out(p, name, T):
 
 
 def miller_programs():
-    """Bodies of the pipelined Miller loop over the NAF digits d_1 .. d_n of 6u + 2
-    (d_0 = 1 is the starting T = Q).  State: f, T, pending lines L1 (and L2 when an
-    addition followed the doubling), P = (xP, yP), Q = (xQ, yQ), nyQ = -yQ.
-
-      ml_start<a>    : (T, L1) = dbl(Q); addition step a (0, +1, -1) gives L2
-      ml_body<n><a>  : f = f^2 * pending (f = pending on the first body);
-                       (T, L1) = dbl(T); addition step a gives L2
-      ml_final<n>    : f = f^2 * pending, times the lines of T + pi(Q) and of
-                       (T + pi(Q)) - pi^2(Q)
-    n is the number of pending lines (1 or 2)."""
-    progs = {}
-
-    def common(p):
-        xP, yP = p.inp("xP"), p.inp("yP")
-        xQ, yQ = f2_in(p, "xQ"), f2_in(p, "yQ")
-        return xP, yP, (xQ, yQ)
-
-    def add_step(p, T, Q, a, xP, yP):
-        if a == 1:
-            return line_add(T, Q, xP, yP)
-        return line_add(T, (Q[0], -Q[1]), xP, yP)
-
-    for a in (0, 1, -1):
-        p = Prog("ml_start%s" % "0pm"[a])
-        xP, yP, Q = common(p)
-        one = F2(p.fconst(1), p.fconst(0))
-        T, l1 = line_dbl((Q[0], Q[1], one), xP, yP)
-        if a:
-            T, l2 = add_step(p, T, Q, a, xP, yP)
-        pt_out(p, "T", T)
-        line_out(p, "L1", l1)
-        if a:
-            line_out(p, "L2", l2)
-        progs[p.name] = p
-    for npend in (1, 2):
-        for a in (0, 1, -1):
-            for first in (0, 1):
-                p = Prog("ml_body%d%s%s" % (npend, "0pm"[a], "_first" if first else ""))
-                xP, yP, Q = common(p)
-                L1 = line_in(p, "L1")
-                L2 = line_in(p, "L2") if npend == 2 else None
-                if first:
-                    f = line_to_f12(L1) if npend == 1 else line_mul_line(L1, L2)
-                else:
-                    f = f12_in(p, "f").sqr()
-                    f = mul_by_line(f, L1) if npend == 1 else f.mul(line_mul_line(L1, L2))
-                f12_out(p, "f", f)
-                T, l1 = line_dbl(pt_in(p, "T"), xP, yP)
-                if a:
-                    T, l2 = add_step(p, T, Q, a, xP, yP)
-                pt_out(p, "T", T)
-                line_out(p, "L1", l1)
-                if a:
-                    line_out(p, "L2", l2)
-                progs[p.name] = p
-    for npend in (1, 2):
-        p = Prog("ml_final%d" % npend)
-        xP, yP, Q = common(p)
-        L1 = line_in(p, "L1")
-        L2 = line_in(p, "L2") if npend == 2 else None
-        f = f12_in(p, "f").sqr()
-        f = mul_by_line(f, L1) if npend == 1 else f.mul(line_mul_line(L1, L2))
-        T = pt_in(p, "T")
-        T, la = line_add(T, twist_frob(Q), xP, yP)
-        _, lb = line_add(T, twist_frob2_neg(Q), xP, yP)
-        f12_out(p, "f", f.mul(line_mul_line(la, lb)))
-        progs[p.name] = p
-    return progs
+    """The Miller loop over the NAF digits of 6u + 2 and the closing additions of pi(Q) and
+    -pi^2(Q) as one program: the scheduler then overlaps the chain of the twist point with the
+    chain of the accumulator across the whole loop."""
+    p = Prog("ml")
+    xP, yP = p.inp("xP"), p.inp("yP")
+    Q = (f2_in(p, "xQ"), f2_in(p, "yQ"))
+    nQ = (Q[0], -Q[1])
+    T = (Q[0], Q[1], F2(p.fconst(1), p.fconst(0)), F2(p.fconst(B3[0]), p.fconst(B3[1])))
+    f = None
+    for d in ATE_NAF[1:]:
+        if f is not None:
+            f = f.sqr()
+        T, l1 = line_dbl(T, xP, yP)
+        if d:
+            T, l2 = line_add(T, Q if d == 1 else nQ, xP, yP)
+            m = line_mul_line(l1, l2)
+            f = m if f is None else f.mul(m)
+        else:
+            f = line_to_f12(l1) if f is None else mul_by_line(f, l1)
+    T, la = line_add(T, twist_frob(Q), xP, yP)
+    _, lb = line_add(T, twist_frob2_neg(Q), xP, yP)
+    f12_out(p, "f", f.mul(line_mul_line(la, lb)))
+    return {p.name: p}
 
 
-def miller_sequence():
-    d = ATE_NAF
-    assert d[0] == 1
-    seq = ["ml_start%s" % "0pm"[d[1]]]
-    pend = 2 if d[1] else 1
-    for i in range(2, len(d)):
-        seq.append("ml_body%d%s%s" % (pend, "0pm"[d[i]], "_first" if i == 2 else ""))
-        pend = 2 if d[i] else 1
-    seq.append("ml_final%d" % pend)
-    return seq
+MILLER_STATE = ["xP", "yP", "xQ.0", "xQ.1", "yQ.0", "yQ.1"] + ["f.%d" % k for k in range(12)]
 
 
-MILLER_STATE = (["xP", "yP", "xQ.0", "xQ.1", "yQ.0", "yQ.1"] + ["f.%d" % k for k in range(12)]
-                + ["T.%s.%d" % (c, k) for c in "XYZ" for k in (0, 1)]
-                + ["L%d.%d.%d" % (n, j, k) for n in (1, 2) for j in range(3) for k in (0, 1)])
-
-
-def cyclo_sqr(X):
+def cyclo_sqr(X, L=None):
     """Granger-Scott squaring of a cyclotomic element over the three F_p4 pairs
-    (w^0, w^3), (w^1, w^4), (w^2, w^5), with s = w^3, s^2 = xi."""
-    a, b = X.a, X.b
-    g = {0: a.c[0], 2: a.c[1], 4: a.c[2], 1: b.c[0], 3: b.c[1], 5: b.c[2]}   # by power of w
+    (w^0, w^3), (w^1, w^4), (w^2, w^5), with s = w^3, s^2 = xi.  L: the same element, from
+    which the terms outside the products are taken (X by default)."""
+    L = L or X
+    def by_w(X):
+        a, b = X.a, X.b
+        return {0: a.c[0], 2: a.c[1], 4: a.c[2], 1: b.c[0], 3: b.c[1], 5: b.c[2]}   # by power of w
+    g, z = by_w(X), by_w(L)
 
     def fp4_sqr(x, y):  # (x + y s)^2 with s^2 = xi: (x^2 + xi y^2, 2xy)
         t0, t1 = x.sqr(), y.sqr()
         return t0 + t1.mul_xi(), (x + y).sqr() - t0 - t1
 
-    z0, z1 = g[0], g[3]
-    z2, z3 = g[1], g[4]
-    z4, z5 = g[2], g[5]
-    t0, t1 = fp4_sqr(z0, z1)
-    n0 = (t0 - z0).scale(2) + t0
-    n1 = (t1 + z1).scale(2) + t1
-    t0, t1 = fp4_sqr(z2, z3)
-    t2, t3 = fp4_sqr(z4, z5)
-    n4 = (t0 - z4).scale(2) + t0
-    n5 = (t1 + z5).scale(2) + t1
+    t0, t1 = fp4_sqr(g[0], g[3])
+    n0 = t0.scale(3) - z[0].scale(2)
+    n1 = t1.scale(3) + z[3].scale(2)
+    t0, t1 = fp4_sqr(g[1], g[4])
+    t2, t3 = fp4_sqr(g[2], g[5])
+    n4 = t0.scale(3) - z[2].scale(2)
+    n5 = t1.scale(3) + z[5].scale(2)
     t0 = t3.mul_xi()
-    n2 = (t0 + z2).scale(2) + t0
-    n3 = (t2 - z3).scale(2) + t2
+    n2 = t0.scale(3) + z[1].scale(2)
+    n3 = t2.scale(3) - z[4].scale(2)
     h = {0: n0, 3: n1, 1: n2, 4: n3, 2: n4, 5: n5}
     return F12(F6(h[0], h[2], h[4]), F6(h[1], h[3], h[5]))
 
 
-def fe_programs():
+def materialised(X):
+    """X with every coefficient a value of its own; X's own expressions stay as they are"""
+    return F12.of([F(c.p, {F(c.p, dict(c.t)).atom(): 1}) if c.t else c for c in X.coeffs()])
+
+
+def f12_programs():
     progs = {}
 
     def mk(name, fn, n_in):
@@ -659,18 +606,35 @@ def fe_programs():
     mk("f12_sqr_mul", lambda X, Y: X.sqr().mul(Y), 2)
     mk("f12_csqr", cyclo_sqr, 1)
     mk("f12_csqr_mul", lambda X, Y: cyclo_sqr(X).mul(Y), 2)
-    # (the conjugate is the inverse in the cyclotomic subgroup: its sign changes fold into
-    # the product's coefficients, so this costs the levels of f12_csqr_mul)
-    mk("f12_csqr_cmul", lambda X, Y: cyclo_sqr(X).mul(Y.conj()), 2)
     mk("f12_frob1", lambda X: frob12(X, 1), 1)
     mk("f12_frob2", lambda X: frob12(X, 2), 1)
     mk("f12_frob3", lambda X: frob12(X, 3), 1)
     mk("f12_conj", lambda X: X.conj(), 1)
-    mk("f12_conj_mul", lambda X, Y: X.conj().mul(Y), 2)
-    mk("f12_frob2_mul", lambda X, Y: frob12(X, 2).mul(Y), 2)
-    # norm: n6 = X conj(X) = a^2 - v b^2 in F_p6; the F_p6 inverse of n6 is (A, B, C) / n2
-    # with A = c0^2 - xi c1 c2, B = xi c2^2 - c0 c1, C = c1^2 - c0 c2,
-    # n2 = c0 A + xi (c2 B + c1 C); t = n2 conj(n2) in F_p
+    return progs
+
+
+# the exponents of the final exponentiation's hard part: (p^4 - p^2 + 1)/r = l0 + l1 p + l2 p^2 + p^3
+# with l2 = 6u^2 + 1, l1 = -36u^3 - 18u^2 - 12u + 1, l0 = l1 - (2 l2 + 6u + 1)
+HARD_L1N, HARD_L2, HARD_L3 = 36 * U**3 + 18 * U**2 + 12 * U - 1, 6 * U**2 + 1, 6 * U + 1
+assert (P**4 - P**2 + 1) // R == -HARD_L1N - 2 * HARD_L2 - HARD_L3 - HARD_L1N * P + HARD_L2 * P**2 + P**3
+
+
+def final_exp_programs():
+    """The final exponentiation f^((p^12 - 1)/r) in two programs around one inversion in F_p
+    (input X, result D, both absolute slots).
+
+    fe_norm: n6 = X conj(X) = a^2 - v b^2 in F_p6; the F_p6 inverse of n6 is (A, B, C) / n2 with
+    A = c0^2 - xi c1 c2, B = xi c2^2 - c0 c1, C = c1^2 - c0 c2, n2 = c0 A + xi (c2 B + c1 C);
+    t = n2 conj(n2) in F_p.
+
+    fe_rest, from tinv = t^{-1}: the easy part f = (conj(X) X^{-1})^{p^2 + 1}, with n6^{-1} =
+    (A, B, C) conj(n2) tinv and conj(X) X^{-1} = conj(X)^2 n6^{-1}; then the hard part from the
+    lowest digit up: one chain of squarings f^{2^i}, and f^{-l1}, f^{l2}, f^{6u + 1} gathered
+    beside it over the signed digits of their exponents (a negative digit takes the conjugate,
+    the inverse in the cyclotomic subgroup).  The chain is 193 squarings, a product level each:
+    a squaring's factors are sums of the products before it, and its coefficients are also
+    made values in the level beside, for the linear terms of the next and for the products."""
+    progs = {}
     p = Prog("fe_norm")
     X = f12_in(p, "X")
     n6 = X.a.mul(X.a) - X.b.mul(X.b).mul_v()
@@ -683,152 +647,38 @@ def fe_programs():
         f2_out(p, nm, v)
     p.out("t", n2.c0 * n2.c0 + n2.c1 * n2.c1)
     progs[p.name] = p
-    # easy part from tinv = t^{-1}: n6^{-1} = (A, B, C) conj(n2) tinv and
-    # conj(X) X^{-1} = conj(X)^2 n6^{-1}
-    p = Prog("fe_easy")
+
+    p = Prog("fe_rest")
     X = f12_in(p, "X")
     A, B, C, n2 = (f2_in(p, nm) for nm in ("nA", "nB", "nC", "n2"))
-    ti = p.inp("tinv")
-    n2i = n2.conj().mul_fp(ti)
+    n2i = n2.conj().mul_fp(p.inp("tinv"))
     n6i = F6(A.mul(n2i), B.mul(n2i), C.mul(n2i))
     cx2 = X.conj().sqr()
-    f12_out(p, "D", F12(cx2.a.mul(n6i), cx2.b.mul(n6i)))
+    e = F12(cx2.a.mul(n6i), cx2.b.mul(n6i))
+    f = materialised(frob12(e, 2).mul(e))
+    digits = [naf(x)[::-1] for x in (HARD_L1N, HARD_L2, HARD_L3)]
+    n = max(len(d) for d in digits)
+    s, z, acc = f, f, [None, None, None]
+    for i in range(n):
+        for k in range(3):
+            d = digits[k][i] if i < len(digits[k]) else 0
+            if d:
+                v = z if d > 0 else z.conj()
+                acc[k] = v if acc[k] is None else materialised(acc[k].mul(v))
+        if i + 1 < n:
+            s = cyclo_sqr(s, z)
+            z = materialised(s)
+    a1, a2, a3 = acc                                  # f^{-l1}, f^{l2}, f^{6u + 1}
+    t0 = a1.mul(cyclo_sqr(a2).mul(a3))                # f^{-l0}
+    r1 = t0.conj().mul(frob12(a1.conj(), 1))
+    r2 = frob12(a2, 2).mul(frob12(f, 3))
+    f12_out(p, "D", r1.mul(r2))
     progs[p.name] = p
     return progs
 
 
-UNAF = naf(U)
-
-
-def wnaf(k, w):
-    """width-w signed digits of k (odd digits |d| < 2^(w-1), most significant first)"""
-    d = []
-    while k:
-        if k & 1:
-            z = k % (1 << w)
-            if z >= 1 << (w - 1):
-                z -= 1 << w
-            k -= z
-        else:
-            z = 0
-        d.append(z)
-        k //= 2
-    return d[::-1]
-
-
-UW4 = wnaf(U, 4)
-
-
-def fe_sequence():
-    """Final exponentiation f^((p^12 - 1)/r) as calls of the F_p12 programs on buffers of
-    12 slots: easy part conj(f) f^{-1}, then (.)^{p^2} (.); hard part through f^u, f^{u^2},
-    f^{u^3} and the p-power split (p^4 - p^2 + 1)/r = l0 + l1 p + l2 p^2 + l3 p^3 with
-    l3 = 1, l2 = 6u^2 + 1, l1 = -36u^3 - 18u^2 - 12u + 1, l0 = -36u^3 - 30u^2 - 18u - 2.
-    Entries are (program, X, Y, D) buffer numbers; "INV" inverts the norm on one lane.
-    Buffer 0 holds the input; the result is left in the buffer returned."""
-    seq = []
-    nbuf = [1]
-    free = []
-
-    def alloc():
-        if free:
-            return free.pop()
-        nbuf[0] += 1
-        return nbuf[0] - 1
-
-    def call(prog, X, Y=None):
-        D = alloc()
-        seq.append((prog, X, X if Y is None else Y, D))
-        return D
-
-    def release(*bs):
-        for b in bs:
-            free.append(b)
-
-    seq.append(("fe_norm", 0, 0, 0))
-    seq.append(("INV", 0, 0, 0))
-    f1 = call("fe_easy", 0)
-    f = call("f12_frob2_mul", f1, f1)
-    release(f1)
-
-    def pow_u(x):
-        # x^u over the width-4 signed digits of u (14 nonzero of 63 against 24 for the NAF):
-        # the odd powers x^3, x^5, x^7 first, a negative digit multiplies by the conjugate
-        x2 = call("f12_csqr", x)
-        tab = {1: x}
-        for e in (3, 5, 7):
-            tab[e] = call("f12_mul", tab[e - 2], x2)
-        release(x2)
-        assert UW4[0] == 1
-        acc = x
-        for d in UW4[1:]:
-            if d == 0:
-                nxt = call("f12_csqr", acc)
-            else:
-                nxt = call("f12_csqr_mul" if d > 0 else "f12_csqr_cmul", acc, tab[abs(d)])
-            if acc != x:
-                release(acc)
-            acc = nxt
-        release(tab[3], tab[5], tab[7])
-        return acc
-
-    a = pow_u(f)
-    b = pow_u(a)
-    c = pow_u(b)
-    c2 = call("f12_csqr", c)
-    c4 = call("f12_csqr", c2)
-    release(c2)
-    c8 = call("f12_csqr", c4)
-    release(c4)
-    c9 = call("f12_mul", c8, c)
-    release(c8, c)
-    c18 = call("f12_csqr", c9)
-    release(c9)
-    c36 = call("f12_csqr", c18)
-    release(c18)
-    b2 = call("f12_csqr", b)
-    b3 = call("f12_mul", b2, b)
-    release(b2, b)
-    b6 = call("f12_csqr", b3)
-    release(b3)
-    b12 = call("f12_csqr", b6)
-    b18 = call("f12_mul", b12, b6)
-    b30 = call("f12_mul", b18, b12)
-    release(b12)
-    a2 = call("f12_csqr", a)
-    a3 = call("f12_mul", a2, a)
-    release(a2, a)
-    a6 = call("f12_csqr", a3)
-    release(a3)
-    a12 = call("f12_csqr", a6)
-    a18 = call("f12_mul", a12, a6)
-    release(a6)
-    f2 = call("f12_csqr", f)
-    t = call("f12_mul", c36, b30)
-    release(b30)
-    u_ = call("f12_mul", a18, f2)
-    release(a18, f2)
-    t0n = call("f12_mul", t, u_)                 # conj(t0n) = f^{l0}
-    release(t, u_)
-    v = call("f12_mul", c36, b18)
-    release(c36, b18)
-    v2 = call("f12_mul", v, a12)
-    release(v, a12)
-    t1 = call("f12_conj_mul", v2, f)             # f^{l1}
-    release(v2)
-    t2 = call("f12_mul", b6, f)                  # f^{l2}
-    release(b6)
-    ft1 = call("f12_frob1", t1)
-    release(t1)
-    r1 = call("f12_conj_mul", t0n, ft1)          # f^{l0} (f^{l1})^p
-    release(t0n, ft1)
-    f3 = call("f12_frob3", f)
-    release(f)
-    r2 = call("f12_frob2_mul", t2, f3)           # (f^{l2})^{p^2} f^{p^3}
-    release(t2, f3)
-    res = call("f12_mul", r1, r2)
-    return seq, res, nbuf[0]
-
+FE_STATE = (["X.%d" % k for k in range(12)] + ["D.%d" % k for k in range(12)] + ["t", "tinv"]
+            + ["%s.%d" % (nm, k) for nm in ("nA", "nB", "nC", "n2") for k in (0, 1)])
 
 # ============================================================================ G2 scalar multiplication (GLS)
 # psi(x, y) = (conj(x) tx, conj(y) ty) acts on G2 as multiplication by lam = p mod r = 6u^2.
@@ -1076,7 +926,7 @@ def operands(v):
 
 # Cost of a level in ns of the interpreter (measured on gfx950): a fixed part, a part per
 # term of the longest lane record, the Montgomery product of a level with products.
-LEVEL_BASE, LEVEL_TERM, LEVEL_MUL = 240, 26, 410
+LEVEL_BASE, LEVEL_TERM, LEVEL_MUL = 430, 25, 520
 
 
 def lane_terms(v):
@@ -1102,16 +952,20 @@ def levels_cost(p, levels):
 def schedule(p, lanes):
     """The cheapest of the stage schedules below (as early / as late as possible) and the
     list schedules."""
-    cand = [schedule_phases(p, lanes, late=False), schedule_phases(p, lanes, late=True)]
-    cand += [schedule_list(p, lanes, bias) for bias in (0, 100, 200, 300, -150)]
+    if len(p.vals) > 4000:  # a whole Miller loop or exponentiation
+        cand = [schedule_list(p, lanes, bias, window) for bias in (0, 200) for window in (3000, 8000)]
+    else:
+        cand = [schedule_phases(p, lanes, late=False), schedule_phases(p, lanes, late=True)]
+        cand += [schedule_list(p, lanes, bias) for bias in (0, 100, 200, 300, -150)]
     return min(cand, key=lambda c: levels_cost(p, c[0]))
 
 
-def schedule_list(p, lanes, bias=0):
+def schedule_list(p, lanes, bias=0, window=1 << 30):
     """List scheduling by the longest remaining path (products and additions weighted by the
-    cost of their levels).  A level either runs every ready operation, or additions alone:
-    the latter when the additions lead the critical path and the products can wait for a
-    shorter level (bias shifts that choice)."""
+    cost of their levels).  A level either runs the ready operations, or additions alone: the
+    latter when the additions lead the critical path and the products can wait for a shorter
+    level (bias shifts that choice).  Operations whose remaining path is shorter than the
+    longest one by more than `window` wait: a chain that could run far ahead would hold slots."""
     vals = p.vals
     n = len(vals)
     live = [False] * n
@@ -1141,16 +995,16 @@ def schedule_list(p, lanes, bias=0):
     levels = []
     level_of = [-1] * n
     while ready:
-        muls = sorted((i for i in ready if vals[i][0] == "mul"), key=lambda i: (-h[i], i))
-        lins = sorted((i for i in ready if vals[i][0] == "lin"), key=lambda i: (-h[i], i))
+        top = max(h[i] for i in ready)
+        cand = sorted((i for i in ready if h[i] >= top - window), key=lambda i: (-h[i], i))
+        muls = [i for i in cand if vals[i][0] == "mul"]
+        lins = [i for i in cand if vals[i][0] == "lin"]
         hm = h[muls[0]] if muls else -1
         hl = h[lins[0]] if lins else -1
         if muls and (not lins or max(hm, hl - wl + wm) < max(hl, hm + wl) + bias):
-            pick = sorted(muls + lins, key=lambda i: (-h[i], i))[:lanes]
+            pick = cand[:lanes]
         else:
-            pick = lins[:lanes]
-        if not pick:
-            pick = muls[:lanes]
+            pick = lins[:lanes] or muls[:lanes]
         L = len(levels)
         levels.append(sorted(pick))
         for i in pick:
@@ -1343,7 +1197,7 @@ class Kernel:
         self.progs = {}
         self.ntemps = self.tbase
         for nm, p in progs.items():
-            enc, used = compile_prog(p, self.io_slot, lambda x: self.cslot[x % P], self.tbase, 512, lanes)
+            enc, used = compile_prog(p, self.io_slot, lambda x: self.cslot[x % P], self.tbase, 1 << SEG_SHIFT, lanes)
             self.progs[nm] = enc
             self.ntemps = max(self.ntemps, used)
         self.nslots = self.ntemps
@@ -1354,15 +1208,16 @@ class Kernel:
             seg = self.segs[head]
             assert 1 <= seg <= 3  # the interpreter packs the bases of segments 1..3 only
             off = int(name.split(".")[1])
-            return (seg << 9) | off
+            return (seg << SEG_SHIFT) | off
         return self.state[name]
 
 
 def encode_term(s, c):
-    """32-bit term: offset of the slot in its segment in 16-byte units (bits 0..10; a slot is
-    48 bytes), signed coefficient (bits 11..23), segment (bits 30..31)"""
-    assert 0 <= s < 2048 and -4096 <= c < 4096
-    return (3 * (s & 511)) | ((c & 0x1fff) << 11) | ((s >> 9) << 30)
+    """32-bit term: offset of the slot in its segment in 16-byte units (bits 0..11; a slot is
+    48 bytes), signed coefficient (bits 12..24), segment (bits 30..31)"""
+    off = 3 * (s & ((1 << SEG_SHIFT) - 1))
+    assert 0 <= s < 4 << SEG_SHIFT and off < 4096 and -4096 <= c < 4096
+    return off | ((c & 0x1fff) << 12) | ((s >> SEG_SHIFT) << 30)
 
 
 def lane_records(op):
@@ -1435,7 +1290,7 @@ class OpTable:
         d = base // 4
         assert base % 4 == 0 and d < 1 << 18 and len(ops) <= WAVE_OPS
         d |= (T > 2) << 19 | (T > 4) << 20 | (T > 6) << 21 | (T > 10) << 22
-        d |= any(s_ >> 9 for op in ops for s_ in [op[1]] + [t[0] for t in op[3]]) << 23
+        d |= any(s_ >> SEG_SHIFT for op in ops for s_ in [op[1]] + [t[0] for t in op[3]]) << 23
         d |= len(ops) << 24
         d |= any(op[0] == OP_MUL for op in ops) << 30 | any(op[0] == OP_LIN for op in ops) << 31
         return d
@@ -1448,13 +1303,16 @@ class OpTable:
 TRACE_LIMITS = tuple((nt, sd) for nt in (8, 12, 20, 28) for sd in (4, 6, 10, 14))
 
 
-def cheapest(make, waves):
+WHOLE_LIMITS = ((12, 6), (20, 6), (12, 10), (20, 10), (28, 10))
+
+
+def cheapest(make, waves, limits=TRACE_LIMITS):
     """trace every program under each (NTERM, SIDE) limit and keep, per program, the trace
     whose schedule costs least"""
     global NTERM, SIDE
     best = {}
     saved = NTERM, SIDE
-    for nt, sd in TRACE_LIMITS:
+    for nt, sd in limits:
         NTERM, SIDE = nt, sd
         for nm, p in make().items():
             c = levels_cost(p, schedule(p, WAVE_OPS * waves)[0])
@@ -1465,19 +1323,19 @@ def cheapest(make, waves):
 
 
 # wavefronts of a workgroup, by kernel family
-ML_WAVES, FE_WAVES, G2_WAVES, G1_WAVES = 2, 2, 2, 2
+ML_WAVES, FE_WAVES, F12_WAVES, G2_WAVES, G1_WAVES = 2, 4, 2, 2, 2
 
 _BUILT = []
 
 
 def build_all():
     if not _BUILT:
-        mk = Kernel("ml", cheapest(miller_programs, ML_WAVES), MILLER_STATE, waves=ML_WAVES)
-        fe_state = ["t", "tinv"] + ["%s.%d" % (nm, k) for nm in ("nA", "nB", "nC", "n2") for k in (0, 1)]
-        fk = Kernel("fe", cheapest(fe_programs, FE_WAVES), fe_state, segs={"X": 1, "Y": 2, "D": 3}, waves=FE_WAVES)
+        mk = Kernel("ml", cheapest(miller_programs, ML_WAVES, WHOLE_LIMITS), MILLER_STATE, waves=ML_WAVES)
+        ek = Kernel("fe", cheapest(final_exp_programs, FE_WAVES, WHOLE_LIMITS), FE_STATE, waves=FE_WAVES)
+        fk = Kernel("f12", cheapest(f12_programs, F12_WAVES), [], segs={"X": 1, "Y": 2, "D": 3}, waves=F12_WAVES)
         gk = Kernel("g2", cheapest(g2_programs, G2_WAVES), G2_STATE, segs={"A": 2}, waves=G2_WAVES)
         g1k = Kernel("g1", cheapest(g1_programs, G1_WAVES), G1_STATE, segs={"A": 2}, waves=G1_WAVES)
-        _BUILT.append((mk, fk, gk, g1k))
+        _BUILT.append((mk, ek, fk, gk, g1k))
     return _BUILT[0]
 
 
@@ -1519,12 +1377,12 @@ def emit(kernels):
     descs = []
     for k in kernels:
         w("// kernel %s: %d slots (%d state, %d constants)" % (k.name, k.nslots, len(k.state), len(k.consts)))
-        assert k.nslots <= 512  # absolute slots are 9-bit offsets in segment 0
+        assert k.nslots <= 1 << SEG_SHIFT  # absolute slots are offsets in segment 0
         w("static constexpr int %s_NSLOT = %d;" % (k.name.upper(), k.nslots))
         w("static constexpr int %s_CBASE = %d;" % (k.name.upper(), k.cbase))
         w("static constexpr int %s_NCONST = %d;" % (k.name.upper(), len(k.consts)))
         w("static constexpr int %s_WAVES = %d;" % (k.name.upper(), k.waves))
-        assert k.waves == 2
+        assert k.waves in (2, 4)
         for nm, s in k.state.items():
             w("static constexpr int %s_%s = %d;" % (k.name.upper(), nm.replace(".", "_"), s))
         for nm, enc in k.progs.items():
@@ -1533,15 +1391,13 @@ def emit(kernels):
                 for v, ops in enumerate(level_blocks(row, k.waves)):
                     nxt[v] = table.add(ops, nxt[v])
             w("static constexpr int PROG_%s = %d;" % (nm.upper(), len(descs)))
-            descs.append((nm, [d | (1 << 18 if nm in CHECKED else 0) for d in nxt]))
-    w("static constexpr int PROG_INV = 255;")
-    assert len(descs) < 255
+            descs.append((nm, [d | (1 << 18 if nm in CHECKED else 0) for d in nxt] + [0] * (4 - k.waves)))
     w("// a program: descriptors of its first level, one per wavefront (bit 18: an addition that")
     w("// reports equal x-coordinates in its H slots)")
-    w("struct ProgDesc { uint32_t d[2]; };")
+    w("struct ProgDesc { uint32_t d[4]; };")
     w("static constexpr ProgDesc PROGS[%d] = {" % len(descs))
     for nm, d in descs:
-        w("  {{0x%xu, 0x%xu}},  // %s" % (d[0], d[1], nm))
+        w("  {{0x%xu, 0x%xu, 0x%xu, 0x%xu}},  // %s" % (*d, nm))
     w("};")
     w("static constexpr int LANE_TERMS_MAX = %d;" % max(LANE_TERMS))
     words = table.finish()
@@ -1554,19 +1410,6 @@ def emit(kernels):
         for x in k.consts:
             w("  {%s}," % ", ".join("0x%08xu" % v for v in limbs29(x * RMONT % P)))
         w("};")
-    mk = kernels[0]
-    seq = miller_sequence()
-    w("static constexpr int ML_SEQ_LEN = %d;" % len(seq))
-    w("__device__ const uint8_t ML_SEQ[%d][1] = {%s};" % (len(seq), ", ".join("{PROG_%s}" % s.upper() for s in seq)))
-    seqf, res_buf, nb = fe_sequence()
-    w("static constexpr int FE_NBUF = %d;" % nb)
-    w("static constexpr int FE_RESULT = %d;" % res_buf)
-    w("static constexpr int FE_SEQ_LEN = %d;" % len(seqf))
-    w("static constexpr int FE_SEQ_INV = %d;  // the entry that stands for tinv = t^{-1}" % [c[0] for c in seqf].index("INV"))
-    w("__device__ const uint8_t FE_SEQ[%d][4] = {" % len(seqf))
-    for prog, X, Y, D in seqf:
-        w("  {%s, %d, %d, %d}," % ("PROG_INV" if prog == "INV" else "PROG_%s" % prog.upper(), X, Y, D))
-    w("};")
     G = gls_constants()
     w("// GLS decomposition on G2: lattice basis rows (signed) and rounding constants G_i")
     w("static constexpr int64_t GLS_B_NEG[4][4] = {%s};" % ", ".join(
@@ -1582,7 +1425,7 @@ def emit(kernels):
 # ============================================================================ checks
 def run_levels(levels, S, segbase=(0, 0, 0, 0, 0, 0, 0, 0)):
     def res(x):
-        return segbase[x >> 9] + (x & 511) if x >> 9 else x
+        return segbase[x >> SEG_SHIFT] + (x & ((1 << SEG_SHIFT) - 1)) if x >> SEG_SHIFT else x
     for row in levels:
         out = []
         for kind, dst, na, terms in row:
@@ -1690,17 +1533,16 @@ def ref_miller(xP, yP, Q):
 
 def check():
     rng = random.Random(5)
-    mk, fk, gk, g1k = build_all()
-    for k in (mk, fk, gk, g1k):
+    mk, ek, fk, gk, g1k = build_all()
+    for k in (mk, ek, fk, gk, g1k):
         for nm, enc in k.progs.items():
             nmul = sum(1 for r in enc for op in r if op[0] == OP_MUL)
             nmlev = sum(1 for r in enc if any(op[0] == OP_MUL for op in r))
             print("%-22s levels %4d  mul-levels %3d  MUL %5d  LIN %5d  width %2d" %
                   (nm, len(enc), nmlev, nmul, sum(len(r) for r in enc) - nmul, max(len(r) for r in enc)),
                   file=sys.stderr)
-        print("kernel %s: %d slots" % (k.name, k.nslots), file=sys.stderr)
+        print("kernel %s: %d slots, %d wavefronts" % (k.name, k.nslots, k.waves), file=sys.stderr)
     # F_p12 programs against the polynomial reference
-    fprogs = fe_programs()
     base = {"X": fk.nslots, "Y": fk.nslots + 12, "D": fk.nslots + 24}
     seg = (0, base["X"], base["Y"], base["D"], 0, 0, 0, 0)
     for trial in range(3):
@@ -1714,7 +1556,7 @@ def check():
         cyc = ref_mul(ref_frob(ref_frob(cyc)), cyc)        # cyclotomic element
         want = {"f12_mul": ref_mul(rx, ry), "f12_frob1": ref_frob(rx), "f12_frob2": ref_frob(ref_frob(rx)),
                 "f12_frob3": ref_frob(ref_frob(ref_frob(rx))), "f12_conj": ref_conj(rx),
-                "f12_conj_mul": ref_mul(ref_conj(rx), ry), "f12_frob2_mul": ref_mul(ref_frob(ref_frob(rx)), ry)}
+                "f12_sqr": ref_mul(rx, rx), "f12_sqr_mul": ref_mul(ref_mul(rx, rx), ry)}
         for nm, wv in want.items():
             S2 = list(S)
             run_levels(fk.progs[nm], S2, seg)
@@ -1729,34 +1571,20 @@ def check():
         S2[base["X"]:base["X"] + 12] = ref_to_mem(cyc)
         run_levels(fk.progs["f12_csqr_mul"], S2, seg)
         assert S2[base["D"]:base["D"] + 12] == ref_to_mem(ref_mul(ref_mul(cyc, cyc), ry)), "csqr_mul"
-        # norm + easy part
-        S2 = list(S)
-        run_levels(fk.progs["fe_norm"], S2, seg)
-        t = S2[fk.state["t"]]
-        S2[fk.state["tinv"]] = pow(t, -1, P)
-        run_levels(fk.progs["fe_easy"], S2, seg)
-        assert S2[base["D"]:base["D"] + 12] == ref_to_mem(ref_mul(ref_conj(rx), ref_inv(rx))), "easy part"
     print("F_p12 programs ok", file=sys.stderr)
-    seqf, res_buf, nb = fe_sequence()
-    print("final exponentiation: %d calls, %d buffers, %d levels (%d with products)" % (
-        len(seqf), nb, sum(len(fk.progs[c[0]]) for c in seqf if c[0] != "INV"),
-        sum(1 for c in seqf if c[0] != "INV" for r in fk.progs[c[0]] if any(op[0] == OP_MUL for op in r))),
-        file=sys.stderr)
-    bufbase = fk.nslots
-    S = [0] * (bufbase + 12 * nb)
-    for x, sl in fk.cslot.items():
+    S = [0] * ek.nslots
+    for x, sl in ek.cslot.items():
         S[sl] = x
     fin = [rng.randrange(P) for _ in range(12)]
-    S[bufbase:bufbase + 12] = fin
-    for prog, X, Y, D in seqf:
-        if prog == "INV":
-            S[fk.state["tinv"]] = pow(S[fk.state["t"]], -1, P)
-            continue
-        run_levels(fk.progs[prog], S, (0, bufbase + 12 * X, bufbase + 12 * Y, bufbase + 12 * D, 0, 0, 0, 0))
-    got = S[bufbase + 12 * res_buf:bufbase + 12 * res_buf + 12]
+    for k in range(12):
+        S[ek.state["X.%d" % k]] = fin[k]
+    run_levels(ek.progs["fe_norm"], S)
+    S[ek.state["tinv"]] = pow(S[ek.state["t"]], -1, P)
+    run_levels(ek.progs["fe_rest"], S)
+    got = [S[ek.state["D.%d" % k]] for k in range(12)]
     assert got == ref_to_mem(ref_pow(ref_from_mem(fin), (P**12 - 1) // R)), "final exponentiation"
     print("final exponentiation ok", file=sys.stderr)
-    # Miller loop: pipelined programs vs the affine reference, compared after the
+    # Miller loop: the program vs the affine reference, compared after the
     # final exponentiation (the two differ by factors in proper subfields)
     g2 = ((10857046999023057135944570762232829481370756359578518086990519993285655852781,
            11559732032986387107991004021392285783925812861821192530917403151452391805634),
@@ -1769,13 +1597,12 @@ def check():
     st = mk.state
     S[st["xP"]], S[st["yP"]] = xP, yP
     S[st["xQ.0"]], S[st["xQ.1"]], S[st["yQ.0"]], S[st["yQ.1"]] = g2[0][0], g2[0][1], g2[1][0], g2[1][1]
-    for nm in miller_sequence():
-        run_levels(mk.progs[nm], S)
+    run_levels(mk.progs["ml"], S)
     f = ref_from_mem([S[st["f.%d" % k]] for k in range(12)])
     g = ref_miller(xP, yP, g2)
     e = (P**12 - 1) // R
     assert ref_pow(f, e) == ref_pow(g, e), "Miller loop"
-    print("Miller loop ok (%d bodies)" % len(miller_sequence()), file=sys.stderr)
+    print("Miller loop ok", file=sys.stderr)
     check_g2(gk, rng)
     check_g1(g1k, rng)
 

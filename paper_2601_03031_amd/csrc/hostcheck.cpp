@@ -245,7 +245,7 @@ API int hc_slp_miller(const uint8_t *P, const uint8_t *Q, uint8_t *out) {
   const fe in[6] = {p.x, p.y, q.x.c0, q.x.c1, q.y.c0, q.y.c1};
   for (int k = 0; k < 6; k++) S[slp::ML_xP + k] = slp::to29(in[k]);
   ld_consts(S, slp::ML_CBASE, slp::ML_CONSTS, slp::ML_NCONST);
-  for (int s = 0; s < slp::ML_SEQ_LEN; s++) slp::run_host(S, slp::ML_SEQ[s][0], 0, 0, 0);
+  slp::run_host(S, slp::PROG_ML, 0, 0, 0);
   fp12 f;
   fe *fw = reinterpret_cast<fe *>(&f);
   for (int k = 0; k < 12; k++) fw[k] = slp::from29(slp::canon29(S[slp::ML_f_0 + k]));
@@ -255,27 +255,25 @@ API int hc_slp_miller(const uint8_t *P, const uint8_t *Q, uint8_t *out) {
 
 // final exponentiation (op 0) or F_p12 product of a and b (op 1) on the engine
 API int hc_slp_f12(int op, const uint8_t *a, const uint8_t *b, uint8_t *out) {
-  static slp::f29 S[slp::FE_NSLOT + 12 * slp::FE_NBUF];
-  auto buf = [](int k) { return slp::FE_NSLOT + 12 * k; };
-  fp12 x = rd12(a), y = rd12(b);
+  fp12 x = rd12(a), y = rd12(b), f;
   const fe *xw = reinterpret_cast<const fe *>(&x), *yw = reinterpret_cast<const fe *>(&y);
-  for (int k = 0; k < 12; k++) { S[buf(0) + k] = slp::to29(xw[k]); S[buf(1) + k] = slp::to29(yw[k]); }
-  ld_consts(S, slp::FE_CBASE, slp::FE_CONSTS, slp::FE_NCONST);
-  int res;
-  if (op == 1) {
-    slp::run_host(S, slp::PROG_F12_MUL, buf(0), buf(1), buf(2));
-    res = 2;
-  } else {
-    for (int e = 0; e < slp::FE_SEQ_LEN; e++) {
-      int prog = slp::FE_SEQ[e][0];
-      if (prog == slp::PROG_INV) { S[slp::FE_tinv] = slp::to29(fp_inv_fast(slp::from29(slp::canon29(S[slp::FE_t])))); continue; }
-      slp::run_host(S, prog, buf(slp::FE_SEQ[e][1]), buf(slp::FE_SEQ[e][2]), buf(slp::FE_SEQ[e][3]));
-    }
-    res = slp::FE_RESULT;
-  }
-  fp12 f;
   fe *fw = reinterpret_cast<fe *>(&f);
-  for (int k = 0; k < 12; k++) fw[k] = slp::from29(slp::canon29(S[buf(res) + k]));
+  if (op == 1) {
+    static slp::f29 S[slp::F12_NSLOT + 36];
+    auto buf = [](int k) { return slp::F12_NSLOT + 12 * k; };
+    for (int k = 0; k < 12; k++) { S[buf(0) + k] = slp::to29(xw[k]); S[buf(1) + k] = slp::to29(yw[k]); }
+    ld_consts(S, slp::F12_CBASE, slp::F12_CONSTS, slp::F12_NCONST);
+    slp::run_host(S, slp::PROG_F12_MUL, buf(0), buf(1), buf(2));
+    for (int k = 0; k < 12; k++) fw[k] = slp::from29(slp::canon29(S[buf(2) + k]));
+  } else {
+    static slp::f29 S[slp::FE_NSLOT];
+    for (int k = 0; k < 12; k++) S[slp::FE_X_0 + k] = slp::to29(xw[k]);
+    ld_consts(S, slp::FE_CBASE, slp::FE_CONSTS, slp::FE_NCONST);
+    slp::run_host(S, slp::PROG_FE_NORM, 0, 0, 0);
+    S[slp::FE_tinv] = slp::to29(fp_inv_fast(slp::from29(slp::canon29(S[slp::FE_t]))));
+    slp::run_host(S, slp::PROG_FE_REST, 0, 0, 0);
+    for (int k = 0; k < 12; k++) fw[k] = slp::from29(slp::canon29(S[slp::FE_D_0 + k]));
+  }
   wr12(out, f);
   return 0;
 }
@@ -627,15 +625,15 @@ API int hc_fold_split_g2(const uint8_t *Qb, const uint8_t *kb, const uint8_t *Ab
 // g^k as the product over t < 4 of pow(g^{2^{16 t}}, chunk of bits [16 t, 16 t + w_t)) with
 // w_t = 16 (t < 3) or 17, on the engine (host model)
 API int hc_gt_pow_split(const uint8_t *gb, const uint8_t *kb, uint8_t *out) {
-  static slp::f29 S[slp::FE_NSLOT + 12 * gtp::NBUF];
+  static slp::f29 S[slp::F12_NSLOT + 12 * gtp::NBUF];
   fp12 g = rd12(gb), acc = f12_one();
   fe k = rd_raw(kb);
   gls::Dec dec = gls::decompose(k.l);
   const fe *gw = reinterpret_cast<const fe *>(&g);
-  ld_consts(S, slp::FE_CBASE, slp::FE_CONSTS, slp::FE_NCONST);
-  for (int i = 0; i < 12; i++) S[slp::FE_NSLOT + i] = slp::to29(gw[i]);
+  ld_consts(S, slp::F12_CBASE, slp::F12_CONSTS, slp::F12_NCONST);
+  for (int i = 0; i < 12; i++) S[slp::F12_NSLOT + i] = slp::to29(gw[i]);
   slp::HostCtx c{S};
-  const int b0 = slp::FE_NSLOT, b17 = slp::FE_NSLOT + 12 * 17;
+  const int b0 = slp::F12_NSLOT, b17 = slp::F12_NSLOT + 12 * 17;
   for (int t = 0; t < 4; t++) {
     if (t) {
       for (int i = 0; i < 16; i++) {
@@ -645,11 +643,11 @@ API int hc_gt_pow_split(const uint8_t *gb, const uint8_t *kb, uint8_t *out) {
     }
     slp::f29 base[12];
     for (int q = 0; q < 12; q++) base[q] = S[b0 + q];
-    int r = gtp::pow_cyc(c, gls::chunk(dec, 16 * t, t < 3 ? 16 : 17), slp::FE_NSLOT);
+    int r = gtp::pow_cyc(c, gls::chunk(dec, 16 * t, t < 3 ? 16 : 17), slp::F12_NSLOT);
     if (r >= 0) {
       fp12 part;
       fe *pw = reinterpret_cast<fe *>(&part);
-      for (int q = 0; q < 12; q++) pw[q] = slp::from29(slp::canon29(S[slp::FE_NSLOT + 12 * r + q]));
+      for (int q = 0; q < 12; q++) pw[q] = slp::from29(slp::canon29(S[slp::F12_NSLOT + 12 * r + q]));
       acc = f12_mul(acc, part);
     }
     for (int q = 0; q < 12; q++) S[b0 + q] = base[q];
@@ -661,19 +659,19 @@ API int hc_gt_pow_split(const uint8_t *gb, const uint8_t *kb, uint8_t *out) {
 // g^k on the engine (host model) for g in the cyclotomic subgroup, k canonical (32 bytes
 // big-endian) through the 4-dimensional Frobenius split
 API int hc_gt_pow_cyc(const uint8_t *gb, const uint8_t *kb, uint8_t *out) {
-  static slp::f29 S[slp::FE_NSLOT + 12 * gtp::NBUF];
+  static slp::f29 S[slp::F12_NSLOT + 12 * gtp::NBUF];
   fp12 g = rd12(gb);
   const fe *gw = reinterpret_cast<const fe *>(&g);
-  for (int i = 0; i < 12; i++) S[slp::FE_NSLOT + i] = slp::to29(gw[i]);
-  ld_consts(S, slp::FE_CBASE, slp::FE_CONSTS, slp::FE_NCONST);
+  for (int i = 0; i < 12; i++) S[slp::F12_NSLOT + i] = slp::to29(gw[i]);
+  ld_consts(S, slp::F12_CBASE, slp::F12_CONSTS, slp::F12_NCONST);
   fe k = rd_raw(kb);
   gls::Dec dec = gls::decompose(k.l);
   slp::HostCtx c{S};
-  int r = gtp::pow_cyc(c, dec, slp::FE_NSLOT);
+  int r = gtp::pow_cyc(c, dec, slp::F12_NSLOT);
   fp12 f;
   fe *fw = reinterpret_cast<fe *>(&f);
   for (int i = 0; i < 12; i++)
-    fw[i] = r < 0 ? (i == 0 ? f_one<FpP>() : fe_zero()) : slp::from29(slp::canon29(S[slp::FE_NSLOT + 12 * r + i]));
+    fw[i] = r < 0 ? (i == 0 ? f_one<FpP>() : fe_zero()) : slp::from29(slp::canon29(S[slp::F12_NSLOT + 12 * r + i]));
   wr12(out, f);
   return 0;
 }
@@ -686,19 +684,15 @@ API int hc_gt_pow_cyc(const uint8_t *gb, const uint8_t *kb, uint8_t *out) {
 // 6 G2 mixed addition, 7 G2 to affine (norm + affine), 8 F_p12 product
 static uint64_t prog_muls(int prog) {
   uint64_t n = 0;
-  for (int v = 0; v < 2; v++)
+  for (int v = 0; v < 4; v++)
     for (uint32_t d = slp::PROGS[prog].d[v]; d; d = slp::blk_word(slp::OPS, d, 0, 1))
       for (int i = 0; i < slp::blk_ops(d); i++) n += slp::term_coef(slp::blk_word(slp::OPS, d, 2 * i, 0)) == 1;
   return n;
 }
 API uint64_t hc_engine_muls(int which) {
-  uint64_t n = 0;
   switch (which) {
-    case 0: for (int s = 0; s < slp::ML_SEQ_LEN; s++) n += prog_muls(slp::ML_SEQ[s][0]); return n;
-    case 1:
-      for (int e = 0; e < slp::FE_SEQ_LEN; e++)
-        if (slp::FE_SEQ[e][0] != slp::PROG_INV) n += prog_muls(slp::FE_SEQ[e][0]);
-      return n;
+    case 0: return prog_muls(slp::PROG_ML);
+    case 1: return prog_muls(slp::PROG_FE_NORM) + prog_muls(slp::PROG_FE_REST);
     case 2: return prog_muls(slp::PROG_G2_PSI);
     case 3: return prog_muls(slp::PROG_G2_TABLE);
     case 4: return prog_muls(slp::PROG_G2_DBL);

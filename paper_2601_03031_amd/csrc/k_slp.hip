@@ -8,13 +8,13 @@
 #include "g1mul.hpp"
 #include "oa_terms.hpp"
 
-// every program family is scheduled for the same number of wavefronts, so that a kernel may
-// run several of them
+// every program family but the final exponentiation's is scheduled for the same number of
+// wavefronts, so that a kernel may run several of them
 #define SLP_W 2
 #define SLP_T (64 * SLP_W)
-static_assert(slp::ML_WAVES == SLP_W && slp::FE_WAVES == SLP_W && slp::G1_WAVES == SLP_W && slp::G2_WAVES == SLP_W,
+#define FE_T (64 * slp::FE_WAVES)
+static_assert(slp::ML_WAVES == SLP_W && slp::F12_WAVES == SLP_W && slp::G1_WAVES == SLP_W && slp::G2_WAVES == SLP_W,
               "programs scheduled for another workgroup size");
-static_assert(slp::ML_SEQ_LEN <= slp::MAX_CALLS && slp::FE_SEQ_LEN <= slp::MAX_CALLS, "call sequence longer than its LDS list");
 typedef slp::DevCtx<SLP_W> Ctx;
 typedef slp::DevCtx<SLP_W, true> CtxInline;  // for kernels with one place that runs calls
 // the call list of a workgroup in LDS
@@ -29,9 +29,9 @@ __device__ __forceinline__ bool g2_inf(const g2_aff &Q) {
 
 using slp::f29;
 
-template <int NCONST>
+template <int NCONST, int T = SLP_T>
 __device__ __forceinline__ void load_consts(f29 *S, int base, const uint32_t (*C)[9]) {
-  for (int c = threadIdx.x; c < NCONST; c += SLP_T) {
+  for (int c = threadIdx.x; c < NCONST; c += T) {
     f29 v;
 #pragma unroll
     for (int j = 0; j < 9; j++) v.l[j] = C[c][j];
@@ -55,8 +55,7 @@ __device__ __forceinline__ void miller_one(CtxInline c, const g1_aff *P, const g
     S[slp::ML_xP + t] = slp::to29(q[t - 2]);  // xQ.0, xQ.1, yQ.0, yQ.1
   }
   load_consts<slp::ML_NCONST>(S, slp::ML_CBASE, slp::ML_CONSTS);
-  for (int e = t; e < slp::ML_SEQ_LEN; e += SLP_T) c.cl[e] = slp::call(slp::ML_SEQ[e][0], 0, 0, 0);
-  c.run_list(0, slp::ML_SEQ_LEN, 0, 0);
+  c.run(slp::PROG_ML, 0, 0, 0);
   if (t < 12) out[t] = slp::from29(slp::canon29(S[slp::ML_f_0 + t]));
 }
 
@@ -66,7 +65,7 @@ __device__ __forceinline__ void miller_one(CtxInline c, const g1_aff *P, const g
 __global__ void __launch_bounds__(SLP_T, 4) ks_miller(const g1_aff *P, uint64_t sp, const g2_aff *Q, uint64_t sq, uint64_t n,
                                                   fp12 *out) {
   __shared__ f29 S[slp::ML_NSLOT];
-  CALL_LIST();
+  __shared__ slp::Call calls_sh[1];
   uint64_t i = blockIdx.x;
   if (i >= n) return;
   miller_one(CtxInline{S, calls_sh}, P + i * sp, Q + i * sq, out + i);
@@ -77,7 +76,7 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_oa_miller(const g1_aff *A, const 
                                                      fp12 *F) {
   CHAIN_PRIORITY();
   __shared__ f29 S[slp::ML_NSLOT];
-  CALL_LIST();
+  __shared__ slp::Call calls_sh[1];
   uint64_t id = blockIdx.x;
   if (id >= nb * 2 * h) return;
   uint64_t k = id / (2 * h), r = id % (2 * h), side = r / h, i = r % h;
@@ -105,17 +104,16 @@ __device__ bool last_arrival(uint32_t *cnt, uint32_t n, uint32_t *flag) {
   return *flag != 0;
 }
 
-#define FE_SLOTS (slp::FE_NSLOT + 12 * slp::FE_NBUF)
-#define FE_BUF(b) ((uint16_t)(slp::FE_NSLOT + 12 * (b)))
+#define F12_BUF(b) ((uint16_t)(slp::F12_NSLOT + 12 * (b)))
 
 // Product of each segment data[g stride + 0 .. len) into data[g stride] in one launch: a
 // workgroup per pair of the first level; of two sibling nodes, the workgroup that finishes
 // second climbs to the parent (arrival counters as in k_jac_tree).
 __global__ void __launch_bounds__(SLP_T, 4) ks_f12_tree(fp12 *data, uint64_t nseg, uint64_t stride, uint64_t len, uint32_t *cnt) {
   CHAIN_PRIORITY();
-  __shared__ f29 S[slp::FE_NSLOT + 36];
+  __shared__ f29 S[slp::F12_NSLOT + 36];
   __shared__ uint32_t arrived;
-  CALL_LIST();
+  __shared__ slp::Call calls_sh[1];
   CtxInline cx{S, calls_sh};
   uint64_t per = (len + 1) / 2;
   uint64_t id = blockIdx.x;
@@ -131,12 +129,12 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_f12_tree(fp12 *data, uint64_t nse
       fe *da = reinterpret_cast<fe *>(seg + a);
       const fe *db = reinterpret_cast<const fe *>(seg + b);
       if (t < 12) {
-        S[slp::FE_NSLOT + t] = slp::to29(da[t]);
-        S[slp::FE_NSLOT + 12 + t] = slp::to29(db[t]);
+        S[slp::F12_NSLOT + t] = slp::to29(da[t]);
+        S[slp::F12_NSLOT + 12 + t] = slp::to29(db[t]);
       }
       __syncthreads();
-      cx.run(slp::PROG_F12_MUL, FE_BUF(0), FE_BUF(1), FE_BUF(2));
-      if (t < 12) da[t] = slp::from29(slp::canon29(S[slp::FE_NSLOT + 24 + t]));
+      cx.run(slp::PROG_F12_MUL, F12_BUF(0), F12_BUF(1), F12_BUF(2));
+      if (t < 12) da[t] = slp::from29(slp::canon29(S[slp::F12_NSLOT + 24 + t]));
     }
     if (n == 1) return;
     uint64_t nn = (n + 1) / 2, qp = q >> 1;
@@ -150,38 +148,34 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_f12_tree(fp12 *data, uint64_t nse
   }
 }
 
-// final exponentiation of one F_p12 element on the engine
-__device__ __forceinline__ void fe_job(CtxInline c, const fp12 *in, fp12 *out) {
-  f29 *S = c.S;
+// Final exponentiation of one F_p12 element: the norm, one inversion in F_p and the rest, on
+// four wavefronts (the chain of squarings is a product level each, and the products gathered
+// beside it fill the other lanes: 274 levels on four wavefronts, some 350 on two).
+__device__ __forceinline__ void fe_job(const fp12 *in, fp12 *out) {
+  __shared__ f29 S[slp::FE_NSLOT];
+  __shared__ slp::Call calls_sh[1];
+  slp::DevCtx<slp::FE_WAVES, true> c{S, calls_sh};
   int t = threadIdx.x;
   const fe *src = reinterpret_cast<const fe *>(in);
-  if (t < 12) S[FE_BUF(0) + t] = slp::to29(src[t]);
-  load_consts<slp::FE_NCONST>(S, slp::FE_CBASE, slp::FE_CONSTS);
-  for (int e = t; e < slp::FE_SEQ_LEN; e += SLP_T) {
-    const uint8_t *q = slp::FE_SEQ[e];
-    if (e != slp::FE_SEQ_INV) c.cl[e] = slp::call(q[0], FE_BUF(q[1]), FE_BUF(q[2]), FE_BUF(q[3]));
-  }
+  if (t < 12) S[slp::FE_X_0 + t] = slp::to29(src[t]);
+  load_consts<slp::FE_NCONST, FE_T>(S, slp::FE_CBASE, slp::FE_CONSTS);
 #pragma unroll 1
-  for (int first = 0; first < slp::FE_SEQ_LEN;) {
-    const int n = first ? slp::FE_SEQ_LEN : slp::FE_SEQ_INV;
-    c.run_list(first, n, 0, 0);
-    if (!first) c.invert(slp::FE_tinv, slp::FE_t);
-    first = n + 1;
+  for (int part = 0; part < 2; part++) {
+    c.run(part ? slp::PROG_FE_REST : slp::PROG_FE_NORM, 0, 0, 0);
+    if (!part) c.invert(slp::FE_tinv, slp::FE_t);
   }
   fe *dst = reinterpret_cast<fe *>(out);
-  if (t < 12) dst[t] = slp::from29(slp::canon29(S[FE_BUF(slp::FE_RESULT) + t]));
+  if (t < 12) dst[t] = slp::from29(slp::canon29(S[slp::FE_D_0 + t]));
 }
 
 // f^((p^12 - 1)/r), a workgroup per input; input s at in[s in_stride], output to
 // (s odd ? out1 : out0)[(s >> 1) ostride]
-__global__ void __launch_bounds__(SLP_T, 4) ks_final_exp(const fp12 *in, uint64_t in_stride, uint64_t n, fp12 *out0, fp12 *out1,
-                                                     uint64_t ostride) {
+__global__ void __launch_bounds__(FE_T, 4) ks_final_exp(const fp12 *in, uint64_t in_stride, uint64_t n, fp12 *out0, fp12 *out1,
+                                                       uint64_t ostride) {
   CHAIN_PRIORITY();
-  __shared__ f29 S[FE_SLOTS];
-  CALL_LIST();
   uint64_t s = blockIdx.x;
   if (s >= n) return;
-  fe_job(CtxInline{S, calls_sh}, in + s * in_stride, ((s & 1) ? out1 : out0) + (s >> 1) * ostride);
+  fe_job(in + s * in_stride, ((s & 1) ? out1 : out0) + (s >> 1) * ostride);
 }
 
 // ---------------------------------------------------------------- G2 scalar multiplications
@@ -266,7 +260,7 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_kzg_terms_split(const g2_aff *h, 
 // out[s] = in[s]^k_s (k in Montgomery F_r form), square-and-multiply with the engine's
 // F_p12 product (inputs need not lie in the cyclotomic subgroup)
 __global__ void __launch_bounds__(SLP_T, 4) ks_gt_pow(const fp12 *in, const fe *k_mont, uint64_t n, fp12 *out) {
-  __shared__ f29 S[slp::FE_NSLOT + 36];
+  __shared__ f29 S[slp::F12_NSLOT + 36];
   CALL_LIST();
   CtxInline c{S, calls_sh};
   __shared__ uint32_t kc[8];
@@ -274,12 +268,12 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_gt_pow(const fp12 *in, const fe *
   if (s >= n) return;
   const int t = threadIdx.x;
   const fe *src = reinterpret_cast<const fe *>(in + s);
-  if (t < 12) S[FE_BUF(0) + t] = slp::to29(src[t]);
+  if (t < 12) S[F12_BUF(0) + t] = slp::to29(src[t]);
   if (t == 0) {
     fe kcan = f_from_mont<FpR>(k_mont[s]);
     for (int w = 0; w < 8; w++) kc[w] = kcan.l[w];
   }
-  load_consts<slp::FE_NCONST>(S, slp::FE_CBASE, slp::FE_CONSTS);
+  load_consts<slp::F12_NCONST>(S, slp::F12_CBASE, slp::F12_CONSTS);
   __syncthreads();
   int top = -1;
   for (int b = 255; b >= 0; b--)
@@ -291,15 +285,19 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_gt_pow(const fp12 *in, const fe *
   }
   // a call per bit below the top one (a squaring, with a product where the bit is set), the
   // accumulator alternating between buffers 1 and 2; buffer 0 holds the base
-  for (int i = t; i < top; i += SLP_T) {
-    const int bit = top - 1 - i, src = i == 0 ? 0 : 2 - (i & 1), dst = 1 + (i & 1);
-    const bool one = kc[bit >> 5] >> (bit & 31) & 1;
-    c.cl[i] = one ? slp::call(slp::PROG_F12_SQR_MUL, FE_BUF(src), FE_BUF(0), FE_BUF(dst))
-                  : slp::call(slp::PROG_F12_SQR, FE_BUF(src), FE_BUF(src), FE_BUF(dst));
+#pragma unroll 1
+  for (int first = 0; first < top; first += slp::MAX_CALLS) {
+    const int n = top - first < slp::MAX_CALLS ? top - first : slp::MAX_CALLS;
+    for (int e = t; e < n; e += SLP_T) {
+      const int i = first + e, bit = top - 1 - i, src = i == 0 ? 0 : 2 - (i & 1), dst = 1 + (i & 1);
+      const bool one = kc[bit >> 5] >> (bit & 31) & 1;
+      c.cl[e] = one ? slp::call(slp::PROG_F12_SQR_MUL, F12_BUF(src), F12_BUF(0), F12_BUF(dst))
+                    : slp::call(slp::PROG_F12_SQR, F12_BUF(src), F12_BUF(src), F12_BUF(dst));
+    }
+    c.run_list(0, n, 0, 0);
   }
-  if (top) c.run_list(0, top, 0, 0);
   const int acc = top == 0 ? 0 : 2 - (top & 1);
-  if (t < 12) dst[t] = slp::from29(slp::canon29(S[FE_BUF(acc) + t]));
+  if (t < 12) dst[t] = slp::from29(slp::canon29(S[F12_BUF(acc) + t]));
 }
 
 // ---------------------------------------------------------------- G1 scalar multiplications
@@ -450,7 +448,7 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_oa_pterms(const g1_aff *A, const 
                                                      fp12 *F) {
   CHAIN_PRIORITY();
   __shared__ f29 S[slp::ML_NSLOT];
-  CALL_LIST();
+  __shared__ slp::Call calls_sh[1];
   uint64_t id = blockIdx.x;
   if (id >= nb * 8 * q) return;
   oat::Term tm = oat::term(id, K, nb, q);
@@ -472,14 +470,14 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_oa_g1terms_next(const g1_aff *A, 
 }
 
 // ---------------------------------------------------------------- cyclotomic G_T powers
-#define GTP_SLOTS (slp::FE_NSLOT + 12 * gtp::NBUF)
+#define GTP_SLOTS (slp::F12_NSLOT + 12 * gtp::NBUF)
 
 // ---------------------------------------------------------------- split multiplications
 // Multiples for the time-split multiplications: M[3 s + m - 1] = G[s]^{2^{16 m}} (cyclotomic
 // squarings), a workgroup per (s, m), m = 1, 2, 3
 __global__ void __launch_bounds__(SLP_T, 4) ks_gt_sqr_mults(const fp12 *G, uint64_t n, fp12 *M) {
   CHAIN_PRIORITY();
-  __shared__ f29 S[slp::FE_NSLOT + 24];
+  __shared__ f29 S[slp::F12_NSLOT + 24];
   CALL_LIST();
   CtxInline c{S, calls_sh};
   uint64_t id = blockIdx.x;
@@ -487,14 +485,14 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_gt_sqr_mults(const fp12 *G, uint6
   uint64_t s = id / 3, m = id % 3 + 1;
   const int t = threadIdx.x;
   const fe *src = reinterpret_cast<const fe *>(G + s);
-  if (t < 12) S[FE_BUF(0) + t] = slp::to29(src[t]);
-  load_consts<slp::FE_NCONST>(S, slp::FE_CBASE, slp::FE_CONSTS);
+  if (t < 12) S[F12_BUF(0) + t] = slp::to29(src[t]);
+  load_consts<slp::F12_NCONST>(S, slp::F12_CBASE, slp::F12_CONSTS);
   __syncthreads();
   for (int e = t; e < 16 * (int)m; e += SLP_T)
-    c.cl[e] = slp::call(slp::PROG_F12_CSQR, FE_BUF(e & 1), FE_BUF(e & 1), FE_BUF(1 - (e & 1)));
+    c.cl[e] = slp::call(slp::PROG_F12_CSQR, F12_BUF(e & 1), F12_BUF(e & 1), F12_BUF(1 - (e & 1)));
   c.run_list(0, 16 * (int)m, 0, 0);  // an even number of squarings: the result is in buffer 0
   fe *dst = reinterpret_cast<fe *>(M + 3 * s + m - 1);
-  if (t < 12) dst[t] = slp::from29(slp::canon29(S[FE_BUF(0) + t]));
+  if (t < 12) dst[t] = slp::from29(slp::canon29(S[F12_BUF(0) + t]));
 }
 
 // point s of a segmented list: P[(s / seg) segstride + s % seg]
@@ -705,12 +703,12 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_oa_combine_split(const fp12 *PX, 
     dec = gls::chunk(gls::decompose(kc.l), 16 * part, part < 3 ? 16 : 17);
   }
   const fe *src = reinterpret_cast<const fe *>(part ? PXm + 3 * s + part - 1 : PX + s);
-  if (t < 12) S[FE_BUF(0) + t] = slp::to29(src[t]);
-  load_consts<slp::FE_NCONST>(S, slp::FE_CBASE, slp::FE_CONSTS);
+  if (t < 12) S[F12_BUF(0) + t] = slp::to29(src[t]);
+  load_consts<slp::F12_NCONST>(S, slp::F12_CBASE, slp::F12_CONSTS);
   __syncthreads();
-  int r = gtp::pow_cyc(c, dec, slp::FE_NSLOT);
+  int r = gtp::pow_cyc(c, dec, slp::F12_NSLOT);
   fe *dst = reinterpret_cast<fe *>(PE + 4 * s + part);
-  if (t < 12) dst[t] = r < 0 ? (t == 0 ? f_one<FpP>() : fe_zero()) : slp::from29(slp::canon29(S[FE_BUF(r) + t]));
+  if (t < 12) dst[t] = r < 0 ? (t == 0 ? f_one<FpP>() : fe_zero()) : slp::from29(slp::canon29(S[F12_BUF(r) + t]));
 }
 
 // Both parts of L_j, R_j from the combine, in one launch.  Blocks [0, 2 nb):
@@ -720,7 +718,7 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_oa_combine_split(const fp12 *PX, 
 __global__ void __launch_bounds__(SLP_T, 4) ks_oa_combine8(const fp12 *U, const fp12 *P, const g1_aff *U1, const g1_jac *P1,
                                                        uint64_t nb, fp12 *L, fp12 *R, g1_aff *L1, g1_aff *R1, uint64_t lK) {
   CHAIN_PRIORITY();
-  __shared__ f29 S[slp::FE_NSLOT + 12 * 11];
+  __shared__ f29 S[slp::F12_NSLOT + 12 * 11];
   CALL_LIST();
   CtxInline c{S, calls_sh};
   uint64_t id = blockIdx.x;
@@ -743,24 +741,22 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_oa_combine8(const fp12 *U, const 
   const int t = threadIdx.x;
   // buffers 0 and 1 the product (alternating, U first), 2..9 the powers
   const fe *u = reinterpret_cast<const fe *>(U + id), *pp = reinterpret_cast<const fe *>(P + 4 * (4 * k + 2 * side));
-  for (int i = t; i < 12 * 9; i += SLP_T) S[i < 12 ? FE_BUF(0) + i : FE_BUF(1) + i] = slp::to29(i < 12 ? u[i] : pp[i - 12]);
-  load_consts<slp::FE_NCONST>(S, slp::FE_CBASE, slp::FE_CONSTS);
-  if (t < 8) c.cl[t] = slp::call(slp::PROG_F12_MUL, FE_BUF(t & 1), FE_BUF(2 + t), FE_BUF(1 - (t & 1)));
+  for (int i = t; i < 12 * 9; i += SLP_T) S[i < 12 ? F12_BUF(0) + i : F12_BUF(1) + i] = slp::to29(i < 12 ? u[i] : pp[i - 12]);
+  load_consts<slp::F12_NCONST>(S, slp::F12_CBASE, slp::F12_CONSTS);
+  if (t < 8) c.cl[t] = slp::call(slp::PROG_F12_MUL, F12_BUF(t & 1), F12_BUF(2 + t), F12_BUF(1 - (t & 1)));
   c.run_list(0, 8, 0, 0);
   fe *dst = reinterpret_cast<fe *>((side ? R : L) + k * lK);
-  if (t < 12) dst[t] = slp::from29(slp::canon29(S[FE_BUF(0) + t]));
+  if (t < 12) dst[t] = slp::from29(slp::canon29(S[F12_BUF(0) + t]));
 }
 
 // final exponentiations of two strided lists: job s < n0 takes in0[s st0] to out0[s], the
 // others in1[(s - n0) st1] to out1[s - n0]
-__global__ void __launch_bounds__(SLP_T, 4) ks_final_exp2(const fp12 *in0, uint64_t st0, uint64_t n0, fp12 *out0, const fp12 *in1,
-                                                      uint64_t st1, uint64_t n1, fp12 *out1) {
+__global__ void __launch_bounds__(FE_T, 4) ks_final_exp2(const fp12 *in0, uint64_t st0, uint64_t n0, fp12 *out0,
+                                                        const fp12 *in1, uint64_t st1, uint64_t n1, fp12 *out1) {
   CHAIN_PRIORITY();
-  __shared__ f29 S[FE_SLOTS];
-  CALL_LIST();
   uint64_t s = blockIdx.x;
   if (s >= n0 + n1) return;
-  fe_job(CtxInline{S, calls_sh}, s < n0 ? in0 + s * st0 : in1 + (s - n0) * st1, s < n0 ? out0 + s : out1 + (s - n0));
+  fe_job(s < n0 ? in0 + s * st0 : in1 + (s - n0) * st1, s < n0 ? out0 + s : out1 + (s - n0));
 }
 
 // The reduced G1 groups of the terms taken ahead (oa_terms.hpp, segment sums in PS) made
@@ -800,7 +796,7 @@ void final_exp(const fp12 *in, uint64_t stride, uint64_t n, fp12 *out0, fp12 *ou
     out1 = out0 + ostride;
     ostride *= 2;
   }
-  if (n) LAUNCH(ks_final_exp, dim3((unsigned)n), dim3(SLP_T), 0, in, stride, n, out0, out1, ostride);
+  if (n) LAUNCH(ks_final_exp, dim3((unsigned)n), dim3(FE_T), 0, in, stride, n, out0, out1, ostride);
 }
 void oa_fold_g2(const g2_aff *Vin, g2_aff *Vout, const fe *Xinv, uint64_t K, uint64_t nb, uint64_t h, uint32_t j, uint32_t lK,
                 hipStream_t st) {
@@ -848,7 +844,7 @@ void oa_combine8(const fp12 *U, const fp12 *P, const g1_aff *U1, const g1_jac *P
 }
 void final_exp2(const fp12 *in0, uint64_t st0, uint64_t n0, fp12 *out0, const fp12 *in1, uint64_t st1, uint64_t n1, fp12 *out1,
                 hipStream_t st) {
-  if (n0 + n1) LAUNCH(ks_final_exp2, dim3((unsigned)(n0 + n1)), dim3(SLP_T), 0, in0, st0, n0, out0, in1, st1, n1, out1);
+  if (n0 + n1) LAUNCH(ks_final_exp2, dim3((unsigned)(n0 + n1)), dim3(FE_T), 0, in0, st0, n0, out0, in1, st1, n1, out1);
 }
 void g1_tree(g1_jac *data, uint64_t nseg, uint64_t stride, uint64_t len, uint32_t *cnt, hipStream_t st) {
   if (len > 1) LAUNCH(ks_jac_tree<false>, dim3((unsigned)(nseg * ((len + 1) / 2))), dim3(SLP_T), 0, data, nseg, stride, len, cnt);

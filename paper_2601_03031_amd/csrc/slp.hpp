@@ -172,12 +172,13 @@ __host__ __device__ __forceinline__ uint64_t seg_bases(uint32_t bx, uint32_t by,
 
 // byte address of the slot that term t names: its segment's base is one shift of the packed
 // bases (bits 26..29 of a term are zero, so t >> 26 is 16 times the segment)
+__host__ __device__ __forceinline__ uint32_t term_off(uint32_t t) { return (t & 0xfffu) << 4; }
 __host__ __device__ __forceinline__ uint32_t term_addr(uint32_t t, uint64_t rel) {
-  return ((t & 0x7ffu) << 4) + ((uint32_t)(rel >> (t >> 26)) & 0xffffu);
+  return term_off(t) + ((uint32_t)(rel >> (t >> 26)) & 0xffffu);
 }
 
-// signed 13-bit coefficient at bits 11..23 of a term
-__host__ __device__ __forceinline__ int term_coef(uint32_t t) { return (int)(t << 8) >> 19; }
+// signed 13-bit coefficient at bits 12..24 of a term
+__host__ __device__ __forceinline__ int term_coef(uint32_t t) { return (int)(t << 7) >> 19; }
 
 // a block descriptor's fields (gen_slp.py OpTable)
 static constexpr uint32_t BLK_OFF = (1u << 18) - 1, BLK_CHK = 1u << 18, BLK_T2 = 1u << 19, BLK_T4 = 1u << 20, BLK_T6 = 1u << 21,
@@ -191,18 +192,20 @@ __host__ __device__ __forceinline__ uint32_t blk_word(const uint32_t *ops, uint3
   return ops[4 * (d & BLK_OFF) + 256 * (i >> 2) + 4 * l + (i & 3)];
 }
 
-// One call of a sequence: the program's first descriptors and the packed segment bases
+// One call of a sequence: the program's first descriptors (one per wavefront) and the packed
+// segment bases
 struct alignas(16) Call {
-  uint32_t d0, d1;
-  uint64_t rel;
+  uint32_t d[4];
+  uint64_t rel, pad;
 };
 __host__ __device__ __forceinline__ Call call(int prog, int x = 0, int y = 0, int d = 0) {
-  return Call{PROGS[prog].d[0], PROGS[prog].d[1], seg_bases(x, y, d)};
+  const ProgDesc &p = PROGS[prog];
+  return Call{{p.d[0], p.d[1], p.d[2], p.d[3]}, seg_bases(x, y, d), 0};
 }
-__host__ __device__ __forceinline__ bool call_is(const Call &c, int prog) { return c.d0 == PROGS[prog].d[0]; }
+__host__ __device__ __forceinline__ bool call_is(const Call &c, int prog) { return c.d[0] == PROGS[prog].d[0]; }
 __host__ __device__ __forceinline__ int call_y(const Call &c) { return (int)(c.rel >> 32 & 0xffffu) / 48; }
 
-static constexpr int MAX_CALLS = 256;
+static constexpr int MAX_CALLS = 128;
 
 // whether an almost-reduced value may be congruent to 0, from its two low limbs alone (it is
 // then -p, 0 or p; another value passes with probability below 2^-56)
@@ -218,6 +221,8 @@ typedef __attribute__((address_space(3))) Call lds_call;
 typedef __attribute__((address_space(3))) uint32_t lds_u32;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) u32x2 lds_u32x2;
 
 // the 9 limbs of the slot at an LDS address (slots are 16-byte aligned)
 __device__ __forceinline__ void get_slot(uint32_t addr, uint32_t *x) {
@@ -255,7 +260,7 @@ template <int N, bool SEG>
 __device__ __forceinline__ void add_terms(uint32_t base, const uint32_t *w, uint64_t rel, int64_t *acc) {
   uint32_t x[N][9];
 #pragma unroll
-  for (int i = 0; i < N; i++) get_slot(SEG ? term_addr(w[i], rel) : ((w[i] & 0x7ffu) << 4) + base, x[i]);
+  for (int i = 0; i < N; i++) get_slot(SEG ? term_addr(w[i], rel) : term_off(w[i]) + base, x[i]);
 #pragma unroll
   for (int i = 0; i < N; i++) {
     const int k = term_coef(w[i]);
@@ -318,28 +323,31 @@ __device__ __forceinline__ void run_block(uint32_t base, uint32_t d, const uint3
 // the first.  The loop is written for the fewest scalar instructions, since one wavefront
 // issues about one instruction in four cycles whatever its kind.
 template <int NW> __device__ __forceinline__ int run_calls(uint32_t base, uint32_t list, int n, int chk, int nchk) {
-  static_assert(NW == 2, "a call entry holds two descriptors");
+  static_assert(NW == 2 || NW == 4, "a call entry holds up to four descriptors");
   base = __builtin_amdgcn_readfirstlane(base);
   list = __builtin_amdgcn_readfirstlane(list);
   n = __builtin_amdgcn_readfirstlane(n);
   chk = __builtin_amdgcn_readfirstlane(chk);
   nchk = __builtin_amdgcn_readfirstlane(nchk);
   const uint32_t lane = threadIdx.x & 63, half = lane >> 1;
-  const bool w1 = threadIdx.x >= 64;
-  const uint32_t end = list + 16u * n;
+  const uint32_t wave4 = threadIdx.x >> 6 << 2;  // where this wavefront's descriptor is in an entry
+  const uint32_t end = list + 32u * n;
   const uint64_t base4 = base * 0x0001000100010001ull;
   const uint32_t chk_mask = nchk ? BLK_CHK : 0;
   uint32_t n_ent = list;  // entry after the next level's call
-  u32x4 ahead = *(const lds_u32x4 *)(uintptr_t)list;
+  uint32_t ahead_d = *(const lds_u32 *)(uintptr_t)(list + wave4);  // that entry
+  u32x2 ahead_rel = *(const lds_u32x2 *)(uintptr_t)(list + 16);
   uint32_t nd = 0, n_chk = 0;  // the next level: descriptor, whether its call is a checked addition,
   uint64_t n_rel = 0;          // segment bases
   auto next_call = [&]() {
-    const u32x4 v = ahead;
-    n_ent += 16;
-    if (n_ent < end) ahead = *(const lds_u32x4 *)(uintptr_t)n_ent;
-    nd = __builtin_amdgcn_readfirstlane(w1 ? v[1] : v[0]);
+    nd = __builtin_amdgcn_readfirstlane(ahead_d);
     n_chk = nd & chk_mask;
-    n_rel = base4 + (__builtin_amdgcn_readfirstlane(v[2]) | (uint64_t)__builtin_amdgcn_readfirstlane(v[3]) << 32);
+    n_rel = base4 + (__builtin_amdgcn_readfirstlane(ahead_rel[0]) | (uint64_t)__builtin_amdgcn_readfirstlane(ahead_rel[1]) << 32);
+    n_ent += 32;
+    if (n_ent < end) {
+      ahead_d = *(const lds_u32 *)(uintptr_t)(n_ent + wave4);
+      ahead_rel = *(const lds_u32x2 *)(uintptr_t)(n_ent + 16);
+    }
   };
   // (all 64 lanes read, those past the block's operations to no effect; straight into the
   // registers that the level reads, since a move of a loaded word here would wait for it)
@@ -377,7 +385,7 @@ template <int NW> __device__ __forceinline__ int run_calls(uint32_t base, uint32
         }
         if (__builtin_amdgcn_readfirstlane((int)z)) {
           // calls run: the entries before n_ent, without the next level's
-          ret = -(int)((n_ent - list) / 16 - (nd ? 1 : 0));
+          ret = -(int)((n_ent - list) / 32 - (nd ? 1 : 0));
           return true;
         }
       }
@@ -402,7 +410,8 @@ template <int NW> __device__ __noinline__ int run_calls_fn(uint32_t base, uint32
 }
 
 // Device context for control code shared with the host model: the workgroup's slots and a list
-// of calls in LDS.  (cl: MAX_CALLS entries for lists and one more for single calls.)  A kernel
+// of calls in LDS.  (cl: MAX_CALLS entries for lists and one more for single calls; a context in
+// line that only runs single calls has one entry.)  A kernel
 // with one place that runs calls has the engine in line, one with several calls it: with the
 // call's scratch traffic a launch of 2^15 F_p12 products took 1.98 ms, in line it takes a
 // quarter of that.
@@ -429,8 +438,10 @@ template <int NW, bool INLINE = false> struct DevCtx {
     __syncthreads();
   }
   __device__ void run(int prog, int bx, int by, int bd) {
-    if (threadIdx.x == 0) cl[MAX_CALLS] = call(prog, bx, by, bd);
-    run_list(MAX_CALLS, MAX_CALLS + 1, 0, 0);
+    // (the list's extra entry; a context in line has no other)
+    const int e = INLINE ? 0 : MAX_CALLS;
+    if (threadIdx.x == 0) cl[e] = call(prog, bx, by, bd);
+    run_list(e, e + 1, 0, 0);
   }
 };
 #endif
@@ -438,12 +449,12 @@ template <int NW, bool INLINE = false> struct DevCtx {
 // Host model: every operation of a level reads before any writes.
 inline void run_host(f29 *S, const Call &c) {
   const uint64_t rel = c.rel;
-  f29 r[64];
-  uint32_t dst[64];
-  uint32_t d[2] = {c.d0, c.d1};
+  f29 r[128];
+  uint32_t dst[128];
+  uint32_t d[4] = {c.d[0], c.d[1], c.d[2], c.d[3]};
   while (d[0]) {
     int n = 0;
-    for (int v = 0; v < 2; v++) {
+    for (int v = 0; v < 4 && d[v]; v++) {
       const int T = blk_terms(d[v]);
       for (int i = 0; i < blk_ops(d[v]); i++, n++) {
         int64_t acc[2][9];
@@ -483,7 +494,7 @@ struct HostCtx {
   int run_list(int first, int n, int chk, int nchk) {
     for (int e = first; e < n; e++) {
       run_host(S, cl[e]);
-      if (nchk && (cl[e].d0 & BLK_CHK)) {
+      if (nchk && (cl[e].d[0] & BLK_CHK)) {
         bool z = true;
         for (int i = 0; i < nchk; i++) z = z && maybe_zero29(S[chk + i].l[0], S[chk + i].l[1]);
         if (z) return -(e + 1);
