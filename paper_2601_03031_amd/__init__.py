@@ -13,10 +13,10 @@ import os
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "lib", "libvc.so")
 
-# open-all runs on the caller's stream and five side streams, and batches run several jobs
+# open-all runs on the caller's stream and four side streams, and batches run several jobs
 # at once on executors of their own; HIP maps streams onto GPU_MAX_HW_QUEUES hardware queues
 # per process (default 4), and streams that share a queue run one after the other.  Raised
-# to 16 here (one job's six streams, or sixteen one-stream jobs, on queues of their own;
+# to 16 here (one job's five streams, or sixteen one-stream jobs, on queues of their own;
 # more queues than that slowed single jobs down in measurements); takes effect only before
 # the process first uses the device.
 HW_QUEUES = 16
@@ -30,7 +30,7 @@ def _raise_hw_queues() -> None:
     if cur < HW_QUEUES:
         os.environ["GPU_MAX_HW_QUEUES"] = str(HW_QUEUES)
         # too late if torch has already started HIP in this process: say so (an open-all at
-        # N = 2^16, b = 256 measured 25.5 ms on 4 queues against 17.5 ms on 16)
+        # N = 2^16, b = 256 measured 12.2 ms on 4 queues against 10.9 ms on 16)
         import sys
         torch = sys.modules.get("torch")
         try:

@@ -130,7 +130,8 @@ void name_last(const char *name) {
 // the same time need executors of their own; each params holds a default one.  An executor
 // owns 1..6 streams: main (the job's stream in batch calls) and the five side streams map
 // onto them in turn, so with fewer than six the side work shares streams (same results,
-// less overlap inside one job, fewer hardware queues per job when many jobs run at once).
+// less overlap inside one job, fewer hardware queues per job when many jobs run at once).  A
+// params' default executor has its own map (DEFAULT_ROLES).
 struct vc_exec {
   int device;
   void *ws = nullptr;
@@ -139,6 +140,7 @@ struct vc_exec {
   uint32_t nown = 0;
   hipStream_t main = nullptr;
   hipStream_t side[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
+  hipStream_t direct = nullptr;  // the G1 side of an open-all whose rounds all run direct
   hipEvent_t ev[23] = {};
   uint32_t *cnt = nullptr;
   uint64_t cnt_n = 0;
@@ -312,8 +314,8 @@ VC_API int vc_exec_graph_stats(const vc_exec *ex, uint64_t stats[2]) {
   return VC_OK;
 }
 
-VC_API int vc_exec_create(int device, uint32_t nstreams, vc_exec **out) {
-  (void)hipGetLastError();  // errors left by other HIP clients are not ours
+// map: the stream (an index into own) of each side role, or NULL for the roles in turn
+static int exec_create(int device, uint32_t nstreams, const uint8_t *map, vc_exec **out) {
   if (!out) return VC_EINVAL;
   *out = nullptr;
   if (nstreams < 1 || nstreams > 6) return VC_EINVAL;
@@ -328,7 +330,8 @@ VC_API int vc_exec_create(int device, uint32_t nstreams, vc_exec **out) {
   }
   if (e == hipSuccess) {
     ex->main = ex->own[0];
-    for (uint32_t i = 0; i < 5; i++) ex->side[i] = ex->own[(i + 1) % nstreams];
+    for (uint32_t i = 0; i < 5; i++) ex->side[i] = ex->own[map ? map[i] : (i + 1) % nstreams];
+    ex->direct = ex->side[map ? 4 : 1];
   }
   for (auto &ev : ex->ev)
     if (e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
@@ -339,6 +342,23 @@ VC_API int vc_exec_create(int device, uint32_t nstreams, vc_exec **out) {
   *out = ex;
   return VC_OK;
 }
+
+VC_API int vc_exec_create(int device, uint32_t nstreams, vc_exec **out) {
+  (void)hipGetLastError();  // errors left by other HIP clients are not ours
+  return exec_create(device, nstreams, nullptr, out);
+}
+
+// The default executor of a params has four streams beside the caller's: Step 2, the folds, the
+// pairing side of the terms of both parities, their G1 side.  HIP maps streams onto 4 hardware
+// queues by default, and roles that share a queue wait for one another's events: with six
+// streams, one of them idle and the rest shared by creation order, an open-all at 2^16, b = 256
+// took 18.0 ms on 4 queues against 11.1 on 16; with these four 12.2 and 10.9 (2^17, b = 34:
+// 27.3 and 19.5 against 20.4 and 19.5; 2^10, b = 1: 17.2 and 12.0 against 12.8 and 11.8).  The
+// order is the best of all maps of the five roles onto 3 to 5 streams on 4 queues, and within
+// noise of the best on 16.  The folds' stream is the one that shares a queue with the caller's
+// there; where all rounds run direct it would hold up the chain (2^16, b = 1: 107 ms against 87),
+// so the G1 side then takes the stream that the terms' G1 side leaves free.
+static const uint8_t DEFAULT_ROLES[5] = {1, 3, 0, 0, 2};
 
 static const uint32_t NWIN = 32;  // 8-bit windows of a 256-bit scalar
 
@@ -364,7 +384,7 @@ VC_API const char *vc_strerror(int code) {
 static int params_alloc(uint32_t log_n, int device, vc_params **out) {
   vc_params *pp = new vc_params();
   pp->device = device;
-  if (int rc = vc_exec_create(device, 6, &pp->ex)) {
+  if (int rc = exec_create(device, 4, DEFAULT_ROLES, &pp->ex)) {
     vc_params_free(pp);
     return rc;
   }
@@ -1180,7 +1200,7 @@ static int open_all_group(const vc_params *cpp, const vc_commitment *const *cms,
   // ---- Step 2 runs on side stream 1, concurrently with Step 1: Merkle tree (Fiat-Shamir),
   // randomized folding tree, HyperEval on g* (Protocol 1 Step 2 and its Sub-protocol).  Its
   // launches are issued after those of the first Step 1 round, which is on the critical path.
-  hipStream_t s1 = ex->side[0], s2 = ex->side[1];
+  hipStream_t s1 = ex->side[0], s2 = ahead ? ex->side[1] : ex->direct;
   if (int rc2 = ev_mark(ex, 0, st)) return rc2;
   auto launch_step2 = [&]() -> int {
     if (int rc2 = ev_wait(ex, 0, s1)) return rc2;
