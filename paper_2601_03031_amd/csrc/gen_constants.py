@@ -56,6 +56,10 @@ w("#include <cstdint>")
 w("namespace bn {")
 w(arr("P_MOD", P))
 w("static constexpr uint32_t P_INV = 0x%08xu;  // -p^{-1} mod 2^32" % ((-pow(P, -1, 1 << 32)) % (1 << 32)))
+w("static constexpr uint32_t P_MOD29[9] = {%s};  // radix 2^29" % ", ".join("0x%08xu" % ((P >> (29 * i)) & 0x1fffffff) for i in range(9)))
+w("static constexpr uint32_t P_INV29 = 0x%08xu;  // -p^{-1} mod 2^29" % ((-pow(P, -1, 1 << 29)) % (1 << 29)))
+w("static constexpr uint32_t R_MOD29[9] = {%s};" % ", ".join("0x%08xu" % ((R >> (29 * i)) & 0x1fffffff) for i in range(9)))
+w("static constexpr uint32_t R_INV29 = 0x%08xu;" % ((-pow(R, -1, 1 << 29)) % (1 << 29)))
 w(arr("P_ONE", mont(1)))
 w(arr("P_R2", RM * RM % P))
 w(arr("P_MINUS_2", P - 2))
