@@ -743,25 +743,6 @@ def j_add(T1, T2):
     return (X3, Y3, Z3), H, S2 - S1
 
 
-def j_madd(T1, A):
-    """madd-2007-bl: T1 Jacobian plus A = (x2, y2) affine"""
-    X1, Y1, Z1 = T1
-    x2, y2 = A
-    Z1Z1 = Z1.sqr()
-    U2 = x2.mul(Z1Z1)
-    S2 = y2.mul(Z1).mul(Z1Z1)
-    H = U2 - X1
-    HH = H.sqr()
-    I = HH.scale(4)
-    J = H.mul(I)
-    rr = (S2 - Y1).scale(2)
-    V = X1.mul(I)
-    X3 = rr.sqr() - J - V.scale(2)
-    Y3 = rr.mul(V - X3) - Y1.mul(J).scale(2)
-    Z3 = (Z1 + H).sqr() - Z1Z1 - HH
-    return (X3, Y3, Z3), H, S2 - Y1
-
-
 def jac_in(p, name):
     return tuple(F2(p.inp("%s.%d" % (name, 2 * c)), p.inp("%s.%d" % (name, 2 * c + 1))) for c in range(3))
 
@@ -772,65 +753,206 @@ def jac_out(p, name, T):
         p.out("%s.%d" % (name, 2 * c + 1), v.c1)
 
 
+# Scalar multiplications run on homogeneous coordinates with the complete formulas for
+# y^2 = x^3 + b (J. Renes, C. Costello, L. Batina, "Complete addition formulas for prime order
+# elliptic curves", 2016, algorithms 7 and 9): two product levels for an addition and two for
+# a doubling (Jacobian formulas take five and three), and no exceptional cases in the groups of
+# odd order r.  b3 multiplies by 3b.
+def rcb_add(P1, P2, b3):
+    X1, Y1, Z1 = P1
+    X2, Y2, Z2 = P2
+    t0, t1, t2 = X1.mul(X2), Y1.mul(Y2), Z1.mul(Z2)
+    t3 = X1.mul(Y2) + X2.mul(Y1)
+    t4 = Y1.mul(Z2) + Y2.mul(Z1)
+    y3 = b3(X1.mul(Z2) + X2.mul(Z1))
+    t0 = t0.scale(3)
+    t2 = b3(t2)
+    z3, t1 = t1 + t2, t1 - t2
+    return (t3.mul(t1) - t4.mul(y3), y3.mul(t0) + t1.mul(z3), z3.mul(t4) + t0.mul(t3))
+
+
+def rcb_dbl(P1, b3):
+    X, Y, Z = P1
+    t0, t1, t2, t3 = Y.sqr(), Y.mul(Z), Z.sqr(), X.mul(Y)
+    t2 = b3(t2)
+    n = t0 - t2.scale(3)
+    return (n.mul(t3).scale(2), t2.mul(t0).scale(8) + n.mul(t0 + t2), t0.mul(t1).scale(8))
+
+
+# A point between two programs is kept as sums: each coordinate a fixed number of slots whose
+# sum it is, so that a program ends in its last products and not in a level of additions.
+def sums_in(p, name, n):
+    f = p.inp("%s.0" % name)
+    for i in range(1, n):
+        f = f + p.inp("%s.%d" % (name, i))
+    return f
+
+
+def sums_out(p, name, f, n):
+    """f as n slots: its products with their coefficients taken into a factor; more terms than
+    slots are added up in the last one"""
+    t = sorted(f.t.items())
+    vs = []
+    for k, (v, c) in enumerate(t):
+        if k == n - 1 and len(t) > n:
+            vs.append(F(p, dict(t[k:])).atom())
+            break
+        if c == 1:
+            vs.append(v)
+            continue
+        node = p.vals[v]
+        if node[0] == "mul":
+            for x, y in ((1, 2), (2, 1)):  # the factor with the smaller coefficients takes c
+                if all(abs(c * k_) <= KMAX for _, k_ in node[x]):
+                    break
+            else:
+                x = None
+            if x:
+                g = tuple((i, c * k_) for i, k_ in node[x])
+                A, B = (g, node[y]) if g <= node[y] else (node[y], g)
+                vs.append(p.new(("mul", A, B)))
+                continue
+        vs.append(F(p, {v: c}).atom())
+    vs += [p.zero] * (n - len(vs))
+    for i, v in enumerate(vs):
+        p.outputs["%s.%d" % (name, i)] = v
+
+
+# G2 works on y^2 = x^3 + b'' with b'' = 4 + 5i, isomorphic to the twist by (x, y) ->
+# (u^2 x, u^3 y), u^6 = b''/b', so that the formulas' 3b'' is a pair of small integers.
+def sixth_root(r):
+    """some u in F_p2 with u^6 = r"""
+    n = P * P - 1
+    m = n
+    while m % 2 == 0:
+        m //= 2
+    while m % 3 == 0:
+        m //= 3
+    x0 = f2pow_int(r, pow(6, -1, m))
+    k = 2
+    while True:
+        g = f2pow_int((k, 1), m)
+        if f2pow_int(g, n // m // 2) != (1, 0) and f2pow_int(g, n // m // 3) != (1, 0):
+            break
+        k += 1
+    x = x0
+    for _ in range(n // m):
+        if f2pow_int(x, 6) == r:
+            return x
+        x = f2mul_int(x, g)
+    raise ValueError("no sixth root")
+
+
+G2_BPP = (4, 5)
+G2_U = sixth_root(f2mul_int(G2_BPP, f2inv_int(f2mul_int(B3, (pow(3, -1, P), 0)))))
+G2_U2 = f2mul_int(G2_U, G2_U)
+G2_U3 = f2mul_int(G2_U2, G2_U)
+G2_UI = f2inv_int(G2_U)
+
+
+def f2conj_int(a):
+    return (a[0], -a[1] % P)
+
+
+# psi on the isomorphic curve: (conj(x) tx, conj(y) ty) with the constants carried over
+G2_TX = f2mul_int(FROB_TX, f2mul_int(G2_U2, f2inv_int(f2conj_int(G2_U2))))
+G2_TY = f2mul_int(FROB_TY, f2mul_int(G2_U3, f2inv_int(f2conj_int(G2_U3))))
+
+
+def b3_g2(a):  # (12 + 15 i) a
+    c0, c1 = 3 * G2_BPP[0], 3 * G2_BPP[1]
+    return F2(a.c0.scale(c0) - a.c1.scale(c1), a.c1.scale(c0) + a.c0.scale(c1))
+
+
+def b3_g1(a):  # b = 3
+    return a.scale(9)
+
+
+G2_SUM, G1_SUM = 4, 2  # slots of a coordinate's component between two programs
+
+
+def pt2_in(p, name, n=G2_SUM):
+    return tuple(F2(sums_in(p, "%s.%d.0" % (name, c), n), sums_in(p, "%s.%d.1" % (name, c), n)) for c in range(3))
+
+
+def pt2_out(p, name, T):
+    for c, v in enumerate(T):
+        sums_out(p, "%s.%d.0" % (name, c), v.c0, G2_SUM)
+        sums_out(p, "%s.%d.1" % (name, c), v.c1, G2_SUM)
+
+
 def g2_programs():
     progs = {}
-    # psi images of Q (B0 = Q)
-    p = Prog("g2_psi")
-    Q = (f2_in(p, "xQ"), f2_in(p, "yQ"))
-    Bj = Q
-    for j in (1, 2, 3):
-        Bj = twist_frob(Bj)
-        f2_out(p, "B%d.x" % j, Bj[0])
-        f2_out(p, "B%d.y" % j, Bj[1])
-    progs[p.name] = p
-    # table TB[d] = sum_{j in d} B_j (Jacobian), the single-bit entries with Z = 1
+
+    def done(p):
+        progs[p.name] = p
+
+    # Q and its psi images on the isomorphic curve, each from Q by one constant a coordinate:
+    # psi^j(x) = conj^j(x) kx
+    p = Prog("g2_bases")
+    x, y = f2_in(p, "xQ"), f2_in(p, "yQ")
+    kx, ky = G2_U2, G2_U3
+    for j in range(4):
+        if j:
+            x, y = x.conj(), y.conj()
+            kx, ky = f2mul_int(f2conj_int(kx), G2_TX), f2mul_int(f2conj_int(ky), G2_TY)
+        f2_out(p, "B%d.x" % j, x.mul_const(kx))
+        f2_out(p, "B%d.y" % j, y.mul_const(ky))
+    done(p)
+    # table TB[d] = sum_{j in d} B_j, the caller's signs on the y
     p = Prog("g2_table")
     one = F2(p.fconst(1), p.fconst(0))
-    B = [(f2_in(p, "xQ"), f2_in(p, "yQ"))] + [(f2_in(p, "B%d.x" % j), f2_in(p, "B%d.y" % j)) for j in range(1, 4)]
     TB = {}
     for j in range(4):
-        TB[1 << j] = (B[j][0], B[j][1], one)
+        TB[1 << j] = (f2_in(p, "B%d.x" % j), f2_in(p, "B%d.y" % j), one)
     for d in range(1, 16):
-        if d & (d - 1) == 0:
-            continue
-        lo = d & -d
-        TB[d], _, _ = j_add(TB[d - lo], TB[lo])
+        lo = d & -d if bin(d).count("1") < 4 else 3
+        if d != lo:
+            TB[d] = rcb_add(TB[d - lo], TB[lo], b3_g2)
     for d in range(1, 16):
         jac_out(p, "TB%d" % d, TB[d])
-    progs[p.name] = p
+    done(p)
     p = Prog("g2_dbl")
-    jac_out(p, "T", j_dbl(jac_in(p, "T")))
-    progs[p.name] = p
+    pt2_out(p, "T", rcb_dbl(pt2_in(p, "T"), b3_g2))
+    done(p)
     p = Prog("g2_dbl_add")
-    T, H, r = j_add(j_dbl(jac_in(p, "T")), jac_in(p, "A"))
-    jac_out(p, "T", T)
-    f2_out(p, "H", H)
-    f2_out(p, "RR", r)
-    progs[p.name] = p
+    pt2_out(p, "T", rcb_add(rcb_dbl(pt2_in(p, "T"), b3_g2), jac_in(p, "A"), b3_g2))
+    done(p)
     p = Prog("g2_add")
-    T, H, r = j_add(jac_in(p, "T"), jac_in(p, "A"))
-    jac_out(p, "T", T)
-    f2_out(p, "H", H)
-    f2_out(p, "RR", r)
-    progs[p.name] = p
+    pt2_out(p, "T", rcb_add(pt2_in(p, "T"), jac_in(p, "A"), b3_g2))
+    done(p)
+    # T += (xQ, yQ) of the twist
     p = Prog("g2_madd")
-    T, H, r = j_madd(jac_in(p, "T"), (F2(p.inp("A.0"), p.inp("A.1")), F2(p.inp("A.2"), p.inp("A.3"))))
-    jac_out(p, "T", T)
+    pt2_out(p, "T", rcb_add(pt2_in(p, "T"), (f2_in(p, "xQ").mul_const(G2_U2), f2_in(p, "yQ").mul_const(G2_U3),
+                                             F2(p.fconst(1), p.fconst(0))), b3_g2))
+    done(p)
+    # T = (xQ, yQ) of the twist
+    p = Prog("g2_load")
+    pt2_out(p, "T", (f2_in(p, "xQ").mul_const(G2_U2), f2_in(p, "yQ").mul_const(G2_U3), F2(p.fconst(1), p.fconst(0))))
+    done(p)
+    # to affine coordinates of the twist: t = N(Z); then x = X conj(Z) t^{-1} u^{-2}, y likewise
+    p = Prog("g2_norm")
+    Z = pt2_in(p, "T")[2]
+    p.out("t", Z.c0 * Z.c0 + Z.c1 * Z.c1)
+    done(p)
+    p = Prog("g2_aff")
+    X, Y, Z = pt2_in(p, "T")
+    ti = p.inp("tinv")
+    Zi = Z.conj().mul_fp(ti)
+    f2_out(p, "ax", X.mul_const(f2mul_int(G2_UI, G2_UI)).mul(Zi))
+    f2_out(p, "ay", Y.mul_const(f2mul_int(f2mul_int(G2_UI, G2_UI), G2_UI)).mul(Zi))
+    done(p)
+    # Jacobian coordinates on the twist (the sums of the MSMs): doubling and addition, which
+    # reports equal x-coordinates (H = 0), then equal points (RR = 0)
+    p = Prog("g2_jdbl")
+    jac_out(p, "J", j_dbl(jac_in(p, "J")))
+    done(p)
+    p = Prog("g2_jadd")
+    T, H, r = j_add(jac_in(p, "J"), jac_in(p, "A"))
+    jac_out(p, "J", T)
     f2_out(p, "H", H)
     f2_out(p, "RR", r)
-    progs[p.name] = p
-    # to affine: t = N(Z); then Zi = conj(Z) / t, x = X Zi^2, y = Y Zi^3
-    p = Prog("g2_norm")
-    Z = F2(p.inp("T.4"), p.inp("T.5"))
-    p.out("t", Z.c0 * Z.c0 + Z.c1 * Z.c1)
-    progs[p.name] = p
-    p = Prog("g2_aff")
-    X, Y, Z = jac_in(p, "T")
-    Zi = Z.conj().mul_fp(p.inp("tinv"))
-    Zi2 = Zi.sqr()
-    f2_out(p, "ax", X.mul(Zi2))
-    f2_out(p, "ay", Y.mul(Zi2.mul(Zi)))
-    progs[p.name] = p
+    done(p)
     return progs
 
 
@@ -839,80 +961,74 @@ GLV_BETA = 0x59E26BCEA0D48BACD4F263F1ACDB5C4F5763473177FFFFFE
 GLV_LAM = 0xB3C4D79D41A917585BFC41088D8DAAA78B17EA66B99C90DD
 
 
-def g1_jin(p, name):
+def g1_in(p, name):
     return tuple(p.inp("%s.%d" % (name, c)) for c in range(3))
 
 
-def g1_jout(p, name, T):
+def pt1_in(p, name):
+    return tuple(sums_in(p, "%s.%d" % (name, c), G1_SUM) for c in range(3))
+
+
+def pt1_out(p, name, T):
     for c, v in enumerate(T):
-        p.out("%s.%d" % (name, c), v)
+        sums_out(p, "%s.%d" % (name, c), v, G1_SUM)
 
 
 def g1_programs():
     progs = {}
+
+    def done(p):
+        progs[p.name] = p
+
     p = Prog("g1_phi")
     p.out("B1.x", p.inp("xP") * p.fconst(GLV_BETA))
-    progs[p.name] = p
-    # table TB[d0 + 4 d1] = d0 B0 + d1 B1 (Jacobian) for the joint 2-bit windows; B0 in
-    # (xP, yP), B1 in (B1.x, B1.y), signs applied by the caller
+    done(p)
+    # table TB[d0 + 4 d1] = d0 B0 + d1 B1 for the joint 2-bit windows; B0 in (xP, yP), B1 in
+    # (B1.x, B1.y), signs applied by the caller
     p = Prog("g1_table")
     one = p.fconst(1)
-    B0 = (p.inp("xP"), p.inp("yP"))
-    B1 = (p.inp("B1.x"), p.inp("B1.y"))
-    TB = {1: (B0[0], B0[1], one), 4: (B1[0], B1[1], one)}
-    TB[2] = j_dbl(TB[1])
-    TB[3], _, _ = j_madd(TB[2], B0)
-    TB[8] = j_dbl(TB[4])
-    TB[12], _, _ = j_madd(TB[8], B1)
+    TB = {1: (p.inp("xP"), p.inp("yP"), one), 4: (p.inp("B1.x"), p.inp("B1.y"), one)}
+    for d in (1, 4):
+        TB[2 * d] = rcb_dbl(TB[d], b3_g1)
+        TB[3 * d] = rcb_add(TB[2 * d], TB[d], b3_g1)
     for d1 in (1, 2, 3):
         for d0 in (1, 2, 3):
-            TB[d0 + 4 * d1], _, _ = j_add(TB[4 * d1], TB[d0])
+            TB[d0 + 4 * d1] = rcb_add(TB[4 * d1], TB[d0], b3_g1)
     for d in range(1, 16):
-        g1_jout(p, "TB%d" % d, TB[d])
-    progs[p.name] = p
-    p = Prog("g1_dbl")
-    g1_jout(p, "T", j_dbl(g1_jin(p, "T")))
-    progs[p.name] = p
+        for c, v in enumerate(TB[d]):
+            p.out("TB%d.%d" % (d, c), v)
+    done(p)
     p = Prog("g1_dbl2")
-    g1_jout(p, "T", j_dbl(j_dbl(g1_jin(p, "T"))))
-    progs[p.name] = p
+    pt1_out(p, "T", rcb_dbl(rcb_dbl(pt1_in(p, "T"), b3_g1), b3_g1))
+    done(p)
     p = Prog("g1_dbl2_add")
-    T, H, r = j_add(j_dbl(j_dbl(g1_jin(p, "T"))), g1_jin(p, "A"))
-    g1_jout(p, "T", T)
-    p.out("H", H)
-    p.out("RR", r)
-    progs[p.name] = p
+    pt1_out(p, "T", rcb_add(rcb_dbl(rcb_dbl(pt1_in(p, "T"), b3_g1), b3_g1), g1_in(p, "A"), b3_g1))
+    done(p)
     p = Prog("g1_add")
-    T, H, r = j_add(g1_jin(p, "T"), g1_jin(p, "A"))
-    g1_jout(p, "T", T)
-    p.out("H", H)
-    p.out("RR", r)
-    progs[p.name] = p
+    pt1_out(p, "T", rcb_add(pt1_in(p, "T"), g1_in(p, "A"), b3_g1))
+    done(p)
+    # T += (xP, yP)
     p = Prog("g1_madd")
-    T, H, r = j_madd(g1_jin(p, "T"), (p.inp("A.0"), p.inp("A.1")))
-    g1_jout(p, "T", T)
-    p.out("H", H)
-    p.out("RR", r)
-    progs[p.name] = p
+    pt1_out(p, "T", rcb_add(pt1_in(p, "T"), (p.inp("xP"), p.inp("yP"), p.fconst(1)), b3_g1))
+    done(p)
     p = Prog("g1_aff")
-    X, Y, Z = g1_jin(p, "T")
+    X, Y, Z = pt1_in(p, "T")
     zi = p.inp("tinv")
-    zi2 = zi * zi
-    p.out("ax", X * zi2)
-    p.out("ay", Y * (zi2 * zi))
-    progs[p.name] = p
+    p.out("ax", X * zi)
+    p.out("ay", Y * zi)
+    done(p)
     return progs
 
 
-G1_STATE = (["T.%d" % k for k in range(3)] + ["xP", "yP", "B1.x", "B1.y"]
-            + ["TB%d.%d" % (d, k) for d in range(1, 16) for k in range(3)]
-            + ["H", "RR", "tinv", "ax", "ay"])
+G1_STATE = (["T.%d.%d" % (c, k) for c in range(3) for k in range(G1_SUM)] + ["xP", "yP", "B1.x", "B1.y", "tinv"]
+            + ["TB%d.%d" % (d, k) for d in range(1, 16) for k in range(3)] + ["ax", "ay"])
 
 
-G2_STATE = (["T.%d" % k for k in range(6)] + ["xQ.0", "xQ.1", "yQ.0", "yQ.1"]
-            + ["B%d.%s.%d" % (j, c, k) for j in range(1, 4) for c in "xy" for k in (0, 1)]
+G2_STATE = (["T.%d.%d.%d" % (c, h, k) for c in range(3) for h in (0, 1) for k in range(G2_SUM)]
+            + ["xQ.0", "xQ.1", "yQ.0", "yQ.1", "t", "tinv"]
+            + ["B%d.%s.%d" % (j, c, k) for j in range(4) for c in "xy" for k in (0, 1)]
             + ["TB%d.%d" % (d, k) for d in range(1, 16) for k in range(6)]
-            + ["H.0", "H.1", "RR.0", "RR.1", "t", "tinv", "ax.0", "ax.1", "ay.0", "ay.1"])
+            + ["J.%d" % k for k in range(6)] + ["H.0", "H.1", "RR.0", "RR.1", "ax.0", "ax.1", "ay.0", "ay.1"])
 
 
 # ============================================================================ scheduling
@@ -1195,10 +1311,12 @@ class Kernel:
         self.consts = consts
         self.tbase = self.cbase + len(consts)
         self.progs = {}
+        self.used = {}  # slots up to the highest one that a program uses
         self.ntemps = self.tbase
         for nm, p in progs.items():
             enc, used = compile_prog(p, self.io_slot, lambda x: self.cslot[x % P], self.tbase, 1 << SEG_SHIFT, lanes)
             self.progs[nm] = enc
+            self.used[nm] = used
             self.ntemps = max(self.ntemps, used)
         self.nslots = self.ntemps
 
@@ -1265,8 +1383,7 @@ class OpTable:
     per group at fixed offsets; blocks of the same number of groups share a row of 64 lanes.
     A block without operations still has one record, for the next descriptor.
 
-    A descriptor: bits 0..17 offset of the block in units of four words, 18 (in a call's first
-    descriptors) a checked addition, 19 / 20 / 21 / 22 more than 2 / 4 / 6 / 10 terms, 23 any
+    A descriptor: bits 0..18 offset of the block in units of four words, 19 / 20 / 21 / 22 more than 2 / 4 / 6 / 10 terms, 23 any
     term or destination in segments 1..3, 24..29 operations, 30 any product, 31 any sum."""
 
     def __init__(self):
@@ -1288,7 +1405,7 @@ class OpTable:
             for g in range(G):
                 self.words[base + 256 * g + 4 * l:base + 256 * g + 4 * l + 4] = r[4 * g:4 * g + 4]
         d = base // 4
-        assert base % 4 == 0 and d < 1 << 18 and len(ops) <= WAVE_OPS
+        assert base % 4 == 0 and d < 1 << 19 and len(ops) <= WAVE_OPS
         d |= (T > 2) << 19 | (T > 4) << 20 | (T > 6) << 21 | (T > 10) << 22
         d |= any(s_ >> SEG_SHIFT for op in ops for s_ in [op[1]] + [t[0] for t in op[3]]) << 23
         d |= len(ops) << 24
@@ -1361,9 +1478,6 @@ def emit_radix():
     return o
 
 
-CHECKED = ("g1_dbl2_add", "g1_add", "g1_madd", "g2_dbl_add", "g2_add", "g2_madd")
-
-
 def emit(kernels):
     o = []
     w = o.append
@@ -1390,10 +1504,9 @@ def emit(kernels):
             for row in reversed(enc):  # last level first: a level names the next one
                 for v, ops in enumerate(level_blocks(row, k.waves)):
                     nxt[v] = table.add(ops, nxt[v])
-            w("static constexpr int PROG_%s = %d;" % (nm.upper(), len(descs)))
-            descs.append((nm, [d | (1 << 18 if nm in CHECKED else 0) for d in nxt] + [0] * (4 - k.waves)))
-    w("// a program: descriptors of its first level, one per wavefront (bit 18: an addition that")
-    w("// reports equal x-coordinates in its H slots)")
+            w("static constexpr int PROG_%s = %d, %s_SLOTS = %d;" % (nm.upper(), len(descs), nm.upper(), k.used[nm]))
+            descs.append((nm, nxt + [0] * (4 - k.waves)))
+    w("// a program: descriptors of its first level, one per wavefront")
     w("struct ProgDesc { uint32_t d[4]; };")
     w("static constexpr ProgDesc PROGS[%d] = {" % len(descs))
     for nm, d in descs:
@@ -1423,7 +1536,7 @@ def emit(kernels):
 
 
 # ============================================================================ checks
-def run_levels(levels, S, segbase=(0, 0, 0, 0, 0, 0, 0, 0)):
+def run_levels(levels, S, segbase=(0, 0, 0, 0)):
     def res(x):
         return segbase[x >> SEG_SHIFT] + (x & ((1 << SEG_SHIFT) - 1)) if x >> SEG_SHIFT else x
     for row in levels:
@@ -1649,56 +1762,83 @@ G2GEN = ((1085704699902305713594457076223282948137075635957851808699051999328565
 def check_g2(gk, rng):
     lam = P % R
     st = gk.state
-    def setpt(S, name, pt):  # Jacobian with Z = 1 from affine
-        (x0, x1), (y0, y1) = pt
-        for k, v in enumerate((x0, x1, y0, y1, 1, 0)):
-            S[st["%s.%d" % (name, k)]] = v
-    def getaff(S, name):
-        v = [S[st["%s.%d" % (name, k)]] for k in range(6)]
-        X, Y, Z = (v[0], v[1]), (v[2], v[3]), (v[4], v[5])
+    def setsum(S, pt):  # T from affine on the isomorphic curve, the sums split at random
+        x, y = (0, 0), (1, 0)
+        z = (0, 0)
+        if pt is not None:
+            x, y, z = f2mul_int(pt[0], G2_U2), f2mul_int(pt[1], G2_U3), (1, 0)
+        for c, v in enumerate((x, y, z)):
+            for h in (0, 1):
+                r = [rng.randrange(P) for _ in range(G2_SUM - 1)]
+                for k, w in enumerate(r + [(v[h] - sum(r)) % P]):
+                    S[st["T.%d.%d.%d" % (c, h, k)]] = w
+    def aff(X, Y, Z, iso=True):
         if Z == (0, 0):
             return None
         zi = f2inv_int(Z)
-        zi2 = f2mul_int(zi, zi)
-        return (f2mul_int(X, zi2), f2mul_int(Y, f2mul_int(zi2, zi)))
+        x, y = f2mul_int(X, zi), f2mul_int(Y, zi)
+        ui2 = f2mul_int(G2_UI, G2_UI)
+        return (f2mul_int(x, ui2), f2mul_int(y, f2mul_int(ui2, G2_UI)))
+    def getsum(S):
+        v = [tuple(sum(S[st["T.%d.%d.%d" % (c, h, k)]] for k in range(G2_SUM)) % P for h in (0, 1)) for c in range(3)]
+        return aff(*v)
+    def gettab(S, d):
+        v = [S[st["TB%d.%d" % (d, k)]] % P for k in range(6)]
+        return aff((v[0], v[1]), (v[2], v[3]), (v[4], v[5]))
     for trial in range(2):
         Q = aff_mul(G2GEN, rng.randrange(1, R))
         S = [0] * gk.nslots
         for x, sl in gk.cslot.items():
             S[sl] = x
         S[st["xQ.0"]], S[st["xQ.1"]], S[st["yQ.0"]], S[st["yQ.1"]] = Q[0][0], Q[0][1], Q[1][0], Q[1][1]
-        run_levels(gk.progs["g2_psi"], S)
-        for j in (1, 2, 3):
-            got = ((S[st["B%d.x.0" % j]], S[st["B%d.x.1" % j]]), (S[st["B%d.y.0" % j]], S[st["B%d.y.1" % j]]))
-            assert got == aff_mul(Q, pow(lam, j, R)), "psi"
+        run_levels(gk.progs["g2_bases"], S)
         run_levels(gk.progs["g2_table"], S)
         for d in range(1, 16):
             want = None
             for j in range(4):
                 if d >> j & 1:
                     want = aff_add(want, aff_mul(Q, pow(lam, j, R)))
-            assert getaff(S, "TB%d" % d) == want, ("table", d)
-        # doubling, addition (with a Jacobian operand at segment 2), mixed addition, to affine
-        A = aff_mul(G2GEN, rng.randrange(1, R))
-        setpt(S, "T", Q)
-        run_levels(gk.progs["g2_dbl"], S)
-        assert getaff(S, "T") == aff_add(Q, Q), "dbl"
-        T2 = aff_add(Q, Q)
-        base = st["TB5.0"]
-        run_levels(gk.progs["g2_add"], S, (0, 0, base, 0, 0, 0, 0, 0))
-        assert getaff(S, "T") == aff_add(T2, getaff(S, "TB5")), "add"
-        T3 = getaff(S, "T")
-        Sa = list(S) + [A[0][0], A[0][1], A[1][0], A[1][1]]
-        run_levels(gk.progs["g2_madd"], Sa, (0, 0, len(S), 0, 0, 0, 0, 0))
-        assert getaff(Sa, "T") == aff_add(T3, A), "madd"
-        run_levels(gk.progs["g2_norm"], Sa)
-        Sa[st["tinv"]] = pow(Sa[st["t"]], -1, P)
-        run_levels(gk.progs["g2_aff"], Sa)
-        assert ((Sa[st["ax.0"]], Sa[st["ax.1"]]), (Sa[st["ay.0"]], Sa[st["ay.1"]])) == aff_add(T3, A), "aff"
-        # degenerate addition reports H = 0 and r = 0
-        setpt(S, "T", Q)
-        setpt(S, "TB1", Q)
-        run_levels(gk.progs["g2_add"], S, (0, 0, st["TB1.0"], 0, 0, 0, 0, 0))
+            assert gettab(S, d) == want, ("table", d)
+        for A in (Q, aff_mul(Q, 7), None):
+            setsum(S, A)
+            run_levels(gk.progs["g2_dbl"], S)
+            A2 = aff_add(A, A)
+            assert getsum(S) == A2, "dbl"
+            base = st["TB5.0"]
+            setsum(S, A)
+            run_levels(gk.progs["g2_dbl_add"], S, (0, 0, base, 0))
+            assert getsum(S) == aff_add(A2, gettab(S, 5)), "dbl_add"
+        for A in (Q, None, gettab(S, 5), (gettab(S, 5)[0], ((-gettab(S, 5)[1][0]) % P, (-gettab(S, 5)[1][1]) % P))):
+            setsum(S, A)
+            run_levels(gk.progs["g2_add"], S, (0, 0, st["TB5.0"], 0))
+            assert getsum(S) == aff_add(A, gettab(S, 5)), "add"
+            run_levels(gk.progs["g2_madd"], S)
+            want = aff_add(aff_add(A, gettab(S, 5)), Q)
+            assert getsum(S) == want, "madd"
+        run_levels(gk.progs["g2_norm"], S)
+        S[st["tinv"]] = pow(S[st["t"]], -1, P)
+        run_levels(gk.progs["g2_aff"], S)
+        assert ((S[st["ax.0"]], S[st["ax.1"]]), (S[st["ay.0"]], S[st["ay.1"]])) == want, "aff"
+        run_levels(gk.progs["g2_load"], S)
+        assert getsum(S) == Q, "load"
+        # the Jacobian programs
+        def setj(name, pt):
+            for k, v in enumerate((*pt[0], *pt[1], 1, 0)):
+                S[st["%s.%d" % (name, k)]] = v
+        def getj():
+            v = [S[st["J.%d" % k]] % P for k in range(6)]
+            X, Y, Z = (v[0], v[1]), (v[2], v[3]), (v[4], v[5])
+            zi = f2inv_int(Z)
+            zi2 = f2mul_int(zi, zi)
+            return (f2mul_int(X, zi2), f2mul_int(Y, f2mul_int(zi2, zi)))
+        setj("J", Q)
+        run_levels(gk.progs["g2_jdbl"], S)
+        assert getj() == aff_add(Q, Q), "jdbl"
+        setj("TB1", Q)
+        run_levels(gk.progs["g2_jadd"], S, (0, 0, st["TB1.0"], 0))
+        assert getj() == aff_add(aff_add(Q, Q), Q), "jadd"
+        setj("J", Q)
+        run_levels(gk.progs["g2_jadd"], S, (0, 0, st["TB1.0"], 0))
         assert S[st["H.0"]] % P == 0 and S[st["H.1"]] % P == 0 and S[st["RR.0"]] % P == 0 and S[st["RR.1"]] % P == 0
     # decomposition
     for k in [0, 1, R - 1] + [rng.randrange(R) for _ in range(2000)]:
@@ -1733,14 +1873,19 @@ def g1_aff_mul(A, k):
 
 def check_g1(g1k, rng):
     st = g1k.state
-    def setj(S, name, pt):
-        S[st[name + ".0"]], S[st[name + ".1"]], S[st[name + ".2"]] = pt[0], pt[1], 1
-    def getj(S, name):
-        X, Y, Z = (S[st["%s.%d" % (name, k)]] % P for k in range(3))
-        if Z == 0:
+    def setsum(S, pt):
+        for c, v in enumerate((0, 1, 0) if pt is None else (pt[0], pt[1], 1)):
+            r = rng.randrange(P)
+            S[st["T.%d.0" % c]], S[st["T.%d.1" % c]] = r, (v - r) % P
+    def aff(X, Y, Z):
+        if Z % P == 0:
             return None
         zi = pow(Z, -1, P)
-        return (X * zi * zi % P, Y * zi * zi * zi % P)
+        return (X * zi % P, Y * zi % P)
+    def getsum(S):
+        return aff(*((S[st["T.%d.0" % c]] + S[st["T.%d.1" % c]]) % P for c in range(3)))
+    def gettab(S, d):
+        return aff(*(S[st["TB%d.%d" % (d, k)]] for k in range(3)))
     for trial in range(3):
         Pt = g1_aff_mul((1, 2), rng.randrange(1, R))
         S = [0] * g1k.nslots
@@ -1754,34 +1899,25 @@ def check_g1(g1k, rng):
         for d in range(1, 16):
             want = g1_aff_add(g1_aff_mul(Pt, d & 3), g1_aff_mul(Pt, (d >> 2) * GLV_LAM % R)) if d & 3 else \
                 g1_aff_mul(Pt, (d >> 2) * GLV_LAM % R)
-            assert getj(S, "TB%d" % d) == want, ("table", d)
-        setj(S, "T", Pt)
-        run_levels(g1k.progs["g1_dbl"], S)
-        assert getj(S, "T") == g1_aff_mul(Pt, 2), "dbl"
-        run_levels(g1k.progs["g1_dbl2"], S)
-        assert getj(S, "T") == g1_aff_mul(Pt, 8), "dbl2"
-        run_levels(g1k.progs["g1_dbl2_add"], S, (0, 0, st["TB7.0"], 0, 0, 0, 0, 0))
-        T32 = g1_aff_add(g1_aff_mul(Pt, 32), getj(S, "TB7"))
-        assert getj(S, "T") == T32, "dbl2_add"
-        # Jacobian addition with a Jacobian operand (Z != 1)
-        Sj = list(S)
-        setj(Sj, "T", g1_aff_mul(Pt, 5))
-        run_levels(g1k.progs["g1_add"], Sj, (0, 0, st["TB6.0"], 0, 0, 0, 0, 0))
-        assert getj(Sj, "T") == g1_aff_add(g1_aff_mul(Pt, 5), getj(S, "TB6")), "add"
-        A = g1_aff_mul((1, 2), rng.randrange(1, R))
-        Sa = list(S) + [A[0], A[1]]
-        run_levels(g1k.progs["g1_madd"], Sa, (0, 0, len(S), 0, 0, 0, 0, 0))
-        assert getj(Sa, "T") == g1_aff_add(T32, A), "madd"
-        Z = Sa[st["T.2"]] % P
-        Sa[st["tinv"]] = pow(Z, -1, P)
-        run_levels(g1k.progs["g1_aff"], Sa)
-        assert (Sa[st["ax"]] % P, Sa[st["ay"]] % P) == g1_aff_add(T32, A), "aff"
-        # degenerate: 4T + A with A = 4T reports H = 0 and r = 0
-        setj(S, "T", Pt)
-        Tq = g1_aff_mul(Pt, 4)
-        setj(S, "TB1", Tq)
-        run_levels(g1k.progs["g1_dbl2_add"], S, (0, 0, st["TB1.0"], 0, 0, 0, 0, 0))
-        assert S[st["H"]] % P == 0 and S[st["RR"]] % P == 0, "degenerate"
+            assert gettab(S, d) == want, ("table", d)
+        T7 = gettab(S, 7)
+        for A in (Pt, T7, (T7[0], -T7[1] % P), None):
+            A4 = None if A is None else g1_aff_mul(A, 4)
+            setsum(S, A)
+            run_levels(g1k.progs["g1_dbl2"], S)
+            assert getsum(S) == A4, "dbl2"
+            setsum(S, A)
+            run_levels(g1k.progs["g1_dbl2_add"], S, (0, 0, st["TB7.0"], 0))
+            assert getsum(S) == g1_aff_add(A4, T7), "dbl2_add"
+            setsum(S, A)
+            run_levels(g1k.progs["g1_add"], S, (0, 0, st["TB7.0"], 0))
+            assert getsum(S) == g1_aff_add(A, T7), "add"
+            run_levels(g1k.progs["g1_madd"], S)
+            want = g1_aff_add(g1_aff_add(A, T7), Pt)
+            assert getsum(S) == want, "madd"
+        S[st["tinv"]] = pow(S[st["T.2.0"]] + S[st["T.2.1"]], -1, P)
+        run_levels(g1k.progs["g1_aff"], S)
+        assert (S[st["ax"]] % P, S[st["ay"]] % P) == want, "aff"
     print("G1 programs ok", file=sys.stderr)
 
 

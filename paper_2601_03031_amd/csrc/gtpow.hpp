@@ -44,7 +44,7 @@ template <class Ctx> __host__ __device__ inline int pow_cyc(Ctx &c, const gls::D
   }
   if (!(dec.neg & 1)) copy12(c, B(1), B(0));
   c.sync();
-  c.run_list(0, 3 + __builtin_popcount(dec.neg & 15u), 0, 0);
+  c.run_list(0, 3 + __builtin_popcount(dec.neg & 15u));
   const int HEAD = 11;
   for (int e = c.lane(); e < HEAD + n; e += c.lanes()) {
     if (e < HEAD) {
@@ -59,7 +59,7 @@ template <class Ctx> __host__ __device__ inline int pow_cyc(Ctx &c, const gls::D
       c.cl[e] = d ? slp::call(slp::PROG_F12_CSQR_MUL, B(src), B(d), B(dst)) : slp::call(slp::PROG_F12_CSQR, B(src), B(src), B(dst));
     }
   }
-  c.run_list(0, HEAD + n, 0, 0);
+  c.run_list(0, HEAD + n);
   return n == 0 ? top : 17 - (n & 1);
 }
 

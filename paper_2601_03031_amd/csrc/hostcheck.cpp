@@ -442,183 +442,175 @@ API int hc_gls(const uint8_t *kb, uint8_t *out, uint32_t *nbits) {
 }
 
 
-// k Q + A on the engine's host model (A may be null); out affine (128 bytes, zeros = identity)
-API int hc_g2_mul(const uint8_t *Qb, const uint8_t *kb, const uint8_t *Ab, uint8_t *out) {
-  static slp::f29 S[slp::G2_NSLOT + 4];
-  g2_aff Q = rdg2(Qb);
-  const fe *q = reinterpret_cast<const fe *>(&Q);
-  for (int i = 0; i < 4; i++) S[slp::G2_xQ_0 + i] = slp::to29(q[i]);
-  bool has_a = false;
-  if (Ab) {
-    g2_aff A = rdg2(Ab);
+// ---- scalar multiplications on the engine's host model, results affine (zeros = identity)
+static fe out29(const slp::f29 &x) { return slp::from29(slp::canon29(x)); }
+
+struct HostG2 {
+  slp::f29 S[slp::G2_NSLOT];
+  slp::HostCtx c{S};
+  void begin(const g2_aff &Q) {
+    ld_consts(S, slp::G2_CBASE, slp::G2_CONSTS, slp::G2_NCONST);
+    const fe *q = reinterpret_cast<const fe *>(&Q);
+    for (int i = 0; i < 4; i++) S[slp::G2_xQ_0 + i] = slp::to29(q[i]);
+  }
+  void mul(const g2_aff &Q, const gls::Dec &dec) {
+    begin(Q);
+    g2m::mul(c, dec, aff_is_inf(Q));
+  }
+  // 2^{16 m} Q in T
+  void dbl_mult(const g2_aff &Q, int m) {
+    begin(Q);
+    if (aff_is_inf(Q)) g2m::load_identity(c);
+    else c.run(slp::PROG_G2_LOAD, 0, 0, 0);
+    for (int i = 0; i < 16 * m; i++) c.run(slp::PROG_G2_DBL, 0, 0, 0);
+  }
+  void add_affine(const g2_aff &A) {
+    if (aff_is_inf(A)) return;
     const fe *a = reinterpret_cast<const fe *>(&A);
-    for (int i = 0; i < 4; i++) S[slp::G2_NSLOT + i] = slp::to29(a[i]);
-    has_a = !aff_is_inf(A);
+    for (int i = 0; i < 4; i++) S[slp::G2_xQ_0 + i] = slp::to29(a[i]);
+    c.run(slp::PROG_G2_MADD, 0, 0, 0);
   }
-  ld_consts(S, slp::G2_CBASE, slp::G2_CONSTS, slp::G2_NCONST);
-  fe k = rd_raw(kb);
-  gls::Dec dec = gls::decompose(k.l);
+  // T += the homogeneous point p
+  void add_hom(const fe *p) {
+    for (int i = 0; i < 6; i++) S[slp::G2_TB1_0 + i] = slp::to29(p[i]);
+    c.run(slp::PROG_G2_ADD, 0, slp::G2_TB1_0, 0);
+  }
+  void hom(fe *p) {
+    for (int i = 0; i < 6; i++) p[i] = out29(g2m::coord(c, i));
+  }
+  g2_aff aff() {
+    c.run(slp::PROG_G2_NORM, 0, 0, 0);
+    const fe t = out29(S[slp::G2_t]);
+    g2_aff r = {};
+    if (fe_is_zero(t)) return r;
+    S[slp::G2_tinv] = slp::to29(fp_inv_fast(t));
+    c.run(slp::PROG_G2_AFF, 0, 0, 0);
+    for (int i = 0; i < 4; i++) reinterpret_cast<fe *>(&r)[i] = out29(S[slp::G2_ax_0 + i]);
+    return r;
+  }
+};
+
+struct HostG1 {
+  slp::f29 S[slp::G1_NSLOT];
   slp::HostCtx c{S};
-  bool inf = g2m::mul_add(c, dec, aff_is_inf(Q), has_a, slp::G2_NSLOT, S[slp::G2_CBASE + 1], S[slp::G2_CBASE]);
-  if (inf) { memset(out, 0, 128); return 0; }
-  c.run(slp::PROG_G2_NORM, 0, 0, 0);
-  S[slp::G2_tinv] = slp::to29(fp_inv_fast(slp::from29(slp::canon29(S[slp::G2_t]))));
-  c.run(slp::PROG_G2_AFF, 0, 0, 0);
-  g2_aff r;
-  fe *rw = reinterpret_cast<fe *>(&r);
-  for (int i = 0; i < 4; i++) rw[i] = slp::from29(slp::canon29(S[slp::G2_ax_0 + i]));
-  wrg2(out, r);
+  void begin(const g1_aff &P) {
+    ld_consts(S, slp::G1_CBASE, slp::G1_CONSTS, slp::G1_NCONST);
+    S[slp::G1_xP] = slp::to29(P.x);
+    S[slp::G1_yP] = slp::to29(P.y);
+  }
+  void mul(const g1_aff &P, const glv::Dec &dec) {
+    begin(P);
+    g1m::mul(c, dec, aff_is_inf(P));
+  }
+  // 2^{32 m} P in T
+  void dbl_mult(const g1_aff &P, int m) {
+    begin(P);
+    S[slp::G1_TB1_0] = slp::to29(P.x);
+    S[slp::G1_TB1_0 + 1] = slp::to29(P.y);
+    S[slp::G1_TB1_0 + 2] = slp::to29(f_one<FpP>());
+    if (aff_is_inf(P)) g1m::load_identity(c);
+    else g1m::load(c, slp::G1_TB1_0);
+    for (int i = 0; i < 16 * m; i++) c.run(slp::PROG_G1_DBL2, 0, 0, 0);
+  }
+  void add_affine(const g1_aff &A) {
+    if (!aff_is_inf(A)) g1m::add_affine(c, slp::to29(A.x), slp::to29(A.y));
+  }
+  void add_hom(const fe *p) {
+    for (int i = 0; i < 3; i++) S[slp::G1_TB1_0 + i] = slp::to29(p[i]);
+    c.run(slp::PROG_G1_ADD, 0, slp::G1_TB1_0, 0);
+  }
+  void hom(fe *p) {
+    for (int i = 0; i < 3; i++) p[i] = out29(g1m::coord(c, i));
+  }
+  g1_aff aff() {
+    const fe z = out29(g1m::coord(c, 2));
+    g1_aff r = {};
+    if (fe_is_zero(z)) return r;
+    S[slp::G1_tinv] = slp::to29(fp_inv_fast(z));
+    c.run(slp::PROG_G1_AFF, 0, 0, 0);
+    r.x = out29(S[slp::G1_ax]);
+    r.y = out29(S[slp::G1_ay]);
+    return r;
+  }
+};
+
+// k Q + A (A may be null); k canonical 32 bytes big-endian
+API int hc_g2_mul(const uint8_t *Qb, const uint8_t *kb, const uint8_t *Ab, uint8_t *out) {
+  static HostG2 h;
+  fe k = rd_raw(kb);
+  h.mul(rdg2(Qb), gls::decompose(k.l));
+  if (Ab) h.add_affine(rdg2(Ab));
+  wrg2(out, h.aff());
   return 0;
 }
 
-
-// k P (+ A) on the engine (host model), affine result; k canonical 32 bytes big-endian
+// k P + A (A may be null)
 API int hc_g1_mul_engine(const uint8_t *Pb, const uint8_t *kb, const uint8_t *Ab, uint8_t *out) {
-  static slp::f29 S[slp::G1_NSLOT + 2];
-  g1_aff P = rdg1(Pb);
-  S[slp::G1_xP] = slp::to29(P.x);
-  S[slp::G1_yP] = slp::to29(P.y);
-  bool has_a = false;
-  if (Ab) {
-    g1_aff A = rdg1(Ab);
-    S[slp::G1_NSLOT] = slp::to29(A.x);
-    S[slp::G1_NSLOT + 1] = slp::to29(A.y);
-    has_a = !aff_is_inf(A);
-  }
-  ld_consts(S, slp::G1_CBASE, slp::G1_CONSTS, slp::G1_NCONST);
+  static HostG1 h;
   fe k = rd_raw(kb);
-  glv::Dec dec = glv::decompose(k.l);
-  slp::HostCtx c{S};
-  bool inf = g1m::mul_add(c, dec, aff_is_inf(P), has_a, slp::G1_NSLOT, S[slp::G1_CBASE + 1]);
-  if (inf) { memset(out, 0, 64); return 0; }
-  S[slp::G1_tinv] = slp::to29(fp_inv_fast(slp::from29(slp::canon29(S[slp::G1_T_2]))));
-  c.run(slp::PROG_G1_AFF, 0, 0, 0);
-  g1_aff r{slp::from29(slp::canon29(S[slp::G1_ax])), slp::from29(slp::canon29(S[slp::G1_ay]))};
-  wrg1(out, r);
+  h.mul(rdg1(Pb), glv::decompose(k.l));
+  if (Ab) h.add_affine(rdg1(Ab));
+  wrg1(out, h.aff());
   return 0;
 }
 
-// k P as the sum over t < 4 of chunk_t(k) (2^{32 t} P) on the engine (host model): the split
-// used to run the four parts in parallel
+// k P as the sum over t < 4 of chunk_t(k) (2^{32 t} P): the split used to run the four parts in
+// parallel
 API int hc_g1_mul_split(const uint8_t *Pb, const uint8_t *kb, uint8_t *out) {
-  static slp::f29 S[slp::G1_NSLOT + 2];
+  static HostG1 h;
   g1_aff P = rdg1(Pb);
   fe k = rd_raw(kb);
   glv::Dec dec = glv::decompose(k.l);
-  g1_jac acc = jac_inf<OpsG1>();
-  g1_jac Pt = jac_from_aff(P);
+  g1_jac acc = jac_inf<OpsG1>(), Pt = jac_from_aff(P);
   for (int t = 0; t < 4; t++) {
     if (t)
       for (int i = 0; i < 32; i++) Pt = jac_dbl(Pt);
-    g1_aff Pa = jac_to_aff(Pt);
-    S[slp::G1_xP] = slp::to29(Pa.x);
-    S[slp::G1_yP] = slp::to29(Pa.y);
-    ld_consts(S, slp::G1_CBASE, slp::G1_CONSTS, slp::G1_NCONST);
-    slp::HostCtx c{S};
-    bool inf = g1m::mul_add(c, glv::chunk(dec, t), aff_is_inf(Pa), false, slp::G1_NSLOT, S[slp::G1_CBASE + 1]);
-    if (!inf) {
-      g1_jac part{slp::from29(slp::canon29(S[slp::G1_T_0])), slp::from29(slp::canon29(S[slp::G1_T_1])),
-                  slp::from29(slp::canon29(S[slp::G1_T_2]))};
-      acc = jac_add(acc, part);
-    }
+    h.mul(jac_to_aff(Pt), glv::chunk(dec, t));
+    acc = jac_madd(acc, h.aff());
   }
   wrg1(out, jac_to_aff(acc));
   return 0;
 }
 
-// The split fold on the engine (host model), as the GPU runs it: multiples 2^{32 t} P by
-// repeated double doublings, the four chunked multiplications into Jacobian partials, then
-// their sum in the table slots plus A (affine; may be null or the identity).  Out affine.
+// The split fold, as the GPU runs it: multiples 2^{32 t} P by repeated double doublings, the four
+// chunked multiplications into homogeneous partials, then their sum plus A (affine; may be null
+// or the identity).
 API int hc_fold_split_g1(const uint8_t *Pb, const uint8_t *kb, const uint8_t *Ab, uint8_t *out) {
-  static slp::f29 S[slp::G1_NSLOT + 2];
+  static HostG1 h;
   g1_aff P = rdg1(Pb);
   fe k = rd_raw(kb);
   glv::Dec dec = glv::decompose(k.l);
-  slp::HostCtx c{S};
   fe part[4][3];
-  bool pinf[4];
   for (int t = 0; t < 4; t++) {
-    ld_consts(S, slp::G1_CBASE, slp::G1_CONSTS, slp::G1_NCONST);
-    g1_aff base = P;
-    if (t && !aff_is_inf(P)) {
-      S[slp::G1_T_0] = slp::to29(P.x);
-      S[slp::G1_T_1] = slp::to29(P.y);
-      S[slp::G1_T_2] = slp::to29(f_one<FpP>());
-      for (int i = 0; i < 16 * t; i++) c.run(slp::PROG_G1_DBL2, 0, 0, 0);
-      S[slp::G1_tinv] = slp::to29(fp_inv_fast(slp::from29(slp::canon29(S[slp::G1_T_2]))));
-      c.run(slp::PROG_G1_AFF, 0, 0, 0);
-      base = {slp::from29(slp::canon29(S[slp::G1_ax])), slp::from29(slp::canon29(S[slp::G1_ay]))};
-    }
-    S[slp::G1_xP] = slp::to29(base.x);
-    S[slp::G1_yP] = slp::to29(base.y);
-    pinf[t] = g1m::mul_add(c, glv::chunk(dec, t), aff_is_inf(base), false, slp::G1_NSLOT, S[slp::G1_CBASE + 1]);
-    for (int q = 0; q < 3; q++)
-      part[t][q] = pinf[t] ? (q < 2 ? f_one<FpP>() : fe_zero()) : slp::from29(slp::canon29(S[slp::G1_T_0 + q]));
+    h.dbl_mult(P, t);
+    const g1_aff base = h.aff();
+    h.mul(base, glv::chunk(dec, t));
+    h.hom(part[t]);
   }
-  for (int t = 0; t < 4; t++)
-    for (int q = 0; q < 3; q++) S[slp::G1_TB1_0 + 3 * t + q] = slp::to29(part[t][q]);
-  bool inf = true;
-  for (int t = 0; t < 4; t++) g1m::add_jac(c, inf, slp::G1_TB1_0 + 3 * t, fe_is_zero(part[t][2]));
-  if (Ab) {
-    g1_aff A = rdg1(Ab);
-    S[slp::G1_NSLOT] = slp::to29(A.x);
-    S[slp::G1_NSLOT + 1] = slp::to29(A.y);
-    if (!aff_is_inf(A)) g1m::add_affine(c, inf, slp::G1_NSLOT, S[slp::G1_CBASE + 1]);
-  }
-  if (inf) { memset(out, 0, 64); return 0; }
-  S[slp::G1_tinv] = slp::to29(fp_inv_fast(slp::from29(slp::canon29(S[slp::G1_T_2]))));
-  c.run(slp::PROG_G1_AFF, 0, 0, 0);
-  g1_aff r{slp::from29(slp::canon29(S[slp::G1_ax])), slp::from29(slp::canon29(S[slp::G1_ay]))};
-  wrg1(out, r);
+  g1m::load_identity(h.c);
+  for (int t = 0; t < 4; t++) h.add_hom(part[t]);
+  if (Ab) h.add_affine(rdg1(Ab));
+  wrg1(out, h.aff());
   return 0;
 }
 
 // the same for G2: multiples 2^{16 t} Q, bits [16 t, 16 t + w_t) of the GLS split
 API int hc_fold_split_g2(const uint8_t *Qb, const uint8_t *kb, const uint8_t *Ab, uint8_t *out) {
-  static slp::f29 S[slp::G2_NSLOT + 4];
+  static HostG2 h;
   g2_aff Q = rdg2(Qb);
   fe k = rd_raw(kb);
   gls::Dec dec = gls::decompose(k.l);
-  slp::HostCtx c{S};
   fe part[4][6];
   for (int t = 0; t < 4; t++) {
-    ld_consts(S, slp::G2_CBASE, slp::G2_CONSTS, slp::G2_NCONST);
-    g2_aff base = Q;
-    const fe *q = reinterpret_cast<const fe *>(&Q);
-    if (t && !aff_is_inf(Q)) {
-      for (int i = 0; i < 6; i++) S[slp::G2_T_0 + i] = slp::to29(i < 4 ? q[i] : i == 4 ? f_one<FpP>() : fe_zero());
-      for (int i = 0; i < 16 * t; i++) c.run(slp::PROG_G2_DBL, 0, 0, 0);
-      c.run(slp::PROG_G2_NORM, 0, 0, 0);
-      S[slp::G2_tinv] = slp::to29(fp_inv_fast(slp::from29(slp::canon29(S[slp::G2_t]))));
-      c.run(slp::PROG_G2_AFF, 0, 0, 0);
-      fe *bw = reinterpret_cast<fe *>(&base);
-      for (int i = 0; i < 4; i++) bw[i] = slp::from29(slp::canon29(S[slp::G2_ax_0 + i]));
-    }
-    const fe *bq = reinterpret_cast<const fe *>(&base);
-    for (int i = 0; i < 4; i++) S[slp::G2_xQ_0 + i] = slp::to29(bq[i]);
-    bool pinf = g2m::mul_add(c, gls::chunk(dec, 16 * t, t < 3 ? 16 : 17), aff_is_inf(base), false, slp::G2_NSLOT,
-                             S[slp::G2_CBASE + 1], S[slp::G2_CBASE]);
-    for (int i = 0; i < 6; i++)
-      part[t][i] = pinf ? ((i == 0 || i == 2) ? f_one<FpP>() : fe_zero()) : slp::from29(slp::canon29(S[slp::G2_T_0 + i]));
+    h.dbl_mult(Q, t);
+    const g2_aff base = h.aff();
+    h.mul(base, gls::chunk(dec, 16 * t, t < 3 ? 16 : 17));
+    h.hom(part[t]);
   }
-  for (int t = 0; t < 4; t++)
-    for (int i = 0; i < 6; i++) S[slp::G2_TB1_0 + 6 * t + i] = slp::to29(part[t][i]);
-  bool inf = true;
-  for (int t = 0; t < 4; t++) g2m::add_jac(c, inf, slp::G2_TB1_0 + 6 * t, fe_is_zero(part[t][4]) && fe_is_zero(part[t][5]));
-  if (Ab) {
-    g2_aff A = rdg2(Ab);
-    const fe *a = reinterpret_cast<const fe *>(&A);
-    for (int i = 0; i < 4; i++) S[slp::G2_NSLOT + i] = slp::to29(a[i]);
-    if (!aff_is_inf(A)) g2m::add_affine(c, inf, slp::G2_NSLOT, S[slp::G2_CBASE + 1], S[slp::G2_CBASE]);
-  }
-  if (inf) { memset(out, 0, 128); return 0; }
-  c.run(slp::PROG_G2_NORM, 0, 0, 0);
-  S[slp::G2_tinv] = slp::to29(fp_inv_fast(slp::from29(slp::canon29(S[slp::G2_t]))));
-  c.run(slp::PROG_G2_AFF, 0, 0, 0);
-  g2_aff r;
-  fe *rw = reinterpret_cast<fe *>(&r);
-  for (int i = 0; i < 4; i++) rw[i] = slp::from29(slp::canon29(S[slp::G2_ax_0 + i]));
-  wrg2(out, r);
+  g2m::load_identity(h.c);
+  for (int t = 0; t < 4; t++) h.add_hom(part[t]);
+  if (Ab) h.add_affine(rdg2(Ab));
+  wrg2(out, h.aff());
   return 0;
 }
 
@@ -680,7 +672,7 @@ API int hc_gt_pow_cyc(const uint8_t *gb, const uint8_t *kb, uint8_t *out) {
 // (9.. : G1 phi + table, two doublings + addition, two doublings, mixed addition, to affine;
 // cyclotomic squaring; the three Frobenius maps):
 // 0 Miller loop (whole sequence), 1 final exponentiation (whole sequence, without the
-// one-lane inversion), 2 G2 psi images, 3 G2 table, 4 G2 doubling, 5 G2 addition,
+// one-lane inversion), 2 G2 signed bases (to the isomorphic curve), 3 G2 table, 4 G2 doubling, 5 G2 addition,
 // 6 G2 mixed addition, 7 G2 to affine (norm + affine), 8 F_p12 product
 static uint64_t prog_muls(int prog) {
   uint64_t n = 0;
@@ -693,10 +685,10 @@ API uint64_t hc_engine_muls(int which) {
   switch (which) {
     case 0: return prog_muls(slp::PROG_ML);
     case 1: return prog_muls(slp::PROG_FE_NORM) + prog_muls(slp::PROG_FE_REST);
-    case 2: return prog_muls(slp::PROG_G2_PSI);
+    case 2: return prog_muls(slp::PROG_G2_BASES);
     case 3: return prog_muls(slp::PROG_G2_TABLE);
     case 4: return prog_muls(slp::PROG_G2_DBL);
-    case 5: return prog_muls(slp::PROG_G2_ADD);
+    case 5: return prog_muls(slp::PROG_G2_DBL_ADD) - prog_muls(slp::PROG_G2_DBL);
     case 6: return prog_muls(slp::PROG_G2_MADD);
     case 7: return prog_muls(slp::PROG_G2_NORM) + prog_muls(slp::PROG_G2_AFF);
     case 8: return prog_muls(slp::PROG_F12_MUL);

@@ -17,6 +17,14 @@ static_assert(slp::ML_WAVES == SLP_W && slp::F12_WAVES == SLP_W && slp::G1_WAVES
               "programs scheduled for another workgroup size");
 typedef slp::DevCtx<SLP_W> Ctx;
 typedef slp::DevCtx<SLP_W, true> CtxInline;  // for kernels with one place that runs calls
+// slots of a kernel that runs only some of a family's programs (the tables' take the most)
+constexpr int most(int a, int b = 0, int c = 0, int d = 0) {
+  const int x = a > b ? a : b, y = c > d ? c : d;
+  return x > y ? x : y;
+}
+constexpr int G1_DBL_SLOTS = most(slp::G1_DBL2_SLOTS, slp::G1_AFF_SLOTS);
+constexpr int G2_AFF_ALL_SLOTS = most(slp::G2_NORM_SLOTS, slp::G2_AFF_SLOTS);
+constexpr int G2_DBL_ALL_SLOTS = most(slp::G2_DBL_SLOTS, slp::G2_LOAD_SLOTS, G2_AFF_ALL_SLOTS);
 // the call list of a workgroup in LDS
 #define CALL_LIST() __shared__ slp::Call calls_sh[slp::MAX_CALLS + 1]
 
@@ -162,7 +170,7 @@ __device__ __forceinline__ void fe_job(const fp12 *in, fp12 *out) {
 #pragma unroll 1
   for (int part = 0; part < 2; part++) {
     c.run(part ? slp::PROG_FE_REST : slp::PROG_FE_NORM, 0, 0, 0);
-    if (!part) c.invert(slp::FE_tinv, slp::FE_t);
+    if (!part) c.invert(slp::FE_tinv, S[slp::FE_t]);
   }
   fe *dst = reinterpret_cast<fe *>(out);
   if (t < 12) dst[t] = slp::from29(slp::canon29(S[slp::FE_D_0 + t]));
@@ -179,71 +187,71 @@ __global__ void __launch_bounds__(FE_T, 4) ks_final_exp(const fp12 *in, uint64_t
 }
 
 // ---------------------------------------------------------------- G2 scalar multiplications
-#define G2_SLOTS (slp::G2_NSLOT + 4)
-#define G2_ABASE slp::G2_NSLOT
+__device__ __forceinline__ fe out29(const f29 &x) { return slp::from29(slp::canon29(x)); }
 
-// T (Jacobian, the identity when inf) to oaff
-__device__ void g2_store_aff(Ctx c, bool inf, g2_aff *oaff) {
-  f29 *S = c.S;
+// T (homogeneous) to affine coordinates of the twist, zeros for the identity
+__device__ void g2_store_aff(Ctx c, g2_aff *oaff) {
   const int t = threadIdx.x;
   fe *o = reinterpret_cast<fe *>(oaff);
-  if (inf) {
+  c.run(slp::PROG_G2_NORM, 0, 0, 0);
+  if (!c.invert(slp::G2_tinv, c.S[slp::G2_t])) {
     if (t < 4) o[t] = fe_zero();
     return;
   }
-  c.run(slp::PROG_G2_NORM, 0, 0, 0);
-  c.invert(slp::G2_tinv, slp::G2_t);
   c.run(slp::PROG_G2_AFF, 0, 0, 0);
-  if (t < 4) o[t] = slp::from29(slp::canon29(S[slp::G2_ax_0 + t]));
+  if (t < 4) o[t] = out29(c.S[slp::G2_ax_0 + t]);
+}
+// T as six field elements (homogeneous, on the isomorphic curve), in the place of a g2_jac
+__device__ void g2_store_hom(Ctx c, g2_jac *out) {
+  const int t = threadIdx.x;
+  if (t < 6) reinterpret_cast<fe *>(out)[t] = out29(g2m::coord(c, t));
 }
 
-// out = k Q + A on the engine (A optional); results written as affine (oaff) or Jacobian (ojac).
-// With lo >= 0 only bits [lo, lo + width) of the GLS split of k are applied (gls::chunk).
-__device__ void g2_job(Ctx c, gls::Dec *dec, const g2_aff *Q, const fe *k_mont, const g2_aff *A, g2_aff *oaff,
-                       g2_jac *ojac, int lo = -1, int width = 0) {
-  f29 *S = c.S;
+// T += A for an affine A of the twist: its coordinates go to xQ, yQ (whose values are spent)
+__device__ void g2_add_affine(Ctx c, const g2_aff *A) {
+  if (g2_inf(*A)) return;
+  const int t = threadIdx.x;
+  if (t < 4) c.S[slp::G2_xQ_0 + t] = slp::to29(reinterpret_cast<const fe *>(A)[t]);
+  c.run(slp::PROG_G2_MADD, 0, 0, 0);
+}
+
+// T = k Q + A on the engine (A optional).  With lo >= 0 only bits [lo, lo + width) of the GLS
+// split of k are applied (gls::chunk).
+__device__ void g2_job(Ctx c, gls::Dec *dec, const g2_aff *Q, const fe *k_mont, const g2_aff *A, int lo = -1, int width = 0) {
   const int t = threadIdx.x;
   if (t == 0) {
     fe kc = f_from_mont<FpR>(*k_mont);
     gls::Dec d = gls::decompose(kc.l);
     *dec = lo < 0 ? d : gls::chunk(d, lo, width);
   }
-  const fe *q = reinterpret_cast<const fe *>(Q);
-  if (t < 4) S[slp::G2_xQ_0 + t] = slp::to29(q[t]);
-  if (A && t >= 4 && t < 8) S[G2_ABASE + t - 4] = slp::to29(reinterpret_cast<const fe *>(A)[t - 4]);
-  load_consts<slp::G2_NCONST>(S, slp::G2_CBASE, slp::G2_CONSTS);
+  if (t >= 64 && t < 68) c.S[slp::G2_xQ_0 + t - 64] = slp::to29(reinterpret_cast<const fe *>(Q)[t - 64]);
+  load_consts<slp::G2_NCONST>(c.S, slp::G2_CBASE, slp::G2_CONSTS);
   __syncthreads();
-  bool qinf = g2_inf(*Q), has_a = A && !g2_inf(*A);
-  const f29 one = S[slp::G2_CBASE + 1], zero = S[slp::G2_CBASE];
-  bool inf = g2m::mul_add(c, *dec, qinf, has_a, G2_ABASE, one, zero);
-  if (ojac) {
-    fe *o = reinterpret_cast<fe *>(ojac);
-    if (t < 6) o[t] = inf ? ((t == 0 || t == 2) ? f_one<FpP>() : fe_zero()) : slp::from29(slp::canon29(S[slp::G2_T_0 + t]));
-    return;
-  }
-  g2_store_aff(c, inf, oaff);
+  g2m::mul(c, *dec, g2_inf(*Q));
+  if (A) g2_add_affine(c, A);
 }
 
 // Vout[i] = Vin[i] + x^{-1} Vin[h + i] for every batch k (Eq. folding); Vout may be Vin
 __global__ void __launch_bounds__(SLP_T, 4) ks_oa_fold_g2(const g2_aff *Vin, g2_aff *Vout, const fe *Xinv, uint64_t K, uint64_t nb,
                                                       uint64_t h, uint32_t j, uint32_t lK) {
-  __shared__ f29 S[G2_SLOTS];
+  __shared__ f29 S[slp::G2_NSLOT];
   CALL_LIST();
   Ctx c{S, calls_sh};
   __shared__ gls::Dec dec;
   uint64_t id = blockIdx.x;
   if (id >= nb * h) return;
   uint64_t k = id / h, i = id % h;
-  g2_job(c, &dec, Vin + k * K + h + i, Xinv + k * lK + (j - 1), Vin + k * K + i, Vout + k * K + i, nullptr);
+  g2_job(c, &dec, Vin + k * K + h + i, Xinv + k * lK + (j - 1), Vin + k * K + i);
+  g2_store_aff(c, Vout + k * K + i);
 }
 
 // terms q_m h_m of the KZG proof of v_l with every multiplication split in four parts (bits
 // [16 p, 16 p + 16) of the GLS split, 17 for p = 3) on the multiples hm[3 m + p - 1] =
-// 2^{16 p} h_m made at setup: S2[4 id + p] (Jacobian) for term id = k (2K - 2) + m
+// 2^{16 p} h_m made at setup: S2[4 id + p] (homogeneous) for term id = k (2K - 2) + m
 __global__ void __launch_bounds__(SLP_T, 4) ks_kzg_terms_split(const g2_aff *h, const g2_aff *hm, const fe *Qc, uint64_t K,
                                                            uint64_t nb, g2_jac *S2) {
   CHAIN_PRIORITY();
-  __shared__ f29 S[G2_SLOTS];
+  __shared__ f29 S[slp::G2_NSLOT];
   CALL_LIST();
   Ctx c{S, calls_sh};
   __shared__ gls::Dec dec;
@@ -252,8 +260,8 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_kzg_terms_split(const g2_aff *h, 
   if (id >= 4 * nb * n) return;
   uint64_t term = id >> 2, m = term % n;
   int part = (int)(id & 3);
-  g2_job(c, &dec, part ? hm + 3 * m + part - 1 : h + m, Qc + term, nullptr, nullptr, S2 + id, 16 * part,
-         part < 3 ? 16 : 17);
+  g2_job(c, &dec, part ? hm + 3 * m + part - 1 : h + m, Qc + term, nullptr, 16 * part, part < 3 ? 16 : 17);
+  g2_store_hom(c, S2 + id);
 }
 
 // ---------------------------------------------------------------- G_T exponentiation
@@ -294,68 +302,61 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_gt_pow(const fp12 *in, const fe *
       c.cl[e] = one ? slp::call(slp::PROG_F12_SQR_MUL, F12_BUF(src), F12_BUF(0), F12_BUF(dst))
                     : slp::call(slp::PROG_F12_SQR, F12_BUF(src), F12_BUF(src), F12_BUF(dst));
     }
-    c.run_list(0, n, 0, 0);
+    c.run_list(0, n);
   }
   const int acc = top == 0 ? 0 : 2 - (top & 1);
   if (t < 12) dst[t] = slp::from29(slp::canon29(S[F12_BUF(acc) + t]));
 }
 
 // ---------------------------------------------------------------- G1 scalar multiplications
-#define G1_SLOTS (slp::G1_NSLOT + 2)
-#define G1_ABASE slp::G1_NSLOT
-
-// T (Jacobian, the identity when inf) to oaff
-__device__ void g1_store_aff(Ctx c, bool inf, g1_aff *oaff) {
-  f29 *S = c.S;
+// T (homogeneous) to affine, zeros for the identity
+__device__ void g1_store_aff(Ctx c, g1_aff *oaff) {
   const int t = threadIdx.x;
   fe *o = reinterpret_cast<fe *>(oaff);
-  if (inf) {
+  if (!c.invert(slp::G1_tinv, g1m::coord(c, 2))) {
     if (t < 2) o[t] = fe_zero();
     return;
   }
-  c.invert(slp::G1_tinv, slp::G1_T_2);
   c.run(slp::PROG_G1_AFF, 0, 0, 0);
-  if (t < 2) o[t] = slp::from29(slp::canon29(S[t ? slp::G1_ay : slp::G1_ax]));
+  if (t < 2) o[t] = out29(c.S[t ? slp::G1_ay : slp::G1_ax]);
+}
+// T as three field elements (homogeneous), in the place of a g1_jac
+__device__ void g1_store_hom(Ctx c, g1_jac *out) {
+  const int t = threadIdx.x;
+  if (t < 3) reinterpret_cast<fe *>(out)[t] = out29(g1m::coord(c, t));
 }
 
-// out = k P + A on the engine (A optional); results written as affine (oaff) or Jacobian (ojac).
-// With chunk >= 0 only that 32-bit part of the GLV split of k is applied (glv::chunk).
-__device__ void g1_job(Ctx c, glv::Dec *dec, const g1_aff *P, const fe *k_mont, const g1_aff *A, g1_aff *oaff,
-                       g1_jac *ojac, int chunk = -1) {
-  f29 *S = c.S;
+// T = k P + A on the engine (A optional).  With chunk >= 0 only that 32-bit part of the GLV split
+// of k is applied (glv::chunk).
+__device__ void g1_job(Ctx c, glv::Dec *dec, const g1_aff *P, const fe *k_mont, const g1_aff *A, int chunk = -1) {
   const int t = threadIdx.x;
   if (t == 0) {
     fe kc = f_from_mont<FpR>(*k_mont);
     glv::Dec d = glv::decompose(kc.l);
     *dec = chunk < 0 ? d : glv::chunk(d, chunk);
   }
-  if (t < 2) S[slp::G1_xP + t] = slp::to29(t ? P->y : P->x);
-  if (A && t >= 2 && t < 4) S[G1_ABASE + t - 2] = slp::to29(t == 3 ? A->y : A->x);
-  load_consts<slp::G1_NCONST>(S, slp::G1_CBASE, slp::G1_CONSTS);
+  if (t >= 64 && t < 66) c.S[slp::G1_xP + t - 64] = slp::to29(t == 65 ? P->y : P->x);
+  load_consts<slp::G1_NCONST>(c.S, slp::G1_CBASE, slp::G1_CONSTS);
   __syncthreads();
-  bool pinf = g1_inf(*P), has_a = A && !g1_inf(*A);
-  bool inf = g1m::mul_add(c, *dec, pinf, has_a, G1_ABASE, S[slp::G1_CBASE + 1]);
-  if (ojac) {
-    fe *o = reinterpret_cast<fe *>(ojac);
-    if (t < 3) o[t] = inf ? (t < 2 ? f_one<FpP>() : fe_zero()) : slp::from29(slp::canon29(S[slp::G1_T_0 + t]));
-    return;
-  }
-  g1_store_aff(c, inf, oaff);
+  g1m::mul(c, *dec, g1_inf(*P));
+  if (A && !g1_inf(*A)) g1m::add_affine(c, slp::to29(A->x), slp::to29(A->y));
 }
 
 // ---------------------------------------------------------------- group sums on the engine
-// Sum of each segment data[g stride + 0 .. len) of Jacobian points into data[g stride] in
-// one launch: a workgroup per pair of the first level; of two sibling nodes, the workgroup
-// that finishes second climbs to the parent (arrival counters as in ks_f12_tree).  The
-// identity is any point with Z = 0; additions meeting equal x are resolved exactly.
-template <bool G2>
-__global__ void __launch_bounds__(SLP_T, 4) ks_jac_tree(void *data, uint64_t nseg, uint64_t stride, uint64_t len, uint32_t *cnt) {
+// Sum of each segment data[g stride + 0 .. len) of points into data[g stride] in one launch: a
+// workgroup per pair of the first level; of two sibling nodes, the workgroup that finishes
+// second climbs to the parent (arrival counters as in ks_f12_tree).  HOM: homogeneous points of
+// the engine's multiplications (G1, or G2 on the isomorphic curve), an addition two levels and
+// never exceptional; otherwise Jacobian G2 points of the twist (the MSM's), the identity any
+// point with Z = 0.
+template <bool G2, bool HOM>
+__global__ void __launch_bounds__(SLP_T, 4) ks_pt_tree(void *data, uint64_t nseg, uint64_t stride, uint64_t len, uint32_t *cnt) {
   if (G2) CHAIN_PRIORITY();
   else AHEAD_PRIORITY();
   constexpr int NC = G2 ? 6 : 3;  // coordinates (F_p elements) per point
-  __shared__ f29 S[G2 ? G2_SLOTS : G1_SLOTS];
-  CALL_LIST();
-  Ctx cx{S, calls_sh};
+  __shared__ f29 S[!G2 ? slp::G1_ADD_SLOTS : HOM ? slp::G2_ADD_SLOTS : most(slp::G2_JADD_SLOTS, slp::G2_JDBL_SLOTS)];
+  __shared__ slp::Call calls_sh[HOM ? 1 : slp::MAX_CALLS + 1];
+  slp::DevCtx<SLP_W, HOM> cx{S, calls_sh};
   __shared__ uint32_t arrived;
   uint64_t per = (len + 1) / 2;
   uint64_t id = blockIdx.x;
@@ -364,7 +365,7 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_jac_tree(void *data, uint64_t nse
   fe *seg = reinterpret_cast<fe *>(data) + g * stride * NC;
   uint32_t *c = cnt + g * tree_counters(len);
   const int t = threadIdx.x;
-  const int T0 = G2 ? slp::G2_T_0 : slp::G1_T_0, A0 = G2 ? slp::G2_TB1_0 : slp::G1_TB1_0;
+  const int A0 = G2 ? slp::G2_TB1_0 : slp::G1_TB1_0, B0 = A0 + NC;
   if (G2) load_consts<slp::G2_NCONST>(S, slp::G2_CBASE, slp::G2_CONSTS);
   else load_consts<slp::G1_NCONST>(S, slp::G1_CBASE, slp::G1_CONSTS);
   uint64_t s = 1, n = per, cb = 0;
@@ -373,18 +374,27 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_jac_tree(void *data, uint64_t nse
     if (b < len) {
       fe *da = seg + a * NC;
       const fe *db = seg + b * NC;
-      bool binf = G2 ? fe_is_zero(db[4]) && fe_is_zero(db[5]) : fe_is_zero(db[2]);
-      if (!binf) {
-        bool inf = G2 ? fe_is_zero(da[4]) && fe_is_zero(da[5]) : fe_is_zero(da[2]);
+      if (HOM) {
+        if (t < 2 * NC) S[A0 + t] = slp::to29(t < NC ? da[t] : db[t - NC]);
+        __syncthreads();
+        if constexpr (G2) {
+          g2m::load(cx, A0);
+          cx.run(slp::PROG_G2_ADD, 0, B0, 0);
+          if (t < NC) da[t] = out29(g2m::coord(cx, t));
+        } else {
+          g1m::load(cx, A0);
+          cx.run(slp::PROG_G1_ADD, 0, B0, 0);
+          if (t < NC) da[t] = out29(g1m::coord(cx, t));
+        }
+      } else if (!(fe_is_zero(db[4]) && fe_is_zero(db[5]))) {
+        bool inf = fe_is_zero(da[4]) && fe_is_zero(da[5]);
         if (t < NC) {
-          S[T0 + t] = slp::to29(da[t]);
+          S[slp::G2_J_0 + t] = slp::to29(da[t]);
           S[A0 + t] = slp::to29(db[t]);
         }
         __syncthreads();
-        if (G2) g2m::add_jac(cx, inf, A0, false);
-        else g1m::add_jac(cx, inf, A0, false);
-        fe one_or_zero = (G2 ? (t == 0 || t == 2) : t < 2) ? f_one<FpP>() : fe_zero();
-        if (t < NC) da[t] = inf ? one_or_zero : slp::from29(slp::canon29(S[T0 + t]));
+        g2m::add_jac(cx, inf, A0, false);
+        if (t < NC) da[t] = inf ? ((t == 0 || t == 2) ? f_one<FpP>() : fe_zero()) : out29(S[slp::G2_J_0 + t]);
       }
     }
     if (n == 1) return;
@@ -399,21 +409,49 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_jac_tree(void *data, uint64_t nse
   }
 }
 
+// (i odd ? out1 : out0)[(i >> 1) ostride] = the homogeneous point in[i stride] in affine
+// coordinates, a workgroup per point
+template <bool G2>
+__global__ void __launch_bounds__(SLP_T, 4) ks_hom_to_aff(const void *in, uint64_t stride, uint64_t n, void *out0, void *out1,
+                                                         uint64_t ostride) {
+  CHAIN_PRIORITY();
+  constexpr int NC = G2 ? 6 : 3;
+  __shared__ f29 S[G2 ? G2_AFF_ALL_SLOTS : slp::G1_AFF_SLOTS];
+  CALL_LIST();
+  Ctx c{S, calls_sh};
+  const uint64_t i = blockIdx.x;
+  if (i >= n) return;
+  const int t = threadIdx.x, A0 = G2 ? slp::G2_TB1_0 : slp::G1_TB1_0;
+  if (t < NC) S[A0 + t] = slp::to29((reinterpret_cast<const fe *>(in) + i * stride * NC)[t]);
+  void *out = i & 1 ? out1 : out0;
+  if (G2) {
+    load_consts<slp::G2_NCONST>(S, slp::G2_CBASE, slp::G2_CONSTS);
+    __syncthreads();
+    g2m::load(c, A0);
+    g2_store_aff(c, reinterpret_cast<g2_aff *>(out) + (i >> 1) * ostride);
+  } else {
+    load_consts<slp::G1_NCONST>(S, slp::G1_CBASE, slp::G1_CONSTS);
+    __syncthreads();
+    g1m::load(c, A0);
+    g1_store_aff(c, reinterpret_cast<g1_aff *>(out) + (i >> 1) * ostride);
+  }
+}
+
 // ---------------------------------------------------------------- Step 1 rounds, fused
 // Round-1 (direct) G1 terms on the engine: b_L[i] A_R[i] (side 0) and b_R[i] A_L[i] (side 1)
-// into S[(2k + side) (K / 2) + i] (Jacobian)
+// into S[(2k + side) (K / 2) + i] (homogeneous)
 __global__ void __launch_bounds__(SLP_T, 4) ks_oa_g1terms(const g1_aff *A, const fe *B, uint64_t K, uint64_t nb, uint64_t h,
                                                       g1_jac *Sout) {
   AHEAD_PRIORITY();
-  __shared__ f29 S[G1_SLOTS];
+  __shared__ f29 S[slp::G1_NSLOT];
   CALL_LIST();
   Ctx c{S, calls_sh};
   __shared__ glv::Dec d1;
   uint64_t id = blockIdx.x;
   if (id >= nb * 2 * h) return;
   uint64_t k = id / (2 * h), r = id % (2 * h), side = r / h, i = r % h;
-  g1_job(c, &d1, A + (side ? k * K + i : k * K + h + i), B + (side ? k * K + h + i : k * K + i), nullptr, nullptr,
-         Sout + (k * 2 + side) * (K / 2) + i);
+  g1_job(c, &d1, A + (side ? k * K + i : k * K + h + i), B + (side ? k * K + h + i : k * K + i), nullptr);
+  g1_store_hom(c, Sout + (k * 2 + side) * (K / 2) + i);
 }
 
 template <int A_, int B_> struct imax { static constexpr int v = A_ > B_ ? A_ : B_; };
@@ -425,7 +463,7 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_oa_fold(const g1_aff *Ain, const 
                                                    g2_aff *Vout, const fe *X, const fe *Xinv, uint64_t K, uint64_t nb,
                                                    uint64_t h, uint32_t j, uint32_t lK) {
   CHAIN_PRIORITY();
-  __shared__ f29 S[imax<G1_SLOTS, G2_SLOTS>::v];
+  __shared__ f29 S[imax<slp::G1_NSLOT, slp::G2_NSLOT>::v];
   CALL_LIST();
   Ctx c{S, calls_sh};
   __shared__ glv::Dec d1;
@@ -436,11 +474,13 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_oa_fold(const g1_aff *Ain, const 
   if (g2) id -= nb * h;
   uint64_t k = id / h, i = id % h, slot = k * lK + (j - 1);
   if (g2) {
-    g2_job(c, &d2, Vin + k * K + h + i, Xinv + slot, Vin + k * K + i, Vout + k * K + i, nullptr);
+    g2_job(c, &d2, Vin + k * K + h + i, Xinv + slot, Vin + k * K + i);
+    g2_store_aff(c, Vout + k * K + i);
     return;
   }
   if (threadIdx.x == 32) Bout[k * K + i] = fr_add(Bin[k * K + i], fr_mul(Bin[k * K + h + i], Xinv[slot]));
-  g1_job(c, &d1, Ain + k * K + h + i, X + slot, Ain + k * K + i, Aout + k * K + i, nullptr);
+  g1_job(c, &d1, Ain + k * K + h + i, X + slot, Ain + k * K + i);
+  g1_store_aff(c, Aout + k * K + i);
 }
 
 // The next round's terms (oa_terms.hpp): the Miller loops into F[out], a workgroup per term
@@ -455,18 +495,19 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_oa_pterms(const g1_aff *A, const 
   miller_one(CtxInline{S, calls_sh}, A + tm.a, V + tm.v, F + tm.out);
 }
 
-// The G1 terms b[v] A[a] of the next round into S1[out] (Jacobian), a workgroup per term
+// The G1 terms b[v] A[a] of the next round into S1[out] (homogeneous), a workgroup per term
 __global__ void __launch_bounds__(SLP_T, 4) ks_oa_g1terms_next(const g1_aff *A, const fe *B, uint64_t K, uint64_t nb, uint64_t q,
                                                            g1_jac *S1) {
   AHEAD_PRIORITY();
-  __shared__ f29 S[G1_SLOTS];
+  __shared__ f29 S[slp::G1_NSLOT];
   CALL_LIST();
   Ctx c{S, calls_sh};
   __shared__ glv::Dec d1;
   uint64_t id = blockIdx.x;
   if (id >= nb * 8 * q) return;
   oat::Term tm = oat::term(id, K, nb, q);
-  g1_job(c, &d1, A + tm.a, B + tm.v, nullptr, nullptr, S1 + tm.out);
+  g1_job(c, &d1, A + tm.a, B + tm.v, nullptr);
+  g1_store_hom(c, S1 + tm.out);
 }
 
 // ---------------------------------------------------------------- cyclotomic G_T powers
@@ -490,7 +531,7 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_gt_sqr_mults(const fp12 *G, uint6
   __syncthreads();
   for (int e = t; e < 16 * (int)m; e += SLP_T)
     c.cl[e] = slp::call(slp::PROG_F12_CSQR, F12_BUF(e & 1), F12_BUF(e & 1), F12_BUF(1 - (e & 1)));
-  c.run_list(0, 16 * (int)m, 0, 0);  // an even number of squarings: the result is in buffer 0
+  c.run_list(0, 16 * (int)m);  // an even number of squarings: the result is in buffer 0
   fe *dst = reinterpret_cast<fe *>(M + 3 * s + m - 1);
   if (t < 12) dst[t] = slp::from29(slp::canon29(S[F12_BUF(0) + t]));
 }
@@ -502,55 +543,49 @@ __device__ __forceinline__ uint64_t seg_index(uint64_t s, uint64_t seg, uint64_t
 
 // prog n times on the same slots
 __device__ void repeat(Ctx c, int prog, int n) {
-  for (int e = threadIdx.x; e < n; e += SLP_T) c.cl[e] = slp::call(prog, 0, 0, 0);
-  c.run_list(0, n, 0, 0);
+  for (int e = threadIdx.x; e < n; e += SLP_T) c.cl[e] = slp::call(prog);
+  c.run_list(0, n);
 }
 
 // 2^{32 m} P (affine) by 16 m double doublings on the engine
 __device__ void g1_dbl_mult(Ctx c, const g1_aff *P, int m, g1_aff *o) {
-  f29 *S = c.S;
   const int t = threadIdx.x;
-  bool inf = g1_inf(*P);
-  if (!inf) {
-    load_consts<slp::G1_NCONST>(S, slp::G1_CBASE, slp::G1_CONSTS);
-    if (t < 3) S[slp::G1_T_0 + t] = slp::to29(t == 2 ? f_one<FpP>() : t ? P->y : P->x);
-    repeat(c, slp::PROG_G1_DBL2, 16 * m);
-  }
-  g1_store_aff(c, inf, o);
+  load_consts<slp::G1_NCONST>(c.S, slp::G1_CBASE, slp::G1_CONSTS);
+  if (t >= 64 && t < 67) c.S[slp::G1_TB1_0 + t - 64] = slp::to29(t == 66 ? f_one<FpP>() : t == 65 ? P->y : P->x);
+  __syncthreads();
+  if (g1_inf(*P)) g1m::load_identity(c);
+  else g1m::load(c, slp::G1_TB1_0);
+  repeat(c, slp::PROG_G1_DBL2, 16 * m);
+  g1_store_aff(c, o);
 }
 
 // 2^{16 m} Q (affine) by 16 m doublings on the engine
 __device__ void g2_dbl_mult(Ctx c, const g2_aff *Q, int m, g2_aff *o) {
-  f29 *S = c.S;
   const int t = threadIdx.x;
-  bool inf = g2_inf(*Q);
-  if (!inf) {
-    load_consts<slp::G2_NCONST>(S, slp::G2_CBASE, slp::G2_CONSTS);
-    const fe *q = reinterpret_cast<const fe *>(Q);
-    if (t < 6) S[slp::G2_T_0 + t] = t < 4 ? slp::to29(q[t]) : slp::to29(t == 4 ? f_one<FpP>() : fe_zero());
-    repeat(c, slp::PROG_G2_DBL, 16 * m);
-  }
-  g2_store_aff(c, inf, o);
+  load_consts<slp::G2_NCONST>(c.S, slp::G2_CBASE, slp::G2_CONSTS);
+  if (t >= 64 && t < 68) c.S[slp::G2_xQ_0 + t - 64] = slp::to29(reinterpret_cast<const fe *>(Q)[t - 64]);
+  __syncthreads();
+  if (g2_inf(*Q)) g2m::load_identity(c);
+  else c.run(slp::PROG_G2_LOAD, 0, 0, 0);
+  repeat(c, slp::PROG_G2_DBL, 16 * m);
+  g2_store_aff(c, o);
 }
 
-// 2^{32 m} P (affine) for a Jacobian P (m = 0: P itself), on the engine
-__device__ void g1_jac_mult_aff(Ctx c, const g1_jac *P, int m, g1_aff *o) {
-  f29 *S = c.S;
+// 2^{32 m} P (affine) for a homogeneous P (m = 0: P itself), on the engine
+__device__ void g1_hom_mult_aff(Ctx c, const g1_jac *P, int m, g1_aff *o) {
   const int t = threadIdx.x;
-  const fe *pj = reinterpret_cast<const fe *>(P);
-  bool inf = fe_is_zero(pj[2]);
-  if (!inf) {
-    load_consts<slp::G1_NCONST>(S, slp::G1_CBASE, slp::G1_CONSTS);
-    if (t < 3) S[slp::G1_T_0 + t] = slp::to29(pj[t]);
-    repeat(c, slp::PROG_G1_DBL2, 16 * m);
-  }
-  g1_store_aff(c, inf, o);
+  load_consts<slp::G1_NCONST>(c.S, slp::G1_CBASE, slp::G1_CONSTS);
+  if (t >= 64 && t < 67) c.S[slp::G1_TB1_0 + t - 64] = slp::to29(reinterpret_cast<const fe *>(P)[t - 64]);
+  __syncthreads();
+  g1m::load(c, slp::G1_TB1_0);
+  repeat(c, slp::PROG_G1_DBL2, 16 * m);
+  g1_store_aff(c, o);
 }
 
 // M[3 s + m - 1] = 2^{16 m} Q_s (affine), Q_s as in seg_index, a workgroup per (s, m), m = 1, 2, 3
 __global__ void __launch_bounds__(SLP_T, 4) ks_g2_dbl_mults(const g2_aff *Q, uint64_t seg, uint64_t segstride, uint64_t n,
                                                         g2_aff *M) {
-  __shared__ f29 S[G2_SLOTS];
+  __shared__ f29 S[G2_DBL_ALL_SLOTS];
   CALL_LIST();
   Ctx c{S, calls_sh};
   uint64_t id = blockIdx.x;
@@ -566,7 +601,7 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_fold_mults(const g1_aff *P, uint6
                                                       uint64_t seg2, uint64_t n2, uint64_t segstride, g1_aff *M1,
                                                       g2_aff *M2) {
   CHAIN_PRIORITY();
-  __shared__ f29 S[imax<G1_SLOTS, G2_SLOTS>::v];
+  __shared__ f29 S[most(G1_DBL_SLOTS, G2_DBL_ALL_SLOTS)];
   CALL_LIST();
   Ctx c{S, calls_sh};
   uint64_t id = blockIdx.x;
@@ -576,6 +611,18 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_fold_mults(const g1_aff *P, uint6
   uint64_t s = id / 3, m = id % 3 + 1;
   if (g2) g2_dbl_mult(c, Q + seg_index(s, seg2, segstride), (int)m, M2 + 3 * s + m - 1);
   else g1_dbl_mult(c, P + seg_index(s, seg1, segstride), (int)m, M1 + 3 * s + m - 1);
+}
+
+// T = the sum of the four parts at J (homogeneous) and A (affine, optional)
+__device__ void g1_sum_parts(Ctx c, const g1_jac *J, const g1_aff *A) {
+  const int t = threadIdx.x;
+  if (t < 12) c.S[slp::G1_TB1_0 + t] = slp::to29(reinterpret_cast<const fe *>(J)[t]);
+  const bool has_a = A && !g1_inf(*A);
+  if (has_a && t >= 64 && t < 66) c.S[slp::G1_xP + t - 64] = slp::to29(t == 65 ? A->y : A->x);
+  __syncthreads();
+  g1m::load(c, slp::G1_TB1_0);
+  if (t < 4) c.cl[t] = t < 3 ? slp::call(slp::PROG_G1_ADD, 0, slp::G1_TB1_0 + 3 * (t + 1)) : slp::call(slp::PROG_G1_MADD);
+  c.run_list(0, has_a ? 4 : 3);
 }
 
 // The fold of round j with every multiplication split in four parts run in parallel (M1
@@ -593,7 +640,7 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_oa_fold_split(const g1_aff *Ain, 
                                                          uint32_t *cnt, uint64_t K, uint64_t nb, uint64_t h, uint32_t j,
                                                          uint32_t lK) {
   CHAIN_PRIORITY();
-  __shared__ f29 S[imax<G1_SLOTS, G2_SLOTS>::v];
+  __shared__ f29 S[imax<slp::G1_NSLOT, slp::G2_NSLOT>::v];
   CALL_LIST();
   Ctx c{S, calls_sh};
   __shared__ glv::Dec d1;
@@ -608,80 +655,61 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_oa_fold_split(const g1_aff *Ain, 
   int part = (int)(id & 3);
   if (!g2) {
     if (part == 0 && t == 32) Bout[k * K + i] = fr_add(Bin[k * K + i], fr_mul(Bin[k * K + h + i], Xinv[slot]));
-    g1_job(c, &d1, part ? M1 + 3 * (k * 2 * h + h + i) + part - 1 : Ain + k * K + h + i, X + slot, nullptr, nullptr,
-           J1 + 4 * s + part, part);
+    g1_job(c, &d1, part ? M1 + 3 * (k * 2 * h + h + i) + part - 1 : Ain + k * K + h + i, X + slot, nullptr, part);
+    g1_store_hom(c, J1 + 4 * s + part);
     if (!last_arrival(cnt + s, 4, &flag)) return;
-    // sum of the parts (in the table slots) and A[i]
-    const fe *pj = reinterpret_cast<const fe *>(J1 + 4 * s);
-    if (t < 12) S[slp::G1_TB1_0 + t] = slp::to29(pj[t]);
-    const g1_aff *A = Ain + k * K + i;
-    if (t >= 12 && t < 14) S[G1_ABASE + t - 12] = slp::to29(t == 13 ? A->y : A->x);
-    __syncthreads();
-    bool inf = true;
-    for (int p = 0; p < 4; p++) g1m::add_jac(c, inf, slp::G1_TB1_0 + 3 * p, fe_is_zero(J1[4 * s + p].Z));
-    if (!g1_inf(*A)) g1m::add_affine(c, inf, G1_ABASE, S[slp::G1_CBASE + 1]);
-    g1_store_aff(c, inf, Aout + k * K + i);
+    g1_sum_parts(c, J1 + 4 * s, Ain + k * K + i);
+    g1_store_aff(c, Aout + k * K + i);
     return;
   }
-  g2_job(c, &d2, part ? M2 + 3 * s + part - 1 : Vin + k * K + h + i, Xinv + slot, nullptr, nullptr, J2 + 4 * s + part,
-         16 * part, part < 3 ? 16 : 17);
+  g2_job(c, &d2, part ? M2 + 3 * s + part - 1 : Vin + k * K + h + i, Xinv + slot, nullptr, 16 * part, part < 3 ? 16 : 17);
+  g2_store_hom(c, J2 + 4 * s + part);
   if (!last_arrival(cnt + n + s, 4, &flag)) return;
-  const fe *pj = reinterpret_cast<const fe *>(J2 + 4 * s);
-  if (t < 24) S[slp::G2_TB1_0 + t] = slp::to29(pj[t]);
-  const fe *a = reinterpret_cast<const fe *>(Vin + k * K + i);
-  if (t >= 24 && t < 28) S[G2_ABASE + t - 24] = slp::to29(a[t - 24]);
+  // sum of the parts (in the table slots) and V[i]
+  if (t < 24) S[slp::G2_TB1_0 + t] = slp::to29(reinterpret_cast<const fe *>(J2 + 4 * s)[t]);
   __syncthreads();
-  bool inf = true;
-  for (int p = 0; p < 4; p++) {
-    const g2_jac &Jp = J2[4 * s + p];
-    g2m::add_jac(c, inf, slp::G2_TB1_0 + 6 * p, fe_is_zero(Jp.Z.c0) && fe_is_zero(Jp.Z.c1));
-  }
-  if (!g2_inf(Vin[k * K + i])) g2m::add_affine(c, inf, G2_ABASE, S[slp::G2_CBASE + 1], S[slp::G2_CBASE]);
-  g2_store_aff(c, inf, Vout + k * K + i);
+  g2m::load(c, slp::G2_TB1_0);
+  if (t < 3) c.cl[t] = slp::call(slp::PROG_G2_ADD, 0, slp::G2_TB1_0 + 6 * (t + 1));
+  c.run_list(0, 3);
+  g2_add_affine(c, Vin + k * K + i);
+  g2_store_aff(c, Vout + k * K + i);
 }
 
 // The G1 terms b[v] A[a] of the next round (oa_terms.hpp, arrays of length 4q) with each
 // multiplication split in four parts: part p on the multiple M[3 (k 4q + a') + p - 1] =
 // 2^{32 p} A[k K + a'] (p > 0) with the p-th 32-bit chunk of the GLV split of b[v], into
-// J[4 term + p]; the last part to finish writes the sum to S1[out] (Jacobian)
+// J[4 term + p]; the last part to finish writes the sum to S1[out] (homogeneous)
 __global__ void __launch_bounds__(SLP_T, 4) ks_oa_g1terms_split(const g1_aff *A, const fe *B, const g1_aff *M, uint64_t K,
                                                             uint64_t nb, uint64_t q, g1_jac *J, uint32_t *cnt, g1_jac *S1) {
   AHEAD_PRIORITY();
-  __shared__ f29 S[G1_SLOTS];
+  __shared__ f29 S[slp::G1_NSLOT];
   CALL_LIST();
   Ctx c{S, calls_sh};
   __shared__ glv::Dec d1;
   __shared__ uint32_t flag;
   uint64_t id = blockIdx.x;
   if (id >= 4 * nb * 8 * q) return;
-  const int t = threadIdx.x;
   uint64_t term = id >> 2, k = term / (8 * q);
   int part = (int)(id & 3);
   oat::Term tm = oat::term(term, K, nb, q);
-  g1_job(c, &d1, part ? M + 3 * (k * 4 * q + (tm.a - k * K)) + part - 1 : A + tm.a, B + tm.v, nullptr, nullptr,
-         J + 4 * term + part, part);
+  g1_job(c, &d1, part ? M + 3 * (k * 4 * q + (tm.a - k * K)) + part - 1 : A + tm.a, B + tm.v, nullptr, part);
+  g1_store_hom(c, J + 4 * term + part);
   if (!last_arrival(cnt + term, 4, &flag)) return;
-  const fe *pj = reinterpret_cast<const fe *>(J + 4 * term);
-  if (t < 12) S[slp::G1_TB1_0 + t] = slp::to29(pj[t]);
-  __syncthreads();
-  bool inf = true;
-  for (int p = 0; p < 4; p++) g1m::add_jac(c, inf, slp::G1_TB1_0 + 3 * p, fe_is_zero(J[4 * term + p].Z));
-  fe *o = reinterpret_cast<fe *>(S1 + tm.out);
-  if (t < 3) o[t] = inf ? (t < 2 ? f_one<FpP>() : fe_zero()) : slp::from29(slp::canon29(S[slp::G1_T_0 + t]));
+  g1_sum_parts(c, J + 4 * term, nullptr);
+  g1_store_hom(c, S1 + tm.out);
 }
-
 
 // The x-dependent part of a round taken ahead, each multiplication split in four parts run
 // in parallel: for s < 4 nb and part p < 4, k_s = (s odd ? k_odd : k_even)[(s >> 2) kstride];
 // blocks [0, 16 nb): PE[4 s + p] = (PX[s]^{2^{16 p}})^{chunk_p}, the Frobenius split of k_s
 // restricted to bits [16 p, 16 p + 16) (17 bits for p = 3); blocks [16 nb, 32 nb):
-// PM[4 s + p] = chunk_p(k_s) (2^{32 p} PX1[s]) (Jacobian).  Multiples come from
+// PM[4 s + p] = chunk_p(k_s) (2^{32 p} PX1[s]) (homogeneous).  Multiples come from
 // ks_gt_sqr_mults and ks_g1_dbl_mults (PXm, PX1m).
 __global__ void __launch_bounds__(SLP_T, 4) ks_oa_combine_split(const fp12 *PX, const fp12 *PXm, const g1_aff *PX1,
                                                             const g1_aff *PX1m, const fe *k_even, const fe *k_odd,
                                                             uint64_t kstride, uint64_t nb, fp12 *PE, g1_jac *PM) {
   CHAIN_PRIORITY();
-  __shared__ f29 S[imax<GTP_SLOTS, G1_SLOTS>::v];
+  __shared__ f29 S[imax<GTP_SLOTS, slp::G1_NSLOT>::v];
   CALL_LIST();
   Ctx c{S, calls_sh};
   __shared__ gls::Dec dec;
@@ -695,7 +723,8 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_oa_combine_split(const fp12 *PX, 
   int part = (int)(id & 3);
   const fe *k = (s & 1 ? k_odd : k_even) + (s >> 2) * kstride;
   if (g1) {
-    g1_job(c, &d1, part ? PX1m + 3 * s + part - 1 : PX1 + s, k, nullptr, nullptr, PM + 4 * s + part, part);
+    g1_job(c, &d1, part ? PX1m + 3 * s + part - 1 : PX1 + s, k, nullptr, part);
+    g1_store_hom(c, PM + 4 * s + part);
     return;
   }
   if (t == 0) {
@@ -713,38 +742,41 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_oa_combine_split(const fp12 *PX, 
 
 // Both parts of L_j, R_j from the combine, in one launch.  Blocks [0, 2 nb):
 // (side ? R : L)[k lK] = U[2k + side] prod_{g in {2 side, 2 side + 1}, p < 4} P[4 (4k + g) + p]
-// (G_T, engine); blocks [2 nb, 4 nb): the G1 parts U1[2k + side] + sum of the 8 Jacobian
-// parts P1[4 (4k + 2 side) + i] (a tree over 8 lanes), affine, into L1 / R1.
+// (G_T); blocks [2 nb, 4 nb): the G1 parts U1[2k + side] + sum of the 8 homogeneous parts
+// P1[4 (4k + 2 side) + i], affine, into L1 / R1.  (The G1 side as Jacobian sums on single lanes
+// with a per-lane inversion held the launch at 0.19 ms.)
 __global__ void __launch_bounds__(SLP_T, 4) ks_oa_combine8(const fp12 *U, const fp12 *P, const g1_aff *U1, const g1_jac *P1,
                                                        uint64_t nb, fp12 *L, fp12 *R, g1_aff *L1, g1_aff *R1, uint64_t lK) {
   CHAIN_PRIORITY();
-  __shared__ f29 S[slp::F12_NSLOT + 12 * 11];
+  __shared__ f29 S[imax<slp::F12_NSLOT + 12 * 11, slp::G1_NSLOT>::v];
   CALL_LIST();
-  CtxInline c{S, calls_sh};
+  Ctx c{S, calls_sh};
   uint64_t id = blockIdx.x;
   if (id >= 4 * nb) return;
-  if (id >= 2 * nb) {
-    id -= 2 * nb;
-    g1_jac *part = reinterpret_cast<g1_jac *>(S);  // 8 Jacobian points in the slot memory
-    uint64_t k = id / 2, side = id % 2;
-    const int t = threadIdx.x;
-    if (t < 8) part[t] = P1[4 * (4 * k + 2 * side) + t];
+  const int t = threadIdx.x;
+  const bool g1 = id >= 2 * nb;
+  if (g1) id -= 2 * nb;
+  const uint64_t k = id / 2, side = id % 2;
+  if (g1) {
+    // the 8 parts in table slots, U1 in xP, yP
+    const fe *p = reinterpret_cast<const fe *>(P1 + 4 * (4 * k + 2 * side));
+    if (t < 24) S[slp::G1_TB1_0 + t] = slp::to29(p[t]);
+    const bool has_u = !g1_inf(U1[id]);
+    if (has_u && t >= 64 && t < 66) S[slp::G1_xP + t - 64] = slp::to29(t == 65 ? U1[id].y : U1[id].x);
+    load_consts<slp::G1_NCONST>(S, slp::G1_CBASE, slp::G1_CONSTS);
     __syncthreads();
-    for (int w = 4; w >= 1; w >>= 1) {
-      if (t < w) part[t] = jac_add(part[t], part[t + w]);
-      __syncthreads();
-    }
-    if (t == 0) (side ? R1 : L1)[k * lK] = jac_to_aff(jac_madd(part[0], U1[id]));
+    g1m::load(c, slp::G1_TB1_0);
+    if (t < 8) c.cl[t] = t < 7 ? slp::call(slp::PROG_G1_ADD, 0, slp::G1_TB1_0 + 3 * (t + 1)) : slp::call(slp::PROG_G1_MADD);
+    c.run_list(0, has_u ? 8 : 7);
+    g1_store_aff(c, (side ? R1 : L1) + k * lK);
     return;
   }
-  uint64_t k = id / 2, side = id % 2;
-  const int t = threadIdx.x;
   // buffers 0 and 1 the product (alternating, U first), 2..9 the powers
   const fe *u = reinterpret_cast<const fe *>(U + id), *pp = reinterpret_cast<const fe *>(P + 4 * (4 * k + 2 * side));
   for (int i = t; i < 12 * 9; i += SLP_T) S[i < 12 ? F12_BUF(0) + i : F12_BUF(1) + i] = slp::to29(i < 12 ? u[i] : pp[i - 12]);
   load_consts<slp::F12_NCONST>(S, slp::F12_CBASE, slp::F12_CONSTS);
   if (t < 8) c.cl[t] = slp::call(slp::PROG_F12_MUL, F12_BUF(t & 1), F12_BUF(2 + t), F12_BUF(1 - (t & 1)));
-  c.run_list(0, 8, 0, 0);
+  c.run_list(0, 8);
   fe *dst = reinterpret_cast<fe *>((side ? R : L) + k * lK);
   if (t < 12) dst[t] = slp::from29(slp::canon29(S[F12_BUF(0) + t]));
 }
@@ -766,19 +798,19 @@ __global__ void __launch_bounds__(FE_T, 4) ks_final_exp2(const fp12 *in0, uint64
 __global__ void __launch_bounds__(SLP_T, 4) ks_g1_finish(const g1_jac *PS, uint64_t nb, uint64_t q, g1_aff *PU1, g1_aff *PX1,
                                                      g1_aff *PX1m) {
   AHEAD_PRIORITY();
-  __shared__ f29 S[G1_SLOTS];
+  __shared__ f29 S[G1_DBL_SLOTS];
   CALL_LIST();
   Ctx c{S, calls_sh};
   uint64_t id = blockIdx.x;
   if (id >= 18 * nb) return;
   if (id < 2 * nb) {
-    g1_jac_mult_aff(c, PS + id * 2 * q, 0, PU1 + id);
+    g1_hom_mult_aff(c, PS + id * 2 * q, 0, PU1 + id);
     return;
   }
   id -= 2 * nb;
   uint64_t s = id >> 2;
   int m = (int)(id & 3);
-  g1_jac_mult_aff(c, PS + nb * 4 * q + s * q, m, m ? PX1m + 3 * s + m - 1 : PX1 + s);
+  g1_hom_mult_aff(c, PS + nb * 4 * q + s * q, m, m ? PX1m + 3 * s + m - 1 : PX1 + s);
 }
 
 namespace ks {
@@ -847,10 +879,18 @@ void final_exp2(const fp12 *in0, uint64_t st0, uint64_t n0, fp12 *out0, const fp
   if (n0 + n1) LAUNCH(ks_final_exp2, dim3((unsigned)(n0 + n1)), dim3(FE_T), 0, in0, st0, n0, out0, in1, st1, n1, out1);
 }
 void g1_tree(g1_jac *data, uint64_t nseg, uint64_t stride, uint64_t len, uint32_t *cnt, hipStream_t st) {
-  if (len > 1) LAUNCH(ks_jac_tree<false>, dim3((unsigned)(nseg * ((len + 1) / 2))), dim3(SLP_T), 0, data, nseg, stride, len, cnt);
+  if (len > 1) LAUNCH((ks_pt_tree<false, true>), dim3((unsigned)(nseg * ((len + 1) / 2))), dim3(SLP_T), 0, data, nseg, stride, len, cnt);
 }
-void g2_tree(g2_jac *data, uint64_t nseg, uint64_t stride, uint64_t len, uint32_t *cnt, hipStream_t st) {
-  if (len > 1) LAUNCH(ks_jac_tree<true>, dim3((unsigned)(nseg * ((len + 1) / 2))), dim3(SLP_T), 0, data, nseg, stride, len, cnt);
+void g2_tree(g2_jac *data, uint64_t nseg, uint64_t stride, uint64_t len, bool hom, uint32_t *cnt, hipStream_t st) {
+  const dim3 grid((unsigned)(nseg * ((len + 1) / 2)));
+  if (len > 1 && hom) LAUNCH((ks_pt_tree<true, true>), grid, dim3(SLP_T), 0, data, nseg, stride, len, cnt);
+  else if (len > 1) LAUNCH((ks_pt_tree<true, false>), grid, dim3(SLP_T), 0, data, nseg, stride, len, cnt);
+}
+void g1_hom_to_aff(const g1_jac *in, uint64_t stride, uint64_t n, g1_aff *out0, g1_aff *out1, uint64_t ostride, hipStream_t st) {
+  if (n) LAUNCH(ks_hom_to_aff<false>, dim3((unsigned)n), dim3(SLP_T), 0, in, stride, n, out0, out1, ostride);
+}
+void g2_hom_to_aff(const g2_jac *in, uint64_t stride, uint64_t n, g2_aff *out, uint64_t ostride, hipStream_t st) {
+  if (n) LAUNCH(ks_hom_to_aff<true>, dim3((unsigned)n), dim3(SLP_T), 0, in, stride, n, out, out + ostride, 2 * ostride);
 }
 void oa_g1terms(const g1_aff *A, const fe *B, uint64_t K, uint64_t nb, uint64_t h, g1_jac *S, hipStream_t st) {
   LAUNCH(ks_oa_g1terms, dim3((unsigned)(nb * 2 * h)), dim3(SLP_T), 0, A, B, K, nb, h, S);

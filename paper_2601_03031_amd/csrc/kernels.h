@@ -160,7 +160,10 @@ void oa_fold_g2(const g2_aff *Vin, g2_aff *Vout, const fe *Xinv, uint64_t K, uin
                 hipStream_t st);
 // sums of Jacobian segments on the engine, one launch (tree_counters(len) counters per segment)
 void g1_tree(g1_jac *data, uint64_t nseg, uint64_t stride, uint64_t len, uint32_t *cnt, hipStream_t st);
-void g2_tree(g2_jac *data, uint64_t nseg, uint64_t stride, uint64_t len, uint32_t *cnt, hipStream_t st);
+// (hom: homogeneous points of the engine, else Jacobian)
+void g2_tree(g2_jac *data, uint64_t nseg, uint64_t stride, uint64_t len, bool hom, uint32_t *cnt, hipStream_t st);
+void g1_hom_to_aff(const g1_jac *in, uint64_t stride, uint64_t n, g1_aff *out0, g1_aff *out1, uint64_t ostride, hipStream_t st);
+void g2_hom_to_aff(const g2_jac *in, uint64_t stride, uint64_t n, g2_aff *out, uint64_t ostride, hipStream_t st);
 // round-1 G1 terms on the engine (same layout as klw::oa_g1terms)
 void oa_g1terms(const g1_aff *A, const fe *B, uint64_t K, uint64_t nb, uint64_t h, g1_jac *S, hipStream_t st);
 void gt_pow(const fp12 *in, const fe *k, uint64_t n, fp12 *out, hipStream_t st);

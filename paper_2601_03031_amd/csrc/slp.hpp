@@ -98,22 +98,42 @@ __host__ __device__ __forceinline__ f29 norm29(const f29 &x) {
   return o;
 }
 
-// canonical residue of an almost-reduced value: x + 2p lies in (0.8 p, 3.2 p), so p is taken
-// off three times where it fits
+// x + y (limbs 0..7 in [0, 2^29) again), and -x limb by limb (limbs are signed)
+__host__ __device__ __forceinline__ f29 add29(const f29 &x, const f29 &y) {
+  f29 o;
+#pragma unroll
+  for (int j = 0; j < 12; j++) o.l[j] = x.l[j] + y.l[j];
+  return norm29(o);
+}
+__host__ __device__ __forceinline__ f29 neg29(const f29 &x) {
+  f29 o;
+#pragma unroll
+  for (int j = 0; j < 12; j++) o.l[j] = 0u - x.l[j];
+  return o;
+}
+
+// canonical residue of an almost-reduced value or a sum of up to four products (in (-2p, 5p)):
+// x + 2p lies in (0, 7p), and 4p, 2p and p are taken off where they fit
 __host__ __device__ __forceinline__ f29 canon29(const f29 &x) {
   f29 y = x;
 #pragma unroll
   for (int j = 0; j < 9; j++) y.l[j] += 2 * P29[j];
   y = norm29(y);
 #pragma unroll
-  for (int k = 0; k < 3; k++) {
+  for (int k = 2; k >= 0; k--) {
     f29 d = y;
 #pragma unroll
-    for (int j = 0; j < 9; j++) d.l[j] -= P29[j];
+    for (int j = 0; j < 9; j++) d.l[j] -= P29[j] << k;
     d = norm29(d);
     if ((int32_t)d.l[8] >= 0) y = d;
   }
   return y;
+}
+__host__ __device__ inline bool zero29(const f29 &x) {
+  const f29 c = canon29(x);
+  uint32_t t = 0;
+  for (int j = 0; j < 9; j++) t |= c.l[j];
+  return t == 0;
 }
 
 // keeps the instructions written before it ahead of those written after it
@@ -181,7 +201,7 @@ __host__ __device__ __forceinline__ uint32_t term_addr(uint32_t t, uint64_t rel)
 __host__ __device__ __forceinline__ int term_coef(uint32_t t) { return (int)(t << 7) >> 19; }
 
 // a block descriptor's fields (gen_slp.py OpTable)
-static constexpr uint32_t BLK_OFF = (1u << 18) - 1, BLK_CHK = 1u << 18, BLK_T2 = 1u << 19, BLK_T4 = 1u << 20, BLK_T6 = 1u << 21,
+static constexpr uint32_t BLK_OFF = (1u << 19) - 1, BLK_T2 = 1u << 19, BLK_T4 = 1u << 20, BLK_T6 = 1u << 21,
                           BLK_T10 = 1u << 22, BLK_SEG = 1u << 23, BLK_MUL = 1u << 30, BLK_LIN = 1u << 31;
 __host__ __device__ __forceinline__ int blk_ops(uint32_t d) { return (int)(d >> 24 & 63u); }
 __host__ __device__ __forceinline__ int blk_terms(uint32_t d) {
@@ -202,18 +222,8 @@ __host__ __device__ __forceinline__ Call call(int prog, int x = 0, int y = 0, in
   const ProgDesc &p = PROGS[prog];
   return Call{{p.d[0], p.d[1], p.d[2], p.d[3]}, seg_bases(x, y, d), 0};
 }
-__host__ __device__ __forceinline__ bool call_is(const Call &c, int prog) { return c.d[0] == PROGS[prog].d[0]; }
-__host__ __device__ __forceinline__ int call_y(const Call &c) { return (int)(c.rel >> 32 & 0xffffu) / 48; }
 
 static constexpr int MAX_CALLS = 128;
-
-// whether an almost-reduced value may be congruent to 0, from its two low limbs alone (it is
-// then -p, 0 or p; another value passes with probability below 2^-56)
-__host__ __device__ __forceinline__ bool maybe_zero29(uint32_t l0, uint32_t l1) {
-  const uint64_t m = (1ull << 58) - 1;
-  const uint64_t v = ((uint64_t)(int64_t)(int32_t)l0 + ((uint64_t)l1 << 29)) & m, pv = (P29[0] + ((uint64_t)P29[1] << 29)) & m;
-  return v == 0 || v == pv || v == ((0 - pv) & m);
-}
 
 #ifdef __HIPCC__
 typedef __attribute__((address_space(3))) f29 lds_f29;
@@ -314,34 +324,28 @@ __device__ __forceinline__ void run_block(uint32_t base, uint32_t d, const uint3
 }
 
 // Runs the calls cl[0 .. n), n > 0 (LDS), on the slots at LDS address `base` with all
-// wavefronts of the workgroup.  After a call of a checked program the slots chk .. chk + nchk
-// (nchk = 1 or 2, 0 for no checks) are looked at: if all may be zero the run stops there and
-// returns the number of calls it ran, negated; otherwise it returns n.
+// wavefronts of the workgroup.
 //
 // Records are fetched one level ahead, across calls too: a level's record names the next
 // level's block, the last one's is 0, and a call's entry (read from LDS a call ahead) names
 // the first.  The loop is written for the fewest scalar instructions, since one wavefront
 // issues about one instruction in four cycles whatever its kind.
-template <int NW> __device__ __forceinline__ int run_calls(uint32_t base, uint32_t list, int n, int chk, int nchk) {
+template <int NW> __device__ __forceinline__ void run_calls(uint32_t base, uint32_t list, int n) {
   static_assert(NW == 2 || NW == 4, "a call entry holds up to four descriptors");
   base = __builtin_amdgcn_readfirstlane(base);
   list = __builtin_amdgcn_readfirstlane(list);
   n = __builtin_amdgcn_readfirstlane(n);
-  chk = __builtin_amdgcn_readfirstlane(chk);
-  nchk = __builtin_amdgcn_readfirstlane(nchk);
   const uint32_t lane = threadIdx.x & 63, half = lane >> 1;
   const uint32_t wave4 = threadIdx.x >> 6 << 2;  // where this wavefront's descriptor is in an entry
   const uint32_t end = list + 32u * n;
   const uint64_t base4 = base * 0x0001000100010001ull;
-  const uint32_t chk_mask = nchk ? BLK_CHK : 0;
   uint32_t n_ent = list;  // entry after the next level's call
   uint32_t ahead_d = *(const lds_u32 *)(uintptr_t)(list + wave4);  // that entry
   u32x2 ahead_rel = *(const lds_u32x2 *)(uintptr_t)(list + 16);
-  uint32_t nd = 0, n_chk = 0;  // the next level: descriptor, whether its call is a checked addition,
-  uint64_t n_rel = 0;          // segment bases
+  uint32_t nd = 0;     // the next level: descriptor,
+  uint64_t n_rel = 0;  // segment bases
   auto next_call = [&]() {
     nd = __builtin_amdgcn_readfirstlane(ahead_d);
-    n_chk = nd & chk_mask;
     n_rel = base4 + (__builtin_amdgcn_readfirstlane(ahead_rel[0]) | (uint64_t)__builtin_amdgcn_readfirstlane(ahead_rel[1]) << 32);
     n_ent += 32;
     if (n_ent < end) {
@@ -362,52 +366,29 @@ template <int NW> __device__ __forceinline__ int run_calls(uint32_t base, uint32
       }
     }
   };
-  int ret = 0;
   // one level from cw, the next fetched to nw; true at the end of the run
   auto step = [&](const u32x4 *cw, u32x4 *nw) -> bool {
     uint32_t w[LANE_TERMS_MAX + 2];
 #pragma unroll
     for (int i = 0; i < LANE_TERMS_MAX + 2; i++) w[i] = cw[i >> 2][i & 3];
-    const uint32_t d = nd, c = n_chk;
+    const uint32_t d = nd;
     const uint64_t rel = n_rel;
     nd = __builtin_amdgcn_readfirstlane(w[1]);
-    const bool tail = nd == 0;
-    if (tail && n_ent < end) next_call();
+    if (!nd && n_ent < end) next_call();
     if (nd) load(nw);
     if (half < (uint32_t)blk_ops(d)) run_block(base, d, w, rel);
     level_sync<NW>();
-    if (tail) {
-      if (c) {
-        bool z = true;
-        for (int i = 0; i < nchk; i++) {
-          const lds_u32 *p = (const lds_u32 *)(uintptr_t)(base + 48 * (chk + i));
-          z = z && maybe_zero29(p[0], p[1]);
-        }
-        if (__builtin_amdgcn_readfirstlane((int)z)) {
-          // calls run: the entries before n_ent, without the next level's
-          ret = -(int)((n_ent - list) / 32 - (nd ? 1 : 0));
-          return true;
-        }
-      }
-      if (!nd) {
-        ret = n;
-        return true;
-      }
-    }
-    return false;
+    return nd == 0;
   };
   u32x4 wa[4] = {}, wb[4] = {};
   next_call();
   load(wa);
   while (!step(wa, wb) && !step(wb, wa)) {}
-  return ret;
 }
 
 // the same as a function: called, it saves and restores some sixty vector registers a lane in
 // scratch memory
-template <int NW> __device__ __noinline__ int run_calls_fn(uint32_t base, uint32_t list, int n, int chk, int nchk) {
-  return run_calls<NW>(base, list, n, chk, nchk);
-}
+template <int NW> __device__ __noinline__ void run_calls_fn(uint32_t base, uint32_t list, int n) { run_calls<NW>(base, list, n); }
 
 // Device context for control code shared with the host model: the workgroup's slots and a list
 // of calls in LDS.  (cl: MAX_CALLS entries for lists and one more for single calls; a context in
@@ -421,27 +402,28 @@ template <int NW, bool INLINE = false> struct DevCtx {
   __device__ int lane() const { return threadIdx.x; }
   __device__ int lanes() const { return 64 * NW; }
   __device__ void sync() { __syncthreads(); }
-  // calls cl[first .. n); returns as run_calls, counted from the list's start
-  __device__ int run_list(int first, int n, int chk, int nchk) {
+  // calls cl[first .. n)
+  __device__ void run_list(int first, int n) {
     __syncthreads();
-    if (first >= n) return n;
+    if (first >= n) return;
     const uint32_t base = (uint32_t)(uintptr_t)(lds_f29 *)S, list = (uint32_t)(uintptr_t)((lds_call *)cl + first);
-    const int r = INLINE ? run_calls<NW>(base, list, n - first, chk, nchk) : run_calls_fn<NW>(base, list, n - first, chk, nchk);
-    return r < 0 ? r - first : n;
+    if (INLINE) run_calls<NW>(base, list, n - first);
+    else run_calls_fn<NW>(base, list, n - first);
   }
-  // slot dst = the inverse of slot src (0 for 0), by the binary GCD on the scalar unit: the value
-  // is the same in all lanes
-  __device__ void invert(int dst, int src) {
-    __syncthreads();
-    const fe r = f_inv_uniform<FpP>(from29(canon29(S[src])), bn::P_R3);
+  // slot dst = the inverse of v (the same in all lanes; 0 for 0), by the binary GCD on the scalar
+  // unit; false if v is 0
+  __device__ bool invert(int dst, const f29 &v) {
+    const fe r = f_inv_uniform<FpP>(from29(canon29(v)), bn::P_R3);
     if (threadIdx.x == 0) S[dst] = to29(r);
     __syncthreads();
+    return !fe_is_zero(r);
   }
   __device__ void run(int prog, int bx, int by, int bd) {
     // (the list's extra entry; a context in line has no other)
     const int e = INLINE ? 0 : MAX_CALLS;
+    __syncthreads();
     if (threadIdx.x == 0) cl[e] = call(prog, bx, by, bd);
-    run_list(e, e + 1, 0, 0);
+    run_list(e, e + 1);
   }
 };
 #endif
@@ -491,16 +473,8 @@ struct HostCtx {
   void sync() {}
   int lane() const { return l; }
   int lanes() const { return 1; }
-  int run_list(int first, int n, int chk, int nchk) {
-    for (int e = first; e < n; e++) {
-      run_host(S, cl[e]);
-      if (nchk && (cl[e].d[0] & BLK_CHK)) {
-        bool z = true;
-        for (int i = 0; i < nchk; i++) z = z && maybe_zero29(S[chk + i].l[0], S[chk + i].l[1]);
-        if (z) return -(e + 1);
-      }
-    }
-    return n;
+  void run_list(int first, int n) {
+    for (int e = first; e < n; e++) run_host(S, cl[e]);
   }
 };
 

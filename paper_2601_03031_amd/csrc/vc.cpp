@@ -1342,7 +1342,8 @@ static int open_all_group(const vc_params *cpp, const vc_commitment *const *cms,
         klw::oa_g1terms(Ab[cur], Bb[cur], K, nb, h, S, sg);
         klw::g1_reduce(S, 2 * nb, K / 2, h, sg);
       }
-      kl::oa_lr_aff(S, K, nb, j, lK, Lg1, Rg1, sg);
+      if (ahead) ks::g1_hom_to_aff(S, K / 2, 2 * nb, Lg1 + (j - 1), Rg1 + (j - 1), lK, sg);
+      else kl::oa_lr_aff(S, K, nb, j, lK, Lg1, Rg1, sg);
       if (int rc2 = ev_mark(ex, 3, sg)) return rc2;
       // round 1 pairs the same A = aux with the same v in every batch of a job: its G_T
       // parts are computed once per job (from the aux rows; the first G rows of V all hold v)
@@ -1443,8 +1444,9 @@ static int open_all_group(const vc_params *cpp, const vc_commitment *const *cms,
     kl::fr_canon(Q, nb * nq, Qc, st);
     kl::msm_slices_g2(Qc, nb, nq, NWIN, kzg_s, pp->htab, S2, st);
   }
-  ks::g2_tree(S2, nb, kzg_len, kzg_len, cnt_kzg, st);
-  kl::g2_to_aff(S2, kzg_len, nb, piv, 1, st);
+  ks::g2_tree(S2, nb, kzg_len, kzg_len, kzg_split, cnt_kzg, st);
+  if (kzg_split) ks::g2_hom_to_aff(S2, kzg_len, nb, piv, 1, st);
+  else kl::g2_to_aff(S2, kzg_len, nb, piv, 1, st);
   // each job's rows of the Step 1 outputs into its bundle
   for (uint32_t x = 0; grp && x < G; x++) {
     void *bx = bundle(x);
