@@ -265,20 +265,15 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_kzg_terms_split(const g2_aff *h, 
 }
 
 // ---------------------------------------------------------------- G_T exponentiation
-// out[s] = in[s]^k_s (k in Montgomery F_r form), square-and-multiply with the engine's
+// out = in^k (k in Montgomery F_r form; kc: 8 words of LDS), square-and-multiply with the engine's
 // F_p12 product (inputs need not lie in the cyclotomic subgroup)
-__global__ void __launch_bounds__(SLP_T, 4) ks_gt_pow(const fp12 *in, const fe *k_mont, uint64_t n, fp12 *out) {
-  __shared__ f29 S[slp::F12_NSLOT + 36];
-  CALL_LIST();
-  CtxInline c{S, calls_sh};
-  __shared__ uint32_t kc[8];
-  uint64_t s = blockIdx.x;
-  if (s >= n) return;
+__device__ void gt_pow_job(Ctx c, const fp12 *in, const fe *k_mont, uint32_t *kc, fp12 *out) {
+  f29 *S = c.S;
   const int t = threadIdx.x;
-  const fe *src = reinterpret_cast<const fe *>(in + s);
+  const fe *src = reinterpret_cast<const fe *>(in);
   if (t < 12) S[F12_BUF(0) + t] = slp::to29(src[t]);
   if (t == 0) {
-    fe kcan = f_from_mont<FpR>(k_mont[s]);
+    fe kcan = f_from_mont<FpR>(*k_mont);
     for (int w = 0; w < 8; w++) kc[w] = kcan.l[w];
   }
   load_consts<slp::F12_NCONST>(S, slp::F12_CBASE, slp::F12_CONSTS);
@@ -286,7 +281,7 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_gt_pow(const fp12 *in, const fe *
   int top = -1;
   for (int b = 255; b >= 0; b--)
     if ((kc[b >> 5] >> (b & 31)) & 1) { top = b; break; }
-  fe *dst = reinterpret_cast<fe *>(out + s);
+  fe *dst = reinterpret_cast<fe *>(out);
   if (top < 0) {
     if (t < 12) dst[t] = t == 0 ? f_one<FpP>() : fe_zero();
     return;
@@ -340,6 +335,43 @@ __device__ void g1_job(Ctx c, glv::Dec *dec, const g1_aff *P, const fe *k_mont, 
   __syncthreads();
   g1m::mul(c, *dec, g1_inf(*P));
   if (A && !g1_inf(*A)) g1m::add_affine(c, slp::to29(A->x), slp::to29(A->y));
+}
+
+// out[i] = k_i P_i, affine, a workgroup per point
+__global__ void __launch_bounds__(SLP_T, 4) ks_g1_mul(const g1_aff *P, const fe *k, uint64_t n, g1_aff *out) {
+  __shared__ f29 S[slp::G1_NSLOT];
+  CALL_LIST();
+  __shared__ glv::Dec dec;
+  Ctx c{S, calls_sh};
+  const uint64_t i = blockIdx.x;
+  if (i >= n) return;
+  g1_job(c, &dec, P + i, k + i, nullptr);
+  g1_store_aff(c, out + i);
+}
+
+// The powers and multiples of a verification in one launch, a workgroup each: X[i]^{kx_i} of n3
+// elements of F_p12, k_i Q on G2 of n2 scalars (one base), k_i P_i on G1 of n1 points, the longest
+// first.  At 2^16 entries in batches of 256 (16, 1 and 276 of them) 1.0 ms, the time of a power;
+// one after another, the multiples with 8 lanes a field element, they took 1.0 + 3.2 + 1.5 ms.
+__global__ void __launch_bounds__(SLP_T, 4) ks_mults(const fp12 *X, const fe *kx, uint64_t n3, fp12 *outx, const g2_aff *Q,
+                                                     const fe *kq, uint64_t n2, g2_aff *outq, const g1_aff *P, const fe *kp,
+                                                     uint64_t n1, g1_aff *outp) {
+  __shared__ f29 S[most(slp::G1_NSLOT, slp::G2_NSLOT, slp::F12_NSLOT + 36)];
+  CALL_LIST();
+  __shared__ glv::Dec d1;
+  __shared__ gls::Dec d2;
+  __shared__ uint32_t kc[8];
+  Ctx c{S, calls_sh};
+  uint64_t i = blockIdx.x;
+  if (i < n3) {
+    gt_pow_job(c, X + i, kx + i, kc, outx + i);
+  } else if ((i -= n3) < n2) {
+    g2_job(c, &d2, Q, kq + i, nullptr);
+    g2_store_aff(c, outq + i);
+  } else if ((i -= n2) < n1) {
+    g1_job(c, &d1, P + i, kp + i, nullptr);
+    g1_store_aff(c, outp + i);
+  }
 }
 
 // ---------------------------------------------------------------- group sums on the engine
@@ -901,7 +933,21 @@ void kzg_terms_split(const g2_aff *h, const g2_aff *hm, const fe *Qc, uint64_t K
 void g2_dbl_mults(const g2_aff *Q, uint64_t seg, uint64_t segstride, uint64_t n, g2_aff *M, hipStream_t st) {
   if (n) LAUNCH(ks_g2_dbl_mults, dim3((unsigned)(3 * n)), dim3(SLP_T), 0, Q, seg, segstride, n, M);
 }
-void gt_pow(const fp12 *in, const fe *k, uint64_t n, fp12 *out, hipStream_t st) {
-  if (n) LAUNCH(ks_gt_pow, dim3((unsigned)n), dim3(SLP_T), 0, in, k, n, out);
+// Multiplications up to which the engine takes them (a workgroup each, the shorter chain: G1 0.63
+// ms at 128 points and 1.4 ms at 2048; with 8 lanes a field element, eight to a workgroup, 1.7 and
+// 2.1 ms).  From 4096 on the chip is full either way (2.0 ms both) and the wide kernels do less work.
+static constexpr uint64_t MUL_MAX = 2048;
+void g1_mul(const g1_aff *P, const fe *k, uint64_t n, g1_aff *out, hipStream_t st) {
+  if (n > MUL_MAX) klw::g1_mul(P, 0, k, n, out, st);
+  else if (n) LAUNCH(ks_g1_mul, dim3((unsigned)n), dim3(SLP_T), 0, P, k, n, out);
+}
+void mults(const fp12 *X, const fe *kx, uint64_t n3, fp12 *outx, const g2_aff *Q, const fe *kq, uint64_t n2, g2_aff *outq,
+           const g1_aff *P, const fe *kp, uint64_t n1, g1_aff *outp, hipStream_t st) {
+  const bool wide1 = n1 > MUL_MAX, wide2 = n2 > MUL_MAX;
+  if (wide1) klw::g1_mul(P, 0, kp, n1, outp, st);
+  if (wide2) klw::g2_mul(Q, 1, kq, n2, outq, st);
+  const uint64_t m1 = wide1 ? 0 : n1, m2 = wide2 ? 0 : n2;
+  if (n3 + m2 + m1)
+    LAUNCH(ks_mults, dim3((unsigned)(n3 + m2 + m1)), dim3(SLP_T), 0, X, kx, n3, outx, Q, kq, m2, outq, P, kp, m1, outp);
 }
 }  // namespace ks

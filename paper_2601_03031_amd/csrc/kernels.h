@@ -166,7 +166,11 @@ void g1_hom_to_aff(const g1_jac *in, uint64_t stride, uint64_t n, g1_aff *out0, 
 void g2_hom_to_aff(const g2_jac *in, uint64_t stride, uint64_t n, g2_aff *out, uint64_t ostride, hipStream_t st);
 // round-1 G1 terms on the engine (same layout as klw::oa_g1terms)
 void oa_g1terms(const g1_aff *A, const fe *B, uint64_t K, uint64_t nb, uint64_t h, g1_jac *S, hipStream_t st);
-void gt_pow(const fp12 *in, const fe *k, uint64_t n, fp12 *out, hipStream_t st);
+// out[i] = k_i P_i
+void g1_mul(const g1_aff *P, const fe *k, uint64_t n, g1_aff *out, hipStream_t st);
+// powers outx[i] = X[i]^{kx_i} in F_p12 (n3), multiples outq[i] = kq_i Q (n2) and outp[i] = kp_i P[i] (n1)
+void mults(const fp12 *X, const fe *kx, uint64_t n3, fp12 *outx, const g2_aff *Q, const fe *kq, uint64_t n2, g2_aff *outq,
+           const g1_aff *P, const fe *kp, uint64_t n1, g1_aff *outp, hipStream_t st);
 // fused round kernels: G1 + G2 fold; Miller loops + G1 terms of the next round (oa_terms.hpp);
 // final exponentiations of two strided lists
 void oa_fold(const g1_aff *Ain, const fe *Bin, g1_aff *Aout, fe *Bout, const g2_aff *Vin, g2_aff *Vout, const fe *X,

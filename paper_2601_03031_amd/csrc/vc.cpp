@@ -1276,7 +1276,7 @@ static int open_all_group(const vc_params *cpp, const vc_commitment *const *cms,
     CK(hipMemcpyAsync(at<void>(ws, o_rle), eval_r, 32ull * pp->L, hipMemcpyHostToDevice, st));
     kl::ev_point(at<uint8_t>(ws, o_rle), pp->L, er, err, st);
     kl::ev_eq(er, lM, lK, K, eT, st);
-    klw::g1_mul(Cj, 0, eT, K, at<g1_aff>(ws, o_pK), st);
+    ks::g1_mul(Cj, eT, K, at<g1_aff>(ws, o_pK), st);
     kl::ev_sum(at<g1_aff>(ws, o_pK), K, at<g1_aff>(bm, pr->o_CF), st);
     kl::ev_r0(C, er, pp->L, at<g1_aff>(bm, pr->o_CF), eT, K, B, st);
   } else {
@@ -1295,7 +1295,7 @@ static int open_all_group(const vc_params *cpp, const vc_commitment *const *cms,
       uint64_t half = 1ull << (k - 1);
       kl::ev_pst_step(eg, half, er + (k - 1), eq + (half - 1), s1);
     }
-    klw::g1_mul(pp->ek, 0, eq, M - 1, at<g1_aff>(ws, o_pW), s1);
+    ks::g1_mul(pp->ek, eq, M - 1, at<g1_aff>(ws, o_pW), s1);
     kl::ev_finish(at<g1_aff>(ws, o_pW), lM, eg, at<g1_aff>(bm, pr->o_We), at<fe>(bm, pr->o_yv), s1);
     return VC_OK;
   };
@@ -2176,9 +2176,8 @@ static int verify_many(const vc_params *pp, const uint8_t *Cb, uint32_t b, uint3
   if (e == hipSuccess) {
     kv::decode(cs, n, tmax, lK, lM, st);
     kv::transcript(cs, n, st);
-    klw::g1_mul(at<g1_aff>(d, o_mb), 0, at<fe>(d, o_ms), (uint64_t)n * nmul, at<g1_aff>(d, o_mo), st);
-    klw::g2_mul(pp->g2gen, 1, at<fe>(d, o_fz), n, at<g2_aff>(d, o_fzg2), st);
-    ks::gt_pow(at<fp12>(d, o_gtb), at<fe>(d, o_gts), 2 * n * lK, at<fp12>(d, o_gtp), st);
+    ks::mults(at<fp12>(d, o_gtb), at<fe>(d, o_gts), 2 * n * lK, at<fp12>(d, o_gtp), pp->g2gen, at<fe>(d, o_fz), n,
+              at<g2_aff>(d, o_fzg2), at<g1_aff>(d, o_mb), at<fe>(d, o_ms), (uint64_t)n * nmul, at<g1_aff>(d, o_mo), st);
     kv::assemble(cs, n, st);
     ks::f12_reduce(at<fp12>(d, o_gto), n, 2 * lK + 1, 2 * lK + 1, ex->cnt, st);
     ks::miller(at<g1_aff>(d, o_pp), 1, at<g2_aff>(d, o_pq), 1, (uint64_t)n * npair, F, st);
@@ -2324,9 +2323,7 @@ VC_API int vc_verify_eval(const vc_params *pp, const uint8_t C[384], const uint8
     kve::decode(c, st);
     kl::ev_eq(c.r, lM, l, K, c.T, st);
     kve::transcript(c, st);
-    klw::g1_mul(c.mb, 0, c.ms, nmul, c.mo, st);
-    klw::g2_mul(pp->g2gen, 1, c.g2s, 1 + lM, c.g2o, st);
-    ks::gt_pow(c.gtb, c.gts, 2 * l, c.gtp, st);
+    ks::mults(c.gtb, c.gts, 2 * l, c.gtp, pp->g2gen, c.g2s, 1 + lM, c.g2o, c.mb, c.ms, nmul, c.mo, st);
     kve::assemble(c, st);
     ks::f12_reduce(c.gto, 1, 2 * l + 1, 2 * l + 1, ex->cnt, st);
     ks::miller(c.pp, 1, c.pq, 1, npair, F, st);
@@ -2565,7 +2562,7 @@ VC_API int vc_verify_all(const vc_params *pp, const uint8_t C[384], uint32_t b, 
   kva::proof(c, st);
   kva::sums(c, st);
   kva::terms(c, st);
-  klw::g1_mul(c.bases, 0, c.scal, T, c.prod, st);
+  ks::g1_mul(c.bases, c.scal, T, c.prod, st);
   kva::segsum(c, st);
   ks::miller(c.pp, 1, c.pq, 1, y.lM + 1, F, st);
   ks::f12_reduce(F, 1, y.lM + 1, y.lM + 1, ex->cnt, st);

@@ -1,0 +1,39 @@
+"""Sizes on both sides of the lines where the dispatch goes from one kernel to another."""
+import random
+
+import numpy as np
+import pytest
+
+from paper_2601_03031_amd import inputs as I
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def vc():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2601_03031_amd as V
+    V.lib()
+    return V
+
+
+@pytest.mark.parametrize("L,b", [(14, 2), (14, 1)])
+def test_verify_products(vc, L, b):
+    """One check of every batch: 64 (20 products each, 1280) and 128 batches (19 each, 2432), the
+    multiplications on the engine and in the wide kernel.  The proofs verify; a byte changed in a
+    round's point of one batch (an invalid encoding or another point) does not."""
+    print("verify_all L=%d b=%d" % (L, b), flush=True)
+    limbs = I.entries(1 << L, 77 + b, 256)
+    m = torch.from_numpy(np.ascontiguousarray(limbs).view(np.uint8).reshape(-1).copy()).cuda()
+    pp = vc.vc_setup(L, I.TRAPDOOR_SEED, 0)
+    cm = vc.vc_commit(pp, m, 256)
+    pr = vc.vc_open_all(pp, cm, b)
+    proofs = vc.vc_proofs_serialize(pr)
+    le = m.reshape(-1)
+    seed = bytes(random.Random(5).randrange(256) for _ in range(32))
+    assert vc.vc_verify_all(pp, cm.C, b, le, proofs, seed)[0] == 1
+    bad = proofs.clone()
+    bad[32 * b + 384 + 20] ^= 1  # L_g1 of round 1 of the first batch
+    assert vc.vc_verify_all(pp, cm.C, b, le, bad, seed)[0] == 0
