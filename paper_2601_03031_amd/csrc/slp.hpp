@@ -410,7 +410,7 @@ template <int NW, bool INLINE = false> struct DevCtx {
     if (INLINE) run_calls<NW>(base, list, n - first);
     else run_calls_fn<NW>(base, list, n - first);
   }
-  // slot dst = the inverse of v (the same in all lanes; 0 for 0), by the binary GCD on the scalar
+  // slot dst = the inverse of v (the same in all lanes; 0 for 0), by division steps on the scalar
   // unit; false if v is 0
   __device__ bool invert(int dst, const f29 &v) {
     const fe r = f_inv_uniform<FpP>(from29(canon29(v)), bn::P_R3);

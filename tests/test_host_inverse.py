@@ -1,0 +1,31 @@
+"""The modular inverse by batched division steps on the host build, against Python's."""
+import ctypes as C
+import os
+import random
+
+import pytest
+
+import oracle as O
+
+HC_PATH = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2601_03031_amd", "lib",
+                       "libvc_hostcheck.so")
+P, R = O.P, O.R
+
+
+@pytest.mark.parametrize("which,mod", [(0, P), (1, R)])
+def test_inverse(which, mod):
+    """Small and large values, powers of two (runs of zero bits longer than a batch), values next to
+    multiples of them, and the zero that maps to zero."""
+    if not os.path.exists(HC_PATH):
+        from paper_2601_03031_amd import build as B
+        B.build_hostcheck()
+    hc = C.CDLL(HC_PATH)
+    rng = random.Random(900 + which)
+    vals = [0, 1, 2, 3, 62, 63, mod - 1, mod - 2, mod // 2, mod // 2 + 1, mod // 3]
+    vals += [1 << s for s in (29, 30, 31, 60, 64, 90, 128, 240, 253)]
+    vals += [(1 << s) + d for s in (30, 60, 120, 250) for d in (-1, 1)]
+    vals += [rng.randrange(mod) for _ in range(300)] + [rng.randrange(1 << 40) for _ in range(40)]
+    for x in vals:
+        o = C.create_string_buffer(32)
+        hc.hc_field(which, 4, O.be32(x), O.be32(x), o)
+        assert int.from_bytes(o.raw, "big") == (pow(x, -1, mod) if x else 0), x
