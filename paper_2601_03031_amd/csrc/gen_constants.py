@@ -63,7 +63,7 @@ w("static constexpr uint32_t R_INV29 = 0x%08xu;" % ((-pow(R, -1, 1 << 29)) % (1 
 w(arr("P_ONE", mont(1)))
 w(arr("P_R2", RM * RM % P))
 w(arr("P_MINUS_2", P - 2))
-w(arr("P_SQRT_EXP", (P + 1) // 4))
+w(arr("P_SQRT_EXP", (P - 3) // 4))
 w(arr("P_HALF", (P - 1) // 2))
 w(arr("R_MOD", R))
 w("static constexpr uint32_t R_INV = 0x%08xu;  // -r^{-1} mod 2^32" % ((-pow(R, -1, 1 << 32)) % (1 << 32)))

@@ -238,6 +238,15 @@ template <class F> DEV bool inverse(const fe &x, fe &out, int *rounds = nullptr)
 
 }  // namespace bingcd
 
+// x^e (canonical, big-endian) by the windowed power on loose limbs
+API int hc_pow_fixed(int which, const uint8_t *x, const uint8_t *e, uint8_t *out) {
+  uint32_t w[8];
+  canon_scalar(w, e);
+  if (which == 0) wr<FpP>(out, f_pow_fixed<FpP>(rd<FpP>(x), w));
+  else wr<FpR>(out, f_pow_fixed<FpR>(rd<FpR>(x), w));
+  return 0;
+}
+
 // batched binary GCD on a canonical integer 0 < x < m (which 0: p, 1: r): x^{-1} mod m
 // (big-endian 32 bytes) and the number of outer rounds; returns 1 if it converged
 API int hc_bingcd(int which, const uint8_t *x, uint8_t *out, int *rounds) {

@@ -27,150 +27,135 @@ __device__ bool lt_words(const fe &a, const uint32_t *m) {
 // canonical y > (p - 1)/2
 __device__ bool larger(const fe &ymont) { return !lt_words(f_from_mont<FpP>(ymont), bn::P_HALF) && !fe_eq(f_from_mont<FpP>(ymont), fe_const(bn::P_HALF)); }
 
-// square root in F_p (p = 3 mod 4): a^((p+1)/4), verified by squaring
-__device__ bool fp_sqrt(const fe &a, fe &r) {
-  r = f_pow<FpP>(a, bn::P_SQRT_EXP);
-  return fe_eq(fp_sqr(r), a);
-}
+// a^((p - 3) / 4): times a, a square root of a or (p = 3 mod 4, -1 no square) of -a
+__device__ __attribute__((noinline)) fe pow_sqrt(const fe &a) { return f_pow_fixed<FpP>(a, bn::P_SQRT_EXP); }
 
-// square root in F_p2 through the norm: with n = a0^2 + a1^2 and s = sqrt(n),
-// x0 = sqrt((a0 +- s)/2), x1 = a1 / (2 x0); verified by squaring
-__device__ bool fp2_sqrt(const fp2 &a, fp2 &r) {
-  if (fe_is_zero(a.c1)) {
-    fe s;
-    if (fp_sqrt(a.c0, s)) { r = {s, fe_zero()}; return true; }
-    if (fp_sqrt(fp_neg(a.c0), s)) { r = {fe_zero(), s}; return true; }
-    return false;
-  }
-  fe n = fp_add(fp_sqr(a.c0), fp_sqr(a.c1)), s;
-  if (!fp_sqrt(n, s)) return false;
-  fe t = fp_half(fp_add(a.c0, s)), x0;
-  if (!fp_sqrt(t, x0)) {
-    t = fp_half(fp_sub(a.c0, s));
-    if (!fp_sqrt(t, x0)) return false;
-  }
-  fe x1 = fp_mul(a.c1, fp_inv_fast(fp_dbl(x0)));
-  r = {x0, x1};
-  fp2 chk = f2_sqr(r);
-  return fe_eq(chk.c0, a.c0) && fe_eq(chk.c1, a.c1);
-}
-
-// compressed G1 (32 bytes): x, flag 0x80 identity, 0x40 y > (p - 1)/2
-__device__ bool g1_decompress(const uint8_t *b, g1_aff &o) {
-  uint8_t buf[32];
-  for (int i = 0; i < 32; i++) buf[i] = b[i];
-  bool inf = buf[0] & 0x80, big = buf[0] & 0x40;
-  buf[0] &= 0x3f;
-  o = {fe_zero(), fe_zero()};
+// A compressed point: of G1 (32 bytes: x, flag 0x80 identity, 0x40 y > (p - 1)/2) into *o1, or of G2
+// (64 bytes: x.c0 || x.c1, the sign that of y.c1, or of y.c0 when y.c1 = 0) into *o2.  One path for
+// both, as the lanes of a wavefront hold points of both kinds: the root of G1's x^3 + 3 and that of
+// the norm of G2's right side are the same call.  Bound by its two powers, chains of 312 products
+// each: the items of a proof of 276 points take 0.38 ms; with a branch for each kind of item and a
+// bit at a time, three powers and an inverse on G2, they took 2.4.
+//
+// On G2 with a = a0 + a1 i, s = sqrt(a0^2 + a1^2), t = (a0 + s) / 2 and w = t^((p-3)/4): x0 = w t has
+// x0^2 = +-t and 1 / x0 = +-w, so that with the upper sign x0 + (a1 / 2 x0) i is a root, and with the
+// lower sign, where (a0 - s) / 2 = -a1^2 / 4t is the square, a1 / 2 x0 + x0 i is.  The square is
+// checked at the end.
+__device__ bool decompress(const uint8_t *b, bool g2, g1_aff *o1, g2_aff *o2) {
+  const int len = g2 ? 64 : 32;
+  const bool inf = b[0] & 0x80, big = b[0] & 0x40;
+  if (g2) *o2 = {f2_zero(), f2_zero()};
+  else *o1 = {fe_zero(), fe_zero()};
   if (inf) {
-    bool z = !big;
-    for (int i = 0; i < 32; i++) z = z && buf[i] == 0;
-    return z;
+    uint32_t any = b[0] & 0x7f;
+    for (int i = 1; i < len; i++) any |= b[i];
+    return any == 0;
   }
-  fe x = rd_be(buf);
-  if (!lt_words(x, bn::P_MOD)) return false;
-  x = f_to_mont<FpP>(x);
-  fe rhs = fp_add(fp_mul(fp_sqr(x), x), f_mul_small<FpP>(f_one<FpP>(), 3));
-  fe y;
-  if (!fp_sqrt(rhs, y)) return false;
-  if (larger(y) != big) y = fp_neg(y);
-  o = {x, y};
-  return true;
-}
-
-// compressed G2 (64 bytes): x.c0 || x.c1, sign from y.c1, or y.c0 when y.c1 = 0
-__device__ bool g2_decompress(const uint8_t *b, g2_aff &o) {
-  uint8_t buf[64];
-  for (int i = 0; i < 64; i++) buf[i] = b[i];
-  bool inf = buf[0] & 0x80, big = buf[0] & 0x40;
-  buf[0] &= 0x3f;
-  o = {f2_zero(), f2_zero()};
-  if (inf) {
-    bool z = !big;
-    for (int i = 0; i < 64; i++) z = z && buf[i] == 0;
-    return z;
-  }
-  fe x0 = rd_be(buf), x1 = rd_be(buf + 32);
+  fe x0 = rd_be(b), x1 = fe_zero();
+  x0.l[7] &= 0x3fffffffu;
+  if (g2) x1 = rd_be(b + 32);
   if (!lt_words(x0, bn::P_MOD) || !lt_words(x1, bn::P_MOD)) return false;
-  fp2 x = {f_to_mont<FpP>(x0), f_to_mont<FpP>(x1)};
-  fp2 rhs = f2_add(f2_mul(f2_sqr(x), x), f2_const(bn::TWIST_B0, bn::TWIST_B1));
+  x0 = f_to_mont<FpP>(x0);
+  fp2 rhs = {fe_zero(), fe_zero()};
+  fe a;
+  if (g2) {
+    x1 = f_to_mont<FpP>(x1);
+    const fp2 x = {x0, x1};
+    rhs = f2_add(f2_mul(f2_sqr(x), x), f2_const(bn::TWIST_B0, bn::TWIST_B1));
+    a = fe_is_zero(rhs.c1) ? rhs.c0 : fp_add(fp_sqr(rhs.c0), fp_sqr(rhs.c1));
+  } else {
+    a = fp_add(fp_mul(fp_sqr(x0), x0), f_mul_small<FpP>(f_one<FpP>(), 3));
+  }
+  const fe s = fp_mul(pow_sqrt(a), a);
+  const bool square = fe_eq(fp_sqr(s), a);
+  if (!g2) {
+    if (!square) return false;
+    *o1 = {x0, larger(s) != big ? fp_neg(s) : s};
+    return true;
+  }
   fp2 y;
-  if (!fp2_sqrt(rhs, y)) return false;
-  bool l = fe_is_zero(y.c1) ? larger(y.c0) : larger(y.c1);
-  if (l != big) y = f2_neg(y);
-  o = {x, y};
+  if (fe_is_zero(rhs.c1)) {
+    y = square ? fp2{s, fe_zero()} : fp2{fe_zero(), s};
+  } else {
+    if (!square) return false;
+    const fe t = fp_half(fp_add(rhs.c0, s)), w = pow_sqrt(t), r = fp_mul(w, t);
+    const bool plus = fe_eq(fp_sqr(r), t);
+    fe h = fp_mul(fp_half(rhs.c1), w);
+    if (!plus) h = fp_neg(h);
+    y = plus ? fp2{r, h} : fp2{h, r};
+  }
+  const fp2 chk = f2_sqr(y);
+  if (!fe_eq(chk.c0, rhs.c0) || !fe_eq(chk.c1, rhs.c1)) return false;
+  const bool l = fe_is_zero(y.c1) ? larger(y.c0) : larger(y.c1);
+  *o2 = {{x0, x1}, l != big ? f2_neg(y) : y};
   return true;
 }
 
-__device__ bool gt_decode(const uint8_t *b, fp12 &f) {
-  fe *w = reinterpret_cast<fe *>(&f);
+// One item of a serialized proof and where it goes.  A lane first finds its item and then decodes
+// it, so that lanes with items of different origin decode together; an F_p12 element is 12 items.
+enum { IT_ZERO1, IT_ZERO, IT_G1, IT_G2, IT_FP, IT_FR, IT_FR_LE };  // IT_ZERO1, IT_ZERO: zeros for a point of G1, a scalar
+struct Item {
+  int kind, bad;  // bad: the flag raised when the bytes are none
+  const uint8_t *src;
+  void *dst;
+};
+__device__ Item item(int kind, const uint8_t *src, void *dst, int bad = VFLAG_BAD_PROOF) { return {kind, bad, src, dst}; }
+// coefficient k of an F_p12 element
+__device__ Item item_gt(const uint8_t *src, fp12 *dst, uint32_t k, int bad = VFLAG_BAD_PROOF) {
+  return {IT_FP, bad, src + 32 * k, reinterpret_cast<fe *>(dst) + k};
+}
+__device__ void decode_item(const Item &it, int *flags) {
   bool ok = true;
-  for (int k = 0; k < 12; k++) {
-    fe c = rd_be(b + 32 * k);
-    ok = ok && lt_words(c, bn::P_MOD);
-    w[k] = f_to_mont<FpP>(c);
+  if (it.kind == IT_G1 || it.kind == IT_G2) {
+    ok = decompress(it.src, it.kind == IT_G2, (g1_aff *)it.dst, (g2_aff *)it.dst);
+  } else if (it.kind == IT_ZERO1) {
+    *(g1_aff *)it.dst = {fe_zero(), fe_zero()};
+  } else if (it.kind == IT_ZERO) {
+    *(fe *)it.dst = fe_zero();
+  } else if (it.kind == IT_FP) {
+    const fe v = rd_be(it.src);
+    ok = lt_words(v, bn::P_MOD);
+    *(fe *)it.dst = f_to_mont<FpP>(v);
+  } else {
+    fe v;
+    if (it.kind == IT_FR) v = rd_be(it.src);
+    else
+      for (int i = 0; i < 8; i++)
+        v.l[i] = (uint32_t)it.src[4 * i] | (uint32_t)it.src[4 * i + 1] << 8 | (uint32_t)it.src[4 * i + 2] << 16 |
+                 (uint32_t)it.src[4 * i + 3] << 24;
+    ok = lt_words(v, bn::R_MOD);
+    *(fe *)it.dst = f_to_mont<FpR>(v);
   }
-  return ok;
+  if (!ok) atomicOr(flags, it.bad);
 }
 
 }  // namespace
 
-// one thread per item of proof blockIdx.y (layout of the serialized proof, vc_proof_get)
+// one thread per item of proof blockIdx.y (layout of the serialized proof, vc_proof_get): the G2
+// points first (the longest), then the G1 points, then the field elements
+__device__ __host__ uint32_t kv_items(uint32_t t, uint32_t l, uint32_t lM) { return 2 + (t + 3 * l + 1 + lM) + (25 * l + 13); }
 __global__ void __launch_bounds__(TPB) kv_decode(const VCtx *cs) {
   const VCtx &c = cs[blockIdx.y];
   uint32_t id = (uint32_t)gtid();
   const uint32_t t = c.t, l = c.lK, lM = c.lM;
-  const uint32_t n_items = t + 4 * l + 3 + 2 * l + lM + 2;
-  if (id >= n_items) return;
-  const uint8_t *pf = c.proof;
-  bool ok = true;
-  if (id < t) {
-    ok = g1_decompress(pf + 32 * id, c.blk[id]);
-  } else if ((id -= t) < 4 * l) {
-    uint32_t r = id / 4, w = id % 4;
-    const uint8_t *q = pf + 32 * t + (uint64_t)r * (2 * 384 + 2 * 32);
-    if (w == 0) ok = gt_decode(q, c.Lgt[r]);
-    else if (w == 1) ok = g1_decompress(q + 384, c.Lg1[r]);
-    else if (w == 2) ok = gt_decode(q + 416, c.Rgt[r]);
-    else ok = g1_decompress(q + 800, c.Rg1[r]);
-  } else if ((id -= 4 * l) < 3) {
-    const uint8_t *q = pf + 32 * t + (uint64_t)l * (2 * 384 + 2 * 32);
-    if (id == 0) ok = g1_decompress(q, *c.Al);
-    else if (id == 1) ok = g2_decompress(q + 32, *c.vl);
-    else ok = g2_decompress(q + 96, *c.piv);
-  } else if (c.fc_only && (id -= 3) < 2 * l + lM + 2 && id != 2 * l + lM) {
-    // sub-array proof: no Step 2 items and no entry
-    if (id < 2 * l) {
-      if (id % 2 == 0) c.Dsib[id / 2] = g1_aff{fe_zero(), fe_zero()};
-      else c.ysib[id / 2] = fe_zero();
-    } else if (id < 2 * l + lM) {
-      c.Wp[id - 2 * l] = g1_aff{fe_zero(), fe_zero()};
-    } else {
-      *c.mi = fe_zero();
-    }
-  } else if (c.fc_only) {
-    if (!gt_decode(c.Cb, *c.C)) atomicOr(c.flags, VFLAG_BAD_INPUT);
-  } else if ((id -= 3) < 2 * l) {
-    const uint8_t *q = pf + 32 * t + (uint64_t)l * (2 * 384 + 2 * 32) + 160 + 64 * (id / 2);
-    if (id % 2 == 0) {
-      ok = g1_decompress(q, c.Dsib[id / 2]);
-    } else {
-      fe y = rd_be(q + 32);
-      ok = lt_words(y, bn::R_MOD);
-      c.ysib[id / 2] = f_to_mont<FpR>(y);
-    }
-  } else if ((id -= 2 * l) < lM) {
-    const uint8_t *q = pf + 32 * t + (uint64_t)l * (2 * 384 + 2 * 32) + 160 + 64 * l + 32 * id;
-    ok = g1_decompress(q, c.Wp[id]);
-  } else if ((id -= lM) == 0) {
-    if (!gt_decode(c.Cb, *c.C)) atomicOr(c.flags, VFLAG_BAD_INPUT);
-  } else {
-    fe m;
-    for (int i = 0; i < 32; i++) reinterpret_cast<uint8_t *>(m.l)[i] = c.mib[i];  // little-endian limbs
-    if (!lt_words(m, bn::R_MOD)) atomicOr(c.flags, VFLAG_BAD_INPUT);
-    *c.mi = f_to_mont<FpR>(m);
-  }
-  if (!ok) atomicOr(c.flags, VFLAG_BAD_PROOF);
+  if (id >= kv_items(t, l, lM)) return;
+  // block commitments, rounds, A_l v_l pi_v, D-tree siblings with their y, W
+  const uint8_t *rounds = c.proof + 32 * t, *tail = rounds + 832ull * l, *dy = tail + 160, *w = dy + 64ull * l;
+  Item it;
+  if (id < 2) it = item(IT_G2, tail + 32 + 64 * id, id ? c.piv : c.vl);
+  else if ((id -= 2) < t) it = item(IT_G1, c.proof + 32 * id, c.blk + id);
+  else if ((id -= t) < 2 * l) it = item(IT_G1, rounds + 832ull * (id / 2) + (id % 2 ? 800 : 384), (id % 2 ? c.Rg1 : c.Lg1) + id / 2);
+  else if ((id -= 2 * l) < 1) it = item(IT_G1, tail, c.Al);
+  // (a sub-array proof has no Step 2 items and no entry: zeros)
+  else if ((id -= 1) < l) it = item(c.fc_only ? IT_ZERO1 : IT_G1, dy + 64 * id, c.Dsib + id);
+  else if ((id -= l) < lM) it = item(c.fc_only ? IT_ZERO1 : IT_G1, w + 32 * id, c.Wp + id);
+  else if ((id -= lM) < 24 * l) {
+    const uint32_t r = id / 24, side = id / 12 % 2;
+    it = item_gt(rounds + 832ull * r + 416 * side, (side ? c.Rgt : c.Lgt) + r, id % 12);
+  } else if ((id -= 24 * l) < l) it = item(c.fc_only ? IT_ZERO : IT_FR, dy + 64 * id + 32, c.ysib + id);
+  else if ((id -= l) < 12) it = item_gt(c.Cb, c.C, id, VFLAG_BAD_INPUT);
+  else it = item(c.fc_only ? IT_ZERO : IT_FR_LE, c.mib, c.mi, VFLAG_BAD_INPUT);
+  decode_item(it, c.flags);
 }
 
 // Fiat-Shamir replay and scalar set-up, a workgroup per proof: chunk digests and the batching
@@ -410,8 +395,7 @@ __global__ void __launch_bounds__(TPB) kv_fe_gather(const fp12 *F, uint64_t npai
 namespace kv {
 void fe_gather(const fp12 *F, uint64_t npair, uint32_t n, fp12 *G, hipStream_t st) { L1(kv_fe_gather, 3ull * n, F, npair, n, G); }
 void decode(const VCtx *cs, uint32_t n, uint32_t tmax, uint32_t lK, uint32_t lM, hipStream_t st) {
-  uint32_t items = tmax + 4 * lK + 3 + 2 * lK + lM + 2;
-  LAUNCH(kv_decode, dim3(nblk(items), n), dim3(TPB), 0, cs);
+  LAUNCH(kv_decode, dim3(nblk(kv_items(tmax, lK, lM)), n), dim3(TPB), 0, cs);
 }
 void transcript(const VCtx *cs, uint32_t n, hipStream_t st) { LAUNCH(kv_transcript, dim3(n), dim3(256), 0, cs); }
 void assemble(const VCtx *cs, uint32_t n, hipStream_t st) { LAUNCH(kv_assemble, dim3(n), dim3(256), 0, cs); }
@@ -546,32 +530,33 @@ __global__ void __launch_bounds__(TPB) kps_serialize(PSCtx c) {
   }
 }
 
-// shared items, one thread each: K block commitments, 2K - 2 D-tree siblings, M - 1 W, C
+// shared items, one thread each: K block commitments, 2K - 2 D-tree siblings, M - 1 W, C (12
+// coefficients)
 __global__ void __launch_bounds__(TPB) kva_decode(VACtx c) {
   const PLayout &y = c.y;
   uint64_t id = gtid(), K = y.K;
   const uint64_t nD = 2 * K - 2, nW = y.M - 1;
-  if (id >= K + nD + nW + 1) return;
-  bool ok = true;
+  if (id >= K + nD + nW + 12) return;
+  Item it;
   if (id < K) {
-    uint64_t j = id, k = j / y.b;
-    ok = g1_decompress(c.proofs + pl_off(y, k * pl_bm(y)) + 32 * (j - k * y.b), c.Cj[j]);
+    const uint64_t k = id / y.b;
+    it = item(IT_G1, c.proofs + pl_off(y, k * pl_bm(y)) + 32 * (id - k * y.b), c.Cj + id);
   } else if ((id -= K) < nD) {
     uint32_t h;
     uint64_t s;
     d_node(id, K, h, s);
     uint64_t j = (s ^ 1) << h, i = j * y.M;
-    ok = g1_decompress(c.proofs + pl_off(y, i) + pl_step2(y, pl_batch(y, i)) + 64 * h, c.Dn[id]);
+    it = item(IT_G1, c.proofs + pl_off(y, i) + pl_step2(y, pl_batch(y, i)) + 64 * h, c.Dn + id);
   } else if ((id -= nD) < nW) {
     uint32_t d;
     uint64_t p;
     w_node(id, d, p);
     uint64_t i = p << (y.lM - d);
-    ok = g1_decompress(c.proofs + pl_off(y, i) + pl_step2(y, 0) + 64ull * y.lK + 32 * d, c.Wn[id]);
+    it = item(IT_G1, c.proofs + pl_off(y, i) + pl_step2(y, 0) + 64ull * y.lK + 32 * d, c.Wn + id);
   } else {
-    if (!gt_decode(c.Cb, *c.C)) atomicOr(c.flags, VFLAG_BAD_INPUT);
+    it = item_gt(c.Cb, c.C, (uint32_t)(id - nW), VFLAG_BAD_INPUT);
   }
-  if (!ok) atomicOr(c.flags, VFLAG_BAD_PROOF);
+  decode_item(it, c.flags);
 }
 
 // the root of every proof's Merkle path from its leaf (m_i, C_j), one thread per proof
@@ -808,7 +793,7 @@ uint64_t nterms(const VACtx &c) { return 3 * c.y.K + 2 * c.y.M - 3; }
 void serialize(const PSCtx &c, hipStream_t st) {
   L1(kps_serialize, c.y.N * (c.y.b + 6ull * c.y.lK + 3 + c.y.lM + c.y.L), c);
 }
-void decode(const VACtx &c, hipStream_t st) { L1(kva_decode, 3 * c.y.K + c.y.M - 2, c); }
+void decode(const VACtx &c, hipStream_t st) { L1(kva_decode, 3 * c.y.K + c.y.M + 9, c); }
 void roots(const VACtx &c, hipStream_t st) { L1(kva_roots, c.y.N, c); }
 void rho(const VACtx &c, hipStream_t st) { LAUNCH(kva_rho, dim3((unsigned)((c.y.K + 63) / 64)), dim3(64), 0, c); }
 void same(const VACtx &c, hipStream_t st) { LAUNCH(kva_same, dim3((unsigned)c.y.N), dim3(256), 0, c); }
@@ -825,43 +810,27 @@ void check(const VACtx &c, hipStream_t st) { LAUNCH(kva_check, dim3(1), dim3(64)
 //   e(C_F - y g1, g2) = prod_d e(W_d, (s_var - r_var) g2),  var = l_M - 1 - d.
 // The pairs and the final equalities are laid out as for one opening proof (kv_compare).
 
-// one thread per item: C_F, the rounds, A_l v_l pi_v, y, W, C and the point
+// one thread per item: v_l, pi_v, then C_F, the rounds' points, A_l and W, then the rounds' and C's
+// coefficients, y and the point
+__device__ __host__ uint32_t kve_items(uint32_t l, uint32_t lM, uint32_t L) { return 2 + (1 + 2 * l + 1 + lM) + (24 * l + 1 + 12 + L); }
 __global__ void __launch_bounds__(TPB) kve_decode(VECtx c) {
   uint32_t id = (uint32_t)gtid();
   const uint32_t l = c.lK, lM = c.lM;
-  if (id >= 1 + 4 * l + 3 + 1 + lM + 1 + c.L) return;
-  const uint8_t *pf = c.proof;
-  bool ok = true;
-  if (id == 0) {
-    ok = g1_decompress(pf, *c.CF);
-  } else if ((id -= 1) < 4 * l) {
-    uint32_t r = id / 4, w = id % 4;
-    const uint8_t *q = pf + 32 + (uint64_t)r * (2 * 384 + 2 * 32);
-    if (w == 0) ok = gt_decode(q, c.Lgt[r]);
-    else if (w == 1) ok = g1_decompress(q + 384, c.Lg1[r]);
-    else if (w == 2) ok = gt_decode(q + 416, c.Rgt[r]);
-    else ok = g1_decompress(q + 800, c.Rg1[r]);
-  } else if ((id -= 4 * l) < 3) {
-    const uint8_t *q = pf + 32 + (uint64_t)l * (2 * 384 + 2 * 32);
-    if (id == 0) ok = g1_decompress(q, *c.Al);
-    else if (id == 1) ok = g2_decompress(q + 32, *c.vl);
-    else ok = g2_decompress(q + 96, *c.piv);
-  } else if ((id -= 3) == 0) {
-    fe v = rd_be(pf + 32 + (uint64_t)l * (2 * 384 + 2 * 32) + 160);
-    ok = lt_words(v, bn::R_MOD);
-    *c.y = f_to_mont<FpR>(v);
-  } else if ((id -= 1) < lM) {
-    ok = g1_decompress(pf + 32 + (uint64_t)l * (2 * 384 + 2 * 32) + 192 + 32 * id, c.W[id]);
-  } else if ((id -= lM) == 0) {
-    if (!gt_decode(c.Cb, *c.C)) atomicOr(c.flags, VFLAG_BAD_INPUT);
-  } else {
-    uint32_t k = id - 1;
-    fe v;
-    for (int q = 0; q < 32; q++) reinterpret_cast<uint8_t *>(v.l)[q] = c.rle[32 * k + q];  // little-endian limbs
-    if (!lt_words(v, bn::R_MOD)) atomicOr(c.flags, VFLAG_BAD_INPUT);
-    c.r[k] = f_to_mont<FpR>(v);
-  }
-  if (!ok) atomicOr(c.flags, VFLAG_BAD_PROOF);
+  if (id >= kve_items(l, lM, c.L)) return;
+  const uint8_t *rounds = c.proof + 32, *tail = rounds + 832ull * l;
+  Item it;
+  if (id < 2) it = item(IT_G2, tail + 32 + 64 * id, id ? c.piv : c.vl);
+  else if ((id -= 2) < 1) it = item(IT_G1, c.proof, c.CF);
+  else if ((id -= 1) < 2 * l) it = item(IT_G1, rounds + 832ull * (id / 2) + (id % 2 ? 800 : 384), (id % 2 ? c.Rg1 : c.Lg1) + id / 2);
+  else if ((id -= 2 * l) < 1) it = item(IT_G1, tail, c.Al);
+  else if ((id -= 1) < lM) it = item(IT_G1, tail + 192 + 32 * id, c.W + id);
+  else if ((id -= lM) < 24 * l) {
+    const uint32_t r = id / 24, side = id / 12 % 2;
+    it = item_gt(rounds + 832ull * r + 416 * side, (side ? c.Rgt : c.Lgt) + r, id % 12);
+  } else if ((id -= 24 * l) < 1) it = item(IT_FR, tail + 160, c.y);
+  else if ((id -= 1) < 12) it = item_gt(c.Cb, c.C, id, VFLAG_BAD_INPUT);
+  else it = item(IT_FR_LE, c.rle + 32 * (id - 12), c.r + (id - 12), VFLAG_BAD_INPUT);
+  decode_item(it, c.flags);
 }
 
 // r_0, the challenges x_j, z, f_v(z) (thread 0), b_l = r_0 sum_j T_j prod_k (x_k^{-1})^{bit_{l-k}(j)}
@@ -991,7 +960,7 @@ __global__ void __launch_bounds__(64) kve_assemble(VECtx c) {
 }
 
 namespace kve {
-void decode(const VECtx &c, hipStream_t st) { L1(kve_decode, 1 + 4 * c.lK + 3 + 1 + c.lM + 1 + c.L, c); }
+void decode(const VECtx &c, hipStream_t st) { L1(kve_decode, kve_items(c.lK, c.lM, c.L), c); }
 void transcript(const VECtx &c, hipStream_t st) { LAUNCH(kve_transcript, dim3(1), dim3(256), 0, c); }
 void assemble(const VECtx &c, hipStream_t st) { LAUNCH(kve_assemble, dim3(1), dim3(64), 0, c); }
 }  // namespace kve
@@ -1024,7 +993,7 @@ __global__ void __launch_bounds__(256) ksa_check(const uint8_t *proofs, uint64_t
   __syncthreads();
   if (t != 0) return;
   g1_aff e;
-  bool ok = g1_decompress(P + 32 * (j - j0), e);
+  bool ok = decompress(P + 32 * (j - j0), false, &e, nullptr);
   if (!ok || !fe_eq(e.x, Cre[j].x) || !fe_eq(e.y, Cre[j].y)) atomicOr(flags, VFLAG_BAD_PROOF);
   if (diff) oddlist[atomicAdd(oddcnt, 1u)] = j;
 }

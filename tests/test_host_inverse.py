@@ -1,4 +1,5 @@
-"""The modular inverse by batched division steps on the host build, against Python's."""
+"""The modular inverse by batched division steps and the windowed power on loose limbs, on the host
+build, against Python's."""
 import ctypes as C
 import os
 import random
@@ -12,14 +13,18 @@ HC_PATH = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__)
 P, R = O.P, O.R
 
 
-@pytest.mark.parametrize("which,mod", [(0, P), (1, R)])
-def test_inverse(which, mod):
-    """Small and large values, powers of two (runs of zero bits longer than a batch), values next to
-    multiples of them, and the zero that maps to zero."""
+@pytest.fixture(scope="module")
+def hc():
     if not os.path.exists(HC_PATH):
         from paper_2601_03031_amd import build as B
         B.build_hostcheck()
-    hc = C.CDLL(HC_PATH)
+    return C.CDLL(HC_PATH)
+
+
+@pytest.mark.parametrize("which,mod", [(0, P), (1, R)])
+def test_inverse(hc, which, mod):
+    """Small and large values, powers of two (runs of zero bits longer than a batch), values next to
+    multiples of them, and the zero that maps to zero."""
     rng = random.Random(900 + which)
     vals = [0, 1, 2, 3, 62, 63, mod - 1, mod - 2, mod // 2, mod // 2 + 1, mod // 3]
     vals += [1 << s for s in (29, 30, 31, 60, 64, 90, 128, 240, 253)]
@@ -29,3 +34,17 @@ def test_inverse(which, mod):
         o = C.create_string_buffer(32)
         hc.hc_field(which, 4, O.be32(x), O.be32(x), o)
         assert int.from_bytes(o.raw, "big") == (pow(x, -1, mod) if x else 0), x
+
+
+@pytest.mark.parametrize("which,mod", [(0, P), (1, R)])
+def test_pow_fixed(hc, which, mod):
+    """Exponents of one bit, runs of ones and zeros, windows cut off at bit 0; bases at the ends of
+    the range."""
+    rng = random.Random(910 + which)
+    exps = [1, 2, 3, 5, 15, 16, 17, 30, (1 << 255) | 1, (1 << 256) - 1, 1 << 255, (P - 3) // 4, mod - 2]
+    exps += [rng.randrange(1, 1 << 256) for _ in range(10)]
+    for x in [0, 1, mod - 1, 2, (1 << 253) % mod] + [rng.randrange(mod) for _ in range(5)]:
+        for e in exps:
+            o = C.create_string_buffer(32)
+            hc.hc_pow_fixed(which, O.be32(x), O.be32(e), o)
+            assert int.from_bytes(o.raw, "big") == pow(x, e, mod), (x, e)
