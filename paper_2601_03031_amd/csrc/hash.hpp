@@ -26,7 +26,27 @@ static constexpr uint32_t K[64] = {
 static constexpr uint32_t H0[8] = {0x6a09e667, 0xbb67ae85, 0x3c6ef372, 0xa54ff53a,
                                    0x510e527f, 0x9b05688c, 0x1f83d9ab, 0x5be0cd19};
 
-DEV uint32_t rotr(uint32_t x, int n) { return (x >> n) | (x << (32 - n)); }
+HD constexpr uint32_t rotr(uint32_t x, int n) { return (x >> n) | (x << (32 - n)); }
+
+// the state after a block of 64 zero bytes, with which expand_message_xmd begins
+struct State {
+  uint32_t h[8];
+};
+constexpr State zero_block_state() {
+  uint32_t w[64] = {}, s[8] = {};
+  for (int i = 0; i < 8; i++) s[i] = H0[i];
+  for (int i = 0; i < 64; i++) {  // (all message words are zero, and so are those derived from them)
+    const uint32_t t1 = s[7] + (rotr(s[4], 6) ^ rotr(s[4], 11) ^ rotr(s[4], 25)) + ((s[4] & s[5]) ^ (~s[4] & s[6])) + K[i] + w[i];
+    const uint32_t t2 = (rotr(s[0], 2) ^ rotr(s[0], 13) ^ rotr(s[0], 22)) + ((s[0] & s[1]) ^ (s[0] & s[2]) ^ (s[1] & s[2]));
+    for (int j = 7; j > 0; j--) s[j] = s[j - 1];
+    s[4] += t1;
+    s[0] = t1 + t2;
+  }
+  State o = {};
+  for (int i = 0; i < 8; i++) o.h[i] = H0[i] + s[i];
+  return o;
+}
+static constexpr State ZPAD = zero_block_state();
 
 // one compression; w[0..16) is the block as big-endian words
 inline NOINL void compress(uint32_t h[8], const uint32_t blk[16]) {
@@ -143,7 +163,8 @@ DEV int cstrlen(const char *s) {
 // expand_message_xmd: start b0 = H(Z_pad || msg || I2OSP(48,2) || 0 || DST || len)
 HD inline void xmd_begin(Hasher &hs) {
   hs.init();
-  for (int i = 0; i < 16; i++) hs.word(0);  // Z_pad, 64 zero bytes
+  for (int i = 0; i < 8; i++) hs.h[i] = ZPAD.h[i];
+  hs.total = 64;
 }
 
 // finish xmd with L = 48 and reduce the 384-bit output mod r; returns Montgomery form
@@ -181,12 +202,23 @@ inline NOINL fe xmd_finish_fr(Hasher &hs, const char *dst) {
 // ---- the same hashes for a message that a workgroup builds together in shared memory:
 // the message is kept as big-endian 32-bit words, lanes write its pieces and the padding
 // in parallel, and every lane then runs the compression on the same words (plain vector
-// code, no per-lane message state).  Coop gives the lane index, the lane count and the
-// barrier; the host model runs it as one lane.
+// code, no per-lane message state).  Coop gives the lane index, the lane count (64: the lanes
+// of one wavefront, which may be one of several with messages of their own; else the whole
+// workgroup), SCHED_WORDS words of shared memory and the barrier; the host model runs it as one lane.
+static constexpr int SCHED = 16, SCHED_STRIDE = 68, SCHED_WORDS = SCHED * SCHED_STRIDE;
 struct Coop {
   int lane, n;
+  uint32_t *sched;
 #ifdef __HIP_DEVICE_COMPILE__
-  __device__ void sync() const { __syncthreads(); }
+  __device__ void sync() const {
+    if (n == 64) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    } else {
+      __syncthreads();
+    }
+  }
 #else
   HD void sync() const {}
 #endif
@@ -209,26 +241,31 @@ template <class F> HD inline void put_field_bytes(uint32_t *w, uint32_t pos, con
   for (int i = 0; i < 32; i++) put_byte(w, pos + i, fe_word(c, 7 - i / 4) >> (24 - 8 * (i & 3)));
 }
 
-HD inline void compress_inl(uint32_t h[8], const uint32_t *blk) {
+// the 64 words W_i + K_i of a block
+HD inline void schedule(const uint32_t *blk, uint32_t *wk) {
   uint32_t w[16];
 #pragma unroll
   for (int i = 0; i < 16; i++) w[i] = blk[i];
-  uint32_t a = h[0], b = h[1], c = h[2], d = h[3], e = h[4], f = h[5], g = h[6], hh = h[7];
 #pragma unroll
   for (int i = 0; i < 64; i++) {
-    uint32_t wi;
-    if (i < 16) {
-      wi = w[i];
-    } else {
+    if (i >= 16) {
       uint32_t w15 = w[(i - 15) & 15], w2 = w[(i - 2) & 15];
       uint32_t s0 = rotr(w15, 7) ^ rotr(w15, 18) ^ (w15 >> 3);
       uint32_t s1 = rotr(w2, 17) ^ rotr(w2, 19) ^ (w2 >> 10);
-      wi = w[i & 15] + s0 + w[(i - 7) & 15] + s1;
-      w[i & 15] = wi;
+      w[i & 15] += s0 + w[(i - 7) & 15] + s1;
     }
+    wk[i] = w[i & 15] + K[i];
+  }
+}
+
+// the 64 rounds of a block whose schedule is done
+HD inline void rounds(uint32_t h[8], const uint32_t *wk) {
+  uint32_t a = h[0], b = h[1], c = h[2], d = h[3], e = h[4], f = h[5], g = h[6], hh = h[7];
+#pragma unroll
+  for (int i = 0; i < 64; i++) {
     uint32_t S1 = rotr(e, 6) ^ rotr(e, 11) ^ rotr(e, 25);
     uint32_t ch = (e & f) ^ (~e & g);
-    uint32_t t1 = hh + S1 + ch + K[i] + wi;
+    uint32_t t1 = hh + S1 + ch + wk[i];
     uint32_t S0 = rotr(a, 2) ^ rotr(a, 13) ^ rotr(a, 22);
     uint32_t mj = (a & b) ^ (a & c) ^ (b & c);
     hh = g;
@@ -267,15 +304,20 @@ __device__ __forceinline__ uint32_t in_vgpr(uint32_t x) {
 HD inline uint32_t in_vgpr(uint32_t x) { return x; }
 #endif
 
-// digest of the nblk padded blocks in w
-HD inline void digest_blocks(const uint32_t *w, int nblk, uint32_t out[8]) {
+// digest of the nblk padded blocks in w from state h0 on; every lane gets it.  The blocks'
+// schedules do not depend on the chain: up to 16 lanes make one each and leave it in shared memory
+// (68 words apart, so that they fall in different banks), and the chain of rounds, in all lanes, only
+// reads them: the 17 blocks of a round's challenge and their reduction mod r 0.050 ms, 0.097 with
+// each lane making the schedules on the way and hashing Z_pad.
+HD inline void digest_blocks(const Coop &cp, const uint32_t *w, int nblk, const uint32_t *h0, uint32_t out[8]) {
   uint32_t h[8];
-  for (int i = 0; i < 8; i++) h[i] = in_vgpr(H0[i]);
-  for (int b = 0; b < nblk; b++) {
-    uint32_t blk[16];
-#pragma unroll
-    for (int i = 0; i < 16; i++) blk[i] = in_vgpr(w[16 * b + i]);
-    compress_inl(h, blk);
+  for (int i = 0; i < 8; i++) h[i] = in_vgpr(h0[i]);
+  for (int first = 0; first < nblk; first += SCHED) {
+    const int n = nblk - first < SCHED ? nblk - first : SCHED;
+    for (int b = cp.lane; b < n; b += cp.n) schedule(w + 16 * (first + b), cp.sched + SCHED_STRIDE * b);
+    cp.sync();
+    for (int b = 0; b < n; b++) rounds(h, cp.sched + SCHED_STRIDE * b);
+    cp.sync();
   }
   for (int i = 0; i < 8; i++) out[i] = h[i];
 }
@@ -285,12 +327,12 @@ HD inline void digest_blocks(const uint32_t *w, int nblk, uint32_t out[8]) {
 HD inline void sha_coop(const Coop &cp, uint32_t *w, uint32_t len, uint32_t out[8]) {
   int nblk = pad_coop(cp, w, len);
   cp.sync();
-  digest_blocks(w, nblk, out);
+  digest_blocks(cp, w, nblk, H0, out);
 }
 
 // hash_to_field to F_r (Montgomery form) of the mlen-byte message at byte 64 of w, whose
-// first 16 words must be zero (Z_pad of expand_message_xmd, L = 48); w needs room for
-// 64 + mlen + the DST suffix + padding (mlen + 64 + 4 + |DST| + 72 bytes), t2 for one
+// first 16 words are not read (Z_pad of expand_message_xmd, L = 48, enters by its state); w needs
+// room for 64 + mlen + the DST suffix + padding (mlen + 64 + 4 + |DST| + 72 bytes), t2 for one
 // block; |DST| <= 21.  Same result as Hasher with xmd_begin / xmd_finish_fr.  The message
 // must be complete (and synchronized) when called.
 HD inline fe xmd_fr_coop(const Coop &cp, uint32_t *w, uint32_t mlen, const char *dst, uint32_t *t2) {
@@ -299,7 +341,9 @@ HD inline fe xmd_fr_coop(const Coop &cp, uint32_t *w, uint32_t mlen, const char 
   for (uint32_t i = cp.lane; i < 4 + dlen; i += cp.n)
     put_byte(w, p + i, i == 1 ? 48u : (i == 0 || i == 2) ? 0u : i < 3 + dlen ? (uint32_t)(uint8_t)dst[i - 3] : dlen);
   uint32_t b0[8], b1[8], b2[8];
-  sha_coop(cp, w, p + 4 + dlen, b0);
+  const int nblk = pad_coop(cp, w, p + 4 + dlen);
+  cp.sync();
+  digest_blocks(cp, w + 16, nblk - 1, ZPAD.h, b0);
   // b1 = H(b0 || 1 || DST || dlen), b2 = H((b0 xor b1) || 2 || DST || dlen): one block each
   for (int i = 0; i < 8; i++)
     if (i % cp.n == cp.lane) t2[i] = b0[i];
@@ -311,7 +355,7 @@ HD inline fe xmd_fr_coop(const Coop &cp, uint32_t *w, uint32_t mlen, const char 
     if (i % cp.n == cp.lane) t2[i] = b0[i] ^ b1[i];
   if (cp.lane == 0) put_byte(t2, 32, 2);
   cp.sync();
-  digest_blocks(t2, 1, b2);
+  digest_blocks(cp, t2, 1, H0, b2);
   uint32_t hw[8], lw[8];
   for (int i = 0; i < 4; i++) { hw[i] = b1[3 - i]; hw[4 + i] = 0; }
   for (int i = 0; i < 4; i++) lw[i] = b2[3 - i];

@@ -374,18 +374,17 @@ API void hc_h2f(const char *dst, const uint8_t *msg, uint64_t len, uint8_t *out)
 // the cooperative form used by the challenge kernels (one lane here): msg (len bytes, at
 // most 1024) after Z_pad
 API void hc_h2f_coop(const char *dst, const uint8_t *msg, uint64_t len, uint8_t *out) {
-  static uint32_t w[16 + 256 + 32], t2[16];
-  for (int i = 0; i < 16; i++) w[i] = 0;
+  static uint32_t w[16 + 256 + 32], t2[16], sched[sha::SCHED_WORDS];
   for (uint64_t i = 0; i < len; i++) sha::put_byte(w, 64 + (uint32_t)i, msg[i]);
-  wr<FpR>(out, sha::xmd_fr_coop(sha::Coop{0, 1}, w, (uint32_t)len, dst, t2));
+  wr<FpR>(out, sha::xmd_fr_coop(sha::Coop{0, 1, sched}, w, (uint32_t)len, dst, t2));
 }
 
 // SHA-256 through the cooperative form (len at most 1024)
 API void hc_sha256_coop(const uint8_t *msg, uint64_t len, uint8_t *out) {
-  static uint32_t w[256 + 32];
+  static uint32_t w[256 + 32], sched[sha::SCHED_WORDS];
   for (uint64_t i = 0; i < len; i++) sha::put_byte(w, (uint32_t)i, msg[i]);
   uint32_t o[8];
-  sha::sha_coop(sha::Coop{0, 1}, w, (uint32_t)len, o);
+  sha::sha_coop(sha::Coop{0, 1, sched}, w, (uint32_t)len, o);
   for (int i = 0; i < 8; i++) {
     out[4 * i] = o[i] >> 24; out[4 * i + 1] = o[i] >> 16; out[4 * i + 2] = o[i] >> 8; out[4 * i + 3] = o[i];
   }

@@ -31,7 +31,7 @@ __global__ void __launch_bounds__(TPB) k_trapdoor(const uint8_t *seed, uint32_t 
 __global__ void __launch_bounds__(64) k_fc_chunks(const g1_aff *Cj, uint64_t K, uint32_t b, uint64_t nb, uint64_t nbj,
                                                  uint32_t *Hq) {
   CHAIN_PRIORITY();
-  __shared__ uint32_t msg[FC_CHUNK * 18 + 18];
+  __shared__ uint32_t msg[FC_CHUNK * 18 + 18], sched[sha::SCHED_WORDS];
   uint64_t id = blockIdx.x;
   uint64_t qmax = (b + FC_CHUNK - 1) / FC_CHUNK;
   if (id >= nb * qmax) return;
@@ -52,7 +52,7 @@ __global__ void __launch_bounds__(64) k_fc_chunks(const g1_aff *Cj, uint64_t K, 
   }
   __syncthreads();
   uint32_t out[8];
-  sha::sha_coop(sha::Coop{t, 64}, msg, 72u * n, out);
+  sha::sha_coop(sha::Coop{t, 64, sched}, msg, 72u * n, out);
   if (t == 0)
     for (int w = 0; w < 8; w++) Hq[id * 8 + w] = out[w];
 }
@@ -66,6 +66,7 @@ __global__ void __launch_bounds__(64) k_fc_sigma(const fp12 *C, uint64_t K, uint
                                                 const uint32_t *Hq, uint32_t *sigma) {
   CHAIN_PRIORITY();
   extern __shared__ uint32_t mw[];
+  __shared__ uint32_t sched[sha::SCHED_WORDS];
   const uint64_t kk = blockIdx.x;
   if (kk >= nb) return;
   const uint64_t k = kk % nbj;  // batch k of job kk / nbj, whose commitment is C[kk / nbj]
@@ -86,7 +87,7 @@ __global__ void __launch_bounds__(64) k_fc_sigma(const fp12 *C, uint64_t K, uint
   }
   __syncthreads();
   uint32_t out[8];
-  sha::sha_coop(sha::Coop{t, 64}, mw, off + 32 * (uint32_t)nq, out);
+  sha::sha_coop(sha::Coop{t, 64, sched}, mw, off + 32 * (uint32_t)nq, out);
   if (t == 0)
     for (int w = 0; w < 8; w++) sigma[kk * 8 + w] = out[w];
 }
@@ -96,18 +97,17 @@ __global__ void __launch_bounds__(64) k_fc_sigma(const fp12 *C, uint64_t K, uint
 __global__ void __launch_bounds__(64) k_fc_r(uint64_t K, uint32_t b, uint64_t nb, uint64_t nbj, const uint32_t *sigma,
                                             fe *B) {
   CHAIN_PRIORITY();
-  __shared__ uint32_t w[16 + 10 + 32], t2[16];
+  __shared__ uint32_t w[16 + 10 + 32], t2[16], sched[sha::SCHED_WORDS];
   uint64_t id = blockIdx.x;
   if (id >= nb * (uint64_t)b) return;
   uint64_t kk = id / b, i = id % b;
   uint64_t a = (kk % nbj) * b + i;  // entry i of batch kk % nbj of its job
   if (a >= K) return;
   const int t = threadIdx.x;
-  if (t < 16) w[t] = 0;
-  else if (t < 24) w[t] = sigma[kk * 8 + t - 16];
-  else if (t < 26) w[t] = t == 24 ? (uint32_t)(i >> 32) : (uint32_t)i;
+  if (t >= 16 && t < 24) w[t] = sigma[kk * 8 + t - 16];
+  else if (t >= 24 && t < 26) w[t] = t == 24 ? (uint32_t)(i >> 32) : (uint32_t)i;
   __syncthreads();
-  fe r = sha::xmd_fr_coop(sha::Coop{t, 64}, w, 40, DSTR_FC_R, t2);
+  fe r = sha::xmd_fr_coop(sha::Coop{t, 64, sched}, w, 40, DSTR_FC_R, t2);
   if (t == 0) B[kk * K + a] = r;
 }
 
@@ -128,13 +128,12 @@ __global__ void __launch_bounds__(64) k_oa_transcript(const fp12 *Lgt, const fp1
                                                      uint32_t lK, const g1_aff *Lg1, const g1_aff *Rg1, fe *X, fe *Xinv,
                                                      int *err, uint32_t zero_round) {
   CHAIN_PRIORITY();
-  __shared__ uint32_t msg[16 + 8 + 2 * (96 + 16) + 32], t2[16];
+  __shared__ uint32_t msg[16 + 8 + 2 * (96 + 16) + 32], t2[16], sched[sha::SCHED_WORDS];
   uint64_t k = blockIdx.x;
   if (k >= nb) return;
   uint64_t slot = k * lK + (j - 1);
   const int t = threadIdx.x;
   const int pre = j > 1 ? 8 : 0;
-  if (t < 16) msg[t] = 0;  // Z_pad
   // element e: x_{j-1} (F_r) if j > 1, then L_gt (12), L_g1 (2), R_gt (12), R_g1 (2)
   const int e = j > 1 ? t - 1 : t;
   if (j > 1 && t == 0) sha::put_words<FpR>(msg + 16, X[slot - 1]);
@@ -145,7 +144,7 @@ __global__ void __launch_bounds__(64) k_oa_transcript(const fp12 *Lgt, const fp1
     sha::put_words<FpP>(msg + 16 + pre + 112 * side + 8 * q, *src);
   }
   __syncthreads();
-  fe x = sha::xmd_fr_coop(sha::Coop{t, 64}, msg, 4 * (pre + 224), DSTR_FC_X, t2);
+  fe x = sha::xmd_fr_coop(sha::Coop{t, 64, sched}, msg, 4 * (pre + 224), DSTR_FC_X, t2);
   if (zero_round == j && k == 0) x = fe_zero();  // test hook: the host forces a zero challenge
   fe xi = f_inv_uniform<FpR>(x, bn::R_R3);
   if (t == 0) {
@@ -181,14 +180,13 @@ __global__ void __launch_bounds__(KZG_T) k_kzg_quotient(const fe *Xinv, const fe
   uint64_t k = blockIdx.x;
   const uint64_t n = 2 * K - 2;
   fe *acc = sh;
-  __shared__ uint32_t zmsg[16 + 8 + 32 + 24], t2[16];
+  __shared__ uint32_t zmsg[16 + 8 + 32 + 24], t2[16], sched[sha::SCHED_WORDS];
   uint32_t t = threadIdx.x;
   // z = H2F(DST_FC_Z, x_l || v_l): lanes encode, every wave hashes (sha::Coop)
-  if (t < 16) zmsg[t] = 0;
   if (t == 16) sha::put_words<FpR>(zmsg + 16, X[k * lK + lK - 1]);
   if (t > 16 && t <= 20) sha::put_words<FpP>(zmsg + 24 + 8 * (t - 17), reinterpret_cast<const fe *>(V + k * K)[t - 17]);
   __syncthreads();
-  const fe zz = sha::xmd_fr_coop(sha::Coop{(int)t, KZG_T}, zmsg, 160, DSTR_FC_Z, t2);
+  const fe zz = sha::xmd_fr_coop(sha::Coop{(int)t, KZG_T, sched}, zmsg, 160, DSTR_FC_Z, t2);
   if (t == 0) zout[k] = zz;
   for (uint64_t m = t; m < n; m += KZG_T) acc[m] = kzg_coef(Xinv, k, lK, m);
   __syncthreads();
@@ -215,13 +213,12 @@ __global__ void __launch_bounds__(KZG_T) k_kzg_quotient_g(const fe *Xinv, const 
   uint64_t k = blockIdx.x;
   const uint64_t n = 2 * K - 2;
   fe *aa = gws + k * 4 * (2 * K - 1), *ab = aa + n;
-  __shared__ uint32_t zmsg[16 + 8 + 32 + 24], t2[16];
+  __shared__ uint32_t zmsg[16 + 8 + 32 + 24], t2[16], sched[sha::SCHED_WORDS];
   uint32_t t = threadIdx.x;
-  if (t < 16) zmsg[t] = 0;
   if (t == 16) sha::put_words<FpR>(zmsg + 16, X[k * lK + lK - 1]);
   if (t > 16 && t <= 20) sha::put_words<FpP>(zmsg + 24 + 8 * (t - 17), reinterpret_cast<const fe *>(V + k * K)[t - 17]);
   __syncthreads();
-  const fe zz = sha::xmd_fr_coop(sha::Coop{(int)t, KZG_T}, zmsg, 160, DSTR_FC_Z, t2);
+  const fe zz = sha::xmd_fr_coop(sha::Coop{(int)t, KZG_T, sched}, zmsg, 160, DSTR_FC_Z, t2);
   if (t == 0) zout[k] = zz;
   for (uint64_t m = t; m < n; m += KZG_T) aa[m] = kzg_coef(Xinv, k, lK, m);
   __syncthreads();

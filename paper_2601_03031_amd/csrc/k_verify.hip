@@ -202,10 +202,9 @@ __global__ void __launch_bounds__(256) kv_transcript(const VCtx *cs) {
   }
   // round challenges x_j = H2F(FC-X, x_{j-1} || L_gt || L_g1 || R_gt || R_g1), the workgroup
   // hashing together: lanes write the message words into shared memory, all compress
-  __shared__ uint32_t xmsg[16 + 8 + 2 * (96 + 16) + 32], xt2[16];
+  __shared__ uint32_t xmsg[16 + 8 + 2 * (96 + 16) + 32], xt2[16], sched[sha::SCHED_WORDS];
   for (uint32_t j = 0; j < l; j++) {
     const int pre = j > 0 ? 8 : 0;
-    if (tid < 16) xmsg[tid] = 0;  // Z_pad
     const int e = j > 0 ? tid - 1 : tid;
     if (j > 0 && tid == 0) sha::put_words<FpR>(xmsg + 16, c.x[j - 1]);
     if (e >= 0 && e < 28) {
@@ -215,7 +214,7 @@ __global__ void __launch_bounds__(256) kv_transcript(const VCtx *cs) {
       sha::put_words<FpP>(xmsg + 16 + pre + 112 * side + 8 * q, *src);
     }
     __syncthreads();
-    fe x = sha::xmd_fr_coop(sha::Coop{tid, 256}, xmsg, 4 * (pre + 224), DSTR_FC_X, xt2);
+    fe x = sha::xmd_fr_coop(sha::Coop{tid, 256, sched}, xmsg, 4 * (pre + 224), DSTR_FC_X, xt2);
     fe xi = f_inv_uniform<FpR>(x, bn::R_R3);
     if (tid == 0) {
       if (fe_is_zero(x)) atomicOr(c.flags, VFLAG_BAD_PROOF);
@@ -856,10 +855,9 @@ __global__ void __launch_bounds__(256) kve_transcript(VECtx c) {
     s_r0 = sha::xmd_finish_fr(hx, DSTR_EVAL);
   }
   // round challenges, the workgroup hashing together (as in kv_transcript)
-  __shared__ uint32_t xmsg[16 + 8 + 2 * (96 + 16) + 32], xt2[16];
+  __shared__ uint32_t xmsg[16 + 8 + 2 * (96 + 16) + 32], xt2[16], sched[sha::SCHED_WORDS];
   for (uint32_t j = 0; j < l; j++) {
     const int pre = j > 0 ? 8 : 0;
-    if (tid < 16) xmsg[tid] = 0;  // Z_pad
     const int e = j > 0 ? tid - 1 : tid;
     if (j > 0 && tid == 0) sha::put_words<FpR>(xmsg + 16, c.x[j - 1]);
     if (e >= 0 && e < 28) {
@@ -869,7 +867,7 @@ __global__ void __launch_bounds__(256) kve_transcript(VECtx c) {
       sha::put_words<FpP>(xmsg + 16 + pre + 112 * side + 8 * q, *src);
     }
     __syncthreads();
-    fe x = sha::xmd_fr_coop(sha::Coop{tid, 256}, xmsg, 4 * (pre + 224), DSTR_FC_X, xt2);
+    fe x = sha::xmd_fr_coop(sha::Coop{tid, 256, sched}, xmsg, 4 * (pre + 224), DSTR_FC_X, xt2);
     fe xi = f_inv_uniform<FpR>(x, bn::R_R3);
     if (tid == 0) {
       if (fe_is_zero(x)) atomicOr(c.flags, VFLAG_BAD_PROOF);
