@@ -1,7 +1,8 @@
 // Kernels of VC.Verify for one opening proof (appendix C; section 3 FC.BVerify with the
 // faster verifier; section 4.2 for the Merkle and folding parts):
 //   kv_decode      point decompression and range checks, one thread per proof element
-//   kv_transcript  Fiat-Shamir replay (r_i, x_j, z, rho_j), f_v(z), b_l, Merkle path, y*
+//   kv_chains      Fiat-Shamir replay (r_i, x_j, z, rho_j), f_v(z), Merkle path, y*
+//   kv_jobs        b_l, the multiplication and power jobs
 //   kv_assemble    point sums and the pairs of the three pairing checks
 //   kv_compare     the final equalities
 // Scalar multiplications, G_T exponentiations, Miller loops and final exponentiations
@@ -158,120 +159,158 @@ __global__ void __launch_bounds__(TPB) kv_decode(const VCtx *cs) {
   decode_item(it, c.flags);
 }
 
-// Fiat-Shamir replay and scalar set-up, a workgroup per proof: chunk digests and the batching
-// coefficients r_u one thread each, the challenge chain (x_j, z, f_v(z)) on thread 0 beside the
-// Merkle path (rho_j, y*) on thread 64, then b_l as a tree of per-thread partial sums and the
-// multiplication jobs in parallel
-__global__ void __launch_bounds__(256) kv_transcript(const VCtx *cs) {
-  const VCtx &c = cs[blockIdx.x];
+// Fiat-Shamir replay, the three chains that do not depend on one another in a workgroup each
+// (blockIdx.x; blockIdx.y: the proof):
+//   0  the challenges x_j with their inverses, z and f_v(z);
+//   1  the chunk digests, sigma and the batching coefficients r_u;
+//   2  the Merkle path, rho_j and y*.
+// Bound by the first, a chain of l hashes of 17 blocks: 0.43 ms at 2^16 entries in batches of 256, 2.0
+// when a workgroup did the three in turn, with an inverse in each round.
+static constexpr uint32_t MAX_CHUNKS = 1024;  // t <= 32768 (K of log N <= 30)
+// words of shared memory: sigma's message (a prefix of 392 bytes and the tag, the digests, padding),
+// then a chunk's message and schedules for each wavefront
+static constexpr uint32_t SIGMA_WORDS = (392 + 32 + 32 * MAX_CHUNKS + 72) / 4, CHUNK_WORDS = 32 * 18 + 18;
+static constexpr uint32_t CHAIN_WORDS = SIGMA_WORDS + 4 * (CHUNK_WORDS + sha::SCHED_WORDS);
+
+// x_1 .. x_l = H2F(FC-X, x_{j-1} || L_gt || L_g1 || R_gt || R_g1) and their inverses, then z =
+// H2F(FC-Z, x_l || v_l) in all lanes, f_v(z) = prod_j (1 + x_j^{-1} z^{2^{l-j+1}}) in lane 0; the
+// workgroup hashes together.  lds: 512 + SCHED_WORDS words
+template <class C> __device__ fe challenge_chain(const C &c, uint32_t l, uint32_t *lds, fe *fz) {
   const int tid = threadIdx.x;
-  const uint32_t t = c.t, l = c.lK;
-  __shared__ uint32_t dig[1024][8];  // chunk digests: t <= 32768 (K of log N <= 30)
-  __shared__ uint32_t sigma[8];
-  __shared__ fe part[256];
-  __shared__ fe s_z, s_rho, s_ystar;
-  const uint32_t nch = (t + 31) / 32;
-  // r_u = H2F(FC-R, sigma || u), sigma over the digests of 32-entry chunks
-  for (uint32_t q = tid; q < nch; q += 256) {
-    sha::Hasher hc;
-    hc.init();
-    for (uint32_t u = q * 32; u < t && u < q * 32 + 32; u++) {
-      hc.u64(c.lo + u);
-      hc.g1(c.blk[u]);
-    }
-    hc.final(dig[q]);
-  }
-  __syncthreads();
-  if (tid == 0) {
-    sha::Hasher hs;
-    hs.init();
-    hs.str(DSTR_FC_R);
-    hs.gt(*c.C);
-    hs.u64(t);
-    for (uint32_t q = 0; q < nch; q++)
-      for (int w = 0; w < 8; w++) hs.word(dig[q][w]);
-    hs.final(sigma);
-  }
-  __syncthreads();
-  for (uint32_t u = tid; u < t; u += 256) {
-    sha::Hasher hs;
-    sha::xmd_begin(hs);
-    for (int w = 0; w < 8; w++) hs.word(sigma[w]);
-    hs.u64(u);
-    c.r[u] = sha::xmd_finish_fr(hs, DSTR_FC_R);
-  }
-  // round challenges x_j = H2F(FC-X, x_{j-1} || L_gt || L_g1 || R_gt || R_g1), the workgroup
-  // hashing together: lanes write the message words into shared memory, all compress
-  __shared__ uint32_t xmsg[16 + 8 + 2 * (96 + 16) + 32], xt2[16], sched[sha::SCHED_WORDS];
+  uint32_t *msg = lds + sha::SCHED_WORDS, *t2 = msg + 16 + 8 + 2 * (96 + 16) + 32;
+  const sha::Coop cp{tid, 256, lds};
   for (uint32_t j = 0; j < l; j++) {
     const int pre = j > 0 ? 8 : 0;
     const int e = j > 0 ? tid - 1 : tid;
-    if (j > 0 && tid == 0) sha::put_words<FpR>(xmsg + 16, c.x[j - 1]);
+    if (j > 0 && tid == 0) sha::put_words<FpR>(msg + 16, c.x[j - 1]);
     if (e >= 0 && e < 28) {
       int side = e / 14, q = e % 14;
       const fe *src = q < 12 ? reinterpret_cast<const fe *>(side ? c.Rgt + j : c.Lgt + j) + q
                              : reinterpret_cast<const fe *>(side ? c.Rg1 + j : c.Lg1 + j) + (q - 12);
-      sha::put_words<FpP>(xmsg + 16 + pre + 112 * side + 8 * q, *src);
+      sha::put_words<FpP>(msg + 16 + pre + 112 * side + 8 * q, *src);
     }
     __syncthreads();
-    fe x = sha::xmd_fr_coop(sha::Coop{tid, 256, sched}, xmsg, 4 * (pre + 224), DSTR_FC_X, xt2);
-    fe xi = f_inv_uniform<FpR>(x, bn::R_R3);
+    const fe x = sha::xmd_fr_coop(cp, msg, 4 * (pre + 224), DSTR_FC_X, t2);
     if (tid == 0) {
       if (fe_is_zero(x)) atomicOr(c.flags, VFLAG_BAD_PROOF);
       c.x[j] = x;
-      c.xinv[j] = xi;
     }
     __syncthreads();
   }
+  if (tid == 0) sha::put_words<FpR>(msg + 16, c.x[l - 1]);
+  if (tid >= 1 && tid <= 4) sha::put_words<FpP>(msg + 24 + 8 * (tid - 1), reinterpret_cast<const fe *>(c.vl)[tid - 1]);
+  for (uint32_t j = tid; j < l; j += 256) c.xinv[j] = f_inv_fast<FpR>(c.x[j], bn::R_R3);
+  __syncthreads();
+  const fe z = sha::xmd_fr_coop(cp, msg, 160, DSTR_FC_Z, t2);
   if (tid == 0) {
-    // z = H2F(FC-Z, x_l || v_l); f_v(z) = prod_j (1 + x_j^{-1} z^{2^{l-j+1}})
-    sha::Hasher hz;
-    sha::xmd_begin(hz);
-    hz.field<FpR>(c.x[l - 1]);
-    hz.g2(*c.vl);
-    fe z = sha::xmd_finish_fr(hz, DSTR_FC_Z);
-    fe fz = f_one<FpR>(), zp = fr_mul(z, z);  // z^{2^1}
+    fe f = f_one<FpR>(), zp = fr_mul(z, z);  // z^{2^1}
     for (int j = (int)l; j >= 1; j--) {      // exponent 2^{l-j+1}: j = l first
-      fz = fr_mul(fz, fr_add(f_one<FpR>(), fr_mul(c.xinv[j - 1], zp)));
+      f = fr_mul(f, fr_add(f_one<FpR>(), fr_mul(c.xinv[j - 1], zp)));
       zp = fr_mul(zp, zp);
     }
-    s_z = z;
-    *c.fz = fz;
-  } else if (tid == 64 && c.fc_only) {
-    s_rho = fe_zero();
-    s_ystar = fe_zero();
-  } else if (tid == 64) {
-    // Merkle path of leaf i = SHA-256(0x00 || m_i || C_j) up to the root
-    const g1_aff &Cj = c.blk[c.j - c.lo];
-    uint32_t mw[8], cw[16], node[8];
-    fe mc = f_from_mont<FpR>(*c.mi);
-    fe cx = f_from_mont<FpP>(Cj.x), cy = f_from_mont<FpP>(Cj.y);
-    for (int q = 0; q < 8; q++) { mw[q] = mc.l[7 - q]; cw[q] = cx.l[7 - q]; cw[8 + q] = cy.l[7 - q]; }
-    sha::merkle_leaf(node, mw, cw);
-    uint64_t pos = c.N + c.i;
-    for (uint32_t h = 0; h < c.L; h++, pos >>= 1) {
-      uint32_t sib[8];
-      const uint8_t *sb = c.mpath + 32 * h;
-      for (int q = 0; q < 8; q++)
-        sib[q] = ((uint32_t)sb[4 * q] << 24) | ((uint32_t)sb[4 * q + 1] << 16) | ((uint32_t)sb[4 * q + 2] << 8) | sb[4 * q + 3];
-      uint32_t o[8];
-      if (pos & 1) sha::merkle_node(o, sib, node);
-      else sha::merkle_node(o, node, sib);
-      for (int q = 0; q < 8; q++) node[q] = o[q];
-    }
-    sha::Hasher hr;
-    sha::xmd_begin(hr);
-    hr.gt(*c.C);
-    for (int q = 0; q < 8; q++) hr.word(node[q]);
-    hr.u64(c.j);
-    fe rho = sha::xmd_finish_fr(hr, DSTR_RHO);
-    fe ystar = fr_mul(rho, *c.mi);
-    for (uint32_t h = 0; h < l; h++) ystar = fr_add(ystar, c.ysib[h]);
-    s_rho = rho;
-    s_ystar = ystar;
+    *fz = f;
   }
-  __syncthreads();
-  // b_l = sum_u r_u prod_k (x_k^{-1})^{bit_{l-k}(a_u)}
+  return z;
+}
+
+__global__ void __launch_bounds__(256) kv_chains(const VCtx *cs) {
+  const VCtx &c = cs[blockIdx.y];
+  const int tid = threadIdx.x;
+  const uint32_t t = c.t, l = c.lK;
+  __shared__ uint32_t lds[CHAIN_WORDS];
+  __shared__ uint32_t sigma[8];
+  if (blockIdx.x == 0) {
+    const fe z = challenge_chain(c, l, lds, c.fz);
+    if (tid == 0) c.ms[t + 2 * l + 3] = z;
+  } else if (blockIdx.x == 1) {
+    // sigma = H(FC-R || C || t || digests of 32-entry chunks); a wavefront per chunk
+    const int wave = tid / 64, lane = tid % 64;
+    uint32_t *msg = lds + SIGMA_WORDS + wave * (CHUNK_WORDS + sha::SCHED_WORDS);
+    const sha::Coop cw{lane, 64, msg + CHUNK_WORDS};
+    const uint32_t nch = (t + 31) / 32, dl = (uint32_t)sha::cstrlen(DSTR_FC_R);
+    for (uint32_t q = wave; q < nch; q += 4) {
+      const uint32_t n = t - 32 * q < 32 ? t - 32 * q : 32, u = 32 * q + lane;
+      if (lane < (int)n) {
+        const uint64_t a = c.lo + u;
+        msg[18 * lane] = (uint32_t)(a >> 32);
+        msg[18 * lane + 1] = (uint32_t)a;
+        sha::put_words<FpP>(msg + 18 * lane + 2, c.blk[u].x);
+        sha::put_words<FpP>(msg + 18 * lane + 10, c.blk[u].y);
+      }
+      cw.sync();
+      uint32_t dig[8];
+      sha::sha_coop(cw, msg, 72u * n, dig);
+      // byte lane of the digest (every lane has it)
+      uint32_t v = 0;
+      for (int w = 0; w < 8; w++) v = lane / 4 == w ? dig[w] : v;
+      if (lane < 32) sha::put_byte(lds, dl + 392 + 32 * q + lane, v >> (24 - 8 * (lane & 3)));
+    }
+    if ((uint32_t)tid < dl) sha::put_byte(lds, tid, (uint8_t)DSTR_FC_R[tid]);
+    if (tid >= 64 && tid < 76) sha::put_field_bytes<FpP>(lds, dl + 32 * (tid - 64), reinterpret_cast<const fe *>(c.C)[tid - 64]);
+    if (tid >= 128 && tid < 136) sha::put_byte(lds, dl + 384 + (tid - 128), tid < 132 ? 0 : (t >> (8 * (135 - tid))) & 0xff);
+    __syncthreads();
+    uint32_t sg[8];
+    sha::sha_coop(sha::Coop{tid, 256, lds + SIGMA_WORDS}, lds, dl + 392 + 32 * nch, sg);
+    if (tid == 0)
+      for (int w = 0; w < 8; w++) sigma[w] = sg[w];
+    __syncthreads();
+    // r_u = H2F(FC-R, sigma || u)
+    for (uint32_t u = tid; u < t; u += 256) {
+      sha::Hasher hs;
+      sha::xmd_begin(hs);
+      for (int w = 0; w < 8; w++) hs.word(sigma[w]);
+      hs.u64(u);
+      c.r[u] = sha::xmd_finish_fr(hs, DSTR_FC_R);
+    }
+  } else if (c.fc_only) {
+    if (tid == 0) {
+      c.ms[t + 2 * l + 1] = fe_zero();
+      c.ms[t + 2 * l + 2] = fe_zero();
+    }
+  } else {
+    // Merkle path of leaf i = SHA-256(0x00 || m_i || C_j) up to the root
+    uint32_t *msg = lds + sha::SCHED_WORDS, *t2 = msg + 16 + 12 * 8 + 8 + 2 + 32;
+    if (tid == 64) {
+      const g1_aff &Cj = c.blk[c.j - c.lo];
+      uint32_t mw[8], cw[16], node[8];
+      fe mc = f_from_mont<FpR>(*c.mi);
+      fe cx = f_from_mont<FpP>(Cj.x), cy = f_from_mont<FpP>(Cj.y);
+      for (int q = 0; q < 8; q++) { mw[q] = mc.l[7 - q]; cw[q] = cx.l[7 - q]; cw[8 + q] = cy.l[7 - q]; }
+      sha::merkle_leaf(node, mw, cw);
+      uint64_t pos = c.N + c.i;
+      for (uint32_t h = 0; h < c.L; h++, pos >>= 1) {
+        uint32_t sib[8];
+        const uint8_t *sb = c.mpath + 32 * h;
+        for (int q = 0; q < 8; q++)
+          sib[q] = ((uint32_t)sb[4 * q] << 24) | ((uint32_t)sb[4 * q + 1] << 16) | ((uint32_t)sb[4 * q + 2] << 8) | sb[4 * q + 3];
+        uint32_t o[8];
+        if (pos & 1) sha::merkle_node(o, sib, node);
+        else sha::merkle_node(o, node, sib);
+        for (int q = 0; q < 8; q++) node[q] = o[q];
+      }
+      for (int q = 0; q < 8; q++) msg[16 + 96 + q] = node[q];
+      msg[16 + 104] = (uint32_t)(c.j >> 32);
+      msg[16 + 105] = (uint32_t)c.j;
+    }
+    if (tid < 12) sha::put_words<FpP>(msg + 16 + 8 * tid, reinterpret_cast<const fe *>(c.C)[tid]);
+    __syncthreads();
+    const fe rho = sha::xmd_fr_coop(sha::Coop{tid, 256, lds}, msg, 4 * 106, DSTR_RHO, t2);
+    if (tid == 0) {
+      fe ystar = fr_mul(rho, *c.mi);
+      for (uint32_t h = 0; h < l; h++) ystar = fr_add(ystar, c.ysib[h]);
+      c.ms[t + 2 * l + 1] = rho;
+      c.ms[t + 2 * l + 2] = ystar;
+    }
+  }
+}
+
+// b_l = sum_u r_u prod_k (x_k^{-1})^{bit_{l-k}(a_u)} as a tree of per-thread partial sums, and the
+// multiplication and power jobs, a workgroup per proof
+__global__ void __launch_bounds__(256) kv_jobs(const VCtx *cs) {
+  const VCtx &c = cs[blockIdx.x];
+  const int tid = threadIdx.x;
+  const uint32_t t = c.t, l = c.lK;
+  __shared__ fe part[256];
   fe acc = fe_zero();
   for (uint32_t u = tid; u < t; u += 256) {
     fe term = c.r[u];
@@ -285,12 +324,13 @@ __global__ void __launch_bounds__(256) kv_transcript(const VCtx *cs) {
     if (tid < sft) part[tid] = fr_add(part[tid], part[tid + sft]);
     __syncthreads();
   }
-  // G1 multiplication jobs: r_u blk_u; x_j Lg1_j; x_j^{-1} Rg1_j; b_l A_l; rho C_j; y* g1; z g1;
-  // then (g1, 0) up to the stride of the job arrays
+  // G1 multiplication jobs: r_u blk_u; x_j Lg1_j; x_j^{-1} Rg1_j; b_l A_l; rho C_j; y* g1; z g1
+  // (the last three scalars are there already); then (g1, 0) up to the stride of the job arrays
   const g1_aff g1 = {fe_const(bn::G1X), fe_const(bn::G1Y)};
   for (uint32_t q = tid; q < c.nmul; q += 256) {
     g1_aff base = g1;
     fe k = fe_zero();
+    bool set = true;
     if (q < t) {
       base = c.blk[q]; k = c.r[q];
     } else if (q < t + 2 * l) {
@@ -299,15 +339,12 @@ __global__ void __launch_bounds__(256) kv_transcript(const VCtx *cs) {
       else { base = c.Rg1[j]; k = c.xinv[j]; }
     } else if (q == t + 2 * l) {
       base = *c.Al; k = part[0];
-    } else if (q == t + 2 * l + 1) {
-      base = c.blk[c.j - c.lo]; k = s_rho;
-    } else if (q == t + 2 * l + 2) {
-      k = s_ystar;
-    } else if (q == t + 2 * l + 3) {
-      k = s_z;
+    } else if (q < t + 2 * l + 4) {
+      if (q == t + 2 * l + 1) base = c.blk[c.j - c.lo];
+      set = false;
     }
     c.mb[q] = base;
-    c.ms[q] = k;
+    if (set) c.ms[q] = k;
   }
   // G_T jobs: L_j^{x_j}, R_j^{1/x_j}
   for (uint32_t q = tid; q < 2 * l; q += 256) {
@@ -316,47 +353,63 @@ __global__ void __launch_bounds__(256) kv_transcript(const VCtx *cs) {
   }
 }
 
-// point sums and pairing inputs, a workgroup per proof (the sum of the t + 2l products as a
-// tree of per-thread partial sums)
+// point sums and pairing inputs, three workgroups per proof (blockIdx.y), as none of the points needs
+// another:
+//   0  the sum of the t + 2l products, as a tree of per-thread partial sums;
+//   1  the first pair of the Step 2 check;
+//   2  the points of the other pairs, a thread each.
+// 0.16 ms at 2^16 entries in batches of 256, two thirds of it the tree; 0.78 with one thread for all but
+// the tree.
 __global__ void __launch_bounds__(256) kv_assemble(const VCtx *cs) {
-  const VCtx &c = cs[blockIdx.x];
-  __shared__ g1_jac sh[256];
+  const VCtx &c = cs[blockIdx.y];
   const int tid = threadIdx.x;
   const uint32_t t = c.t, l = c.lK, lM = c.lM;
-  g1_jac acc = jac_inf<OpsG1>();
-  for (uint32_t u = tid; u < t + 2 * l; u += 256) acc = jac_madd(acc, c.mo[u]);
-  sh[tid] = acc;
-  __syncthreads();
-  for (int sft = 128; sft > 0; sft >>= 1) {
-    if (tid < sft) sh[tid] = jac_add(sh[tid], sh[tid + sft]);
-    __syncthreads();
-  }
-  // G_T product C prod L^x R^{1/x} gathers in gto[0..2l] with C last
-  for (uint32_t q = tid; q < 2 * l; q += 256) c.gto[q] = c.gtp[q];
-  if (tid != 0) return;
-  *c.Cg1 = jac_to_aff(sh[0]);
-  *c.bA = c.mo[t + 2 * l];
-  g1_jac D = jac_from_aff(c.mo[t + 2 * l + 1]);
-  for (uint32_t h = 0; h < l; h++) D = jac_madd(D, c.Dsib[h]);
-  g1_aff P0 = jac_to_aff(jac_madd(D, aff_neg(c.mo[t + 2 * l + 2])));
-  g1_aff g1 = {fe_const(bn::G1X), fe_const(bn::G1Y)};
-  g2_aff g2 = {f2_const(bn::G2X0, bn::G2X1), f2_const(bn::G2Y0, bn::G2Y1)};
-  g1_aff Pk = jac_to_aff(jac_madd(jac_from_aff(*c.g1beta), aff_neg(c.mo[t + 2 * l + 3])));
-  g2_aff Qk = jac_to_aff(jac_madd(jac_from_aff(*c.vl), aff_neg(*c.fzg2)));
   // pairs: (A_l, v_l) | (beta g1 - z g1, pi_v), (-g1, v_l - f_v(z) g2) | (D* - y* g1, -g2), (W_d, s'_d g2)
-  c.pp[0] = *c.Al; c.pq[0] = *c.vl;
-  c.pp[1] = Pk; c.pq[1] = *c.piv;
-  c.pp[2] = aff_neg(g1); c.pq[2] = Qk;
-  c.pp[3] = P0; c.pq[3] = aff_neg(g2);
-  uint64_t a = c.a;
-  for (uint32_t d = 0; d < lM; d++) {
-    uint32_t var = lM - 1 - d;
-    c.pp[4 + d] = c.Wp[d];
-    g2_aff q = c.vk[var];
-    if ((a >> var) & 1) q = jac_to_aff(jac_madd(jac_from_aff(q), aff_neg(g2)));
-    c.pq[4 + d] = q;
+  const g1_aff g1 = {fe_const(bn::G1X), fe_const(bn::G1Y)};
+  const g2_aff g2 = {f2_const(bn::G2X0, bn::G2X1), f2_const(bn::G2Y0, bn::G2Y1)};
+  if (blockIdx.x == 0) {
+    __shared__ g1_jac sh[256];
+    g1_jac acc = jac_inf<OpsG1>();
+    for (uint32_t u = tid; u < t + 2 * l; u += 256) acc = jac_madd(acc, c.mo[u]);
+    sh[tid] = acc;
+    __syncthreads();
+    for (int sft = 128; sft > 0; sft >>= 1) {
+      if (tid < sft) sh[tid] = jac_add(sh[tid], sh[tid + sft]);
+      __syncthreads();
+    }
+    // G_T product C prod L^x R^{1/x} gathers in gto[0..2l] with C last
+    for (uint32_t q = tid; q < 2 * l; q += 256) c.gto[q] = c.gtp[q];
+    if (tid == 0) {
+      *c.Cg1 = jac_to_aff(sh[0]);
+      *c.bA = c.mo[t + 2 * l];
+      c.gto[2 * l] = *c.C;
+    }
+  } else if (blockIdx.x == 1) {
+    if (tid == 0) {
+      g1_jac D = jac_from_aff(c.mo[t + 2 * l + 1]);
+      for (uint32_t h = 0; h < l; h++) D = jac_madd(D, c.Dsib[h]);
+      c.pp[3] = jac_to_aff(jac_madd(D, aff_neg(c.mo[t + 2 * l + 2])));
+      c.pq[3] = aff_neg(g2);
+    } else if (tid == 64) {
+      c.pp[0] = *c.Al; c.pq[0] = *c.vl;
+      c.pp[1] = jac_to_aff(jac_madd(jac_from_aff(*c.g1beta), aff_neg(c.mo[t + 2 * l + 3])));
+      c.pq[1] = *c.piv;
+    }
+  } else {
+    // thread 0: v_l - f_v(z) g2; thread 1 + d: s'_d g2, that is s_var g2 or, with bit var of a, less g2
+    for (uint32_t q = tid; q < 1 + lM; q += 256) {
+      const uint32_t d = q - 1, var = lM - 1 - d;
+      const bool sub = q == 0 || ((uint64_t)c.a >> var & 1);
+      g2_aff Q = q == 0 ? *c.vl : c.vk[var];
+      const g2_aff S = q == 0 ? *c.fzg2 : g2;
+      if (sub) Q = jac_to_aff(jac_madd(jac_from_aff(Q), aff_neg(S)));
+      if (q == 0) {
+        c.pp[2] = aff_neg(g1); c.pq[2] = Q;
+      } else {
+        c.pp[4 + d] = c.Wp[d]; c.pq[4 + d] = Q;
+      }
+    }
   }
-  c.gto[2 * l] = *c.C;
 }
 
 // the final equalities, a thread per proof
@@ -396,8 +449,11 @@ void fe_gather(const fp12 *F, uint64_t npair, uint32_t n, fp12 *G, hipStream_t s
 void decode(const VCtx *cs, uint32_t n, uint32_t tmax, uint32_t lK, uint32_t lM, hipStream_t st) {
   LAUNCH(kv_decode, dim3(nblk(kv_items(tmax, lK, lM)), n), dim3(TPB), 0, cs);
 }
-void transcript(const VCtx *cs, uint32_t n, hipStream_t st) { LAUNCH(kv_transcript, dim3(n), dim3(256), 0, cs); }
-void assemble(const VCtx *cs, uint32_t n, hipStream_t st) { LAUNCH(kv_assemble, dim3(n), dim3(256), 0, cs); }
+void transcript(const VCtx *cs, uint32_t n, hipStream_t st) {
+  LAUNCH(kv_chains, dim3(3, n), dim3(256), 0, cs);
+  LAUNCH(kv_jobs, dim3(n), dim3(256), 0, cs);
+}
+void assemble(const VCtx *cs, uint32_t n, hipStream_t st) { LAUNCH(kv_assemble, dim3(3, n), dim3(256), 0, cs); }
 void compare(const VCtx *cs, uint32_t n, hipStream_t st) {
   LAUNCH(kv_compare, dim3((n + 63) / 64), dim3(64), 0, cs, n);
 }
@@ -832,13 +888,14 @@ __global__ void __launch_bounds__(TPB) kve_decode(VECtx c) {
   decode_item(it, c.flags);
 }
 
-// r_0, the challenges x_j, z, f_v(z) (thread 0), b_l = r_0 sum_j T_j prod_k (x_k^{-1})^{bit_{l-k}(j)}
+// r_0 (thread 0), the challenges x_j, z, f_v(z), b_l = r_0 sum_j T_j prod_k (x_k^{-1})^{bit_{l-k}(j)}
 // as a tree, and the jobs (one workgroup)
 __global__ void __launch_bounds__(256) kve_transcript(VECtx c) {
   const int tid = threadIdx.x;
   const uint32_t l = c.lK, lM = c.lM;
   __shared__ fe part[256];
   __shared__ fe s_r0, s_z;
+  __shared__ uint32_t lds[sha::SCHED_WORDS + 512];
   if (tid == 0) {
     sha::Hasher hs;
     hs.init();
@@ -854,42 +911,8 @@ __global__ void __launch_bounds__(256) kve_transcript(VECtx c) {
     hx.u64(0);
     s_r0 = sha::xmd_finish_fr(hx, DSTR_EVAL);
   }
-  // round challenges, the workgroup hashing together (as in kv_transcript)
-  __shared__ uint32_t xmsg[16 + 8 + 2 * (96 + 16) + 32], xt2[16], sched[sha::SCHED_WORDS];
-  for (uint32_t j = 0; j < l; j++) {
-    const int pre = j > 0 ? 8 : 0;
-    const int e = j > 0 ? tid - 1 : tid;
-    if (j > 0 && tid == 0) sha::put_words<FpR>(xmsg + 16, c.x[j - 1]);
-    if (e >= 0 && e < 28) {
-      int side = e / 14, q = e % 14;
-      const fe *src = q < 12 ? reinterpret_cast<const fe *>(side ? c.Rgt + j : c.Lgt + j) + q
-                             : reinterpret_cast<const fe *>(side ? c.Rg1 + j : c.Lg1 + j) + (q - 12);
-      sha::put_words<FpP>(xmsg + 16 + pre + 112 * side + 8 * q, *src);
-    }
-    __syncthreads();
-    fe x = sha::xmd_fr_coop(sha::Coop{tid, 256, sched}, xmsg, 4 * (pre + 224), DSTR_FC_X, xt2);
-    fe xi = f_inv_uniform<FpR>(x, bn::R_R3);
-    if (tid == 0) {
-      if (fe_is_zero(x)) atomicOr(c.flags, VFLAG_BAD_PROOF);
-      c.x[j] = x;
-      c.xinv[j] = xi;
-    }
-    __syncthreads();
-  }
-  if (tid == 0) {
-    sha::Hasher hz;
-    sha::xmd_begin(hz);
-    hz.field<FpR>(c.x[l - 1]);
-    hz.g2(*c.vl);
-    fe z = sha::xmd_finish_fr(hz, DSTR_FC_Z);
-    fe fz = f_one<FpR>(), zp = fr_mul(z, z);
-    for (int j = (int)l; j >= 1; j--) {
-      fz = fr_mul(fz, fr_add(f_one<FpR>(), fr_mul(c.xinv[j - 1], zp)));
-      zp = fr_mul(zp, zp);
-    }
-    s_z = z;
-    c.g2s[0] = fz;
-  }
+  const fe z = challenge_chain(c, l, lds, c.g2s);
+  if (tid == 0) s_z = z;
   __syncthreads();
   fe acc = fe_zero();
   for (uint64_t j = tid; j < c.K; j += 256) {
@@ -931,36 +954,40 @@ __global__ void __launch_bounds__(256) kve_transcript(VECtx c) {
   }
 }
 
-// point sums and the pairs (one thread)
-__global__ void __launch_bounds__(64) kve_assemble(VECtx c) {
-  if (gtid() != 0) return;
-  const uint32_t l = c.lK, lM = c.lM;
-  g1_jac acc = jac_from_aff(c.mo[2 * l + 1]);  // r_0 C_F
-  for (uint32_t u = 0; u < 2 * l; u++) acc = jac_madd(acc, c.mo[u]);
-  *c.Cg1 = jac_to_aff(acc);
-  *c.bA = c.mo[2 * l];
-  g1_aff g1 = {fe_const(bn::G1X), fe_const(bn::G1Y)};
-  g2_aff g2 = {f2_const(bn::G2X0, bn::G2X1), f2_const(bn::G2Y0, bn::G2Y1)};
-  g1_aff Pk = jac_to_aff(jac_madd(jac_from_aff(*c.g1beta), aff_neg(c.mo[2 * l + 3])));
-  g2_aff Qk = jac_to_aff(jac_madd(jac_from_aff(*c.vl), aff_neg(c.g2o[0])));
-  g1_aff P0 = jac_to_aff(jac_madd(jac_from_aff(*c.CF), aff_neg(c.mo[2 * l + 2])));
+// point sums and the pairs, a thread for each point (blockIdx.x 0: on G1, 1: on G2)
+__global__ void __launch_bounds__(256) kve_assemble(VECtx c) {
+  const uint32_t l = c.lK, lM = c.lM, tid = threadIdx.x;
+  const g1_aff g1 = {fe_const(bn::G1X), fe_const(bn::G1Y)};
+  const g2_aff g2 = {f2_const(bn::G2X0, bn::G2X1), f2_const(bn::G2Y0, bn::G2Y1)};
   // pairs: (A_l, v_l) | (beta g1 - z g1, pi_v), (-g1, v_l - f_v(z) g2) | (C_F - y g1, -g2), (W_d, (s - r)_var g2)
-  c.pp[0] = *c.Al; c.pq[0] = *c.vl;
-  c.pp[1] = Pk; c.pq[1] = *c.piv;
-  c.pp[2] = aff_neg(g1); c.pq[2] = Qk;
-  c.pp[3] = P0; c.pq[3] = aff_neg(g2);
-  for (uint32_t d = 0; d < lM; d++) {
-    c.pp[4 + d] = c.W[d];
-    c.pq[4 + d] = jac_to_aff(jac_madd(jac_from_aff(c.vk[lM - 1 - d]), aff_neg(c.g2o[1 + d])));
+  if (blockIdx.x == 0) {
+    if (tid == 0) {
+      g1_jac acc = jac_from_aff(c.mo[2 * l + 1]);  // r_0 C_F
+      for (uint32_t u = 0; u < 2 * l; u++) acc = jac_madd(acc, c.mo[u]);
+      *c.Cg1 = jac_to_aff(acc);
+      *c.bA = c.mo[2 * l];
+    } else if (tid == 64 || tid == 65) {
+      const bool p0 = tid == 65;
+      c.pp[p0 ? 3 : 1] = jac_to_aff(jac_madd(jac_from_aff(p0 ? *c.CF : *c.g1beta), aff_neg(c.mo[2 * l + (p0 ? 2 : 3)])));
+      c.pq[p0 ? 3 : 1] = p0 ? aff_neg(g2) : *c.piv;
+    } else if (tid == 128) {
+      c.pp[0] = *c.Al; c.pq[0] = *c.vl;
+      c.gto[2 * l] = *c.C;
+    }
+    for (uint32_t q = tid; q < 2 * l; q += 256) c.gto[q] = c.gtp[q];
+    return;
   }
-  for (uint32_t q = 0; q < 2 * l; q++) c.gto[q] = c.gtp[q];
-  c.gto[2 * l] = *c.C;
+  for (uint32_t q = tid; q < 1 + lM; q += 256) {
+    const g2_aff Q = jac_to_aff(jac_madd(jac_from_aff(q == 0 ? *c.vl : c.vk[lM - q]), aff_neg(c.g2o[q])));
+    c.pp[q == 0 ? 2 : 3 + q] = q == 0 ? aff_neg(g1) : c.W[q - 1];
+    c.pq[q == 0 ? 2 : 3 + q] = Q;
+  }
 }
 
 namespace kve {
 void decode(const VECtx &c, hipStream_t st) { L1(kve_decode, kve_items(c.lK, c.lM, c.L), c); }
 void transcript(const VECtx &c, hipStream_t st) { LAUNCH(kve_transcript, dim3(1), dim3(256), 0, c); }
-void assemble(const VECtx &c, hipStream_t st) { LAUNCH(kve_assemble, dim3(1), dim3(64), 0, c); }
+void assemble(const VECtx &c, hipStream_t st) { LAUNCH(kve_assemble, dim3(2), dim3(256), 0, c); }
 }  // namespace kve
 
 // ------------------------------------------------------------------ all sub-array proofs at once

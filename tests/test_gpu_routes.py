@@ -37,3 +37,22 @@ def test_verify_products(vc, L, b):
     bad = proofs.clone()
     bad[32 * b + 384 + 20] ^= 1  # L_g1 of round 1 of the first batch
     assert vc.vc_verify_all(pp, cm.C, b, le, bad, seed)[0] == 0
+
+
+@pytest.mark.parametrize("b", [31, 33, 64])
+def test_verify_chunks(vc, b):
+    """Batches whose last chunk of 32 block commitments is short, one over, or full (2^12 entries,
+    64 subvectors): a proof of the first and of the last batch verifies, with another entry it does
+    not."""
+    L = 12
+    print("verify L=%d b=%d" % (L, b), flush=True)
+    limbs = I.entries(1 << L, 90 + b, 256)
+    ints = I.limbs_to_ints(limbs)
+    m = torch.from_numpy(np.ascontiguousarray(limbs).view(np.uint8).reshape(-1).copy()).cuda()
+    pp = vc.vc_setup(L, I.TRAPDOOR_SEED, 0)
+    cm = vc.vc_commit(pp, m, 256)
+    pr = vc.vc_open_all(pp, cm, b)
+    for i in (0, (1 << L) - 1):
+        proof = vc.vc_proof_get(pr, i)
+        assert vc.vc_verify(pp, cm.C, b, i, ints[i], proof) == 1, i
+        assert vc.vc_verify(pp, cm.C, b, i, ints[i] ^ 1, proof) == 0, i
