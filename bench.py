@@ -133,7 +133,7 @@ def method_work(L, b, limbs, c):
         j0 += 1
     direct = [j for j, _ in rounds if not ahead or j < j0]
     taken = [j for j, _ in rounds if ahead and j >= j0]
-    by_kernel = {"k_msm_slices<OpsG1>": msm, "ks_miller": mpair(K),
+    by_kernel = {"k_msm_slices<lane::G1>": msm, "ks_miller": mpair(K),
                  "ks_oa_pterms": sum(miller[j] for j in taken),
                  "ks_final_exp2": sum(fexp[j] for j in taken),
                  "ks_final_exp": sum(fexp[j] for j in direct) + c["final_exp"]}
@@ -157,7 +157,7 @@ def work_model(L, b, limbs, costs):
     g2_fold = costs["e_g2_mul"] + costs["e_g2_madd"] + costs["e_g2_to_aff"]
     nq = 2 * K - 2
     w = {
-        "k_msm_slices<OpsG1>": nz_digits * costs["g1_madd"] + blocks * 2048 * costs["g1_add"],
+        "k_msm_slices<lane::G1>": nz_digits * costs["g1_madd"] + blocks * 2048 * costs["g1_add"],
         "ks_miller": K * costs["e_miller"],
         "kw_hyper_terms": lM * (M // 2) * costs["g1_mul"],
     }
@@ -169,7 +169,7 @@ def work_model(L, b, limbs, costs):
         w["ks_jac_tree<true>"] = nb * (4 * nq - 1) * costs["e_g2_add"]
     else:
         kzg_blocks = nb * (-(-nq // 32))
-        w["k_msm_slices<OpsG2>"] = (nb * nq * 32 * 255 // 256) * costs["g2_madd"] + kzg_blocks * 510 * costs["g2_add"]
+        w["k_msm_slices<lane::G2>"] = (nb * nq * 32 * 255 // 256) * costs["g2_madd"] + kzg_blocks * 510 * costs["g2_add"]
         w["ks_jac_tree<true>"] = (kzg_blocks - nb) * costs["e_g2_add"]
     if lK >= 2 and nb * K <= AHEAD_MAX_PAIRS:
         # rounds j < j0 direct (the device is full), rounds j >= j0 from terms of the arrays of
@@ -330,7 +330,7 @@ def batched_jobs(V, torch, n_jobs=64, seed=5, setups=BATCH_SETUPS, reps=2, peak=
         # what the library executes for it
         fmul += method_work(L, min(L * L, pp.K), limbs, costs)["open_all"]
         w = work_model(L, min(L * L, pp.K), limbs, costs)
-        fexec += sum(v for k, v in w.items() if k not in ("k_msm_slices<OpsG1>", "ks_miller"))
+        fexec += sum(v for k, v in w.items() if k not in ("k_msm_slices<lane::G1>", "ks_miller"))
         m = torch.from_numpy(np.ascontiguousarray(limbs).view(np.uint8).reshape(-1).copy()).cuda()
         ents.append((pp, m, 256))
         jobs.append((pp, V.vc_commit(pp, m, 256), min(L * L, pp.K)))
@@ -792,7 +792,7 @@ def main():
     kernels = {k: {"launches": c // psteps, "ms_per_step": round(ms / psteps, 4),
                    "share": round(ms / total_prof, 4) if total_prof else None}
                for k, (c, ms) in sorted(prof.items(), key=lambda kv: -kv[1][1])}
-    msm_ms = (prof.get("k_msm_slices<OpsG1>", (0, 0))[1] + prof.get("kw_sum_g1", (0, 0))[1]) / psteps
+    msm_ms = (prof.get("k_msm_slices<lane::G1>", (0, 0))[1] + prof.get("kw_sum_g1", (0, 0))[1]) / psteps
     tops = lambda fm, ms: fm * MADS_PER_FMUL / (ms / 1e3) / 1e12   # 10^12 multiply-adds per second
     open_med = statistics.median(open_ms)
     extra = {"commit_ms": round(statistics.median(commit_ms), 3),
@@ -809,7 +809,7 @@ def main():
         limbs2, _, _, p2, _ = run_workload(V, torch, L2, b2, 256, 3, 1, 1)
         _, c2, o2, _, _ = run_workload(V, torch, L2, b2, 256, 3, n2, 1, profile=None)
         method2 = method_work(L2, b2, limbs2, costs)
-        msm2 = p2.get("k_msm_slices<OpsG1>", (0, 0))[1] + p2.get("kw_sum_g1", (0, 0))[1]
+        msm2 = p2.get("k_msm_slices<lane::G1>", (0, 0))[1] + p2.get("kw_sum_g1", (0, 0))[1]
         fbytes = fold_bytes(L2)
         fold_k = sorted(k for k in p2 if k.startswith("k_ytree"))
         fold_ms = sum(p2[k][1] for k in fold_k)

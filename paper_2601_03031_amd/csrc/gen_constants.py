@@ -77,6 +77,8 @@ w(arr("R_R1", RM % R))  # 2^256 mod r
 bt = f2mul((3, 0), f2inv(XI))
 w(arr("TWIST_B0", mont(bt[0])))
 w(arr("TWIST_B1", mont(bt[1])))
+# 3 b' for the one-lane formulas, radix 2^29 with factor 2^261
+w("static constexpr uint32_t TWIST_3B29[2][9] = {%s};" % ", ".join("{%s}" % ", ".join("0x%08xu" % ((3 * c * 2**261 % P) >> (29 * i) & 0x1fffffff) for i in range(9)) for c in bt))
 # Frobenius coefficients: gamma1[k] = xi^{k(p-1)/6}, gamma2[k] = xi^{k(p^2-1)/6} (in F_p),
 # gamma3[k] = xi^{k(p^3-1)/6}
 g1 = [f2pow(XI, k * (P - 1) // 6) for k in range(6)]

@@ -9,6 +9,7 @@
 #include "pairing.hpp"
 #include "hash.hpp"
 #include "slp.hpp"
+#include "lane29.hpp"
 #include "gls.hpp"
 #include "g2mul.hpp"
 #include "gtpow.hpp"
@@ -893,6 +894,27 @@ API uint64_t hc_engine_muls(int which) {
   return 0;
 }
 
+
+// The one-lane group law: sum of n affine points as mixed additions of the first m to the identity,
+// of the others to the identity, and the two sums added
+template <class L, class A> static A lane_sum(const A *p, int n, int m) {
+  lane::pt<L> s[2] = {lane::identity<L>(), lane::identity<L>()};
+  for (int i = 0; i < n; i++)
+    if (!aff_is_inf(p[i])) s[i >= m] = lane::madd<L>(s[i >= m], L::in(p[i].x), L::in(p[i].y));
+  return jac_to_aff(lane::to_jac<L>(lane::add<L>(s[0], s[1])));
+}
+API int hc_lane_sum(int grp, const uint8_t *pts, int n, int m, uint8_t *out) {
+  if (grp == 0) {
+    g1_aff p[64];
+    for (int i = 0; i < n; i++) p[i] = rdg1(pts + 64 * i);
+    wrg1(out, lane_sum<lane::G1>(p, n, m));
+  } else {
+    g2_aff p[64];
+    for (int i = 0; i < n; i++) p[i] = rdg2(pts + 128 * i);
+    wrg2(out, lane_sum<lane::G2>(p, n, m));
+  }
+  return 0;
+}
 
 // k P on G1 through the GLV split (host build of the device formulas); P, out affine BE
 API int hc_g1_mul_glv(const uint8_t *Pb, const uint8_t *kb, uint8_t *out, uint8_t *dec_out) {

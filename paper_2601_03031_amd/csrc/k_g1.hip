@@ -3,6 +3,7 @@
 // points went through scratch memory)
 #define VC_INLINE_HELPERS 1
 #include "kcommon.hpp"
+#include "lane29.hpp"
 
 #define MSM_MAXE 8192
 #define MSM_G2_MAXE 8192  // S nwin for the G2 MSM (with its 256 Jacobian G2 points, 48 KB, 82 KB of LDS)
@@ -126,78 +127,101 @@ __global__ void __launch_bounds__(TPB) k_check_curve(const aff<O> *p, uint64_t n
 // scan.  S nwin <= MSM_MAXE (G1), MSM_G2_MAXE (G2).  (A tree over bucket ranges that merges
 // (S, W) pairs with doublings does a quarter of the scan's additions but measured slower:
 // with one block per CU at N = 2^16 the block's latency sets the time, and its doubling
-// chains are longer than the scan's eight steps.)  One (j, slice) block: blk = j nslice + slice.
-template <class O>
-__device__ __forceinline__ void msm_slice(const fe *scal, uint64_t M, uint32_t nwin, uint32_t S, const aff<O> *table,
-                                          jac<O> *partial, uint64_t blk) {
+// chains are longer than the scan's eight steps.)  Bound by the issue of its products: the
+// complete additions on one-lane limbs (lane29.hpp) take 1024 rows of 1024 bases in 4.2 ms, Jacobian
+// ones on packed elements took 6.5.  A block takes g consecutive slices of a row (g divides their
+// number): blk = (j nslice + slice) / g, and leaves their sum in the first one's place.
+template <class L>
+__device__ __forceinline__ void msm_slice(const fe *scal, uint64_t M, uint32_t nwin, uint32_t S, const aff<typename L::O> *table,
+                                          jac<typename L::O> *partial, uint64_t blk, uint32_t g) {
+  typedef lane::pt<L> pt;
   __shared__ uint32_t cnt[256];
   __shared__ uint32_t off[256];
-  constexpr uint32_t MAXE = sizeof(typename O::T) > sizeof(fe) ? MSM_G2_MAXE : MSM_MAXE;
+  constexpr uint32_t MAXE = sizeof(typename L::T) > sizeof(lane::fl) ? MSM_G2_MAXE : MSM_MAXE;
   // the sorted digits and, once the buckets are summed, the bucket sums share one array
-  constexpr size_t ENT_B = MAXE * sizeof(uint32_t), RED_B = 256 * sizeof(jac<O>);
+  constexpr size_t ENT_B = MAXE * sizeof(uint32_t), RED_B = 256 * sizeof(pt);
   __shared__ __align__(16) uint8_t pool[ENT_B > RED_B ? ENT_B : RED_B];
   uint32_t *ent = reinterpret_cast<uint32_t *>(pool);
-  jac<O> *red = reinterpret_cast<jac<O> *>(pool);
-  uint32_t nslice = (uint32_t)((M + S - 1) / S);
-  uint64_t j = blk / nslice;
-  uint32_t sl = blk % nslice;
-  uint64_t a0 = (uint64_t)sl * S;
-  uint32_t na = (uint32_t)((a0 + S <= M) ? S : (M - a0));
-  uint32_t t = threadIdx.x;
-  cnt[t] = 0;
-  __syncthreads();
-  const fe *sc = scal + j * M + a0;
-  uint32_t ne = na * nwin;
-  for (uint32_t e = t; e < ne; e += 256) {
-    uint32_t a = e / nwin, w = e % nwin;
-    uint32_t d = (sc[a].l[w >> 2] >> ((w & 3) * 8)) & 0xff;
-    if (d) atomicAdd(&cnt[d], 1u);
-  }
-  __syncthreads();
-  if (t == 0) {
-    uint32_t s = 0;
-    for (int d = 0; d < 256; d++) { off[d] = s; s += cnt[d]; }
-  }
-  __syncthreads();
-  uint32_t start = off[t], len = cnt[t];
-  __syncthreads();
-  for (uint32_t e = t; e < ne; e += 256) {
-    uint32_t a = e / nwin, w = e % nwin;
-    uint32_t d = (sc[a].l[w >> 2] >> ((w & 3) * 8)) & 0xff;
-    if (d) {
-      uint32_t pos = atomicAdd(&off[d], 1u);
-      ent[pos] = w * (uint32_t)M + (uint32_t)(a0 + a);
+  pt *red = reinterpret_cast<pt *>(pool);
+  const uint32_t nslice = (uint32_t)((M + S - 1) / S);
+  const uint64_t j = blk * g / nslice;
+  const uint32_t t = threadIdx.x;
+  pt acc = lane::identity<L>();
+#pragma unroll 1
+  for (uint32_t sl = blk * g % nslice, sub = 0; sub < g; sl++, sub++) {
+    const uint64_t a0 = (uint64_t)sl * S;
+    const uint32_t na = (uint32_t)((a0 + S <= M) ? S : (M - a0));
+    cnt[t] = 0;
+    __syncthreads();  // (also: the digits of the slice before are read)
+    const fe *sc = scal + j * M + a0;
+    const uint32_t ne = na * nwin;
+    for (uint32_t e = t; e < ne; e += 256) {
+      uint32_t a = e / nwin, w = e % nwin;
+      uint32_t d = (sc[a].l[w >> 2] >> ((w & 3) * 8)) & 0xff;
+      if (d) atomicAdd(&cnt[d], 1u);
+    }
+    __syncthreads();
+    if (t == 0) {
+      uint32_t s = 0;
+      for (int d = 0; d < 256; d++) { off[d] = s; s += cnt[d]; }
+    }
+    __syncthreads();
+    const uint32_t start = off[t], len = t ? cnt[t] : 0;
+    __syncthreads();
+    for (uint32_t e = t; e < ne; e += 256) {
+      uint32_t a = e / nwin, w = e % nwin;
+      uint32_t d = (sc[a].l[w >> 2] >> ((w & 3) * 8)) & 0xff;
+      if (d) {
+        uint32_t pos = atomicAdd(&off[d], 1u);
+        ent[pos] = w * (uint32_t)M + (uint32_t)(a0 + a);
+      }
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (uint32_t q = 0; q < len; q++) {
+      const aff<typename L::O> p = table[ent[start + q]];
+      if (!aff_is_inf(p)) acc = lane::madd<L>(acc, L::in(p.x), L::in(p.y));
     }
   }
-  __syncthreads();
-  jac<O> acc = jac_inf<O>();
-  for (uint32_t q = 0; q < len; q++) acc = jac_madd(acc, table[ent[start + q]]);
-  if (t == 0) acc = jac_inf<O>();
   __syncthreads();  // every bucket is summed before the sums overwrite the digits
   red[t] = acc;
   __syncthreads();
   // suffix sums T_d = sum_{d' >= d} B_{d'}
+#pragma unroll 1
   for (uint32_t s = 1; s < 256; s <<= 1) {
-    jac<O> v = red[t];
-    if (t + s < 256) v = jac_add(v, red[t + s]);
+    pt v = red[t];
+    if (t + s < 256) v = lane::add<L>(v, red[t + s]);
     __syncthreads();
     red[t] = v;
     __syncthreads();
   }
-  if (t == 0) red[0] = jac_inf<O>();
+  if (t == 0) red[0] = lane::identity<L>();
   __syncthreads();
   // sum_{d >= 1} T_d
+#pragma unroll 1
   for (uint32_t s = 128; s >= 1; s >>= 1) {
-    if (t < s) red[t] = jac_add(red[t], red[t + s]);
+    if (t < s) red[t] = lane::add<L>(red[t], red[t + s]);
     __syncthreads();
   }
-  if (t == 0) partial[blk] = red[0];
+  if (t == 0) partial[blk * g] = lane::to_jac<L>(red[0]);
+  else if (t < g) partial[blk * g + t] = jac_inf<typename L::O>();
 }
 
-template <class O>
+template <class L>
 __global__ void __launch_bounds__(256) k_msm_slices(const fe *scal, uint64_t M, uint32_t nwin, uint32_t S,
-                                                    const aff<O> *table, jac<O> *partial) {
-  msm_slice<O>(scal, M, nwin, S, table, partial, blockIdx.x);
+                                                    const aff<typename L::O> *table, jac<typename L::O> *partial, uint32_t g) {
+  msm_slice<L>(scal, M, nwin, S, table, partial, blockIdx.x, g);
+}
+
+// Slices of a row that one block sums into its buckets before it reduces them: as many (a power of
+// two, up to 8) as leave MIN_BLOCKS blocks, two rounds of the 512 that are resident: the reduction of
+// a block is worth 20 additions in every thread, its digits 32 a slice (2^20 entries, four slices a
+// row: 4.2 ms against 4.4 with a block for each).
+static uint32_t msm_group(uint64_t K, uint64_t nslice) {
+  static constexpr uint64_t MIN_BLOCKS = 1024;
+  uint32_t g = 1;
+  while (g < 8 && nslice % (2 * g) == 0 && K * nslice / (2 * g) >= MIN_BLOCKS) g *= 2;
+  return g;
 }
 
 // ================================================================ batched commit
@@ -228,7 +252,7 @@ __device__ __forceinline__ uint32_t job_of_k(const CJob *J, uint32_t n, uint64_t
 __global__ void __launch_bounds__(256) k_msm_batch(const CJob *J, uint32_t n, uint64_t total) {
   for (uint64_t b = blockIdx.x; b < total; b += gridDim.x) {
     const CJob &c = J[job_of_blk(J, n, b)];
-    msm_slice<OpsG1>(c.m, c.M, c.nwin, c.S, c.table, c.part, b - c.blk0);
+    msm_slice<lane::G1>(c.m, c.M, c.nwin, c.S, c.table, c.part, b - c.blk0, 1);
     __syncthreads();  // the next block reuses the shared arrays
   }
 }
@@ -410,8 +434,9 @@ void diag_mad(uint32_t seed, uint32_t iters, unsigned blocks, uint64_t *out, hip
 }
 void msm_slices(const fe *scal, uint64_t K, uint64_t M, uint32_t nwin, uint32_t S, const g1_aff *table, g1_jac *partial,
                 hipStream_t st) {
-  uint64_t nslice = (M + S - 1) / S;
-  LAUNCH(k_msm_slices<OpsG1>, dim3((unsigned)(K * nslice)), dim3(256), 0, scal, M, nwin, S, table, partial);
+  const uint64_t nslice = (M + S - 1) / S;
+  const uint32_t g = msm_group(K, nslice);
+  LAUNCH(k_msm_slices<lane::G1>, dim3((unsigned)(K * nslice / g)), dim3(256), 0, scal, M, nwin, S, table, partial, g);
 }
 void msm_batch(const CJob *J, uint32_t n, uint64_t total, unsigned grid, hipStream_t st) {
   if (total) LAUNCH(k_msm_batch, dim3(grid), dim3(256), 0, J, n, total);
@@ -430,8 +455,9 @@ void commit_pad(const CJob *J, uint32_t n, uint64_t Kmax, const fp12 *Fc, fp12 *
 void commit_store(const CJob *J, uint32_t n, const fp12 *Cs, hipStream_t st) { L1(k_commit_store, n, J, n, Cs); }
 void msm_slices_g2(const fe *scal, uint64_t K, uint64_t M, uint32_t nwin, uint32_t S, const g2_aff *table, g2_jac *partial,
                    hipStream_t st) {
-  uint64_t nslice = (M + S - 1) / S;
-  LAUNCH(k_msm_slices<OpsG2>, dim3((unsigned)(K * nslice)), dim3(256), 0, scal, M, nwin, S, table, partial);
+  const uint64_t nslice = (M + S - 1) / S;
+  const uint32_t g = msm_group(K, nslice);
+  LAUNCH(k_msm_slices<lane::G2>, dim3((unsigned)(K * nslice / g)), dim3(256), 0, scal, M, nwin, S, table, partial, g);
 }
 void fr_canon(const fe *in, uint64_t n, fe *out, hipStream_t st) { L1(k_fr_canon, n, in, n, out); }
 void g1_reduce(g1_jac *data, uint64_t nseg, uint64_t stride, uint64_t len, uint32_t *cnt, hipStream_t st) {
