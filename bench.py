@@ -43,7 +43,8 @@ TRAFFIC_BYTES = {"ks_final_exp2": round((417.0 * 2.000 + 14.2 * 1.000) * 1024),
 FOLD_SPLIT_MAX = 256                       # folds of at most this many pairs run split in four parts
 DIRECT_MIN = 512                           # rounds of more pairs than this run direct in the ahead mode
 KZG_SPLIT_MAX = 8192                       # KZG proofs of at most this many split jobs run split
-WIDE_FOLD_MIN = 4096                       # direct-round Miller loops / G2 folds of this many pairs run wide
+WIDE_FOLD_MIN = 4096
+LANE_MIN = 4096                       # direct-round Miller loops / G2 folds of this many pairs run wide
 
 
 def op_costs():
@@ -154,12 +155,13 @@ def work_model(L, b, limbs, costs):
     nz_digits = int(np.count_nonzero(np.ascontiguousarray(limbs).view(np.uint8)))
     S = min(M, 8192 // (4 if int(limbs[:, 1:].max()) == 0 else 32))
     blocks = K * ((M + S - 1) // S)
+    g1_fold = costs["e_g1_mul"] + costs["e_g1_madd"] + costs["e_g1_to_aff"]
     g2_fold = costs["e_g2_mul"] + costs["e_g2_madd"] + costs["e_g2_to_aff"]
     nq = 2 * K - 2
     w = {
         "k_msm_slices<lane::G1>": nz_digits * costs["g1_madd"] + blocks * 2048 * costs["g1_add"],
         "ks_miller": K * costs["e_miller"],
-        "kw_hyper_terms": lM * (M // 2) * costs["g1_mul"],
+        "kn_hyper_terms": lM * (M // 2) * costs["g1_mul"],
     }
     # KZG proof: with few terms, split multiplications; otherwise a G2 MSM over 8-bit windows
     # of the fixed SRS points (about 255/256 of the (term, window) pairs have a nonzero digit;
@@ -180,14 +182,14 @@ def work_model(L, b, limbs, costs):
         direct = [K >> j for j in range(1, j0)]
         nbr = lambda h: 1 if h == K // 2 else nb   # round 1's pairings are computed once for all batches
         qs = [K >> j for j in range(j0, lK + 1)]
-        g1_fold = costs["e_g1_mul"] + costs["e_g1_madd"] + costs["e_g1_to_aff"]
         split = [nb * h for h in rounds if nb * h <= FOLD_SPLIT_MAX]
         whole = [nb * h for h in rounds if nb * h > FOLD_SPLIT_MAX]
         g1_sum = 3 * costs["e_g1_add"] + costs["e_g1_madd"] + costs["e_g1_to_aff"]
         g2_sum = 3 * costs["e_g2_add"] + costs["e_g2_madd"] + costs["e_g2_to_aff"]
         w.update({
             "ks_oa_miller": sum(nbr(h) * 2 * h for h in direct) * costs["e_miller"],
-            "ks_oa_g1terms": sum(nb * 2 * h for h in direct) * costs["e_g1_mul"],
+            "ks_oa_g1terms": sum(nb * 2 * h for h in direct if nb * 2 * h < LANE_MIN) * costs["e_g1_mul"],
+            "kn_oa_g1terms": sum(nb * 2 * h for h in direct if nb * 2 * h >= LANE_MIN) * costs["g1_mul"],
             "ks_final_exp": (sum(2 * nbr(h) for h in direct) + 1) * costs["e_final_exp"],
             "ks_f12_tree": (K - 1 + sum(2 * nbr(h) * (h - 1) for h in direct)
                             + sum(2 * nb * (2 * q - 1) + 4 * nb * (q - 1) for q in qs)) * costs["e_f12_mul"],
@@ -223,9 +225,11 @@ def work_model(L, b, limbs, costs):
             "kw_oa_miller": sum(nbr(h) * 2 * h for h in wide) * costs["miller"],
             "ks_final_exp": (sum(2 * nbr(h) for h in rounds) + 1) * costs["e_final_exp"],
             "ks_f12_tree": (K - 1 + sum(2 * nbr(h) * (h - 1) for h in rounds)) * costs["e_f12_mul"],
-            "ks_oa_fold_g2": sum(nb * h for h in rounds) * g2_fold,
-            "kw_oa_fold_g1": sum(nb * h for h in rounds) * (costs["g1_mul"] + costs["g1_madd"] + costs["g1_to_aff"]),
-            "kw_oa_g1terms": sum(nb * 2 * h for h in rounds) * costs["g1_mul"],
+            "kn_oa_fold_g2": sum(nb * h for h in rounds if nb * h >= LANE_MIN) * g2_fold,
+            "kn_oa_fold_g1": sum(nb * h for h in rounds if nb * h >= LANE_MIN) * g1_fold,
+            "ks_oa_fold": sum(nb * h for h in rounds if nb * h < LANE_MIN) * (g1_fold + g2_fold),
+            "kn_oa_g1terms": sum(nb * 2 * h for h in rounds if nb * 2 * h >= LANE_MIN) * costs["g1_mul"],
+            "ks_oa_g1terms": sum(nb * 2 * h for h in rounds if nb * 2 * h < LANE_MIN) * costs["e_g1_mul"],
         })
     return w
 

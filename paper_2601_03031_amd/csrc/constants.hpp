@@ -23,7 +23,8 @@ static constexpr uint32_t P_R3[8] = {0xda1530dfu, 0xb1cd6dafu, 0xa7283db6u, 0x62
 static constexpr uint32_t R_R1[8] = {0x4ffffffbu, 0xac96341cu, 0x9f60cd29u, 0x36fc7695u, 0x7879462eu, 0x666ea36fu, 0x9a07df2fu, 0x0e0a77c1u};
 static constexpr uint32_t TWIST_B0[8] = {0x77b802a8u, 0x3bf938e3u, 0x3633535du, 0x020b1b27u, 0x49755260u, 0x26b7edf0u, 0x4384a86du, 0x2514c632u};
 static constexpr uint32_t TWIST_B1[8] = {0xd1dcff67u, 0x38e7ecccu, 0x93ce0d3eu, 0x65f0b37du, 0x22ac00aau, 0xd749d0ddu, 0x4a688d4du, 0x0141b9ceu};
-static constexpr uint32_t TWIST_3B29[2][9] = {{0x095cc5c1u, 0x016b1649u, 0x13202c16u, 0x05967b15u, 0x0b150904u, 0x0c884f0eu, 0x1423d855u, 0x02e3530fu, 0x001b2ff4u}, {0x01e5cc12u, 0x15bda508u, 0x18588eb7u, 0x00f3e938u, 0x18f2b0b4u, 0x03bffebeu, 0x13752c37u, 0x0ec49a37u, 0x0017dd10u}};
+static constexpr int32_t P_ONE29[9] = {-176370655, -199481511, -128831276, 21759002, 178483129, -45989682, -237679608, 86689705, 903222};
+static constexpr int32_t TWIST_3B29[2][9] = {{157074881, 23795273, -215995370, 93747990, 185927940, 210259726, -198977451, 48452368, 1781748}, {31837202, -172120824, -128414024, 15984953, -118312780, 62914239, -210424777, 247765560, 1563920}};
 static constexpr uint32_t FROB1_1_0[8] = {0x33144907u, 0xaf9ba696u, 0x87afb78au, 0xca6b1d73u, 0xf08a2087u, 0x11bded5eu, 0x1a1f3a7cu, 0x02f34d75u};
 static constexpr uint32_t FROB1_1_1[8] = {0x4c492d72u, 0xa222ae23u, 0x565de15bu, 0xd00f02a4u, 0x53dfc926u, 0xdc2ff3a2u, 0xb3899551u, 0x10a75716u};
 static constexpr uint32_t FROB2_1[8] = {0x00fa1bf2u, 0xca8d8005u, 0x68b39769u, 0xf0c5d614u, 0xad0d4418u, 0x0e201271u, 0xbad856e6u, 0x04290f65u};

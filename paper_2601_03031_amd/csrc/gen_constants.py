@@ -77,8 +77,23 @@ w(arr("R_R1", RM % R))  # 2^256 mod r
 bt = f2mul((3, 0), f2inv(XI))
 w(arr("TWIST_B0", mont(bt[0])))
 w(arr("TWIST_B1", mont(bt[1])))
-# 3 b' for the one-lane formulas, radix 2^29 with factor 2^261
-w("static constexpr uint32_t TWIST_3B29[2][9] = {%s};" % ", ".join("{%s}" % ", ".join("0x%08xu" % ((3 * c * 2**261 % P) >> (29 * i) & 0x1fffffff) for i in range(9)) for c in bt))
+
+
+def centred29(x):
+    """radix 2^29, limbs 0 .. 7 in [-2^28, 2^28)"""
+    v = []
+    for i in range(9):
+        d = x & 0x1fffffff
+        if i < 8 and d >= 1 << 28:
+            d -= 1 << 29
+        v.append(d if i < 8 else x)
+        x = (x - d) >> 29
+    return "{%s}" % ", ".join(map(str, v))
+
+
+# for the one-lane formulas, with factor 2^261: 1 and 3 b'
+w("static constexpr int32_t P_ONE29[9] = %s;" % centred29(2**261 % P))
+w("static constexpr int32_t TWIST_3B29[2][9] = {%s};" % ", ".join(centred29(3 * c * 2**261 % P) for c in bt))
 # Frobenius coefficients: gamma1[k] = xi^{k(p-1)/6}, gamma2[k] = xi^{k(p^2-1)/6} (in F_p),
 # gamma3[k] = xi^{k(p^3-1)/6}
 g1 = [f2pow(XI, k * (P - 1) // 6) for k in range(6)]

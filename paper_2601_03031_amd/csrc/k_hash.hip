@@ -111,16 +111,6 @@ __global__ void __launch_bounds__(64) k_fc_r(uint64_t K, uint32_t b, uint64_t nb
   if (t == 0) B[kk * K + a] = r;
 }
 
-// affine G1 parts of L_j, R_j from the reduced term sums, one thread per (batch, side)
-__global__ void __launch_bounds__(TPB) k_oa_lr_aff(const g1_jac *S, uint64_t K, uint64_t nb, uint32_t j, uint32_t lK,
-                                                   g1_aff *Lg1, g1_aff *Rg1) {
-  uint64_t id = gtid();
-  if (id >= 2 * nb) return;
-  uint64_t k = id / 2, side = id % 2;
-  g1_aff a = jac_to_aff(S[(k * 2 + side) * (K / 2)]);
-  (side ? Rg1 : Lg1)[k * lK + (j - 1)] = a;
-}
-
 // per batch: hash L_j, R_j into x_j, keep x_j and 1/x_j.  A workgroup of 64 per batch:
 // lanes encode x_{j-1} and the 28 coordinates of L_j, R_j in parallel (sha::Coop), and the
 // inverse runs on the scalar unit.
@@ -296,9 +286,6 @@ void fc_sigma(const fp12 *C, uint64_t K, uint32_t b, uint64_t nb, uint64_t nbj, 
 }
 void fc_r(uint64_t K, uint32_t b, uint64_t nb, uint64_t nbj, const uint32_t *sigma, fe *B, hipStream_t st) {
   LAUNCH(k_fc_r, dim3((unsigned)(nb * b)), dim3(64), 0, K, b, nb, nbj, sigma, B);
-}
-void oa_lr_aff(const g1_jac *S, uint64_t K, uint64_t nb, uint32_t j, uint32_t lK, g1_aff *Lg1, g1_aff *Rg1, hipStream_t st) {
-  L1(k_oa_lr_aff, 2 * nb, S, K, nb, j, lK, Lg1, Rg1);
 }
 void oa_transcript(const fp12 *Lgt, const fp12 *Rgt, uint64_t nb, uint32_t j, uint32_t lK, const g1_aff *Lg1,
                    const g1_aff *Rg1, fe *X, fe *Xinv, int *err, uint32_t zero_round, hipStream_t st) {

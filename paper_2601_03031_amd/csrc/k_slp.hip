@@ -231,20 +231,6 @@ __device__ void g2_job(Ctx c, gls::Dec *dec, const g2_aff *Q, const fe *k_mont, 
   if (A) g2_add_affine(c, A);
 }
 
-// Vout[i] = Vin[i] + x^{-1} Vin[h + i] for every batch k (Eq. folding); Vout may be Vin
-__global__ void __launch_bounds__(SLP_T, 4) ks_oa_fold_g2(const g2_aff *Vin, g2_aff *Vout, const fe *Xinv, uint64_t K, uint64_t nb,
-                                                      uint64_t h, uint32_t j, uint32_t lK) {
-  __shared__ f29 S[slp::G2_NSLOT];
-  CALL_LIST();
-  Ctx c{S, calls_sh};
-  __shared__ gls::Dec dec;
-  uint64_t id = blockIdx.x;
-  if (id >= nb * h) return;
-  uint64_t k = id / h, i = id % h;
-  g2_job(c, &dec, Vin + k * K + h + i, Xinv + k * lK + (j - 1), Vin + k * K + i);
-  g2_store_aff(c, Vout + k * K + i);
-}
-
 // terms q_m h_m of the KZG proof of v_l with every multiplication split in four parts (bits
 // [16 p, 16 p + 16) of the GLS split, 17 for p = 3) on the multiples hm[3 m + p - 1] =
 // 2^{16 p} h_m made at setup: S2[4 id + p] (homogeneous) for term id = k (2K - 2) + m
@@ -862,10 +848,6 @@ void final_exp(const fp12 *in, uint64_t stride, uint64_t n, fp12 *out0, fp12 *ou
   }
   if (n) LAUNCH(ks_final_exp, dim3((unsigned)n), dim3(FE_T), 0, in, stride, n, out0, out1, ostride);
 }
-void oa_fold_g2(const g2_aff *Vin, g2_aff *Vout, const fe *Xinv, uint64_t K, uint64_t nb, uint64_t h, uint32_t j, uint32_t lK,
-                hipStream_t st) {
-  LAUNCH(ks_oa_fold_g2, dim3((unsigned)(nb * h)), dim3(SLP_T), 0, Vin, Vout, Xinv, K, nb, h, j, lK);
-}
 void oa_fold(const g1_aff *Ain, const fe *Bin, g1_aff *Aout, fe *Bout, const g2_aff *Vin, g2_aff *Vout, const fe *X,
              const fe *Xinv, uint64_t K, uint64_t nb, uint64_t h, uint32_t j, uint32_t lK, hipStream_t st) {
   LAUNCH(ks_oa_fold, dim3((unsigned)(2 * nb * h)), dim3(SLP_T), 0, Ain, Bin, Aout, Bout, Vin, Vout, X, Xinv, K, nb, h, j, lK);
@@ -933,20 +915,19 @@ void kzg_terms_split(const g2_aff *h, const g2_aff *hm, const fe *Qc, uint64_t K
 void g2_dbl_mults(const g2_aff *Q, uint64_t seg, uint64_t segstride, uint64_t n, g2_aff *M, hipStream_t st) {
   if (n) LAUNCH(ks_g2_dbl_mults, dim3((unsigned)(3 * n)), dim3(SLP_T), 0, Q, seg, segstride, n, M);
 }
-// Multiplications up to which the engine takes them (a workgroup each, the shorter chain: G1 0.63
-// ms at 128 points and 1.4 ms at 2048; with 8 lanes a field element, eight to a workgroup, 1.7 and
-// 2.1 ms).  From 4096 on the chip is full either way (2.0 ms both) and the wide kernels do less work.
+// Multiplications up to which the engine takes them, a workgroup each: on G1 0.63 ms at 128 points and
+// 1.4 at 2048, when the chip is full; single lanes take 0.9 to 1.1 ms up to 65536 (k_lane.hip).
 static constexpr uint64_t MUL_MAX = 2048;
 void g1_mul(const g1_aff *P, const fe *k, uint64_t n, g1_aff *out, hipStream_t st) {
-  if (n > MUL_MAX) klw::g1_mul(P, 0, k, n, out, st);
+  if (n > MUL_MAX) kn::g1_mul(P, 0, k, n, out, st);
   else if (n) LAUNCH(ks_g1_mul, dim3((unsigned)n), dim3(SLP_T), 0, P, k, n, out);
 }
 void mults(const fp12 *X, const fe *kx, uint64_t n3, fp12 *outx, const g2_aff *Q, const fe *kq, uint64_t n2, g2_aff *outq,
            const g1_aff *P, const fe *kp, uint64_t n1, g1_aff *outp, hipStream_t st) {
-  const bool wide1 = n1 > MUL_MAX, wide2 = n2 > MUL_MAX;
-  if (wide1) klw::g1_mul(P, 0, kp, n1, outp, st);
-  if (wide2) klw::g2_mul(Q, 1, kq, n2, outq, st);
-  const uint64_t m1 = wide1 ? 0 : n1, m2 = wide2 ? 0 : n2;
+  const bool many1 = n1 > MUL_MAX, many2 = n2 > MUL_MAX;
+  if (many1) kn::g1_mul(P, 0, kp, n1, outp, st);
+  if (many2) kn::g2_mul(Q, 1, kq, n2, outq, st);
+  const uint64_t m1 = many1 ? 0 : n1, m2 = many2 ? 0 : n2;
   if (n3 + m2 + m1)
     LAUNCH(ks_mults, dim3((unsigned)(n3 + m2 + m1)), dim3(SLP_T), 0, X, kx, n3, outx, Q, kq, m2, outq, P, kp, m1, outp);
 }

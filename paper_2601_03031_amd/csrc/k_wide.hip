@@ -62,79 +62,6 @@ __device__ __forceinline__ bool scalar_is_zero(const uint32_t k[8]) {
   return t == 0;
 }
 
-// k P on G2 with the 4-dimensional split k = sum_j k_j lam^j (psi = the twisted Frobenius
-// acts as lam = p mod r): bases B_j = sign(k_j) psi^j(P), a table of the 15 nonzero subset
-// sums (Jacobian), then one doubling and at most one addition per bit of max |k_j| (65 bits)
-__device__ __forceinline__ g2_jac g2_mul_gls(const g2_aff &P, const gls::Dec &d) {
-  if (aff_is_inf(P) || d.nbits == 0) return jac_inf<OpsG2>();
-  g2_aff B[4];
-  B[0] = P;
-  for (int j = 1; j < 4; j++) B[j] = g2_frobenius(B[j - 1]);
-  for (int j = 0; j < 4; j++)
-    if (d.neg >> j & 1) B[j] = aff_neg(B[j]);
-  g2_jac T[16];
-  T[0] = jac_inf<OpsG2>();
-  for (int e = 1; e < 16; e++) {
-    const int j = __builtin_ctz(e);  // the lowest set bit: T[e] = T[e without it] + B_j
-    T[e] = (e & (e - 1)) ? jac_madd(T[e & (e - 1)], B[j]) : jac_from_aff(B[j]);
-  }
-  int t = (int)d.nbits - 1;
-  g2_jac acc = T[gls::digit(d, (uint32_t)t)];
-  for (t = t - 1; t >= 0; t--) {
-    acc = jac_dbl(acc);
-    uint32_t dg = gls::digit(d, (uint32_t)t);
-    if (dg) acc = jac_add(acc, T[dg]);
-  }
-  return acc;
-}
-
-// scalar multiplication by a canonical scalar: GLV split on G1, GLS split on G2
-__device__ __forceinline__ g1_jac mul_any(const g1_aff &P, const uint32_t kk[8]) { return g1_mul_glv(P, glv::decompose(kk)); }
-__device__ __forceinline__ g2_jac mul_any(const g2_aff &P, const uint32_t kk[8]) { return g2_mul_gls(P, gls::decompose(kk)); }
-
-// ---------------------------------------------------------------- scalar multiplications
-template <class O>
-__global__ void __launch_bounds__(TPBW) kw_mul(const void *P, int broadcast, const void *k, uint64_t n, void *out) {
-  uint64_t i = wgid();
-  if (i >= n) return;
-  uint32_t kk[8];
-  wscalar(kk, wld<fe>(k, i));
-  wst(out, i, jac_to_aff(mul_any(wld<aff<O>>(P, broadcast ? 0 : i), kk)));
-}
-
-// terms of <A_R, b_L> (side 0) and <A_L, b_R> (side 1), Jacobian
-__global__ void __launch_bounds__(TPBW) kw_oa_g1terms(const void *A, const void *B, uint64_t K, uint64_t nb, uint64_t h,
-                                                     void *S) {
-  uint64_t id = wgid();
-  if (id >= nb * 2 * h) return;
-  uint64_t k = id / (2 * h), r = id % (2 * h), side = r / h, i = r % h;
-  fe c = wld<fe>(B, side ? k * K + h + i : k * K + i);
-  g1_jac out = jac_inf<OpsG1>();
-  if (!fe_is_zero(c)) {
-    uint32_t kk[8];
-    wscalar(kk, c);
-    out = mul_any(wld<g1_aff>(A, side ? k * K + i : k * K + h + i), kk);
-  }
-  wst(S, (k * 2 + side) * (K / 2) + i, out);
-}
-
-// A_j = A_L o A_R^{x_j}, b_j = b_L + b_R / x_j; x_j enters through its GLV split (per batch);
-// the folded arrays go to Aout, Bout (which may be Ain, Bin)
-__global__ void __launch_bounds__(TPBW) kw_oa_fold_g1(const void *Ain, const void *Bin, void *Aout, void *Bout, const void *Xinv,
-                                                     const glv::Dec *dec, uint64_t K, uint64_t nb, uint64_t h, uint32_t j,
-                                                     uint32_t lK) {
-  uint64_t id = wgid();
-  if (id >= nb * h) return;
-  uint64_t k = id / h, i = id % h, slot = k * lK + (j - 1);
-  glv::Dec d = dec[k];
-  g1_jac t = g1_mul_glv(wld<g1_aff>(Ain, k * K + h + i), d);
-  g1_aff a = jac_to_aff(jac_madd(t, wld<g1_aff>(Ain, k * K + i)));
-  fe bl = wld<fe>(Bin, k * K + i), br = wld<fe>(Bin, k * K + h + i);
-  fe b = fr_add(bl, fr_mul(br, wld<fe>(Xinv, slot)));
-  wst(Aout, k * K + i, a);
-  wst(Bout, k * K + i, b);
-}
-
 // Miller values of the direct rounds on the wide layout, for rounds whose batches fill the
 // device: the pairs of L_j (side 0: A[h + i] with V[i]) and R_j (side 1: A[i] with V[h + i]),
 // C consecutive pairs per 8-lane group sharing one accumulator (one F_p12 squaring per step for
@@ -195,46 +122,6 @@ __global__ void __launch_bounds__(TPBW) kw_oa_miller(const void *A, const void *
   wst(F, (k * 2 + side) * (K / 2) + ch, f);
 }
 
-// v_j = v_L o v_R^{1/x_j} (Eq. folding) on the wide layout: the direct rounds, where the batches
-// fill the device and throughput decides; Vout may be Vin
-__global__ void __launch_bounds__(TPBW) kw_oa_fold_g2(const void *Vin, void *Vout, const void *Xinv, uint64_t K,
-                                                     uint64_t nb, uint64_t h, uint32_t j, uint32_t lK) {
-  uint64_t id = wgid();
-  if (id >= nb * h) return;
-  uint64_t k = id / h, i = id % h, slot = k * lK + (j - 1);
-  uint32_t kk[8];
-  wscalar(kk, wld<fe>(Xinv, slot));
-  g2_jac t = mul_any(wld<g2_aff>(Vin, k * K + h + i), kk);
-  wst(Vout, k * K + i, jac_to_aff(jac_madd(t, wld<g2_aff>(Vin, k * K + i))));
-}
-
-// HyperEval terms (canonical differences of the folded table g* times PST keys) of every job:
-// term r of level d of job x goes to S[(d G + x) M / 2 + r]
-__global__ void __launch_bounds__(TPBW) kw_hyper_terms(const S2Job *J, uint32_t G, uint64_t K, const void *ek, uint64_t M,
-                                                      uint32_t lM, void *S) {
-  uint64_t id = wgid();
-  uint64_t per = M / 2;
-  if (id >= G * lM * per) return;
-  const uint64_t x = id / (lM * per);
-  // g*, the root row of the y-tree, as an element offset (fe here is one limb per lane)
-  const void *g = J[x].Y;
-  const uint64_t g0 = (2 * K - 2) * M;
-  id %= lM * per;
-  uint32_t d = (uint32_t)(id / per);
-  uint64_t r = id % per;
-  uint32_t k = lM - d;
-  uint64_t half = 1ull << (k - 1);
-  uint64_t p = r / half, c = r % half;
-  fe q = fr_sub(wld<fe>(g, g0 + p * (2 * half) + half + c), wld<fe>(g, g0 + p * (2 * half) + c));
-  g1_jac out = jac_inf<OpsG1>();
-  if (!fe_is_zero(q)) {
-    uint32_t kk[8];
-    wunpack(kk, q);
-    out = mul_any(wld<g1_aff>(ek, (1ull << (k - 1)) - 1 + c), kk);
-  }
-  wst(S, (d * G + x) * per + r, out);
-}
-
 // W of every job at level d: segment s = x 2^d + p (reduced at in + s stride) is W_x[2^d - 1 + p]
 __global__ void __launch_bounds__(TPBW) kw_w_aff(const S2Job *J, uint32_t G, const void *in, uint64_t stride, uint32_t d) {
   uint64_t s = wgid();
@@ -242,17 +129,6 @@ __global__ void __launch_bounds__(TPBW) kw_w_aff(const S2Job *J, uint32_t G, con
   const uint64_t x = s >> d, p = s & ((1ull << d) - 1);
   g1_aff a = jac_to_aff(wld<g1_jac>(in, s * stride));
   wst(J[x].W, (1ull << d) - 1 + p, a);
-}
-
-// the D-tree's leaves D_j = rho_j C_j of every job
-__global__ void __launch_bounds__(TPBW) kw_d_leaves(const S2Job *J, uint32_t G, uint64_t K) {
-  uint64_t id = wgid();
-  if (id >= G * K) return;
-  const S2Job &jb = J[id / K];
-  const uint64_t j = id % K;
-  uint32_t kk[8];
-  wscalar(kk, wld<fe>(jb.rho, j));
-  wst(jb.D, j, jac_to_aff(mul_any(wld<g1_aff>(jb.Cj, j), kk)));
 }
 
 // ---------------------------------------------------------------- sums
@@ -368,19 +244,6 @@ namespace klw {
     if (dbg::on()) dbg::check(#kern, st);                                                    \
   } while (0)
 
-void g1_mul(const void *P, int bc, const void *k, uint64_t n, void *out, hipStream_t st) {
-  if (n) LW(kw_mul<OpsG1>, n, P, bc, k, n, out);
-}
-void g2_mul(const void *P, int bc, const void *k, uint64_t n, void *out, hipStream_t st) {
-  if (n) LW(kw_mul<OpsG2>, n, P, bc, k, n, out);
-}
-void oa_g1terms(const void *A, const void *B, uint64_t K, uint64_t nb, uint64_t h, void *S, hipStream_t st) {
-  LW(kw_oa_g1terms, nb * 2 * h, A, B, K, nb, h, S);
-}
-void oa_fold_g1(const void *Ain, const void *Bin, void *Aout, void *Bout, const void *Xinv, const void *dec, uint64_t K,
-                uint64_t nb, uint64_t h, uint32_t j, uint32_t lK, hipStream_t st) {
-  LW(kw_oa_fold_g1, nb * h, Ain, Bin, Aout, Bout, Xinv, static_cast<const glv::Dec *>(dec), K, nb, h, j, lK);
-}
 uint64_t oa_miller(const void *A, const void *V, uint64_t K, uint64_t nb, uint64_t h, void *F, hipStream_t st) {
   // two pairs per product when the round has pairs enough to keep the device full with half
   // as many groups (2^20, b = 1: 886 -> 810 ms), four from 2^19 pairs; fewer pairs keep one
@@ -396,18 +259,8 @@ uint64_t oa_miller(const void *A, const void *V, uint64_t K, uint64_t nb, uint64
   LW(kw_oa_miller<1>, nb * 2 * h, A, V, K, nb, h, F);
   return h;
 }
-void oa_fold_g2(const void *Vin, void *Vout, const void *Xinv, uint64_t K, uint64_t nb, uint64_t h, uint32_t j,
-                uint32_t lK, hipStream_t st) {
-  LW(kw_oa_fold_g2, nb * h, Vin, Vout, Xinv, K, nb, h, j, lK);
-}
-void hyper_terms(const S2Job *J, uint32_t G, uint64_t K, const void *ek, uint64_t M, uint32_t lM, void *S, hipStream_t st) {
-  LW(kw_hyper_terms, G * lM * (M / 2), J, G, K, ek, M, lM, S);
-}
 void w_aff(const S2Job *J, uint32_t G, const void *in, uint64_t stride, uint32_t d, hipStream_t st) {
   LW(kw_w_aff, (uint64_t)G << d, J, G, in, stride, d);
-}
-void d_leaves(const S2Job *J, uint32_t G, uint64_t K, hipStream_t st) {
-  LW(kw_d_leaves, G * K, J, G, K);
 }
 void g1_reduce(void *data, uint64_t nseg, uint64_t stride, uint64_t len, hipStream_t st) {
   for (uint64_t s = 1; s < len; s <<= 1) {

@@ -90,7 +90,6 @@ void fc_chunks(const g1_aff *Cj, uint64_t K, uint32_t b, uint64_t nb, uint64_t n
 void fc_sigma(const fp12 *C, uint64_t K, uint32_t b, uint64_t nb, uint64_t nbj, const uint32_t *Hq, uint32_t *sigma,
               hipStream_t st);
 void fc_r(uint64_t K, uint32_t b, uint64_t nb, uint64_t nbj, const uint32_t *sigma, fe *B, hipStream_t st);
-void oa_lr_aff(const g1_jac *S, uint64_t K, uint64_t nb, uint32_t j, uint32_t lK, g1_aff *Lg1, g1_aff *Rg1, hipStream_t st);
 // x_j = H'(x_{j-1} || L_j || R_j) per batch (zero_round == j: batch 0's challenge is forced to
 // zero, a test hook for the zero-challenge error; 0 leaves every challenge as hashed)
 void oa_transcript(const fp12 *Lgt, const fp12 *Rgt, uint64_t nb, uint32_t j, uint32_t lK, const g1_aff *Lg1,
@@ -121,23 +120,11 @@ void ev_finish(const g1_aff *prod, uint32_t lM, const fe *g, g1_aff *W, fe *y, h
 // Wide-layout kernels (k_wide.hip, 8 lanes per field element); same memory layouts
 // as above, passed untyped because the register types differ in that unit.
 namespace klw {
-void g1_mul(const void *P, int bc, const void *k, uint64_t n, void *out, hipStream_t st);
-void g2_mul(const void *P, int bc, const void *k, uint64_t n, void *out, hipStream_t st);
-void oa_g1terms(const void *A, const void *B, uint64_t K, uint64_t nb, uint64_t h, void *S, hipStream_t st);
-void oa_fold_g1(const void *Ain, const void *Bin, void *Aout, void *Bout, const void *Xinv, const void *dec, uint64_t K,
-                uint64_t nb, uint64_t h, uint32_t j, uint32_t lK, hipStream_t st);
 // the direct rounds' Miller values, several pairs per product: returns the products per batch
 // and side (stride K/2), the length of the F_p12 tree that follows
 uint64_t oa_miller(const void *A, const void *V, uint64_t K, uint64_t nb, uint64_t h, void *F, hipStream_t st);
-void oa_fold_g2(const void *Vin, void *Vout, const void *Xinv, uint64_t K, uint64_t nb, uint64_t h, uint32_t j,
-                uint32_t lK, hipStream_t st);
-// HyperEval terms of every job's g* (the root row of its y-tree): level d of job x at
-// S + (d G + x) M / 2, so the M / 2 terms of a level of all jobs are contiguous
-void hyper_terms(const S2Job *J, uint32_t G, uint64_t K, const void *ek, uint64_t M, uint32_t lM, void *S, hipStream_t st);
 // W of every job at level d from the reduced segment sums (segment x 2^d + p at in + (x 2^d + p) stride)
 void w_aff(const S2Job *J, uint32_t G, const void *in, uint64_t stride, uint32_t d, hipStream_t st);
-// D_j = rho_j C_j, the D-tree's leaves of every job
-void d_leaves(const S2Job *J, uint32_t G, uint64_t K, hipStream_t st);
 void g1_reduce(void *data, uint64_t nseg, uint64_t stride, uint64_t len, hipStream_t st);
 void g1_to_aff(const void *in, uint64_t stride, uint64_t n, void *out, uint64_t ostride, hipStream_t st);
 void sum_g1(const void *data, uint64_t nseg, uint64_t len, void *out, hipStream_t st);
@@ -146,6 +133,28 @@ void commit_sums(const CJob *J, uint32_t n, uint64_t total, void *Cp, hipStream_
 void dlevel(const S2Job *J, uint32_t G, uint64_t K, uint32_t h, hipStream_t st);
 void diag_field(int which, int op, const void *a, const void *b, uint64_t n, void *out, hipStream_t st);
 }  // namespace klw
+
+// one lane per element (k_lane.hip): the direct rounds with points enough to fill the device, and
+// multiplications that no chain waits for
+namespace kn {
+// G1 terms of a direct round, homogeneous, into S[(2 k + side) (K / 2) + i]: the terms or the sums of
+// some consecutive ones; returns how many per batch and side
+uint64_t oa_g1terms(const g1_aff *A, const fe *B, uint64_t K, uint64_t nb, uint64_t h, g1_jac *S, hipStream_t st);
+// whether a direct round of nb batches folds on single lanes (else ks::oa_fold)
+bool fold_lanes(uint64_t nb, uint64_t h);
+void oa_fold_g1(const g1_aff *Ain, const fe *Bin, g1_aff *Aout, fe *Bout, const fe *Xinv, const glv::Dec *dec, uint64_t K,
+                uint64_t nb, uint64_t h, uint32_t j, uint32_t lK, hipStream_t st);
+void oa_fold_g2(const g2_aff *Vin, g2_aff *Vout, const fe *Xinv, uint64_t K, uint64_t nb, uint64_t h, uint32_t j, uint32_t lK,
+                hipStream_t st);
+// out[i] = k_i P_i, or k_i P_0 with bc
+void g1_mul(const g1_aff *P, int bc, const fe *k, uint64_t n, g1_aff *out, hipStream_t st);
+void g2_mul(const g2_aff *P, int bc, const fe *k, uint64_t n, g2_aff *out, hipStream_t st);
+// HyperEval terms of every job's g* (the root row of its y-tree): level d of job x at
+// S + (d G + x) M / 2, so the M / 2 terms of a level of all jobs are contiguous
+void hyper_terms(const S2Job *J, uint32_t G, uint64_t K, const g1_aff *ek, uint64_t M, uint32_t lM, g1_jac *S, hipStream_t st);
+// D_j = rho_j C_j, the D-tree's leaves of every job
+void d_leaves(const S2Job *J, uint32_t G, uint64_t K, hipStream_t st);
+}  // namespace kn
 
 // wave-cooperative engine (k_slp.hip): a 64-lane workgroup per pairing / product / element
 namespace ks {
@@ -156,15 +165,13 @@ void f12_reduce(fp12 *data, uint64_t nseg, uint64_t stride, uint64_t len, uint32
 // input s at in[s stride]; output to (s odd ? out1 : out0)[(s >> 1) ostride], or to
 // out0[s ostride] when out1 is NULL
 void final_exp(const fp12 *in, uint64_t stride, uint64_t n, fp12 *out0, fp12 *out1, uint64_t ostride, hipStream_t st);
-void oa_fold_g2(const g2_aff *Vin, g2_aff *Vout, const fe *Xinv, uint64_t K, uint64_t nb, uint64_t h, uint32_t j, uint32_t lK,
-                hipStream_t st);
 // sums of Jacobian segments on the engine, one launch (tree_counters(len) counters per segment)
 void g1_tree(g1_jac *data, uint64_t nseg, uint64_t stride, uint64_t len, uint32_t *cnt, hipStream_t st);
 // (hom: homogeneous points of the engine, else Jacobian)
 void g2_tree(g2_jac *data, uint64_t nseg, uint64_t stride, uint64_t len, bool hom, uint32_t *cnt, hipStream_t st);
 void g1_hom_to_aff(const g1_jac *in, uint64_t stride, uint64_t n, g1_aff *out0, g1_aff *out1, uint64_t ostride, hipStream_t st);
 void g2_hom_to_aff(const g2_jac *in, uint64_t stride, uint64_t n, g2_aff *out, uint64_t ostride, hipStream_t st);
-// round-1 G1 terms on the engine (same layout as klw::oa_g1terms)
+// G1 terms of a direct round on the engine (layout as kn::oa_g1terms, one each)
 void oa_g1terms(const g1_aff *A, const fe *B, uint64_t K, uint64_t nb, uint64_t h, g1_jac *S, hipStream_t st);
 // out[i] = k_i P_i
 void g1_mul(const g1_aff *P, const fe *k, uint64_t n, g1_aff *out, hipStream_t st);

@@ -7,13 +7,16 @@
 // limbs of the factors of product n within A_n 2^28 and B_n 2^28 (one "unit": 2^28), a sum of products
 // with one reduction keeps its 64-bit columns below 2^63 if the A_n B_n add up to at most 12:
 // 9 sum A_n B_n + 18 (the reduction's) < 128 = 2^63 / 2^56.  Its value is below 0.5 p + sum |a_n b_n| /
-// 169 p, so that no sum of a formula needs a reduction by p: the coordinates stay below 2 p.
+// 169 p, so that no sum of a formula needs a reduction by p: with one point's coordinates below 2 p and
+// the other's below 2 p, or below 32 p and affine, those of the sum are below 2 p.
 //
 // The group law is the complete one for y^2 = x^3 + b (J. Renes, C. Costello, L. Batina, "Complete
 // addition formulas for prime order elliptic curves", 2016): homogeneous coordinates, the identity
 // (0 : 1 : 0) and no exceptional case in groups of odd order.
 #pragma once
 #include "curve.hpp"
+#include "glv.hpp"
+#include "gls.hpp"
 
 namespace lane {
 
@@ -75,6 +78,20 @@ HD __forceinline__ fl norm(const fl &a) {
   return o;
 }
 
+// columns 9 .. 17, each of the lower eight with 2^28 added, as centred limbs
+HD __forceinline__ fl centred(const int64_t *c) {
+  fl o;
+  int64_t carry = 0;
+#pragma unroll
+  for (int j = 0; j < 8; j++) {
+    const int64_t v = c[9 + j] + carry;
+    o.l[j] = ((int32_t)v & MASK) - HALF;
+    carry = v >> 29;
+  }
+  o.l[8] = (int32_t)(c[17] + carry);
+  return o;
+}
+
 // (sum_n a_n b_n) 2^{-261} mod p, N products and one reduction.  Written row by row in this order
 // because a multiply-add that needs the one before it issues at half the rate.
 template <int N> HD __forceinline__ fl dot(const fl *const *a, const fl *const *b) {
@@ -103,16 +120,33 @@ template <int N> HD __forceinline__ fl dot(const fl *const *a, const fl *const *
     LANE_ORDER();
     c[k + 1] += c[k] >> 29;
   }
-  fl o;
-  int64_t carry = 0;
+  return centred(c);
+}
+// a^2 2^{-261}: each product of two limbs once (limbs within three units)
+HD __forceinline__ fl sqr(const fl &a) {
+  int64_t c[18];
 #pragma unroll
-  for (int j = 0; j < 8; j++) {
-    const int64_t v = c[9 + j] + carry;
-    o.l[j] = ((int32_t)v & MASK) - HALF;
-    carry = v >> 29;
+  for (int k = 0; k < 18; k++) c[k] = k >= 9 && k < 17 ? HALF : 0;
+  int32_t d[9];
+#pragma unroll
+  for (int j = 0; j < 9; j++) d[j] = 2 * a.l[j];
+#pragma unroll
+  for (int j = 0; j < 9; j++) c[j] += (int64_t)a.l[0] * (j ? d[j] : a.l[0]);
+#pragma unroll
+  for (int k = 0; k < 9; k++) {
+    LANE_ORDER();
+    const uint32_t t = (uint32_t)c[k] * FpP::INV29;
+    LANE_ORDER();
+#pragma unroll
+    for (int j = k + 1; j < 9; j++) c[k + 1 + j] += (int64_t)a.l[k + 1] * (j > k + 1 ? d[j] : a.l[j]);
+    LANE_ORDER();
+    const int32_t m = (int32_t)(t << 3) >> 3;
+#pragma unroll
+    for (int j = 0; j < 9; j++) c[k + j] += (int64_t)m * (int32_t)FpP::M29[j];
+    LANE_ORDER();
+    c[k + 1] += c[k] >> 29;
   }
-  o.l[8] = (int32_t)(c[17] + carry);
-  return o;
+  return centred(c);
 }
 HD __forceinline__ fl mul(const fl &a, const fl &b) {
   const fl *x[1] = {&a}, *y[1] = {&b};
@@ -128,7 +162,8 @@ HD __forceinline__ fl mul4(const fl &a, const fl &b, const fl &c, const fl &d, c
   return dot<4>(x, y);
 }
 
-// a packed element (limbs in [0, 2^29), two units; value below 32 p), and back, canonical
+// a packed element (limbs in [0, 2^29), two units; value below 32 p), and back (of a value below 8 p),
+// canonical
 HD __forceinline__ fl in(const fe &x) {
   uint32_t w[9];
   r29::split<5>(x, w);
@@ -137,6 +172,15 @@ HD __forceinline__ fl in(const fe &x) {
   for (int j = 0; j < 9; j++) o.l[j] = (int32_t)w[j];
   return o;
 }
+// 2^261 mod p, and a packed element below 0.7 p with centred limbs (a formula takes one factor of each
+// product as large as `in` leaves it, not both)
+HD __forceinline__ fl small_one() {
+  fl o;
+#pragma unroll
+  for (int j = 0; j < 9; j++) o.l[j] = bn::P_ONE29[j];
+  return o;
+}
+HD __forceinline__ fl in_small(const fe &x) { return mul(in(x), small_one()); }
 HD __forceinline__ fe out(const fl &x) {
   fl k;  // 2^256
 #pragma unroll
@@ -179,7 +223,10 @@ struct G1 {
   static HD __forceinline__ T times(const T &a, int k) { return lane::times(a, k); }
   static HD __forceinline__ T mul(const T &a, const T &b) { return lane::mul(a, b); }
   static HD __forceinline__ T mul2(const T &a, const T &b, const T &c, const T &d) { return lane::mul2(a, b, c, d); }
-  static HD __forceinline__ T b3(const T &a) { return norm_times(a, 9); }
+  static HD __forceinline__ T sqr(const T &a) { return lane::sqr(a); }
+  static HD __forceinline__ T norm_times(const T &a, int k) { return lane::norm_times(a, k); }
+  static HD __forceinline__ T b3(const T &a) { return lane::norm_times(a, 9); }
+  static HD __forceinline__ fe inv(const fe &a) { return fp_inv_fast(a); }
 };
 struct fl2 {
   fl c0, c1;
@@ -188,6 +235,7 @@ struct G2 {
   using T = fl2;
   using O = OpsG2;
   static HD __forceinline__ T in(const fp2 &x) { return {lane::in(x.c0), lane::in(x.c1)}; }
+  static HD __forceinline__ T in_small(const fp2 &x) { return {lane::in_small(x.c0), lane::in_small(x.c1)}; }
   static HD __forceinline__ fp2 out(const T &x) { return {lane::out(x.c0), lane::out(x.c1)}; }
   static HD __forceinline__ T zero() { return T{}; }
   static HD __forceinline__ T some() { return T{{{1}}, {}}; }
@@ -203,12 +251,17 @@ struct G2 {
     return {lane::mul4(a.c0, b.c0, lane::neg(a.c1), b.c1, c.c0, d.c0, lane::neg(c.c1), d.c1),
             lane::mul4(a.c0, b.c1, a.c1, b.c0, c.c0, d.c1, c.c1, d.c0)};
   }
+  static HD __forceinline__ T sqr(const T &a) {
+    return {lane::mul(lane::add(a.c0, a.c1), lane::sub(a.c0, a.c1)), lane::mul(lane::add(a.c0, a.c0), a.c1)};
+  }
+  static HD __forceinline__ T norm_times(const T &a, int k) { return {lane::norm_times(a.c0, k), lane::norm_times(a.c1, k)}; }
+  static HD __forceinline__ fp2 inv(const fp2 &a) { return f2_inv(a); }
   static HD __forceinline__ T b3(const T &a) {
     T k;
 #pragma unroll
     for (int j = 0; j < 9; j++) {
-      k.c0.l[j] = (int32_t)bn::TWIST_3B29[0][j];
-      k.c1.l[j] = (int32_t)bn::TWIST_3B29[1][j];
+      k.c0.l[j] = bn::TWIST_3B29[0][j];
+      k.c1.l[j] = bn::TWIST_3B29[1][j];
     }
     return mul(a, k);
   }
@@ -238,10 +291,80 @@ template <class L> HD __forceinline__ pt<L> madd(const pt<L> &p, const typename 
   return add_tail<L>(L::mul(p.X, x), L::mul(p.Y, y), L::mul2(p.X, y, p.Y, x), L::add(p.Y, L::mul(p.Z, y)),
                      L::b3(L::add(p.X, L::mul(p.Z, x))), L::b3(p.Z));
 }
+template <class L> HD __forceinline__ pt<L> dbl(const pt<L> &p) {
+  using T = typename L::T;
+  const T t0 = L::sqr(p.Y), t1 = L::mul(p.Y, p.Z), t2 = L::b3(L::sqr(p.Z)), t3 = L::mul(p.X, p.Y);
+  const T n = L::norm(L::sub(t0, L::times(t2, 3))), e = L::norm_times(t0, 8);
+  return {L::mul(n, L::times(t3, 2)), L::mul2(e, t2, n, L::add(t0, t2)), L::mul(e, t1)};
+}
+// the affine point, packed; zeros for the identity
+template <class L> HD __forceinline__ aff<typename L::O> to_aff(const pt<L> &p) {
+  using O = typename L::O;
+  const typename O::T z = L::out(p.Z);
+  if (O::is_zero(z)) return aff_inf<O>();
+  const typename L::T zi = L::in(L::inv(z));
+  return {L::out(L::mul(p.X, zi)), L::out(L::mul(p.Y, zi))};
+}
 // to Jacobian coordinates, packed: (X Z, Y Z^2, Z)
 template <class L> HD __forceinline__ jac<typename L::O> to_jac(const pt<L> &p) {
   const typename L::T yz = L::mul(p.Y, p.Z);
   return {L::out(L::mul(p.X, p.Z)), L::out(L::mul(yz, p.Z)), L::out(p.Z)};
+}
+
+// ---------------------------------------------------------------- scalar multiplication
+// k P on G1 with the split k = k_0 + k_1 lam (glv.hpp): the table of d_0 B_0 + d_1 B_1, d_j < 4, in
+// scratch memory, two doublings and at most one addition per two bits
+HD __forceinline__ pt<G1> mul_lane(const g1_aff &P, const glv::Dec &d) {
+  if (aff_is_inf(P) || d.nbits == 0) return identity<G1>();
+  pt<G1> T[16];
+  const fl x = in_small(P.x), y = in_small(P.y), x1 = mul(x, in(fe_const(bn::GLV_BETA))), one = small_one();
+  const fl y0 = d.neg & 1 ? neg(y) : y, y1 = d.neg & 2 ? neg(y) : y;
+#pragma unroll 1
+  for (int s = 1; s <= 4; s *= 4) {  // the multiples of B_0, of B_1
+    const fl &bx = s == 1 ? x : x1, &by = s == 1 ? y0 : y1;
+    T[s] = {bx, by, one};
+    T[2 * s] = madd<G1>(T[s], bx, by);
+    T[3 * s] = madd<G1>(T[2 * s], bx, by);
+  }
+#pragma unroll 1
+  for (int e = 5; e < 16; e++)
+    if (e & 3) T[e] = add<G1>(T[e & 12], T[e & 3]);
+  const int n = (int)(d.nbits + 1) / 2;
+  pt<G1> acc = T[glv::digit2(d, (uint32_t)(n - 1))];
+#pragma unroll 1
+  for (int w = n - 2; w >= 0; w--) {
+#pragma unroll 1
+    for (int i = 0; i < 2; i++) acc = dbl<G1>(acc);
+    const uint32_t dg = glv::digit2(d, (uint32_t)w);
+    if (dg) acc = add<G1>(acc, T[dg]);
+  }
+  return acc;
+}
+
+// k Q on G2 with the split k = sum_j k_j lam^j (gls.hpp): the table of the 15 subset sums of
+// sign(k_j) psi^j(Q), a doubling and at most one addition per bit
+HD __forceinline__ pt<G2> mul_lane(const g2_aff &Q, const gls::Dec &d) {
+  if (aff_is_inf(Q) || d.nbits == 0) return identity<G2>();
+  pt<G2> T[16];
+  const fl2 one = {small_one(), {}};
+  g2_aff B = Q;
+#pragma unroll 1
+  for (int j = 0; j < 4; j++) {
+    if (j) B = g2_frobenius(B);
+    const fl2 x = G2::in_small(B.x), yy = G2::in_small(B.y), y = d.neg >> j & 1 ? G2::neg(yy) : yy;
+    T[1 << j] = {x, y, one};
+#pragma unroll 1
+    for (int e = 1; e < 1 << j; e++) T[e + (1 << j)] = madd<G2>(T[e], x, y);
+  }
+  const int n = (int)d.nbits;
+  pt<G2> acc = T[gls::digit(d, (uint32_t)(n - 1))];
+#pragma unroll 1
+  for (int t = n - 2; t >= 0; t--) {
+    acc = dbl<G2>(acc);
+    const uint32_t dg = gls::digit(d, (uint32_t)t);
+    if (dg) acc = add<G2>(acc, T[dg]);
+  }
+  return acc;
 }
 
 }  // namespace lane

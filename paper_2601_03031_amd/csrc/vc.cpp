@@ -183,8 +183,8 @@ static constexpr uint64_t AHEAD_MAX_PAIRS = 4096;
 static constexpr uint64_t DIRECT_MIN = 512;
 // folds of at most this many pairs (batches x h) run as four-part split multiplications
 static constexpr uint64_t FOLD_SPLIT_MAX = 256;
-// direct-round Miller loops and G2 folds of at least this many (batch, index) pairs run on the
-// wide layout (8 lanes per element, throughput), smaller ones on the engine (latency)
+// direct-round Miller loops of at least this many (batch, index) pairs run on the wide layout (8
+// lanes per element, throughput), smaller ones on the engine (latency)
 static constexpr uint64_t WIDE_FOLD_MIN = 4096;
 // bases per block of the KZG proof's G2 MSM (times 32 windows: at most 8192 digits): long
 // slices when the MSMs of all batches give at least KZG_LONG_MIN_BLOCKS blocks (the bucket
@@ -456,11 +456,11 @@ VC_API int vc_setup(uint32_t log_n, const uint8_t seed[32], int device, vc_param
   fe *s = at<fe>(ws, o_s), *beta = at<fe>(ws, o_beta), *w = at<fe>(ws, o_w), *pw = at<fe>(ws, o_pw);
   kl::trapdoor(at<uint8_t>(ws, o_seed), pp->lM, s, beta, st);
   kl::ek_weights(pp->lM, s, w, 2 * M - 1, st);
-  klw::g1_mul(pp->g1gen, 1, w, 2 * M - 1, pp->ek, st);
-  klw::g2_mul(pp->g2gen, 1, s, lM, pp->vk, st);
+  kn::g1_mul(pp->g1gen, 1, w, 2 * M - 1, pp->ek, st);
+  kn::g2_mul(pp->g2gen, 1, s, lM, pp->vk, st);
   kl::pow_table(beta, pw, 2 * K - 1, st);
-  klw::g2_mul(pp->g2gen, 1, pw, 2 * K - 1, pp->h, st);
-  klw::g1_mul(pp->g1gen, 1, beta, 1, pp->g1beta, st);
+  kn::g2_mul(pp->g2gen, 1, pw, 2 * K - 1, pp->h, st);
+  kn::g1_mul(pp->g1gen, 1, beta, 1, pp->g1beta, st);
   params_tables(pp, st);
   e = hipGetLastError();
   if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -1209,9 +1209,9 @@ static int open_all_group(const vc_params *cpp, const vc_commitment *const *cms,
     for (uint64_t s = N / 2; s >= 1; s /= 2) kl::merkle_level(J, G, s, st);
     kl::rho(J, G, K, st);
     kl::ytree(J, G, M, K, lK, st);
-    klw::d_leaves(J, G, K, st);
+    kn::d_leaves(J, G, K, st);
     for (uint32_t h = 1; h <= lK; h++) klw::dlevel(J, G, K, h, st);
-    klw::hyper_terms(J, G, K, pp->ek, M, lM, HS, st);
+    kn::hyper_terms(J, G, K, pp->ek, M, lM, HS, st);
     for (uint32_t d = 0; d < lM; d++) {
       // level d of every job: G 2^d segments of M / 2^{d+1} terms, contiguous
       uint64_t half = M >> (d + 1);
@@ -1335,15 +1335,8 @@ static int open_all_group(const vc_params *cpp, const vc_commitment *const *cms,
     const uint64_t h = K >> j;
     const int cur = (j - 1) & 1, nxt = j & 1;
     if (!ahead || j < j0) {
-      if (ahead) {
-        ks::oa_g1terms(Ab[cur], Bb[cur], K, nb, h, S, sg);
-        ks::g1_tree(S, 2 * nb, K / 2, h, cnt_g1dir, sg);
-      } else {
-        klw::oa_g1terms(Ab[cur], Bb[cur], K, nb, h, S, sg);
-        klw::g1_reduce(S, 2 * nb, K / 2, h, sg);
-      }
-      if (ahead) ks::g1_hom_to_aff(S, K / 2, 2 * nb, Lg1 + (j - 1), Rg1 + (j - 1), lK, sg);
-      else kl::oa_lr_aff(S, K, nb, j, lK, Lg1, Rg1, sg);
+      ks::g1_tree(S, 2 * nb, K / 2, kn::oa_g1terms(Ab[cur], Bb[cur], K, nb, h, S, sg), cnt_g1dir, sg);
+      ks::g1_hom_to_aff(S, K / 2, 2 * nb, Lg1 + (j - 1), Rg1 + (j - 1), lK, sg);
       if (int rc2 = ev_mark(ex, 3, sg)) return rc2;
       // round 1 pairs the same A = aux with the same v in every batch of a job: its G_T
       // parts are computed once per job (from the aux rows; the first G rows of V all hold v)
@@ -1414,13 +1407,16 @@ static int open_all_group(const vc_params *cpp, const vc_commitment *const *cms,
       }
     } else {
       if (int rc2 = stream_wait(ex, 4, st, sg)) return rc2;
-      kl::glv_dec(X, nb, j, lK, gdec, sg);
-      klw::oa_fold_g1(Ab[cur], Bb[cur], Ab[nxt], Bb[nxt], Xinv, gdec, K, nb, h, j, lK, sg);
-      if (int rc2 = stream_wait(ex, 5, st, sf)) return rc2;
-      if (nb * h >= WIDE_FOLD_MIN) klw::oa_fold_g2(Vb[cur], Vb[nxt], Xinv, K, nb, h, j, lK, sf);
-      else ks::oa_fold_g2(Vb[cur], Vb[nxt], Xinv, K, nb, h, j, lK, sf);
+      if (kn::fold_lanes(nb, h)) {
+        kl::glv_dec(X, nb, j, lK, gdec, sg);
+        kn::oa_fold_g1(Ab[cur], Bb[cur], Ab[nxt], Bb[nxt], Xinv, gdec, K, nb, h, j, lK, sg);
+        if (int rc2 = stream_wait(ex, 5, st, sf)) return rc2;
+        kn::oa_fold_g2(Vb[cur], Vb[nxt], Xinv, K, nb, h, j, lK, sf);
+        if (int rc2 = stream_wait(ex, 12, sf, st)) return rc2;
+      } else {
+        ks::oa_fold(Ab[cur], Bb[cur], Ab[nxt], Bb[nxt], Vb[cur], Vb[nxt], X, Xinv, K, nb, h, j, lK, sg);
+      }
       if (int rc2 = stream_wait(ex, 11, sg, st)) return rc2;
-      if (int rc2 = stream_wait(ex, 12, sf, st)) return rc2;
     }
     if (j == std::min<uint32_t>(2, lK))
       if (int rc2 = step2 ? launch_step2() : eval_r ? launch_pst() : VC_OK) return rc2;

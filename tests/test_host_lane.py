@@ -42,3 +42,20 @@ def test_sums(hc, grp):
         o = C.create_string_buffer(size)
         hc.hc_lane_sum(grp, b"".join(pts), len(pts), m, o)
         assert o.raw == want, (len(pts), m)
+
+
+@pytest.mark.parametrize("grp", [0, 1])
+def test_multiplication(hc, grp):
+    """k P over the split of k: the scalars at the ends, those whose split has one part only or negative
+    parts, and random ones; the identity."""
+    gen = O.generators()[grp]
+    op, size = ((O.g1_op, 64), (O.g2_op, 128))[grp]
+    rng = random.Random(710 + grp)
+    rnd = lambda: op("mul", gen, O.be32(rng.randrange(1, O.R)))
+    P = rnd()
+    ks = [0, 1, 2, 3, 4, 5, 15, 16, 17, O.R - 1, O.R - 2, 1 << 64, (1 << 64) - 1, 1 << 127, O.R >> 1]
+    cases = [(P, k) for k in ks] + [(bytes(size), 5)] + [(rnd(), rng.randrange(O.R)) for _ in range(300 if grp == 0 else 120)]
+    for p, k in cases:
+        o = C.create_string_buffer(size)
+        hc.hc_lane_mul(grp, p, O.be32(k), o)
+        assert o.raw == (op("mul", p, O.be32(k)) if any(p) else bytes(size)), k
