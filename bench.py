@@ -43,8 +43,8 @@ TRAFFIC_BYTES = {"ks_final_exp2": round((417.0 * 2.000 + 14.2 * 1.000) * 1024),
 FOLD_SPLIT_MAX = 256                       # folds of at most this many pairs run split in four parts
 DIRECT_MIN = 512                           # rounds of more pairs than this run direct in the ahead mode
 KZG_SPLIT_MAX = 8192                       # KZG proofs of at most this many split jobs run split
-WIDE_FOLD_MIN = 4096
-LANE_MIN = 4096                       # direct-round Miller loops / G2 folds of this many pairs run wide
+LANE_MILLER_MIN = 4096                     # direct-round Miller loops of this many pairs run two lanes a pairing
+LANE_MIN = 4096                            # direct-round terms and folds of this many run on single lanes
 
 
 def op_costs():
@@ -138,8 +138,8 @@ def method_work(L, b, limbs, c):
                  "ks_oa_pterms": sum(miller[j] for j in taken),
                  "ks_final_exp2": sum(fexp[j] for j in taken),
                  "ks_final_exp": sum(fexp[j] for j in direct) + c["final_exp"]}
-    wide = [j for j in direct if (1 if j == 1 else nb) * (K >> j) >= WIDE_FOLD_MIN]
-    by_kernel["kw_oa_miller"] = sum(miller[j] for j in wide)
+    wide = [j for j in direct if (1 if j == 1 else nb) * (K >> j) >= LANE_MILLER_MIN]
+    by_kernel["kn_oa_miller"] = sum(miller[j] for j in wide)
     by_kernel["ks_oa_miller"] = sum(miller[j] for j in direct if j not in wide)
     return {"phases": phases, "open_all": sum(v for k, v in phases.items() if k not in ("commit_msm", "fc_commit")),
             "commit": msm + fc_commit, "by_kernel": {k: v for k, v in by_kernel.items() if v}}
@@ -219,10 +219,10 @@ def work_model(L, b, limbs, costs):
         })
     else:
         nbr = lambda h: 1 if h == K // 2 else nb   # round 1's pairings are computed once for all batches
-        wide = [h for h in rounds if nbr(h) * h >= WIDE_FOLD_MIN]
+        wide = [h for h in rounds if nbr(h) * h >= LANE_MILLER_MIN]
         w.update({
             "ks_oa_miller": sum(nbr(h) * 2 * h for h in rounds if h not in wide) * costs["e_miller"],
-            "kw_oa_miller": sum(nbr(h) * 2 * h for h in wide) * costs["miller"],
+            "kn_oa_miller": sum(nbr(h) * 2 * h for h in wide) * costs["miller"],
             "ks_final_exp": (sum(2 * nbr(h) for h in rounds) + 1) * costs["e_final_exp"],
             "ks_f12_tree": (K - 1 + sum(2 * nbr(h) * (h - 1) for h in rounds)) * costs["e_f12_mul"],
             "kn_oa_fold_g2": sum(nb * h for h in rounds if nb * h >= LANE_MIN) * g2_fold,

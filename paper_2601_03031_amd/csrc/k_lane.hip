@@ -109,6 +109,255 @@ __global__ void __launch_bounds__(LT) kn_d_leaves(const S2Job *J, uint32_t G, ui
   jb.D[j] = mul_aff<L1_>(jb.Cj[j], jb.rho[j], glv::decompose);
 }
 
+// ---------------------------------------------------------------- Miller loops
+// Two lanes a pairing, lane p of them with component p of every element of F_p2 (p = 0, 1): the state of
+// a pairing, 24 elements of F_p, then fits the registers of its lanes, and a product in F_p2 is one
+// sum of two products in each.  Sums of products over F_p2 have one reduction, so that F_p6 products
+// and the product by a line are taken by their definition (a third of the reductions that the forms
+// with fewer products need, and no sums before or after).
+namespace {
+
+using lane::fl;
+
+__device__ __forceinline__ fl other(const fl &a) {  // the other lane's
+  fl o;
+#pragma unroll
+  for (int j = 0; j < 9; j++) o.l[j] = __builtin_amdgcn_mov_dpp(a.l[j], 0xB1, 0xF, 0xF, true);
+  return o;
+}
+__device__ __forceinline__ fl pick(bool c, const fl &a, const fl &b) {
+  fl o;
+#pragma unroll
+  for (int j = 0; j < 9; j++) o.l[j] = c ? a.l[j] : b.l[j];
+  return o;
+}
+// a second factor b as both lanes use it: a b = own(a) x + other(a) y, with (x, y) = (b_0, -b_1) in lane
+// 0 and (b_0, b_1) in lane 1
+struct fac {
+  fl x, y;
+};
+__device__ __forceinline__ fac factor(bool p, const fl &b) {
+  const fl o = other(b);
+  return {pick(p, o, b), pick(p, b, lane::neg(o))};
+}
+// sums of one, two and three products a b, the other lane's a given
+__device__ __forceinline__ fl prod(const fl &a, const fl &ao, const fac &b) { return lane::mul2(a, b.x, ao, b.y); }
+__device__ __forceinline__ fl prod2(const fl &a, const fl &ao, const fac &b, const fl &c, const fl &co, const fac &d) {
+  return lane::mul4(a, b.x, ao, b.y, c, d.x, co, d.y);
+}
+__device__ __forceinline__ fl prod3(const fl &a, const fl &ao, const fac &b, const fl &c, const fl &co, const fac &d, const fl &e,
+                                    const fl &eo, const fac &f) {
+  const fl *x[6] = {&a, &ao, &c, &co, &e, &eo}, *y[6] = {&b.x, &b.y, &d.x, &d.y, &f.x, &f.y};
+  return lane::dot<6>(x, y);
+}
+__device__ __forceinline__ fl mul2_(bool p, const fl &a, const fl &b) { return prod(a, other(a), factor(p, b)); }
+// a^2: (a_0 + a_1)(a_0 - a_1) in lane 0, 2 a_1 a_0 in lane 1
+__device__ __forceinline__ fl sqr2_(bool p, const fl &a) {
+  const fl o = other(a);
+  return lane::mul(lane::add(a, pick(p, a, o)), pick(p, o, lane::sub(a, o)));
+}
+// k a + b, a - b and (9 + i) a, reduced: limbs of one unit, within 0.51 p
+__device__ __forceinline__ fl red(const fl &a, int k, const fl &b) { return lane::reduce(a, k, b); }
+__device__ __forceinline__ fl red_sub(const fl &a, const fl &b) { return lane::reduce(b, -1, a); }
+__device__ __forceinline__ fl xi(bool p, const fl &a) {
+  const fl o = other(a);
+  return red(a, 9, pick(p, o, lane::neg(o)));
+}
+
+struct six {
+  fl c[3];  // over 1, v, v^2
+};
+// a b in F_p6 (limbs of one unit)
+__device__ __forceinline__ six mul6(bool p, const six &a, const six &b) {
+  const fl o0 = other(a.c[0]), o1 = other(a.c[1]), o2 = other(a.c[2]);
+  const fac b0 = factor(p, b.c[0]), b1 = factor(p, b.c[1]), b2 = factor(p, b.c[2]);
+  const fac x1 = factor(p, xi(p, b.c[1])), x2 = factor(p, xi(p, b.c[2]));
+  return {{prod3(a.c[0], o0, b0, a.c[1], o1, x2, a.c[2], o2, x1), prod3(a.c[0], o0, b1, a.c[1], o1, b0, a.c[2], o2, x2),
+           prod3(a.c[0], o0, b2, a.c[1], o1, b1, a.c[2], o2, b0)}};
+}
+struct twelve {
+  six a, b;  // a + b w, w^2 = v
+};
+// f^2 = (a + b)(a + v b) - t - v t + 2 t w, t = a b
+__device__ __forceinline__ void sqr12(bool p, twelve &f) {
+  six x = f.a, y = f.b, t = {}, r = {};
+#pragma unroll 1
+  for (int k = 0; k < 2; k++) {  // (one copy of the product's code for both)
+    r = mul6(p, x, y);
+    if (k == 0) {
+      t = r;
+      const fl v0 = xi(p, f.b.c[2]);
+#pragma unroll
+      for (int i = 0; i < 3; i++) {
+        x.c[i] = red(f.a.c[i], 1, f.b.c[i]);
+        y.c[i] = red(f.a.c[i], 1, i ? f.b.c[i - 1] : v0);
+      }
+    }
+  }
+  const fl t0 = xi(p, t.c[2]);
+#pragma unroll
+  for (int i = 0; i < 3; i++) {
+    f.a.c[i] = red_sub(lane::sub(r.c[i], t.c[i]), i ? t.c[i - 1] : t0);
+    f.b.c[i] = red(t.c[i], 2, fl{});
+  }
+}
+// f g = t0 + v t1 + (t2 - t0 - t1) w, t0 = a a', t1 = b b', t2 = (a + b)(a' + b')
+__device__ __forceinline__ twelve mul12(bool p, const twelve &f, const twelve &g) {
+  six x = f.a, y = g.a, t[3] = {};
+#pragma unroll 1
+  for (int k = 0; k < 3; k++) {
+    const six r = mul6(p, x, y);
+    if (k == 0) {
+      t[0] = r;
+      x = f.b;
+      y = g.b;
+    } else if (k == 1) {
+      t[1] = r;
+#pragma unroll
+      for (int i = 0; i < 3; i++) {
+        x.c[i] = red(f.a.c[i], 1, f.b.c[i]);
+        y.c[i] = red(g.a.c[i], 1, g.b.c[i]);
+      }
+    } else {
+      t[2] = r;
+    }
+  }
+  const fl v0 = xi(p, t[1].c[2]);
+  twelve o;
+#pragma unroll
+  for (int i = 0; i < 3; i++) {
+    o.a.c[i] = red(t[0].c[i], 1, i ? t[1].c[i - 1] : v0);
+    o.b.c[i] = red_sub(lane::sub(t[2].c[i], t[0].c[i]), t[1].c[i]);
+  }
+  return o;
+}
+// f (l0 + l1 w + l3 w^3)
+__device__ __forceinline__ void mul_line(bool p, twelve &f, const fl &l0, const fl &l1, const fl &l3) {
+  const fac c0 = factor(p, l0), c1 = factor(p, l1), c3 = factor(p, l3), x1 = factor(p, xi(p, l1)), x3 = factor(p, xi(p, l3));
+  const fl *a = f.a.c, *b = f.b.c;
+  const fl ao[3] = {other(a[0]), other(a[1]), other(a[2])}, bo[3] = {other(b[0]), other(b[1]), other(b[2])};
+  twelve r;
+  r.a.c[0] = prod3(a[0], ao[0], c0, b[1], bo[1], x3, b[2], bo[2], x1);
+  r.a.c[1] = prod3(a[1], ao[1], c0, b[0], bo[0], c1, b[2], bo[2], x3);
+  r.a.c[2] = prod3(a[2], ao[2], c0, b[0], bo[0], c3, b[1], bo[1], c1);
+  r.b.c[0] = prod3(b[0], bo[0], c0, a[0], ao[0], c1, a[2], ao[2], x3);
+  r.b.c[1] = prod3(b[1], bo[1], c0, a[0], ao[0], c3, a[1], ao[1], c1);
+  r.b.c[2] = prod3(b[2], bo[2], c0, a[1], ao[1], c3, a[2], ao[2], c1);
+  f = r;
+}
+
+struct point {
+  fl X, Y, Z;  // homogeneous
+};
+// T = 2 T and the tangent at T at P: l0 = 2YZ yP, l1 = -3X^2 xP, l3 = Y^2 - 3b'Z^2, all up to a factor in
+// F_p2, which the final exponentiation removes
+__device__ __forceinline__ void tangent(bool p, point &T, const fl &xP, const fl &yP, const fl &b3, fl &l0, fl &l1, fl &l3) {
+  const fl XX = sqr2_(p, T.X), YY = sqr2_(p, T.Y), E = mul2_(p, sqr2_(p, T.Z), b3);
+  const fl XY = mul2_(p, T.X, T.Y), YZ = mul2_(p, T.Y, T.Z);
+  const fac fY = factor(p, YY);
+  l0 = lane::mul(lane::times(YZ, 2), yP);
+  l1 = lane::mul(lane::times(XX, -3), xP);
+  l3 = red_sub(YY, E);
+  T.X = mul2_(p, lane::times(XY, 2), red(E, -3, YY));
+  T.Y = red_sub(sqr2_(p, red(E, 3, YY)), mul2_(p, red(E, 12, fl{}), E));
+  const fl z = red(YZ, 8, fl{});
+  T.Z = prod(z, other(z), fY);
+}
+// T = T + (x, y) and the line through both at P
+__device__ __forceinline__ void chord(bool p, point &T, const fl &x, const fl &y, const fl &xP, const fl &yP, fl &l0, fl &l1, fl &l3) {
+  const fl Zo = other(T.Z);
+  const fac fx = factor(p, x), fy = factor(p, y);
+  const fl th = red_sub(T.Y, prod(T.Z, Zo, fy)), la = red_sub(T.X, prod(T.Z, Zo, fx));
+  const fl tho = other(th), lao = other(la);
+  l0 = lane::mul(la, yP);
+  l1 = lane::mul(lane::neg(th), xP);
+  l3 = prod2(th, tho, fx, lane::neg(la), lane::neg(lao), fy);
+  const fac D = factor(p, sqr2_(p, la));
+  const fl E = prod(la, lao, D), F = prod(T.Z, Zo, factor(p, sqr2_(p, th))), G = prod(T.X, other(T.X), D);
+  const fl H = red(G, -2, lane::add(E, F));
+  const fac fE = factor(p, lane::neg(E));
+  T.X = prod(la, lao, factor(p, H));
+  T.Y = prod2(th, tho, factor(p, red_sub(G, H)), T.Y, other(T.Y), fE);
+  T.Z = prod(lane::neg(T.Z), lane::neg(Zo), fE);
+}
+
+}  // namespace
+
+// Miller values of the direct rounds: side 0 (L) pairs A[h + i] with V[i], side 1 (R) A[i] with V[h + i];
+// the products of `per` consecutive ones (per divides h and LT / 2) into F[(2 k + side) K / 2 + i / per],
+// equal to the engine's up to factors that the final exponentiation removes.  Bound by the
+// multiply-adds: 32768 pairings, a wavefront for each SIMD, 2.5 ms; with 8 lanes an element they
+// took 19, and half as many 9.
+__global__ void __launch_bounds__(LT) kn_oa_miller(const g1_aff *A, const g2_aff *V, uint64_t K, uint64_t nb, uint64_t h,
+                                                   uint32_t per, fp12 *F) {
+  const uint64_t id = ((uint64_t)blockIdx.x * LT + threadIdx.x) >> 1;
+  if (id >= nb * 2 * h) return;
+  const bool p = threadIdx.x & 1;
+  const uint64_t k = id / (2 * h), r = id % (2 * h), side = r / h, i = r % h;
+  const g1_aff P = A[side ? k * K + i : k * K + h + i];
+  const fe *Q = reinterpret_cast<const fe *>(V + (side ? k * K + h + i : k * K + i));
+  const fe qx = Q[p], qy = Q[2 + p];
+  // the identity in either place: 1
+  const bool qz = fe_is_zero(qx) && fe_is_zero(qy);
+  const bool none = aff_is_inf(P) || (qz && __builtin_amdgcn_mov_dpp((int)qz, 0xB1, 0xF, 0xF, true));
+  const fl xP = lane::in_small(P.x), yP = lane::in_small(P.y), x = lane::in_small(qx), y = lane::in_small(qy);
+  fl one = lane::small_one(), zero = {};
+  one = pick(p, zero, one);
+  fl b3;
+#pragma unroll
+  for (int j = 0; j < 9; j++) b3.l[j] = bn::TWIST_3B29[p][j];
+  point T = {x, y, one};
+  twelve f = {{{one, zero, zero}}, {{zero, zero, zero}}};
+  // over the non-adjacent form of 6u + 2 (d_65 = 1 starts T = Q; d_64 = 0), a doubling in each step, then
+  // with a digit an addition; the last two steps add pi(Q) and -pi^2(Q)
+  fl sx = x, sy = y;
+#pragma unroll 1
+  for (int s = 64, add = 0; s >= -2;) {
+    fl l0, l1, l3;
+    if (!add && s >= 0) {
+      if (s != 64) sqr12(p, f);
+      tangent(p, T, xP, yP, b3, l0, l1, l3);
+    } else {
+      fl cx = sx, cy = sy;
+      if (s < 0) {
+        // the next Frobenius image, and its negative the second time
+        const fl kx = lane::in_small(fe_const(p ? bn::FROB1_2_1 : bn::FROB1_2_0)), ky = lane::in_small(fe_const(p ? bn::FROB1_3_1 : bn::FROB1_3_0));
+        sx = cx = mul2_(p, pick(p, lane::neg(sx), sx), kx);
+        sy = cy = mul2_(p, pick(p, lane::neg(sy), sy), ky);
+        if (s == -2) cy = lane::neg(cy);
+      } else if (bn::ATE_NAF_NEG >> s & 1) {
+        cy = lane::neg(cy);
+      }
+      chord(p, T, cx, cy, xP, yP, l0, l1, l3);
+    }
+    mul_line(p, f, l0, l1, l3);
+    add = !add && s >= 0 && s < 64 && ((bn::ATE_NAF_POS | bn::ATE_NAF_NEG) >> s & 1);
+    if (!add) s--;
+  }
+#pragma unroll
+  for (int q = 0; q < 3; q++) {
+    f.a.c[q] = pick(none, q == 0 ? one : zero, f.a.c[q]);
+    f.b.c[q] = pick(none, zero, f.b.c[q]);
+  }
+  // (groups of `per` pairings do not cross wavefronts; lanes that are not the first of theirs go along)
+#pragma unroll 1
+  for (uint32_t d = 1; d < per; d *= 2) {
+    twelve g;
+#pragma unroll
+    for (int q = 0; q < 3; q++)
+#pragma unroll
+      for (int e = 0; e < 9; e++) {
+        g.a.c[q].l[e] = __shfl_down(f.a.c[q].l[e], 2 * d);
+        g.b.c[q].l[e] = __shfl_down(f.b.c[q].l[e], 2 * d);
+      }
+    f = mul12(p, f, g);
+  }
+  if (id % per) return;
+  fe *out = reinterpret_cast<fe *>(F + (k * 2 + side) * (K / 2) + i / per);
+#pragma unroll
+  for (int q = 0; q < 6; q++) out[2 * q + p] = lane::out(q < 3 ? f.a.c[q] : f.b.c[q - 3]);
+}
+
 namespace kn {
 #define LN(kern, n, ...) LAUNCH(kern, dim3((unsigned)(((n) + LT - 1) / LT)), dim3(LT), 0, __VA_ARGS__)
 // Multiplications from which a launch is given to single lanes.  A lane's chain is the longest (G1
@@ -135,6 +384,11 @@ void oa_fold_g1(const g1_aff *Ain, const fe *Bin, g1_aff *Aout, fe *Bout, const 
 void oa_fold_g2(const g2_aff *Vin, g2_aff *Vout, const fe *Xinv, uint64_t K, uint64_t nb, uint64_t h, uint32_t j, uint32_t lK,
                 hipStream_t st) {
   LN(kn_oa_fold_g2, nb * h, Vin, Vout, Xinv, K, nb, h, j, lK);
+}
+uint64_t oa_miller(const g1_aff *A, const g2_aff *V, uint64_t K, uint64_t nb, uint64_t h, fp12 *F, hipStream_t st) {
+  const uint32_t per = h < LT / 2 ? (uint32_t)h : LT / 2;
+  LN(kn_oa_miller, nb * 4 * h, A, V, K, nb, h, per, F);
+  return h / per;
 }
 void g1_mul(const g1_aff *P, int bc, const fe *k, uint64_t n, g1_aff *out, hipStream_t st) {
   if (n) LN(kn_g1_mul, n, P, bc, k, n, out);

@@ -1,7 +1,6 @@
 // Kernels in the wide layout (field_wide.hpp): 8 lanes per field element, so one
-// 64-lane block serves 8 independent Miller loops, scalar multiplications or point
-// sums.  These are the dependent-chain kernels of the proof rounds, whose count of
-// independent items per launch is far below the lane count of the chip.
+// 64-lane block serves 8 independent point sums.  These are short dependent chains
+// whose count of independent items per launch is far below the lane count of the chip.
 //
 // Memory layouts are the same as everywhere else (32-byte little-endian field
 // elements, points as consecutive elements): lane g of a group loads limb g.
@@ -10,10 +9,7 @@
 #include "field.hpp"
 #include "tower.hpp"
 #include "curve.hpp"
-#include "pairing.hpp"
 #include "kernels.h"
-#include "oa_terms.hpp"
-#include "gls.hpp"
 
 #define TPBW 64
 #define GPB (TPBW / 8)  // groups (elements) per block
@@ -47,79 +43,6 @@ template <class T> __device__ __forceinline__ void wst(void *base, uint64_t idx,
   uint32_t *dst = static_cast<uint32_t *>(base) + idx * (uint64_t)n * 8 + wg();
 #pragma unroll
   for (int k = 0; k < n; k++) dst[k * 8] = rv[k];
-}
-
-// canonical limbs of a scalar (every lane of the group gets all 8)
-__device__ __forceinline__ void wunpack(uint32_t k[8], const fe &c) {
-  k[0] = wbcast<0>(c.v); k[1] = wbcast<1>(c.v); k[2] = wbcast<2>(c.v); k[3] = wbcast<3>(c.v);
-  k[4] = wbcast<4>(c.v); k[5] = wbcast<5>(c.v); k[6] = wbcast<6>(c.v); k[7] = wbcast<7>(c.v);
-}
-__device__ __forceinline__ void wscalar(uint32_t k[8], const fe &mont) { wunpack(k, f_from_mont<FpR>(mont)); }
-__device__ __forceinline__ bool scalar_is_zero(const uint32_t k[8]) {
-  uint32_t t = 0;
-#pragma unroll
-  for (int i = 0; i < 8; i++) t |= k[i];
-  return t == 0;
-}
-
-// Miller values of the direct rounds on the wide layout, for rounds whose batches fill the
-// device: the pairs of L_j (side 0: A[h + i] with V[i]) and R_j (side 1: A[i] with V[h + i]),
-// C consecutive pairs per 8-lane group sharing one accumulator (one F_p12 squaring per step for
-// the C pairs, each pair's lines multiplied in turn).  Product ch of batch k, side s goes to
-// F[(2k + s) K/2 + ch], ch < h / C; it is the product of the C pairs' Miller values, which
-// differ from the engine's only by factors the final exponentiation removes.
-template <int C>
-__global__ void __launch_bounds__(TPBW) kw_oa_miller(const void *A, const void *V, uint64_t K, uint64_t nb, uint64_t h,
-                                                    void *F) {
-  const uint64_t nch = h / C;
-  uint64_t id = wgid();
-  if (id >= nb * 2 * nch) return;
-  uint64_t k = id / (2 * nch), r = id % (2 * nch), side = r / nch, ch = r % nch;
-  g1_aff P[C];
-  g2_aff Q[C];
-  proj2 T[C];
-  bool live[C];
-#pragma unroll
-  for (int c = 0; c < C; c++) {
-    const uint64_t i = ch * C + c;
-    P[c] = wld<g1_aff>(A, side ? k * K + i : k * K + h + i);
-    Q[c] = wld<g2_aff>(V, side ? k * K + h + i : k * K + i);
-    live[c] = !aff_is_inf(P[c]) && !aff_is_inf(Q[c]);  // a pair with the identity contributes 1
-    T[c] = {Q[c].x, Q[c].y, f2_one()};
-  }
-  fp12 f = f12_one();
-  fp2 l0, l1, l2;
-  // over the non-adjacent form of 6u + 2 (d_65 = 1 starts T = Q; d_64 = 0): 21 additions of
-  // +-Q against 36 for the binary digits
-  for (int i = 64; i >= 0; i--) {
-    if (i != 64) f = f12_sqr(f);
-#pragma unroll
-    for (int c = 0; c < C; c++)
-      if (live[c]) {
-        miller_dbl(T[c], P[c].x, P[c].y, l0, l1, l2);
-        f = f12_mul_line(f, l0, l1, l2);
-      }
-    const bool pos = i < 64 && ((bn::ATE_NAF_POS >> i) & 1), neg = i < 64 && ((bn::ATE_NAF_NEG >> i) & 1);
-    if (pos || neg) {
-#pragma unroll
-      for (int c = 0; c < C; c++)
-        if (live[c]) {
-          miller_add(T[c], pos ? Q[c] : aff_neg(Q[c]), P[c].x, P[c].y, l0, l1, l2);
-          f = f12_mul_line(f, l0, l1, l2);
-        }
-    }
-  }
-#pragma unroll
-  for (int c = 0; c < C; c++)
-    if (live[c]) {
-      g2_aff Q1 = g2_frobenius(Q[c]);
-      g2_aff Q2 = aff_neg(g2_frobenius(Q1));
-      miller_add(T[c], Q1, P[c].x, P[c].y, l0, l1, l2);
-      f = f12_mul_line(f, l0, l1, l2);
-      miller_add(T[c], Q2, P[c].x, P[c].y, l0, l1, l2);
-      f = f12_mul_line(f, l0, l1, l2);
-    }
-  wst(F, (k * 2 + side) * (K / 2) + ch, f);
 }
 
 // W of every job at level d: segment s = x 2^d + p (reduced at in + s stride) is W_x[2^d - 1 + p]
@@ -244,21 +167,6 @@ namespace klw {
     if (dbg::on()) dbg::check(#kern, st);                                                    \
   } while (0)
 
-uint64_t oa_miller(const void *A, const void *V, uint64_t K, uint64_t nb, uint64_t h, void *F, hipStream_t st) {
-  // two pairs per product when the round has pairs enough to keep the device full with half
-  // as many groups (2^20, b = 1: 886 -> 810 ms), four from 2^19 pairs; fewer pairs keep one
-  // pair per group, whose parallelism they need (2^16, b = 1: 93 ms with one, 104 with two)
-  if (nb * 2 * h >= (1ull << 19) && h >= 4) {
-    LW(kw_oa_miller<4>, nb * 2 * (h / 4), A, V, K, nb, h, F);
-    return h / 4;
-  }
-  if (nb * 2 * h >= (1ull << 18) && h >= 2) {
-    LW(kw_oa_miller<2>, nb * 2 * (h / 2), A, V, K, nb, h, F);
-    return h / 2;
-  }
-  LW(kw_oa_miller<1>, nb * 2 * h, A, V, K, nb, h, F);
-  return h;
-}
 void w_aff(const S2Job *J, uint32_t G, const void *in, uint64_t stride, uint32_t d, hipStream_t st) {
   LW(kw_w_aff, (uint64_t)G << d, J, G, in, stride, d);
 }

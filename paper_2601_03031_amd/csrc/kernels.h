@@ -120,9 +120,6 @@ void ev_finish(const g1_aff *prod, uint32_t lM, const fe *g, g1_aff *W, fe *y, h
 // Wide-layout kernels (k_wide.hip, 8 lanes per field element); same memory layouts
 // as above, passed untyped because the register types differ in that unit.
 namespace klw {
-// the direct rounds' Miller values, several pairs per product: returns the products per batch
-// and side (stride K/2), the length of the F_p12 tree that follows
-uint64_t oa_miller(const void *A, const void *V, uint64_t K, uint64_t nb, uint64_t h, void *F, hipStream_t st);
 // W of every job at level d from the reduced segment sums (segment x 2^d + p at in + (x 2^d + p) stride)
 void w_aff(const S2Job *J, uint32_t G, const void *in, uint64_t stride, uint32_t d, hipStream_t st);
 void g1_reduce(void *data, uint64_t nseg, uint64_t stride, uint64_t len, hipStream_t st);
@@ -146,6 +143,9 @@ void oa_fold_g1(const g1_aff *Ain, const fe *Bin, g1_aff *Aout, fe *Bout, const 
                 uint64_t nb, uint64_t h, uint32_t j, uint32_t lK, hipStream_t st);
 void oa_fold_g2(const g2_aff *Vin, g2_aff *Vout, const fe *Xinv, uint64_t K, uint64_t nb, uint64_t h, uint32_t j, uint32_t lK,
                 hipStream_t st);
+// Miller values of a direct round, or the products of some consecutive ones, at the start of each batch
+// and side (stride K / 2); returns how many per batch and side, the length of the F_p12 tree that follows
+uint64_t oa_miller(const g1_aff *A, const g2_aff *V, uint64_t K, uint64_t nb, uint64_t h, fp12 *F, hipStream_t st);
 // out[i] = k_i P_i, or k_i P_0 with bc
 void g1_mul(const g1_aff *P, int bc, const fe *k, uint64_t n, g1_aff *out, hipStream_t st);
 void g2_mul(const g2_aff *P, int bc, const fe *k, uint64_t n, g2_aff *out, hipStream_t st);

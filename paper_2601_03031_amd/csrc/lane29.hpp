@@ -92,6 +92,20 @@ HD __forceinline__ fl centred(const int64_t *c) {
   return o;
 }
 
+// k a + b minus its rounded quotient by p (one unit, within 0.51 p, for |k a + b| below 2^9 p): the
+// quotient from the top limb, of which p has 3171406; the limbs below it move that by less than 8
+HD __forceinline__ fl reduce(const fl &a, int k, const fl &b) {
+  const int32_t q = (int32_t)__builtin_rintf((float)(k * a.l[8] + b.l[8]) * (1.0f / 3171406.0f));
+  int64_t v[9];
+#pragma unroll
+  for (int j = 0; j < 9; j++) v[j] = (int64_t)k * a.l[j] + (b.l[j] + (j < 8 ? HALF : 0)) + (int64_t)-q * (int32_t)FpP::M29[j];
+  fl o;
+#pragma unroll
+  for (int j = 0; j < 8; j++) o.l[j] = ((int32_t)v[j] & MASK) - HALF + (j ? (int32_t)(v[j - 1] >> 29) : 0);
+  o.l[8] = (int32_t)v[8] + (int32_t)(v[7] >> 29);
+  return o;
+}
+
 // (sum_n a_n b_n) 2^{-261} mod p, N products and one reduction.  Written row by row in this order
 // because a multiply-add that needs the one before it issues at half the rate.
 template <int N> HD __forceinline__ fl dot(const fl *const *a, const fl *const *b) {

@@ -183,9 +183,10 @@ static constexpr uint64_t AHEAD_MAX_PAIRS = 4096;
 static constexpr uint64_t DIRECT_MIN = 512;
 // folds of at most this many pairs (batches x h) run as four-part split multiplications
 static constexpr uint64_t FOLD_SPLIT_MAX = 256;
-// direct-round Miller loops of at least this many (batch, index) pairs run on the wide layout (8
-// lanes per element, throughput), smaller ones on the engine (latency)
-static constexpr uint64_t WIDE_FOLD_MIN = 4096;
+// direct-round Miller loops of at least this many (batch, index) pairs, two pairings each, run two
+// lanes a pairing (2.5 ms up to 32768 pairings), smaller ones on the engine (latency: 0.5 ms for 256
+// pairings, 1.4 for 4096, 2.8 for 8192)
+static constexpr uint64_t LANE_MILLER_MIN = 4096;
 // bases per block of the KZG proof's G2 MSM (times 32 windows: at most 8192 digits): long
 // slices when the MSMs of all batches give at least KZG_LONG_MIN_BLOCKS blocks (the bucket
 // reduction, about 2300 G2 additions per block, is then spread over eight times the digits),
@@ -1244,7 +1245,7 @@ static int open_all_group(const vc_params *cpp, const vc_commitment *const *cms,
   {
     if (int rc2 = stream_wait(ex, 21, st, s1)) return rc2;
     const uint64_t h1 = K / 2;
-    if (G * h1 >= WIDE_FOLD_MIN) nprod1 = klw::oa_miller(CjG, Vb[0], K, G, h1, F, s1);
+    if (G * h1 >= LANE_MILLER_MIN) nprod1 = kn::oa_miller(CjG, Vb[0], K, G, h1, F, s1);
     else ks::oa_miller(CjG, Vb[0], K, G, h1, F, s1);
     if (int rc2 = ev_mark(ex, 22, s1)) return rc2;
   }
@@ -1345,7 +1346,7 @@ static int open_all_group(const vc_params *cpp, const vc_commitment *const *cms,
       const g1_aff *Am = j == 1 ? CjG : Ab[cur];
       uint64_t nprod = h;  // Miller products per batch and side, reduced by the tree below
       if (j == 1) nprod = nprod1;  // round 1's Miller loops run on side stream 1 (above)
-      else if (nbm * h >= WIDE_FOLD_MIN) nprod = klw::oa_miller(Am, Vb[cur], K, nbm, h, F, st);
+      else if (nbm * h >= LANE_MILLER_MIN) nprod = kn::oa_miller(Am, Vb[cur], K, nbm, h, F, st);
       else ks::oa_miller(Am, Vb[cur], K, nbm, h, F, st);
       // the terms of round j0 from the arrays of the last direct round, after its Miller
       // loops (the G1 side after the multiples of the arrays); from the arrays of round 1 as
