@@ -904,10 +904,9 @@ template <class L, class A> static A lane_sum(const A *p, int n, int m) {
   return jac_to_aff(lane::to_jac<L>(lane::add<L>(s[0], s[1])));
 }
 // k P by the one-lane multiplication
-API int hc_lane_mul(int grp, const uint8_t *Pb, const uint8_t *kb, uint8_t *out) {
+API int hc_lane_mul(const uint8_t *Pb, const uint8_t *kb, uint8_t *out) {
   const fe k = rd_raw(kb);
-  if (grp == 0) wrg1(out, lane::to_aff<lane::G1>(lane::mul_lane(rdg1(Pb), glv::decompose(k.l))));
-  else wrg2(out, lane::to_aff<lane::G2>(lane::mul_lane(rdg2(Pb), gls::decompose(k.l))));
+  wrg1(out, lane::to_aff<lane::G1>(lane::mul_lane(rdg1(Pb), glv::decompose(k.l))));
   return 0;
 }
 API int hc_lane_sum(int grp, const uint8_t *pts, int n, int m, uint8_t *out) {

@@ -4,6 +4,8 @@
 #define VC_INLINE_HELPERS 1
 #include "kcommon.hpp"
 #include "lane29.hpp"
+#include "gls.hpp"
+#include "oa_terms.hpp"
 
 #define LT 64  // threads of a workgroup: one wavefront, so that they spread over the SIMDs
 
@@ -11,8 +13,24 @@ namespace {
 
 using lane::pt;
 typedef lane::G1 L1_;
-typedef lane::G2 L2_;
 using lane::mul_lane;
+
+// the sum of `per` consecutive lanes' points, in the first of them
+__device__ __forceinline__ pt<L1_> sum_groups(pt<L1_> t, pt<L1_> *sh, uint32_t per) {
+  sh[threadIdx.x] = t;
+  __syncthreads();
+#pragma unroll 1
+  for (uint32_t s = 1; s < per; s *= 2) {
+    const bool on = threadIdx.x % (2 * s) == 0;
+    if (on) t = lane::add<L1_>(t, sh[threadIdx.x + s]);
+    __syncthreads();
+    if (on) sh[threadIdx.x] = t;
+    __syncthreads();
+  }
+  return t;
+}
+// homogeneous, packed, in the place of a Jacobian point
+__device__ __forceinline__ g1_jac hom(const pt<L1_> &t) { return {lane::out(t.X), lane::out(t.Y), lane::out(t.Z)}; }
 
 }  // namespace
 
@@ -43,45 +61,36 @@ __global__ void __launch_bounds__(LT) kn_oa_g1terms(const g1_aff *A, const fe *B
     const fe c = f_from_mont<FpR>(B[side ? k * K + h + i : k * K + i]);
     t = mul_lane(A[side ? k * K + i : k * K + h + i], glv::decompose(c.l));
   }
-  sh[threadIdx.x] = t;
-  __syncthreads();
-#pragma unroll 1
-  for (uint32_t s = 1; s < per; s *= 2) {
-    const bool on = threadIdx.x % (2 * s) == 0;
-    if (on) t = lane::add<L1_>(t, sh[threadIdx.x + s]);
-    __syncthreads();
-    if (on) sh[threadIdx.x] = t;
-    __syncthreads();
-  }
-  if (live && threadIdx.x % per == 0) S[(k * 2 + side) * (K / 2) + i / per] = {lane::out(t.X), lane::out(t.Y), lane::out(t.Z)};
+  t = sum_groups(t, sh, per);
+  if (live && threadIdx.x % per == 0) S[(k * 2 + side) * (K / 2) + i / per] = hom(t);
 }
 
-// v_j = v_L o v_R^{1/x_j}; Vout may be Vin
-__global__ void __launch_bounds__(LT) kn_oa_fold_g2(const g2_aff *Vin, g2_aff *Vout, const fe *Xinv, uint64_t K, uint64_t nb,
-                                                    uint64_t h, uint32_t j, uint32_t lK) {
+// the same for the G1 terms b[v] A[a] taken a round ahead (oa_terms.hpp; per divides q and LT): the
+// groups' sums at the start of each group's place in S1
+__global__ void __launch_bounds__(LT) kn_oa_g1terms_next(const g1_aff *A, const fe *B, uint64_t K, uint64_t nb, uint64_t q,
+                                                         uint32_t per, g1_jac *S1) {
+  __shared__ pt<L1_> sh[LT];
   const uint64_t id = (uint64_t)blockIdx.x * LT + threadIdx.x;
-  if (id >= nb * h) return;
-  const uint64_t k = id / h, i = id % h;
-  const fe c = f_from_mont<FpR>(Xinv[k * lK + (j - 1)]);
-  pt<L2_> t = mul_lane(Vin[k * K + h + i], gls::decompose(c.l));
-  const g2_aff l = Vin[k * K + i];
-  if (!aff_is_inf(l)) t = lane::madd<L2_>(t, L2_::in(l.x), L2_::in(l.y));
-  Vout[k * K + i] = lane::to_aff<L2_>(t);
+  const bool live = id < nb * 8 * q;
+  const oat::Term tm = oat::term(live ? id : 0, K, nb, q);
+  pt<L1_> t = lane::identity<L1_>();
+  if (live) {
+    const fe c = f_from_mont<FpR>(B[tm.v]);
+    t = mul_lane(A[tm.a], glv::decompose(c.l));
+  }
+  t = sum_groups(t, sh, per);
+  const uint64_t len = id % (8 * q) < 4 * q ? 2 * q : q, at = tm.out % len;  // (both areas hold whole groups)
+  if (live && threadIdx.x % per == 0) S1[tm.out - at + at / per] = hom(t);
 }
 
 // out[i] = k_i P_i (P_0 with broadcast), affine
-template <class L, class Dec>
-__device__ __forceinline__ aff<typename L::O> mul_aff(const aff<typename L::O> &P, const fe &k_mont, Dec (*split)(const uint32_t *)) {
+__device__ __forceinline__ g1_aff mul_aff(const g1_aff &P, const fe &k_mont) {
   const fe c = f_from_mont<FpR>(k_mont);
-  return lane::to_aff<L>(mul_lane(P, split(c.l)));
+  return lane::to_aff<L1_>(mul_lane(P, glv::decompose(c.l)));
 }
 __global__ void __launch_bounds__(LT) kn_g1_mul(const g1_aff *P, int broadcast, const fe *k, uint64_t n, g1_aff *out) {
   const uint64_t i = (uint64_t)blockIdx.x * LT + threadIdx.x;
-  if (i < n) out[i] = mul_aff<L1_>(P[broadcast ? 0 : i], k[i], glv::decompose);
-}
-__global__ void __launch_bounds__(LT) kn_g2_mul(const g2_aff *P, int broadcast, const fe *k, uint64_t n, g2_aff *out) {
-  const uint64_t i = (uint64_t)blockIdx.x * LT + threadIdx.x;
-  if (i < n) out[i] = mul_aff<L2_>(P[broadcast ? 0 : i], k[i], gls::decompose);
+  if (i < n) out[i] = mul_aff(P[broadcast ? 0 : i], k[i]);
 }
 
 // HyperEval terms (canonical differences of the folded table g* times PST keys) of every job:
@@ -106,7 +115,7 @@ __global__ void __launch_bounds__(LT) kn_d_leaves(const S2Job *J, uint32_t G, ui
   if (id >= G * K) return;
   const S2Job &jb = J[id / K];
   const uint64_t j = id % K;
-  jb.D[j] = mul_aff<L1_>(jb.Cj[j], jb.rho[j], glv::decompose);
+  jb.D[j] = mul_aff(jb.Cj[j], jb.rho[j]);
 }
 
 // ---------------------------------------------------------------- Miller loops
@@ -246,6 +255,80 @@ __device__ __forceinline__ void mul_line(bool p, twelve &f, const fl &l0, const 
   f = r;
 }
 
+// G2 with a lane for each component of its coordinates (lane29.hpp's group law on the lane's own)
+struct G2pair {
+  using T = fl;
+  static __device__ __forceinline__ bool p() { return threadIdx.x & 1; }
+  static __device__ __forceinline__ T zero() { return T{}; }
+  static __device__ __forceinline__ T some() { return T{{!p()}}; }
+  static __device__ __forceinline__ T one() { return pick(p(), T{}, lane::small_one()); }
+  static __device__ __forceinline__ T add(const T &a, const T &b) { return lane::add(a, b); }
+  static __device__ __forceinline__ T sub(const T &a, const T &b) { return lane::sub(a, b); }
+  static __device__ __forceinline__ T neg(const T &a) { return lane::neg(a); }
+  static __device__ __forceinline__ T norm(const T &a) { return lane::norm(a); }
+  static __device__ __forceinline__ T times(const T &a, int k) { return lane::times(a, k); }
+  static __device__ __forceinline__ T norm_times(const T &a, int k) { return lane::norm_times(a, k); }
+  static __device__ __forceinline__ T mul(const T &a, const T &b) { return mul2_(p(), a, b); }
+  static __device__ __forceinline__ T mul2(const T &a, const T &b, const T &c, const T &d) {
+    return prod2(a, other(a), factor(p(), b), c, other(c), factor(p(), d));
+  }
+  static __device__ __forceinline__ T sqr(const T &a) { return sqr2_(p(), a); }
+  static __device__ __forceinline__ T b3(const T &a) {
+    T k;
+#pragma unroll
+    for (int j = 0; j < 9; j++) k.l[j] = bn::TWIST_3B29[p()][j];
+    return mul(a, k);
+  }
+};
+
+// k Q on G2 with the split k = sum_j k_j lam^j (gls.hpp): the table of the 15 subset sums of
+// sign(k_j) psi^j(Q), a doubling and at most one addition per bit.  x, y: this lane's components of Q;
+// inf and d are the same in both lanes
+__device__ __forceinline__ pt<G2pair> mul_pair(const fe &qx, const fe &qy, bool inf, const gls::Dec &d) {
+  if (inf || d.nbits == 0) return lane::identity<G2pair>();
+  const bool p = G2pair::p();
+  pt<G2pair> T[16];
+  fl x = lane::in_small(qx), y = lane::in_small(qy);
+  const fl kx = lane::in_small(fe_const(p ? bn::FROB1_2_1 : bn::FROB1_2_0)), ky = lane::in_small(fe_const(p ? bn::FROB1_3_1 : bn::FROB1_3_0));
+#pragma unroll 1
+  for (int j = 0; j < 4; j++) {
+    if (j) {
+      x = mul2_(p, pick(p, lane::neg(x), x), kx);
+      y = mul2_(p, pick(p, lane::neg(y), y), ky);
+    }
+    const fl s = pick(d.neg >> j & 1, lane::neg(y), y);
+    T[1 << j] = {x, s, G2pair::one()};
+#pragma unroll 1
+    for (int e = 1; e < 1 << j; e++) T[e + (1 << j)] = lane::madd<G2pair>(T[e], x, s);
+  }
+  const int n = (int)d.nbits;
+  pt<G2pair> acc = T[gls::digit(d, (uint32_t)(n - 1))];
+#pragma unroll 1
+  for (int t = n - 2; t >= 0; t--) {
+    acc = lane::dbl<G2pair>(acc);
+    const uint32_t dg = gls::digit(d, (uint32_t)t);
+    if (dg) acc = lane::add<G2pair>(acc, T[dg]);
+  }
+  return acc;
+}
+__device__ __forceinline__ fe other_fe(const fe &a) {
+  fe o;
+#pragma unroll
+  for (int j = 0; j < 8; j++) o.l[j] = __builtin_amdgcn_mov_dpp(a.l[j], 0xB1, 0xF, 0xF, true);
+  return o;
+}
+// this lane's components of the affine point; zeros for the identity
+__device__ __forceinline__ void to_aff_pair(const pt<G2pair> &t, fe &x, fe &y) {
+  const fe z = lane::out(t.Z), zo = other_fe(z), n = fp_add(fp_sqr(z), fp_sqr(zo));
+  x = y = fe_zero();
+  if (fe_is_zero(n)) return;  // (a sum of two squares is zero for zeros only: -1 is no square)
+  const fe w = fp_mul(z, fp_inv_fast(n));
+  const fl zi = lane::in(G2pair::p() ? fp_neg(w) : w);
+  x = lane::out(G2pair::mul(t.X, zi));
+  y = lane::out(G2pair::mul(t.Y, zi));
+}
+__device__ __forceinline__ bool both(bool c) { return c && __builtin_amdgcn_mov_dpp((int)c, 0xB1, 0xF, 0xF, true); }
+
 struct point {
   fl X, Y, Z;  // homogeneous
 };
@@ -283,6 +366,41 @@ __device__ __forceinline__ void chord(bool p, point &T, const fl &x, const fl &y
 
 }  // namespace
 
+// v_j = v_L o v_R^{1/x_j}, two lanes a point (half the chain and half the state of one lane a point: 16384
+// of them 1.5 ms for 2.5); Vout may be Vin
+__global__ void __launch_bounds__(LT) kn_oa_fold_g2(const g2_aff *Vin, g2_aff *Vout, const fe *Xinv, uint64_t K, uint64_t nb,
+                                                    uint64_t h, uint32_t j, uint32_t lK) {
+  const uint64_t id = ((uint64_t)blockIdx.x * LT + threadIdx.x) >> 1;
+  if (id >= nb * h) return;
+  const bool p = G2pair::p();
+  const uint64_t k = id / h, i = id % h;
+  const fe c = f_from_mont<FpR>(Xinv[k * lK + (j - 1)]);
+  const fe *r = reinterpret_cast<const fe *>(Vin + k * K + h + i), *l = reinterpret_cast<const fe *>(Vin + k * K + i);
+  const fe rx = r[p], ry = r[2 + p], lx = l[p], ly = l[2 + p];
+  pt<G2pair> t = mul_pair(rx, ry, both(fe_is_zero(rx) && fe_is_zero(ry)), gls::decompose(c.l));
+  if (!both(fe_is_zero(lx) && fe_is_zero(ly))) t = lane::madd<G2pair>(t, lane::in_small(lx), lane::in_small(ly));
+  fe x, y;
+  to_aff_pair(t, x, y);
+  fe *o = reinterpret_cast<fe *>(Vout + k * K + i);
+  o[p] = x;
+  o[2 + p] = y;
+}
+
+// out[i] = k_i P_i (P_0 with broadcast) on G2, two lanes a point
+__global__ void __launch_bounds__(LT) kn_g2_mul(const g2_aff *P, int broadcast, const fe *k, uint64_t n, g2_aff *out) {
+  const uint64_t i = ((uint64_t)blockIdx.x * LT + threadIdx.x) >> 1;
+  if (i >= n) return;
+  const bool p = G2pair::p();
+  const fe c = f_from_mont<FpR>(k[i]);
+  const fe *q = reinterpret_cast<const fe *>(P + (broadcast ? 0 : i));
+  const fe qx = q[p], qy = q[2 + p];
+  fe x, y;
+  to_aff_pair(mul_pair(qx, qy, both(fe_is_zero(qx) && fe_is_zero(qy)), gls::decompose(c.l)), x, y);
+  fe *o = reinterpret_cast<fe *>(out + i);
+  o[p] = x;
+  o[2 + p] = y;
+}
+
 // Miller values of the direct rounds: side 0 (L) pairs A[h + i] with V[i], side 1 (R) A[i] with V[h + i];
 // the products of `per` consecutive ones (per divides h and LT / 2) into F[(2 k + side) K / 2 + i / per],
 // equal to the engine's up to factors that the final exponentiation removes.  Bound by the
@@ -299,7 +417,7 @@ __global__ void __launch_bounds__(LT) kn_oa_miller(const g1_aff *A, const g2_aff
   const fe qx = Q[p], qy = Q[2 + p];
   // the identity in either place: 1
   const bool qz = fe_is_zero(qx) && fe_is_zero(qy);
-  const bool none = aff_is_inf(P) || (qz && __builtin_amdgcn_mov_dpp((int)qz, 0xB1, 0xF, 0xF, true));
+  const bool none = aff_is_inf(P) || both(qz);
   const fl xP = lane::in_small(P.x), yP = lane::in_small(P.y), x = lane::in_small(qx), y = lane::in_small(qy);
   fl one = lane::small_one(), zero = {};
   one = pick(p, zero, one);
@@ -360,11 +478,11 @@ __global__ void __launch_bounds__(LT) kn_oa_miller(const g1_aff *A, const g2_aff
 
 namespace kn {
 #define LN(kern, n, ...) LAUNCH(kern, dim3((unsigned)(((n) + LT - 1) / LT)), dim3(LT), 0, __VA_ARGS__)
-// Multiplications from which a launch is given to single lanes.  A lane's chain is the longest (G1
-// 0.9 to 1.1 ms, G2 2.4, whatever the number up to 65536, a wavefront for each SIMD), but it does the least work
-// for it: with 8 lanes a field element 65536 G1 terms took 7.5 ms and 32768 G2 folds 9.4, and none
-// less than 1.7.  The engine's workgroup for each takes 0.4 ms (G1) to 0.7 (a fold) up to 2048 of them, and
-// 1.5 ms for 8192 terms, with the whole chip.
+// Multiplications from which a launch is given to lanes.  A lane's chain is the longest (G1 0.9 to 1.1
+// ms, a G2 fold on two lanes 1.5, whatever the number up to a wavefront for each SIMD), but it does the least
+// work for it: the engine's workgroup for each takes 0.4 ms (G1) to 0.85 (a fold) for a few, and
+// 1.5 ms for 8192 terms, with the whole chip.  With the line at 1024 an open-all of 2^10 entries, b = 1,
+// took 9.4 ms against 8.75, one of 2^17, b = 34, 16.5 against 16.8.
 static constexpr uint64_t LANE_MIN = 4096;
 
 uint64_t oa_g1terms(const g1_aff *A, const fe *B, uint64_t K, uint64_t nb, uint64_t h, g1_jac *S, hipStream_t st) {
@@ -376,6 +494,15 @@ uint64_t oa_g1terms(const g1_aff *A, const fe *B, uint64_t K, uint64_t nb, uint6
   LN(kn_oa_g1terms, nb * 2 * h, A, B, K, nb, h, per, S);
   return h / per;
 }
+uint64_t oa_g1terms_next(const g1_aff *A, const fe *B, uint64_t K, uint64_t nb, uint64_t q, g1_jac *S1, hipStream_t st) {
+  if (nb * 8 * q < LANE_MIN) {
+    ks::oa_g1terms_next(A, B, K, nb, q, S1, st);
+    return 1;
+  }
+  const uint32_t per = q < LT ? (uint32_t)q : LT;
+  LN(kn_oa_g1terms_next, nb * 8 * q, A, B, K, nb, q, per, S1);
+  return per;
+}
 bool fold_lanes(uint64_t nb, uint64_t h) { return nb * h >= LANE_MIN; }
 void oa_fold_g1(const g1_aff *Ain, const fe *Bin, g1_aff *Aout, fe *Bout, const fe *Xinv, const glv::Dec *dec, uint64_t K,
                 uint64_t nb, uint64_t h, uint32_t j, uint32_t lK, hipStream_t st) {
@@ -383,7 +510,7 @@ void oa_fold_g1(const g1_aff *Ain, const fe *Bin, g1_aff *Aout, fe *Bout, const 
 }
 void oa_fold_g2(const g2_aff *Vin, g2_aff *Vout, const fe *Xinv, uint64_t K, uint64_t nb, uint64_t h, uint32_t j, uint32_t lK,
                 hipStream_t st) {
-  LN(kn_oa_fold_g2, nb * h, Vin, Vout, Xinv, K, nb, h, j, lK);
+  LN(kn_oa_fold_g2, 2 * nb * h, Vin, Vout, Xinv, K, nb, h, j, lK);
 }
 uint64_t oa_miller(const g1_aff *A, const g2_aff *V, uint64_t K, uint64_t nb, uint64_t h, fp12 *F, hipStream_t st) {
   const uint32_t per = h < LT / 2 ? (uint32_t)h : LT / 2;
@@ -394,7 +521,7 @@ void g1_mul(const g1_aff *P, int bc, const fe *k, uint64_t n, g1_aff *out, hipSt
   if (n) LN(kn_g1_mul, n, P, bc, k, n, out);
 }
 void g2_mul(const g2_aff *P, int bc, const fe *k, uint64_t n, g2_aff *out, hipStream_t st) {
-  if (n) LN(kn_g2_mul, n, P, bc, k, n, out);
+  if (n) LN(kn_g2_mul, 2 * n, P, bc, k, n, out);
 }
 void hyper_terms(const S2Job *J, uint32_t G, uint64_t K, const g1_aff *ek, uint64_t M, uint32_t lM, g1_jac *S, hipStream_t st) {
   LN(kn_hyper_terms, G * lM * (M / 2), J, G, K, ek, M, lM, S);

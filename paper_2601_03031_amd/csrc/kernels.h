@@ -137,6 +137,8 @@ namespace kn {
 // G1 terms of a direct round, homogeneous, into S[(2 k + side) (K / 2) + i]: the terms or the sums of
 // some consecutive ones; returns how many per batch and side
 uint64_t oa_g1terms(const g1_aff *A, const fe *B, uint64_t K, uint64_t nb, uint64_t h, g1_jac *S, hipStream_t st);
+// G1 terms of the next round (oa_terms.hpp), homogeneous; returns how many consecutive ones are summed
+uint64_t oa_g1terms_next(const g1_aff *A, const fe *B, uint64_t K, uint64_t nb, uint64_t q, g1_jac *S1, hipStream_t st);
 // whether a direct round of nb batches folds on single lanes (else ks::oa_fold)
 bool fold_lanes(uint64_t nb, uint64_t h);
 void oa_fold_g1(const g1_aff *Ain, const fe *Bin, g1_aff *Aout, fe *Bout, const fe *Xinv, const glv::Dec *dec, uint64_t K,

@@ -16,7 +16,6 @@
 #pragma once
 #include "curve.hpp"
 #include "glv.hpp"
-#include "gls.hpp"
 
 namespace lane {
 
@@ -351,32 +350,6 @@ HD __forceinline__ pt<G1> mul_lane(const g1_aff &P, const glv::Dec &d) {
     for (int i = 0; i < 2; i++) acc = dbl<G1>(acc);
     const uint32_t dg = glv::digit2(d, (uint32_t)w);
     if (dg) acc = add<G1>(acc, T[dg]);
-  }
-  return acc;
-}
-
-// k Q on G2 with the split k = sum_j k_j lam^j (gls.hpp): the table of the 15 subset sums of
-// sign(k_j) psi^j(Q), a doubling and at most one addition per bit
-HD __forceinline__ pt<G2> mul_lane(const g2_aff &Q, const gls::Dec &d) {
-  if (aff_is_inf(Q) || d.nbits == 0) return identity<G2>();
-  pt<G2> T[16];
-  const fl2 one = {small_one(), {}};
-  g2_aff B = Q;
-#pragma unroll 1
-  for (int j = 0; j < 4; j++) {
-    if (j) B = g2_frobenius(B);
-    const fl2 x = G2::in_small(B.x), yy = G2::in_small(B.y), y = d.neg >> j & 1 ? G2::neg(yy) : yy;
-    T[1 << j] = {x, y, one};
-#pragma unroll 1
-    for (int e = 1; e < 1 << j; e++) T[e + (1 << j)] = madd<G2>(T[e], x, y);
-  }
-  const int n = (int)d.nbits;
-  pt<G2> acc = T[gls::digit(d, (uint32_t)(n - 1))];
-#pragma unroll 1
-  for (int t = n - 2; t >= 0; t--) {
-    acc = dbl<G2>(acc);
-    const uint32_t dg = gls::digit(d, (uint32_t)t);
-    if (dg) acc = add<G2>(acc, T[dg]);
   }
   return acc;
 }

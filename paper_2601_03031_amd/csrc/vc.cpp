@@ -1323,12 +1323,13 @@ static int open_all_group(const vc_params *cpp, const vc_commitment *const *cms,
   auto launch_g1terms = [&](uint32_t jn) -> int {
     uint64_t q = K >> jn;
     int par = jn & 1, src = (jn - 2) & 1;
+    uint64_t per = 1;  // consecutive terms summed already
     if (split_round(jn - 1))
       ks::oa_g1terms_split(Ab[src], Bb[src], FM1[(jn - 1) & 1], K, nb, q, GJ, cnt_g1s, PS[par], sq);
     else
-      ks::oa_g1terms_next(Ab[src], Bb[src], K, nb, q, PS[par], sq);
-    ks::g1_tree(PS[par], 2 * nb, 2 * q, 2 * q, cnt_gu[par], sq);
-    ks::g1_tree(PS[par] + nb * 4 * q, 4 * nb, q, q, cnt_gxy[par], sq);
+      per = kn::oa_g1terms_next(Ab[src], Bb[src], K, nb, q, PS[par], sq);
+    ks::g1_tree(PS[par], 2 * nb, 2 * q, 2 * q / per, cnt_gu[par], sq);
+    ks::g1_tree(PS[par] + nb * 4 * q, 4 * nb, q, q / per, cnt_gxy[par], sq);
     ks::g1_finish(PS[par], nb, q, PU1[par], PX1[par], PX1m[par], sq);
     return ev_mark(ex, 8 + par, sq);
   };
