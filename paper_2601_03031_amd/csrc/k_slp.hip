@@ -251,8 +251,10 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_kzg_terms_split(const g2_aff *h, 
 }
 
 // ---------------------------------------------------------------- G_T exponentiation
-// out = in^k (k in Montgomery F_r form; kc: 8 words of LDS), square-and-multiply with the engine's
-// F_p12 product (inputs need not lie in the cyclotomic subgroup)
+// out = in^k (k in Montgomery F_r form; kc: 16 words of LDS), square-and-multiply.  The input may be any
+// element: one of the cyclotomic subgroup, as every pairing value is (x^{p^4} x = x^{p^2}: two Frobenius
+// maps and a product), takes its squarings, half as long as the general ones, and the non-adjacent form of
+// k, as its inverse is its conjugate: a power 0.70 ms for 1.03
 __device__ void gt_pow_job(Ctx c, const fp12 *in, const fe *k_mont, uint32_t *kc, fp12 *out) {
   f29 *S = c.S;
   const int t = threadIdx.x;
@@ -264,6 +266,33 @@ __device__ void gt_pow_job(Ctx c, const fp12 *in, const fe *k_mont, uint32_t *kc
   }
   load_consts<slp::F12_NCONST>(S, slp::F12_CBASE, slp::F12_CONSTS);
   __syncthreads();
+  c.run(slp::PROG_F12_FROB2, F12_BUF(0), F12_BUF(0), F12_BUF(1));
+  c.run(slp::PROG_F12_FROB2, F12_BUF(1), F12_BUF(1), F12_BUF(2));
+  c.run(slp::PROG_F12_MUL, F12_BUF(2), F12_BUF(0), F12_BUF(3));
+  bool same = true;
+  if (t < 12) {
+    const f29 x = slp::canon29(S[F12_BUF(1) + t]), y = slp::canon29(S[F12_BUF(3) + t]);
+    for (int i = 0; i < 9; i++) same = same && x.l[i] == y.l[i];
+  }
+  const bool cyc = __syncthreads_and(same);
+  if (cyc) c.run(slp::PROG_F12_CONJ, F12_BUF(0), F12_BUF(0), F12_BUF(3));
+  // the digits: +1 where a bit of kc[0 .. 8) is set, -1 of kc[8 .. 16); the non-adjacent form is (3k - k) / 2
+  // digit by digit
+  if (t == 0) {
+    uint32_t h[9], carry = 0;
+    for (int w = 0; w < 8; w++) {
+      const uint64_t v = 3ull * kc[w] + carry;
+      h[w] = (uint32_t)v;
+      carry = (uint32_t)(v >> 32);
+    }
+    h[8] = 0;  // 3 k is below 2^256
+    for (int w = 0; w < 8; w++) {
+      const uint32_t k0 = kc[w], k1 = w < 7 ? kc[w + 1] : 0, p0 = h[w] & ~k0, p1 = h[w + 1] & ~k1, n0 = k0 & ~h[w], n1 = k1 & ~h[w + 1];
+      kc[8 + w] = cyc ? n0 >> 1 | n1 << 31 : 0;
+      if (cyc) kc[w] = p0 >> 1 | p1 << 31;
+    }
+  }
+  __syncthreads();
   int top = -1;
   for (int b = 255; b >= 0; b--)
     if ((kc[b >> 5] >> (b & 31)) & 1) { top = b; break; }
@@ -272,16 +301,17 @@ __device__ void gt_pow_job(Ctx c, const fp12 *in, const fe *k_mont, uint32_t *kc
     if (t < 12) dst[t] = t == 0 ? f_one<FpP>() : fe_zero();
     return;
   }
-  // a call per bit below the top one (a squaring, with a product where the bit is set), the
-  // accumulator alternating between buffers 1 and 2; buffer 0 holds the base
+  const int sqr = cyc ? slp::PROG_F12_CSQR : slp::PROG_F12_SQR, sqr_mul = cyc ? slp::PROG_F12_CSQR_MUL : slp::PROG_F12_SQR_MUL;
+  // a call per bit below the top one (a squaring, with a product where the digit is not zero),
+  // the accumulator alternating between buffers 1 and 2; buffer 0 holds the base, 3 its conjugate
 #pragma unroll 1
   for (int first = 0; first < top; first += slp::MAX_CALLS) {
     const int n = top - first < slp::MAX_CALLS ? top - first : slp::MAX_CALLS;
     for (int e = t; e < n; e += SLP_T) {
       const int i = first + e, bit = top - 1 - i, src = i == 0 ? 0 : 2 - (i & 1), dst = 1 + (i & 1);
-      const bool one = kc[bit >> 5] >> (bit & 31) & 1;
-      c.cl[e] = one ? slp::call(slp::PROG_F12_SQR_MUL, F12_BUF(src), F12_BUF(0), F12_BUF(dst))
-                    : slp::call(slp::PROG_F12_SQR, F12_BUF(src), F12_BUF(src), F12_BUF(dst));
+      const bool one = kc[bit >> 5] >> (bit & 31) & 1, minus = kc[8 + (bit >> 5)] >> (bit & 31) & 1;
+      c.cl[e] = one || minus ? slp::call(sqr_mul, F12_BUF(src), F12_BUF(minus ? 3 : 0), F12_BUF(dst))
+                    : slp::call(sqr, F12_BUF(src), F12_BUF(src), F12_BUF(dst));
     }
     c.run_list(0, n);
   }
@@ -337,16 +367,16 @@ __global__ void __launch_bounds__(SLP_T, 4) ks_g1_mul(const g1_aff *P, const fe 
 
 // The powers and multiples of a verification in one launch, a workgroup each: X[i]^{kx_i} of n3
 // elements of F_p12, k_i Q on G2 of n2 scalars (one base), k_i P_i on G1 of n1 points, the longest
-// first.  At 2^16 entries in batches of 256 (16, 1 and 276 of them) 1.0 ms, the time of a power;
+// first.  At 2^16 entries in batches of 256 (16, 1 and 276 of them) 0.71 ms, the time of a power;
 // one after another, the multiples with 8 lanes a field element, they took 1.0 + 3.2 + 1.5 ms.
 __global__ void __launch_bounds__(SLP_T, 4) ks_mults(const fp12 *X, const fe *kx, uint64_t n3, fp12 *outx, const g2_aff *Q,
                                                      const fe *kq, uint64_t n2, g2_aff *outq, const g1_aff *P, const fe *kp,
                                                      uint64_t n1, g1_aff *outp) {
-  __shared__ f29 S[most(slp::G1_NSLOT, slp::G2_NSLOT, slp::F12_NSLOT + 36)];
+  __shared__ f29 S[most(slp::G1_NSLOT, slp::G2_NSLOT, slp::F12_NSLOT + 48)];
   CALL_LIST();
   __shared__ glv::Dec d1;
   __shared__ gls::Dec d2;
-  __shared__ uint32_t kc[8];
+  __shared__ uint32_t kc[16];
   Ctx c{S, calls_sh};
   uint64_t i = blockIdx.x;
   if (i < n3) {
