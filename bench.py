@@ -168,11 +168,11 @@ def work_model(L, b, limbs, costs):
     # 2 x 255 additions per block of 32 bases); then the engine tree over the partial sums
     if 4 * nb * nq <= KZG_SPLIT_MAX:
         w["ks_kzg_terms_split"] = 4 * nb * nq * costs["e_g2_part"]
-        w["ks_jac_tree<true>"] = nb * (4 * nq - 1) * costs["e_g2_add"]
+        w["(ks_pt_tree<true, true>)"] = nb * (4 * nq - 1) * costs["e_g2_add"]
     else:
         kzg_blocks = nb * (-(-nq // 32))
         w["k_msm_slices<lane::G2>"] = (nb * nq * 32 * 255 // 256) * costs["g2_madd"] + kzg_blocks * 510 * costs["g2_add"]
-        w["ks_jac_tree<true>"] = (kzg_blocks - nb) * costs["e_g2_add"]
+        w["(ks_pt_tree<true, false>)"] = (kzg_blocks - nb) * costs["e_g2_add"]
     if lK >= 2 and nb * K <= AHEAD_MAX_PAIRS:
         # rounds j < j0 direct (the device is full), rounds j >= j0 from terms of the arrays of
         # round j - 1 (q = K >> j)
@@ -193,7 +193,7 @@ def work_model(L, b, limbs, costs):
             "ks_final_exp": (sum(2 * nbr(h) for h in direct) + 1) * costs["e_final_exp"],
             "ks_f12_tree": (K - 1 + sum(2 * nbr(h) * (h - 1) for h in direct)
                             + sum(2 * nb * (2 * q - 1) + 4 * nb * (q - 1) for q in qs)) * costs["e_f12_mul"],
-            "ks_jac_tree<false>": (sum(2 * nb * (h - 1) for h in direct)
+            "(ks_pt_tree<false, true>)": (sum(2 * nb * (h - 1) for h in direct)
                                    + sum(2 * nb * (2 * q - 1) + 4 * nb * (q - 1) for q in qs)) * costs["e_g1_add"],
             "ks_oa_fold": sum(whole) * (g1_fold + g2_fold),
             "ks_oa_fold_split": sum(split) * (4 * costs["e_g1_part"] + g1_sum + 4 * costs["e_g2_part"] + g2_sum),
