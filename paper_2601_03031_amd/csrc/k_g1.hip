@@ -128,7 +128,7 @@ __global__ void __launch_bounds__(TPB) k_check_curve(const aff<O> *p, uint64_t n
 // (S, W) pairs with doublings does a quarter of the scan's additions but measured slower:
 // with one block per CU at N = 2^16 the block's latency sets the time, and its doubling
 // chains are longer than the scan's eight steps.)  Bound by the issue of its products: the
-// complete additions on one-lane limbs (lane29.hpp) take 1024 rows of 1024 bases in 4.2 ms, Jacobian
+// complete additions on one-lane limbs (lane29.hpp) take 1024 rows of 1024 bases in 3.7 ms, Jacobian
 // ones on packed elements took 6.5.  A block takes g consecutive slices of a row (g divides their
 // number): blk = (j nslice + slice) / g, and leaves their sum in the first one's place.
 template <class L>
@@ -143,6 +143,14 @@ __device__ __forceinline__ void msm_slice(const fe *scal, uint64_t M, uint32_t n
   __shared__ __align__(16) uint8_t pool[ENT_B > RED_B ? ENT_B : RED_B];
   uint32_t *ent = reinterpret_cast<uint32_t *>(pool);
   pt *red = reinterpret_cast<pt *>(pool);
+  // Scalars of all 32 windows take signed digits: with 128 added to every byte, a byte less 128 is the
+  // digit, -128 .. 127 (the top byte of a scalar below r stays below 256), and 128 buckets take two
+  // threads each (2^20 entries 3.7 ms against 4.2 with 255 buckets, a thread each: the halves are of more
+  // even length, and the reduction is half as wide).  Shorter scalars, whose top window would need one
+  // more, keep digits 0 .. 255.
+  const bool sgn = nwin == 32;
+  const uint32_t nbkt = sgn ? 128 : 256;  // bucket d is at place d - 1
+  __shared__ uint32_t rec[MAXE / 32 * 8];
   const uint32_t nslice = (uint32_t)((M + S - 1) / S);
   const uint64_t j = blk * g / nslice;
   const uint32_t t = threadIdx.x;
@@ -152,54 +160,72 @@ __device__ __forceinline__ void msm_slice(const fe *scal, uint64_t M, uint32_t n
     const uint64_t a0 = (uint64_t)sl * S;
     const uint32_t na = (uint32_t)((a0 + S <= M) ? S : (M - a0));
     cnt[t] = 0;
-    __syncthreads();  // (also: the digits of the slice before are read)
     const fe *sc = scal + j * M + a0;
+    if (sgn)
+      for (uint32_t a = t; a < na; a += 256) {
+        uint64_t c = 0;
+        for (int q = 0; q < 8; q++) {
+          c += (uint64_t)sc[a].l[q] + 0x80808080u;
+          rec[8 * a + q] = (uint32_t)c;
+          c >>= 32;
+        }
+      }
+    __syncthreads();  // (also: the digits of the slice before are read)
+    // digit w of scalar a: its magnitude, and bit 31 where it is negative
+    auto digit = [&](uint32_t a, uint32_t w) -> uint32_t {
+      const uint32_t b = ((sgn ? rec[8 * a + (w >> 2)] : sc[a].l[w >> 2]) >> ((w & 3) * 8)) & 0xff;
+      return !sgn ? b : b >= 128 ? b - 128 : (128 - b) | 0x80000000u;
+    };
     const uint32_t ne = na * nwin;
     for (uint32_t e = t; e < ne; e += 256) {
-      uint32_t a = e / nwin, w = e % nwin;
-      uint32_t d = (sc[a].l[w >> 2] >> ((w & 3) * 8)) & 0xff;
-      if (d) atomicAdd(&cnt[d], 1u);
+      const uint32_t d = digit(e / nwin, e % nwin) & 0xff;
+      if (d) atomicAdd(&cnt[d - 1], 1u);
     }
     __syncthreads();
     if (t == 0) {
       uint32_t s = 0;
-      for (int d = 0; d < 256; d++) { off[d] = s; s += cnt[d]; }
+      for (uint32_t d = 0; d < nbkt; d++) { off[d] = s; s += cnt[d]; }
     }
     __syncthreads();
-    const uint32_t start = off[t], len = t ? cnt[t] : 0;
+    // (two threads a bucket: the first takes the first half of its digits)
+    const uint32_t place = t & (nbkt - 1), half = sgn ? (cnt[place] + 1) / 2 : cnt[place];
+    const uint32_t start = off[place] + (t < nbkt ? 0 : half), len = t < nbkt ? half : cnt[place] - half;
     __syncthreads();
     for (uint32_t e = t; e < ne; e += 256) {
-      uint32_t a = e / nwin, w = e % nwin;
-      uint32_t d = (sc[a].l[w >> 2] >> ((w & 3) * 8)) & 0xff;
-      if (d) {
-        uint32_t pos = atomicAdd(&off[d], 1u);
-        ent[pos] = w * (uint32_t)M + (uint32_t)(a0 + a);
+      const uint32_t a = e / nwin, w = e % nwin, d = digit(a, w);
+      if (d & 0xff) {
+        const uint32_t pos = atomicAdd(&off[(d & 0xff) - 1], 1u);
+        ent[pos] = (w * (uint32_t)M + (uint32_t)(a0 + a)) | (d & 0x80000000u);
       }
     }
     __syncthreads();
 #pragma unroll 1
     for (uint32_t q = 0; q < len; q++) {
-      const aff<typename L::O> p = table[ent[start + q]];
-      if (!aff_is_inf(p)) acc = lane::madd<L>(acc, L::in(p.x), L::in(p.y));
+      const uint32_t e = ent[start + q];
+      const aff<typename L::O> p = table[e & 0x7fffffffu];
+      if (!aff_is_inf(p)) acc = lane::madd<L>(acc, L::in(p.x), L::neg_if(L::in(p.y), e >> 31));
     }
   }
   __syncthreads();  // every bucket is summed before the sums overwrite the digits
   red[t] = acc;
   __syncthreads();
-  // suffix sums T_d = sum_{d' >= d} B_{d'}
-#pragma unroll 1
-  for (uint32_t s = 1; s < 256; s <<= 1) {
-    pt v = red[t];
-    if (t + s < 256) v = lane::add<L>(v, red[t + s]);
-    __syncthreads();
-    red[t] = v;
+  if (sgn) {
+    if (t < nbkt) red[t] = lane::add<L>(red[t], red[t + nbkt]);
     __syncthreads();
   }
-  if (t == 0) red[0] = lane::identity<L>();
-  __syncthreads();
+  // suffix sums T_d = sum_{d' >= d} B_{d'}
+#pragma unroll 1
+  for (uint32_t s = 1; s < nbkt; s <<= 1) {
+    pt v;
+    if (t < nbkt) v = red[t];
+    if (t + s < nbkt) v = lane::add<L>(v, red[t + s]);
+    __syncthreads();
+    if (t < nbkt) red[t] = v;
+    __syncthreads();
+  }
   // sum_{d >= 1} T_d
 #pragma unroll 1
-  for (uint32_t s = 128; s >= 1; s >>= 1) {
+  for (uint32_t s = nbkt / 2; s >= 1; s >>= 1) {
     if (t < s) red[t] = lane::add<L>(red[t], red[t + s]);
     __syncthreads();
   }
@@ -215,8 +241,8 @@ __global__ void __launch_bounds__(256) k_msm_slices(const fe *scal, uint64_t M, 
 
 // Slices of a row that one block sums into its buckets before it reduces them: as many (a power of
 // two, up to 8) as leave MIN_BLOCKS blocks, two rounds of the 512 that are resident: the reduction of
-// a block is worth 20 additions in every thread, its digits 32 a slice (2^20 entries, four slices a
-// row: 4.2 ms against 4.4 with a block for each).
+// a block is worth 16 additions in half of its threads, its digits 32 a slice in all (2^20 entries, four
+// slices a row: 4.2 ms against 4.4 with a block for each, before the signed digits).
 static uint32_t msm_group(uint64_t K, uint64_t nslice) {
   static constexpr uint64_t MIN_BLOCKS = 1024;
   uint32_t g = 1;

@@ -48,6 +48,13 @@ HD __forceinline__ fl neg(const fl &a) {
   for (int j = 0; j < 9; j++) o.l[j] = -a.l[j];
   return o;
 }
+// -a for m = 1, a for 0
+HD __forceinline__ fl neg_if(const fl &a, uint32_t m) {
+  fl o;
+#pragma unroll
+  for (int j = 0; j < 9; j++) o.l[j] = (a.l[j] ^ -(int32_t)m) + (int32_t)m;
+  return o;
+}
 // k a (k units more a limb), k a with the carries taken once (one unit again, for |k| up to 16 and
 // limbs within two units)
 HD __forceinline__ fl times(const fl &a, int k) {
@@ -232,6 +239,7 @@ struct G1 {
   static HD __forceinline__ T add(const T &a, const T &b) { return lane::add(a, b); }
   static HD __forceinline__ T sub(const T &a, const T &b) { return lane::sub(a, b); }
   static HD __forceinline__ T neg(const T &a) { return lane::neg(a); }
+  static HD __forceinline__ T neg_if(const T &a, uint32_t m) { return lane::neg_if(a, m); }
   static HD __forceinline__ T norm(const T &a) { return lane::norm(a); }
   static HD __forceinline__ T times(const T &a, int k) { return lane::times(a, k); }
   static HD __forceinline__ T mul(const T &a, const T &b) { return lane::mul(a, b); }
@@ -255,6 +263,7 @@ struct G2 {
   static HD __forceinline__ T add(const T &a, const T &b) { return {lane::add(a.c0, b.c0), lane::add(a.c1, b.c1)}; }
   static HD __forceinline__ T sub(const T &a, const T &b) { return {lane::sub(a.c0, b.c0), lane::sub(a.c1, b.c1)}; }
   static HD __forceinline__ T neg(const T &a) { return {lane::neg(a.c0), lane::neg(a.c1)}; }
+  static HD __forceinline__ T neg_if(const T &a, uint32_t m) { return {lane::neg_if(a.c0, m), lane::neg_if(a.c1, m)}; }
   static HD __forceinline__ T norm(const T &a) { return {lane::norm(a.c0), lane::norm(a.c1)}; }
   static HD __forceinline__ T times(const T &a, int k) { return {lane::times(a.c0, k), lane::times(a.c1, k)}; }
   static HD __forceinline__ T mul(const T &a, const T &b) {

@@ -4,6 +4,7 @@ import random
 import numpy as np
 import pytest
 
+import oracle as O
 from paper_2601_03031_amd import inputs as I
 
 torch = pytest.importorskip("torch")
@@ -56,3 +57,21 @@ def test_verify_chunks(vc, b):
         proof = vc.vc_proof_get(pr, i)
         assert vc.vc_verify(pp, cm.C, b, i, ints[i], proof) == 1, i
         assert vc.vc_verify(pp, cm.C, b, i, ints[i] ^ 1, proof) == 0, i
+
+
+@pytest.mark.parametrize("L", [4, 7])
+def test_msm_digits(vc, L):
+    """Entries whose bytes are 0, 1, 0x7f, 0x80, 0x81 and 0xff, alone and in runs (the signed digits' ends
+    and their carries), and those next to 0 and r: every C_j and C as the oracle's."""
+    print("msm digits L=%d" % L, flush=True)
+    N = 1 << L
+    runs = [int.from_bytes(bytes([0x2f] + [b] * 31), "big") for b in (0x00, 0x01, 0x7f, 0x80, 0x81, 0xff)]
+    vals = runs + [0, 1, 127, 128, 129, 255, 256, O.R - 1, O.R - 128, O.R - 129, 1 << 253, (1 << 248) - 1, (1 << 128) - 1]
+    vals += [0x80 << 8 * i for i in range(31)] + [0x7f80 << 8 * i for i in range(30)]
+    vals = [v % O.R for v in (vals * (N // len(vals) + 1))[:N]] if len(vals) < N else vals[:N]
+    limbs = np.frombuffer(b"".join(v.to_bytes(32, "little") for v in vals), dtype=np.uint64).reshape(N, 4).copy()
+    ocm = O.Commitment(O.Params(L, I.TRAPDOOR_SEED), I.limbs_to_bytes(limbs))
+    m = torch.from_numpy(limbs.view(np.uint8).reshape(-1).copy()).cuda()
+    cm = vc.vc_commit(vc.vc_setup(L, I.TRAPDOOR_SEED, 0), m, 256)
+    assert cm.export("Cj") == b"".join(ocm.Cj)
+    assert cm.C == ocm.C
