@@ -36,6 +36,7 @@ PEAK_MAD_TOPS = 256 * 64 * 2.4e9 / 2 / 1e12   # v_mad_u64_u32 issues at half rat
 PEAK_HBM_GBS = 8000.0
 MADS_PER_FMUL = 136                        # 8x32-bit CIOS: 64 + 64 products + 8 reduction words
 AHEAD_MAX_PAIRS = 4096                     # the library's switch to next-round terms (batches x K)
+AHEAD_FEW_PAIRS, AHEAD_FEW_BATCHES = 1024, 4
 # HBM bytes per launch from rocprofv3 FETCH_SIZE / WRITE_SIZE, scaled by a reference copy
 # (profiles/ks_final_exp2_n16_b256_hbm_counters.md); valid for the kernel build it was taken on
 TRAFFIC_BYTES = {"ks_final_exp2": round((417.0 * 2.000 + 14.2 * 1.000) * 1024),
@@ -45,6 +46,10 @@ DIRECT_MIN = 512                           # rounds of more pairs than this run 
 KZG_SPLIT_MAX = 8192                       # KZG proofs of at most this many split jobs run split
 LANE_MILLER_MIN = 4096                     # direct-round Miller loops of this many pairs run two lanes a pairing
 LANE_MIN = 4096                            # direct-round terms and folds of this many run on single lanes
+
+
+def takes_ahead(nb, K):
+    return nb * K <= AHEAD_MAX_PAIRS and (nb <= AHEAD_FEW_BATCHES or nb * K <= AHEAD_FEW_PAIRS)
 
 
 def op_costs():
@@ -128,7 +133,7 @@ def method_work(L, b, limbs, c):
               "step1_final_exp": sum(fexp.values()), "step1_sparse_g1": sparse, "step1_fold_g1": fold_g1,
               "step1_fold_g2": fold_g2, "step1_kzg": kzg, "step2": step2}
     # attribution to the kernels that carry each part of the work in the library's schedule
-    ahead = lK >= 2 and nb * K <= AHEAD_MAX_PAIRS
+    ahead = lK >= 2 and takes_ahead(nb, K)
     j0 = 2
     while j0 < lK and nb * (K >> j0) > DIRECT_MIN:
         j0 += 1
@@ -173,7 +178,7 @@ def work_model(L, b, limbs, costs):
         kzg_blocks = nb * (-(-nq // 32))
         w["k_msm_slices<lane::G2>"] = (nb * nq * 32 * 255 // 256) * costs["g2_madd"] + kzg_blocks * 510 * costs["g2_add"]
         w["(ks_pt_tree<true, false>)"] = (kzg_blocks - nb) * costs["e_g2_add"]
-    if lK >= 2 and nb * K <= AHEAD_MAX_PAIRS:
+    if lK >= 2 and takes_ahead(nb, K):
         # rounds j < j0 direct (the device is full), rounds j >= j0 from terms of the arrays of
         # round j - 1 (q = K >> j)
         j0 = 2

@@ -173,10 +173,12 @@ struct vc_params {
   vc_exec *ex = nullptr;  // default executor of calls on these params
 };
 
-// Step 1 takes the next round's terms ahead (oa_terms.hpp) when the batches leave the
-// device mostly idle: at most this many (batch, index) pairs per round.  Beyond it the
-// doubled Miller-loop count of that scheme costs more than the shorter chain saves.
-static constexpr uint64_t AHEAD_MAX_PAIRS = 4096;
+// Step 1 takes the next round's terms ahead (oa_terms.hpp) when the batches leave the device mostly
+// idle: at most AHEAD_MAX_PAIRS (batch, index) pairs per round, and few batches or few pairs.  Beyond
+// that the doubled Miller-loop count and the three times as many final exponentiations of that scheme
+// cost more than the shorter chain saves (ms direct / ahead; batches x K: 32 x 32 8.1 / 8.5, 16 x 64 10.4 / 9.6,
+// 4 x 256 13.5 / 11.7, 3 x 1024 18.9 / 18.0; 32 x 64 9.6 / 11.1, 8 x 256 12.4 / 13.2, 64 x 64 13.3 / 16.0).
+static constexpr uint64_t AHEAD_MAX_PAIRS = 4096, AHEAD_FEW_PAIRS = 1024, AHEAD_FEW_BATCHES = 4;
 // in the ahead mode, rounds of more than this many pairs (batches x h) still run direct: the
 // device is full there and the terms taken ahead (twice the Miller loops) cost more than the
 // shorter chain saves; the first round at or below it is the first taken ahead
@@ -1070,7 +1072,9 @@ static int open_all_group(const vc_params *cpp, const vc_commitment *const *cms,
   size_t o_rle = t.take<uint8_t>(ev * 32 * pp->L), o_er = t.take<fe>(ev * pp->L), o_T = t.take<fe>(ev * K),
          o_pK = t.take<g1_aff>(ev * K), o_eg = t.take<fe>(ev * M), o_eq = t.take<fe>(ev * M), o_pW = t.take<g1_aff>(ev * M);
   // Step 1 arrays of alternate rounds, and the terms taken one round ahead (oa_terms.hpp)
-  const bool ahead = lK >= 2 && nb * K <= (ex ? ex->ahead_max : AHEAD_MAX_PAIRS);
+  // (a bound set by the caller is the only one)
+  const bool few = nb <= AHEAD_FEW_BATCHES || nb * K <= AHEAD_FEW_PAIRS || (ex && ex->ahead_set);
+  const bool ahead = lK >= 2 && few && nb * K <= (ex ? ex->ahead_max : AHEAD_MAX_PAIRS);
   const uint64_t nterm = ahead ? 2 * nb * K : 0;
   size_t o_A2 = t.take<g1_aff>(nb * K), o_V2 = t.take<g2_aff>(nb * K), o_B2 = t.take<fe>(nb * K);
   size_t o_F2 = t.take<fp12>(2 * nterm), o_PS = t.take<g1_jac>(2 * nterm);
