@@ -158,7 +158,8 @@ void hyper_terms(const S2Job *J, uint32_t G, uint64_t K, const g1_aff *ek, uint6
 void d_leaves(const S2Job *J, uint32_t G, uint64_t K, hipStream_t st);
 }  // namespace kn
 
-// wave-cooperative engine (k_slp.hip): a 64-lane workgroup per pairing / product / element
+// the engine (k_slp.hip): a workgroup of two wavefronts per pairing / product / element (of four per final
+// exponentiation)
 namespace ks {
 void miller(const g1_aff *P, uint64_t sp, const g2_aff *Q, uint64_t sq, uint64_t n, fp12 *out, hipStream_t st);
 void oa_miller(const g1_aff *A, const g2_aff *V, uint64_t K, uint64_t nb, uint64_t h, fp12 *F, hipStream_t st);
