@@ -46,7 +46,7 @@ struct PLayout {
   uint64_t N, K, M, nb, len_full, len_last;
 };
 
-// Serialization of every proof of an open-all bundle (kps_serialize)
+// Serialization of every proof of an open-all bundle (kps_first, kps_copy)
 struct PSCtx {
   PLayout y;
   const g1_aff *Cj, *Lg1, *Rg1, *Al, *D, *W;

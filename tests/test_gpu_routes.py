@@ -1,4 +1,5 @@
 """Sizes on both sides of the lines where the dispatch goes from one kernel to another."""
+import ctypes as C
 import random
 
 import numpy as np
@@ -75,3 +76,22 @@ def test_msm_digits(vc, L):
     cm = vc.vc_commit(vc.vc_setup(L, I.TRAPDOOR_SEED, 0), m, 256)
     assert cm.export("Cj") == b"".join(ocm.Cj)
     assert cm.C == ocm.C
+
+
+@pytest.mark.parametrize("L,b", [(5, 3), (8, 16), (7, 1)])
+def test_serialize(vc, L, b):
+    """All proofs in one launch equal the proofs gathered one by one (a short last batch, one batch, a batch
+    per subvector), to a 16-byte boundary and to one that is not."""
+    print("serialize L=%d b=%d" % (L, b), flush=True)
+    limbs = I.entries(1 << L, 60 + b, 256)
+    m = torch.from_numpy(np.ascontiguousarray(limbs).view(np.uint8).reshape(-1).copy()).cuda()
+    pp = vc.vc_setup(L, I.TRAPDOOR_SEED, 0)
+    pr = vc.vc_open_all(pp, vc.vc_commit(pp, m, 256), b)
+    want = b"".join(vc.vc_proof_get(pr, i) for i in range(1 << L))
+    assert bytes(vc.vc_proofs_serialize(pr).cpu().numpy().tobytes()) == want
+    buf = torch.zeros(len(want) + 64, dtype=torch.uint8, device="cuda")
+    n = C.c_uint64(0)
+    assert vc.lib().vc_proofs_serialize(pr.ptr, C.c_void_p(buf.data_ptr() + 5), len(want), C.byref(n)) == 0
+    out = buf.cpu().numpy().tobytes()
+    assert n.value == len(want) and out[5:5 + len(want)] == want
+    assert not any(out[:5]) and not any(out[5 + len(want):])
