@@ -15,6 +15,7 @@
 #include "gtpow.hpp"
 #include "g1mul.hpp"
 #include "oa_terms.hpp"
+#include "proof_grid.hpp"
 
 #define API extern "C" __attribute__((visibility("default")))
 
@@ -987,4 +988,11 @@ API void hc_oa_term(uint64_t id, uint64_t K, uint64_t nb, uint64_t q, uint64_t *
   out[0] = t.a;
   out[1] = t.v;
   out[2] = t.out;
+}
+
+// the launch grid of a workgroup for each of N proofs
+API void hc_proof_grid(uint64_t N, uint32_t *xy) {
+  const ProofGrid g = proof_grid(N);
+  xy[0] = g.x;
+  xy[1] = g.y;
 }

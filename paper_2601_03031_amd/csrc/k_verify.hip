@@ -607,10 +607,13 @@ template <bool ALIGNED> __global__ void __launch_bounds__(TPB) kps_first(PSCtx c
   put_unit<ALIGNED>(o, u);
 }
 
+// proof of this workgroup (proof_grid)
+__device__ __forceinline__ uint64_t proof_id() { return ((uint64_t)blockIdx.y << 16) + blockIdx.x; }
+
 // every other unit, a workgroup per proof
 template <bool ALIGNED> __global__ void __launch_bounds__(256) kps_copy(PSCtx c) {
   const PLayout &y = c.y;
-  const uint64_t i = blockIdx.x, k = pl_batch(y, i), j = i / y.M, a = i % y.M, first = k * pl_bm(y);
+  const uint64_t i = proof_id(), k = pl_batch(y, i), j = i / y.M, a = i % y.M, first = k * pl_bm(y);
   const uint32_t t = pl_t(y, k), l = y.lK, pre = t + 26 * l + 5, n = pre + 2 * l + y.lM + y.L;
   uint8_t *o = c.out + pl_off(y, i);
   const uint8_t *f = c.out + pl_off(y, first);
@@ -904,12 +907,13 @@ namespace kva {
 uint64_t nterms(const VACtx &c) { return 3 * c.y.K + 2 * c.y.M - 3; }
 void serialize(const PSCtx &c, hipStream_t st) {
   const uint64_t n = c.y.nb * (c.y.b + 26ull * c.y.lK + 5) + 2 * c.y.K - 2 + c.y.M - 1;
+  const ProofGrid g = proof_grid(c.y.N);
   if (reinterpret_cast<uintptr_t>(c.out) & 15) {
     L1(kps_first<false>, n, c);
-    LAUNCH(kps_copy<false>, dim3((unsigned)c.y.N), dim3(256), 0, c);
+    LAUNCH(kps_copy<false>, dim3(g.x, g.y), dim3(256), 0, c);
   } else {
     L1(kps_first<true>, n, c);
-    LAUNCH(kps_copy<true>, dim3((unsigned)c.y.N), dim3(256), 0, c);
+    LAUNCH(kps_copy<true>, dim3(g.x, g.y), dim3(256), 0, c);
   }
 }
 void decode(const VACtx &c, hipStream_t st) { L1(kva_decode, 3 * c.y.K + c.y.M + 9, c); }

@@ -5,6 +5,7 @@
 #include "field.hpp"
 #include "tower.hpp"
 #include "curve.hpp"
+#include "proof_grid.hpp"
 
 #define VFLAG_BAD_INPUT 1  // commitment or m_i malformed: the call returns VC_EINVAL
 #define VFLAG_BAD_PROOF 2  // a proof element does not decode: reject

@@ -95,3 +95,19 @@ def test_serialize(vc, L, b):
     out = buf.cpu().numpy().tobytes()
     assert n.value == len(want) and out[5:5 + len(want)] == want
     assert not any(out[:5]) and not any(out[5 + len(want):])
+
+
+def test_serialize_two_dimensions(vc):
+    """2^17 proofs: the workgroups of the second half lie in the grid's second dimension.  All proofs
+    verify, and some of both halves equal the proofs gathered one by one."""
+    L, b = 17, 256
+    print("serialize L=%d b=%d" % (L, b), flush=True)
+    m = I.device_entries(1 << L, 171)
+    pp = vc.vc_setup(L, I.TRAPDOOR_SEED, 0)
+    cm = vc.vc_commit(pp, m, 256)
+    pr = vc.vc_open_all(pp, cm, b)
+    proofs = vc.vc_proofs_serialize(pr)
+    offs = vc.proof_offsets(pp, b)
+    for i in (0, 1, 65535, 65536, 65537, 100003, 131071):
+        assert proofs[offs[i]:offs[i + 1]].cpu().numpy().tobytes() == vc.vc_proof_get(pr, i), i
+    assert vc.vc_verify_all(pp, cm.C, b, m, proofs, bytes(range(32))) == (1, 0)
