@@ -904,10 +904,17 @@ template <class L, class A> static A lane_sum(const A *p, int n, int m) {
     if (!aff_is_inf(p[i])) s[i >= m] = lane::madd<L>(s[i >= m], L::in(p[i].x), L::in(p[i].y));
   return jac_to_aff(lane::to_jac<L>(lane::add<L>(s[0], s[1])));
 }
+// a table of the one-lane multiplications
+struct HostTable {
+  lane::pt<lane::G1> *t;
+  template <class L> void put(int e, const lane::pt<L> &v) const { t[e] = v; }
+  template <class L> lane::pt<L> get(int e) const { return t[e]; }
+};
 // k P by the one-lane multiplication
 API int hc_lane_mul(const uint8_t *Pb, const uint8_t *kb, uint8_t *out) {
   const fe k = rd_raw(kb);
-  wrg1(out, lane::to_aff<lane::G1>(lane::mul_lane(rdg1(Pb), glv::decompose(k.l))));
+  lane::pt<lane::G1> tab[16];
+  wrg1(out, lane::to_aff<lane::G1>(lane::mul_lane(rdg1(Pb), glv::decompose(k.l), HostTable{tab})));
   return 0;
 }
 API int hc_lane_sum(int grp, const uint8_t *pts, int n, int m, uint8_t *out) {

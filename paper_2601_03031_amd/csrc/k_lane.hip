@@ -1,6 +1,12 @@
 // Scalar multiplications on one lane per element (lane29.hpp): the direct rounds of open-all, where
 // there are points enough to give every SIMD a wavefront of 64 of them, and those that no chain
 // waits for.
+//
+// A lane's table of 15 multiples (1.7 KB) is in memory of the caller's workspace, a slot for each
+// workgroup; a launch has at most as many workgroups as stay resident (two wavefronts on each SIMD, by
+// their registers: kn::TABLE_SLOTS) and each takes blocks of 64 in turn.  As an array of the lane's own
+// it would be scratch memory, which the runtime keeps for every hardware queue and for every lane
+// that the device could hold: 0.8 GB a queue, 12 GB on sixteen, that no workspace or budget counts.
 #define VC_INLINE_HELPERS 1
 #include "kcommon.hpp"
 #include "lane29.hpp"
@@ -14,6 +20,49 @@ namespace {
 using lane::pt;
 typedef lane::G1 L1_;
 using lane::mul_lane;
+
+// The lane's table: points of 27 words in seven 16-byte pieces, the same piece of the 64 lanes side by side
+struct Table {
+  uint4 *at;
+  __device__ explicit Table(void *mem) : at(static_cast<uint4 *>(mem) + (uint64_t)blockIdx.x * (kn::TABLE_SLOT_BYTES / 16) + threadIdx.x) {}
+  template <class L> __device__ __forceinline__ void put(int e, const pt<L> &t) const {
+    uint4 *p = at + (e - 1) * (7 * LT);
+    uint32_t w[28];
+#pragma unroll
+    for (int j = 0; j < 9; j++) {
+      w[j] = t.X.l[j];
+      w[9 + j] = t.Y.l[j];
+      w[18 + j] = t.Z.l[j];
+    }
+    w[27] = 0;
+#pragma unroll
+    for (int q = 0; q < 7; q++) p[q * LT] = uint4{w[4 * q], w[4 * q + 1], w[4 * q + 2], w[4 * q + 3]};
+  }
+  template <class L> __device__ __forceinline__ pt<L> get(int e) const {
+    const uint4 *p = at + (e - 1) * (7 * LT);
+    uint32_t w[28];
+#pragma unroll
+    for (int q = 0; q < 7; q++) {
+      const uint4 v = p[q * LT];
+      w[4 * q] = v.x;
+      w[4 * q + 1] = v.y;
+      w[4 * q + 2] = v.z;
+      w[4 * q + 3] = v.w;
+    }
+    pt<L> t;
+#pragma unroll
+    for (int j = 0; j < 9; j++) {
+      t.X.l[j] = w[j];
+      t.Y.l[j] = w[9 + j];
+      t.Z.l[j] = w[18 + j];
+    }
+    return t;
+  }
+};
+static_assert(kn::TABLE_SLOT_BYTES == 15 * 7 * 16 * LT, "15 points of seven 16-byte pieces a lane");
+
+// the blocks of 64 threads' work that a workgroup takes in turn
+#define FOR_BLOCKS(id, n) for (uint64_t id = (uint64_t)blockIdx.x * LT + threadIdx.x, n_ = (n); id - threadIdx.x < n_; id += (uint64_t)gridDim.x * LT)
 
 // the sum of `per` consecutive lanes' points, in the first of them
 __device__ __forceinline__ pt<L1_> sum_groups(pt<L1_> t, pt<L1_> *sh, uint32_t per) {
@@ -35,87 +84,97 @@ __device__ __forceinline__ g1_jac hom(const pt<L1_> &t) { return {lane::out(t.X)
 }  // namespace
 
 // A_j = A_L o A_R^{x_j}, b_j = b_L + b_R / x_j; x_j enters through its GLV split (per batch)
-__global__ void __launch_bounds__(LT) kn_oa_fold_g1(const g1_aff *Ain, const fe *Bin, g1_aff *Aout, fe *Bout, const fe *Xinv,
+__global__ void __launch_bounds__(LT, 2) kn_oa_fold_g1(const g1_aff *Ain, const fe *Bin, g1_aff *Aout, fe *Bout, const fe *Xinv,
                                                     const glv::Dec *dec, uint64_t K, uint64_t nb, uint64_t h, uint32_t j,
-                                                    uint32_t lK) {
-  const uint64_t id = (uint64_t)blockIdx.x * LT + threadIdx.x;
-  if (id >= nb * h) return;
-  const uint64_t k = id / h, i = id % h;
-  pt<L1_> t = mul_lane(Ain[k * K + h + i], dec[k]);
-  const g1_aff l = Ain[k * K + i];
-  if (!aff_is_inf(l)) t = lane::madd<L1_>(t, lane::in(l.x), lane::in(l.y));
-  Aout[k * K + i] = lane::to_aff<L1_>(t);
-  Bout[k * K + i] = fr_add(Bin[k * K + i], fr_mul(Bin[k * K + h + i], Xinv[k * lK + (j - 1)]));
+                                                    uint32_t lK, void *tab) {
+  const Table T(tab);
+  FOR_BLOCKS(id, nb * h) {
+    if (id >= nb * h) return;
+    const uint64_t k = id / h, i = id % h;
+    pt<L1_> t = mul_lane(Ain[k * K + h + i], dec[k], T);
+    const g1_aff l = Ain[k * K + i];
+    if (!aff_is_inf(l)) t = lane::madd<L1_>(t, lane::in(l.x), lane::in(l.y));
+    Aout[k * K + i] = lane::to_aff<L1_>(t);
+    Bout[k * K + i] = fr_add(Bin[k * K + i], fr_mul(Bin[k * K + h + i], Xinv[k * lK + (j - 1)]));
+  }
 }
 
 // the G1 terms of <A_R, b_L> (side 0) and <A_L, b_R> (side 1), the sums of `per` consecutive ones
 // (per divides h and LT): S[(2 k + side) (K / 2) + i / per], homogeneous
-__global__ void __launch_bounds__(LT) kn_oa_g1terms(const g1_aff *A, const fe *B, uint64_t K, uint64_t nb, uint64_t h,
-                                                    uint32_t per, g1_jac *S) {
+__global__ void __launch_bounds__(LT, 2) kn_oa_g1terms(const g1_aff *A, const fe *B, uint64_t K, uint64_t nb, uint64_t h,
+                                                    uint32_t per, g1_jac *S, void *tab) {
   __shared__ pt<L1_> sh[LT];
-  const uint64_t id = (uint64_t)blockIdx.x * LT + threadIdx.x;
-  const bool live = id < nb * 2 * h;
-  const uint64_t k = id / (2 * h), r = id % (2 * h), side = r / h, i = r % h;
-  pt<L1_> t = lane::identity<L1_>();
-  if (live) {
-    const fe c = f_from_mont<FpR>(B[side ? k * K + h + i : k * K + i]);
-    t = mul_lane(A[side ? k * K + i : k * K + h + i], glv::decompose(c.l));
+  const Table T(tab);
+  FOR_BLOCKS(id, nb * 2 * h) {
+    const bool live = id < nb * 2 * h;
+    const uint64_t k = id / (2 * h), r = id % (2 * h), side = r / h, i = r % h;
+    pt<L1_> t = lane::identity<L1_>();
+    if (live) {
+      const fe c = f_from_mont<FpR>(B[side ? k * K + h + i : k * K + i]);
+      t = mul_lane(A[side ? k * K + i : k * K + h + i], glv::decompose(c.l), T);
+    }
+    t = sum_groups(t, sh, per);
+    if (live && threadIdx.x % per == 0) S[(k * 2 + side) * (K / 2) + i / per] = hom(t);
   }
-  t = sum_groups(t, sh, per);
-  if (live && threadIdx.x % per == 0) S[(k * 2 + side) * (K / 2) + i / per] = hom(t);
 }
 
 // the same for the G1 terms b[v] A[a] taken a round ahead (oa_terms.hpp; per divides q and LT): the
 // groups' sums at the start of each group's place in S1
-__global__ void __launch_bounds__(LT) kn_oa_g1terms_next(const g1_aff *A, const fe *B, uint64_t K, uint64_t nb, uint64_t q,
-                                                         uint32_t per, g1_jac *S1) {
+__global__ void __launch_bounds__(LT, 2) kn_oa_g1terms_next(const g1_aff *A, const fe *B, uint64_t K, uint64_t nb, uint64_t q,
+                                                         uint32_t per, g1_jac *S1, void *tab) {
   __shared__ pt<L1_> sh[LT];
-  const uint64_t id = (uint64_t)blockIdx.x * LT + threadIdx.x;
-  const bool live = id < nb * 8 * q;
-  const oat::Term tm = oat::term(live ? id : 0, K, nb, q);
-  pt<L1_> t = lane::identity<L1_>();
-  if (live) {
-    const fe c = f_from_mont<FpR>(B[tm.v]);
-    t = mul_lane(A[tm.a], glv::decompose(c.l));
+  const Table T(tab);
+  FOR_BLOCKS(id, nb * 8 * q) {
+    const bool live = id < nb * 8 * q;
+    const oat::Term tm = oat::term(live ? id : 0, K, nb, q);
+    pt<L1_> t = lane::identity<L1_>();
+    if (live) {
+      const fe c = f_from_mont<FpR>(B[tm.v]);
+      t = mul_lane(A[tm.a], glv::decompose(c.l), T);
+    }
+    t = sum_groups(t, sh, per);
+    const uint64_t len = id % (8 * q) < 4 * q ? 2 * q : q, at = tm.out % len;  // (both areas hold whole groups)
+    if (live && threadIdx.x % per == 0) S1[tm.out - at + at / per] = hom(t);
   }
-  t = sum_groups(t, sh, per);
-  const uint64_t len = id % (8 * q) < 4 * q ? 2 * q : q, at = tm.out % len;  // (both areas hold whole groups)
-  if (live && threadIdx.x % per == 0) S1[tm.out - at + at / per] = hom(t);
 }
 
 // out[i] = k_i P_i (P_0 with broadcast), affine
-__device__ __forceinline__ g1_aff mul_aff(const g1_aff &P, const fe &k_mont) {
+__device__ __forceinline__ g1_aff mul_aff(const g1_aff &P, const fe &k_mont, const Table &T) {
   const fe c = f_from_mont<FpR>(k_mont);
-  return lane::to_aff<L1_>(mul_lane(P, glv::decompose(c.l)));
+  return lane::to_aff<L1_>(mul_lane(P, glv::decompose(c.l), T));
 }
-__global__ void __launch_bounds__(LT) kn_g1_mul(const g1_aff *P, int broadcast, const fe *k, uint64_t n, g1_aff *out) {
-  const uint64_t i = (uint64_t)blockIdx.x * LT + threadIdx.x;
-  if (i < n) out[i] = mul_aff(P[broadcast ? 0 : i], k[i]);
+__global__ void __launch_bounds__(LT, 2) kn_g1_mul(const g1_aff *P, int broadcast, const fe *k, uint64_t n, g1_aff *out, void *tab) {
+  const Table T(tab);
+  FOR_BLOCKS(i, n)
+    if (i < n) out[i] = mul_aff(P[broadcast ? 0 : i], k[i], T);
 }
 
 // HyperEval terms (canonical differences of the folded table g* times PST keys) of every job:
 // term r of level d of job x goes to S[(d G + x) M / 2 + r], Jacobian
-__global__ void __launch_bounds__(LT) kn_hyper_terms(const S2Job *J, uint32_t G, uint64_t K, const g1_aff *ek, uint64_t M,
-                                                     uint32_t lM, g1_jac *S) {
-  uint64_t id = (uint64_t)blockIdx.x * LT + threadIdx.x;
+__global__ void __launch_bounds__(LT, 2) kn_hyper_terms(const S2Job *J, uint32_t G, uint64_t K, const g1_aff *ek, uint64_t M,
+                                                     uint32_t lM, g1_jac *S, void *tab) {
+  const Table T(tab);
   const uint64_t per = M / 2;
-  if (id >= G * lM * per) return;
-  const uint64_t x = id / (lM * per);
-  const fe *g = J[x].Y + (2 * K - 2) * M;  // g*, the root row of the y-tree
-  id %= lM * per;
-  const uint32_t d = (uint32_t)(id / per);
-  const uint64_t r = id % per, half = 1ull << (lM - d - 1), p = r / half, c = r % half;
-  const fe q = fr_sub(g[p * (2 * half) + half + c], g[p * (2 * half) + c]);
-  S[(d * G + x) * per + r] = lane::to_jac<L1_>(mul_lane(ek[half - 1 + c], glv::decompose(q.l)));
+  FOR_BLOCKS(id, G * lM * per) {
+    if (id >= G * lM * per) return;
+    const uint64_t x = id / (lM * per);
+    const fe *g = J[x].Y + (2 * K - 2) * M;  // g*, the root row of the y-tree
+    const uint32_t d = (uint32_t)(id / per % lM);
+    const uint64_t r = id % per, half = 1ull << (lM - d - 1), p = r / half, c = r % half;
+    const fe q = fr_sub(g[p * (2 * half) + half + c], g[p * (2 * half) + c]);
+    S[(d * G + x) * per + r] = lane::to_jac<L1_>(mul_lane(ek[half - 1 + c], glv::decompose(q.l), T));
+  }
 }
 
 // the D-tree's leaves D_j = rho_j C_j of every job
-__global__ void __launch_bounds__(LT) kn_d_leaves(const S2Job *J, uint32_t G, uint64_t K) {
-  const uint64_t id = (uint64_t)blockIdx.x * LT + threadIdx.x;
-  if (id >= G * K) return;
-  const S2Job &jb = J[id / K];
-  const uint64_t j = id % K;
-  jb.D[j] = mul_aff(jb.Cj[j], jb.rho[j]);
+__global__ void __launch_bounds__(LT, 2) kn_d_leaves(const S2Job *J, uint32_t G, uint64_t K, void *tab) {
+  const Table T(tab);
+  FOR_BLOCKS(id, G * K) {
+    if (id >= G * K) return;
+    const S2Job &jb = J[id / K];
+    const uint64_t j = id % K;
+    jb.D[j] = mul_aff(jb.Cj[j], jb.rho[j], T);
+  }
 }
 
 // ---------------------------------------------------------------- Miller loops
@@ -284,10 +343,9 @@ struct G2pair {
 // k Q on G2 with the split k = sum_j k_j lam^j (gls.hpp): the table of the 15 subset sums of
 // sign(k_j) psi^j(Q), a doubling and at most one addition per bit.  x, y: this lane's components of Q;
 // inf and d are the same in both lanes
-__device__ __forceinline__ pt<G2pair> mul_pair(const fe &qx, const fe &qy, bool inf, const gls::Dec &d) {
+__device__ __forceinline__ pt<G2pair> mul_pair(const fe &qx, const fe &qy, bool inf, const gls::Dec &d, const Table &T) {
   if (inf || d.nbits == 0) return lane::identity<G2pair>();
   const bool p = G2pair::p();
-  pt<G2pair> T[16];
   fl x = lane::in_small(qx), y = lane::in_small(qy);
   const fl kx = lane::in_small(fe_const(p ? bn::FROB1_2_1 : bn::FROB1_2_0)), ky = lane::in_small(fe_const(p ? bn::FROB1_3_1 : bn::FROB1_3_0));
 #pragma unroll 1
@@ -297,17 +355,17 @@ __device__ __forceinline__ pt<G2pair> mul_pair(const fe &qx, const fe &qy, bool 
       y = mul2_(p, pick(p, lane::neg(y), y), ky);
     }
     const fl s = pick(d.neg >> j & 1, lane::neg(y), y);
-    T[1 << j] = {x, s, G2pair::one()};
+    T.put(1 << j, pt<G2pair>{x, s, G2pair::one()});
 #pragma unroll 1
-    for (int e = 1; e < 1 << j; e++) T[e + (1 << j)] = lane::madd<G2pair>(T[e], x, s);
+    for (int e = 1; e < 1 << j; e++) T.put(e + (1 << j), lane::madd<G2pair>(T.get<G2pair>(e), x, s));
   }
   const int n = (int)d.nbits;
-  pt<G2pair> acc = T[gls::digit(d, (uint32_t)(n - 1))];
+  pt<G2pair> acc = T.get<G2pair>((int)gls::digit(d, (uint32_t)(n - 1)));
 #pragma unroll 1
   for (int t = n - 2; t >= 0; t--) {
     acc = lane::dbl<G2pair>(acc);
     const uint32_t dg = gls::digit(d, (uint32_t)t);
-    if (dg) acc = lane::add<G2pair>(acc, T[dg]);
+    if (dg) acc = lane::add<G2pair>(acc, T.get<G2pair>((int)dg));
   }
   return acc;
 }
@@ -368,37 +426,43 @@ __device__ __forceinline__ void chord(bool p, point &T, const fl &x, const fl &y
 
 // v_j = v_L o v_R^{1/x_j}, two lanes a point (half the chain and half the state of one lane a point: 16384
 // of them 1.5 ms for 2.5); Vout may be Vin
-__global__ void __launch_bounds__(LT) kn_oa_fold_g2(const g2_aff *Vin, g2_aff *Vout, const fe *Xinv, uint64_t K, uint64_t nb,
-                                                    uint64_t h, uint32_t j, uint32_t lK) {
-  const uint64_t id = ((uint64_t)blockIdx.x * LT + threadIdx.x) >> 1;
-  if (id >= nb * h) return;
+__global__ void __launch_bounds__(LT, 2) kn_oa_fold_g2(const g2_aff *Vin, g2_aff *Vout, const fe *Xinv, uint64_t K, uint64_t nb,
+                                                    uint64_t h, uint32_t j, uint32_t lK, void *tab) {
+  const Table T(tab);
   const bool p = G2pair::p();
-  const uint64_t k = id / h, i = id % h;
-  const fe c = f_from_mont<FpR>(Xinv[k * lK + (j - 1)]);
-  const fe *r = reinterpret_cast<const fe *>(Vin + k * K + h + i), *l = reinterpret_cast<const fe *>(Vin + k * K + i);
-  const fe rx = r[p], ry = r[2 + p], lx = l[p], ly = l[2 + p];
-  pt<G2pair> t = mul_pair(rx, ry, both(fe_is_zero(rx) && fe_is_zero(ry)), gls::decompose(c.l));
-  if (!both(fe_is_zero(lx) && fe_is_zero(ly))) t = lane::madd<G2pair>(t, lane::in_small(lx), lane::in_small(ly));
-  fe x, y;
-  to_aff_pair(t, x, y);
-  fe *o = reinterpret_cast<fe *>(Vout + k * K + i);
-  o[p] = x;
-  o[2 + p] = y;
+  FOR_BLOCKS(lid, 2 * nb * h) {
+    const uint64_t id = lid >> 1;
+    if (id >= nb * h) return;
+    const uint64_t k = id / h, i = id % h;
+    const fe c = f_from_mont<FpR>(Xinv[k * lK + (j - 1)]);
+    const fe *r = reinterpret_cast<const fe *>(Vin + k * K + h + i), *l = reinterpret_cast<const fe *>(Vin + k * K + i);
+    const fe rx = r[p], ry = r[2 + p], lx = l[p], ly = l[2 + p];
+    pt<G2pair> t = mul_pair(rx, ry, both(fe_is_zero(rx) && fe_is_zero(ry)), gls::decompose(c.l), T);
+    if (!both(fe_is_zero(lx) && fe_is_zero(ly))) t = lane::madd<G2pair>(t, lane::in_small(lx), lane::in_small(ly));
+    fe x, y;
+    to_aff_pair(t, x, y);
+    fe *o = reinterpret_cast<fe *>(Vout + k * K + i);
+    o[p] = x;
+    o[2 + p] = y;
+  }
 }
 
 // out[i] = k_i P_i (P_0 with broadcast) on G2, two lanes a point
-__global__ void __launch_bounds__(LT) kn_g2_mul(const g2_aff *P, int broadcast, const fe *k, uint64_t n, g2_aff *out) {
-  const uint64_t i = ((uint64_t)blockIdx.x * LT + threadIdx.x) >> 1;
-  if (i >= n) return;
+__global__ void __launch_bounds__(LT, 2) kn_g2_mul(const g2_aff *P, int broadcast, const fe *k, uint64_t n, g2_aff *out, void *tab) {
+  const Table T(tab);
   const bool p = G2pair::p();
-  const fe c = f_from_mont<FpR>(k[i]);
-  const fe *q = reinterpret_cast<const fe *>(P + (broadcast ? 0 : i));
-  const fe qx = q[p], qy = q[2 + p];
-  fe x, y;
-  to_aff_pair(mul_pair(qx, qy, both(fe_is_zero(qx) && fe_is_zero(qy)), gls::decompose(c.l)), x, y);
-  fe *o = reinterpret_cast<fe *>(out + i);
-  o[p] = x;
-  o[2 + p] = y;
+  FOR_BLOCKS(lid, 2 * n) {
+    const uint64_t i = lid >> 1;
+    if (i >= n) return;
+    const fe c = f_from_mont<FpR>(k[i]);
+    const fe *q = reinterpret_cast<const fe *>(P + (broadcast ? 0 : i));
+    const fe qx = q[p], qy = q[2 + p];
+    fe x, y;
+    to_aff_pair(mul_pair(qx, qy, both(fe_is_zero(qx) && fe_is_zero(qy)), gls::decompose(c.l), T), x, y);
+    fe *o = reinterpret_cast<fe *>(out + i);
+    o[p] = x;
+    o[2 + p] = y;
+  }
 }
 
 // Miller values of the direct rounds: side 0 (L) pairs A[h + i] with V[i], side 1 (R) A[i] with V[h + i];
@@ -478,53 +542,48 @@ __global__ void __launch_bounds__(LT) kn_oa_miller(const g1_aff *A, const g2_aff
 
 namespace kn {
 #define LN(kern, n, ...) LAUNCH(kern, dim3((unsigned)(((n) + LT - 1) / LT)), dim3(LT), 0, __VA_ARGS__)
-// Multiplications from which a launch is given to lanes.  A lane's chain is the longest (G1 0.9 to 1.1
-// ms, a G2 fold on two lanes 1.5, whatever the number up to a wavefront for each SIMD), but it does the least
-// work for it: the engine's workgroup for each takes 0.4 ms (G1) to 0.85 (a fold) for a few, and
-// 1.5 ms for 8192 terms, with the whole chip.  With the line at 1024 an open-all of 2^10 entries, b = 1,
-// took 9.4 ms against 8.75, one of 2^17, b = 34, 16.5 against 16.8.
-static constexpr uint64_t LANE_MIN = 4096;
+// with a table for each workgroup
+#define LNT(kern, n, ...) LAUNCH(kern, dim3((unsigned)table_slots(n)), dim3(LT), 0, __VA_ARGS__)
 
-uint64_t oa_g1terms(const g1_aff *A, const fe *B, uint64_t K, uint64_t nb, uint64_t h, g1_jac *S, hipStream_t st) {
+uint64_t oa_g1terms(const g1_aff *A, const fe *B, uint64_t K, uint64_t nb, uint64_t h, g1_jac *S, void *tab, hipStream_t st) {
   if (nb * 2 * h < LANE_MIN) {
     ks::oa_g1terms(A, B, K, nb, h, S, st);
     return h;
   }
   const uint32_t per = h < LT ? (uint32_t)h : LT;
-  LN(kn_oa_g1terms, nb * 2 * h, A, B, K, nb, h, per, S);
+  LNT(kn_oa_g1terms, nb * 2 * h, A, B, K, nb, h, per, S, tab);
   return h / per;
 }
-uint64_t oa_g1terms_next(const g1_aff *A, const fe *B, uint64_t K, uint64_t nb, uint64_t q, g1_jac *S1, hipStream_t st) {
+uint64_t oa_g1terms_next(const g1_aff *A, const fe *B, uint64_t K, uint64_t nb, uint64_t q, g1_jac *S1, void *tab, hipStream_t st) {
   if (nb * 8 * q < LANE_MIN) {
     ks::oa_g1terms_next(A, B, K, nb, q, S1, st);
     return 1;
   }
   const uint32_t per = q < LT ? (uint32_t)q : LT;
-  LN(kn_oa_g1terms_next, nb * 8 * q, A, B, K, nb, q, per, S1);
+  LNT(kn_oa_g1terms_next, nb * 8 * q, A, B, K, nb, q, per, S1, tab);
   return per;
 }
-bool fold_lanes(uint64_t nb, uint64_t h) { return nb * h >= LANE_MIN; }
 void oa_fold_g1(const g1_aff *Ain, const fe *Bin, g1_aff *Aout, fe *Bout, const fe *Xinv, const glv::Dec *dec, uint64_t K,
-                uint64_t nb, uint64_t h, uint32_t j, uint32_t lK, hipStream_t st) {
-  LN(kn_oa_fold_g1, nb * h, Ain, Bin, Aout, Bout, Xinv, dec, K, nb, h, j, lK);
+                uint64_t nb, uint64_t h, uint32_t j, uint32_t lK, void *tab, hipStream_t st) {
+  LNT(kn_oa_fold_g1, nb * h, Ain, Bin, Aout, Bout, Xinv, dec, K, nb, h, j, lK, tab);
 }
 void oa_fold_g2(const g2_aff *Vin, g2_aff *Vout, const fe *Xinv, uint64_t K, uint64_t nb, uint64_t h, uint32_t j, uint32_t lK,
-                hipStream_t st) {
-  LN(kn_oa_fold_g2, 2 * nb * h, Vin, Vout, Xinv, K, nb, h, j, lK);
+                void *tab, hipStream_t st) {
+  LNT(kn_oa_fold_g2, 2 * nb * h, Vin, Vout, Xinv, K, nb, h, j, lK, tab);
 }
 uint64_t oa_miller(const g1_aff *A, const g2_aff *V, uint64_t K, uint64_t nb, uint64_t h, fp12 *F, hipStream_t st) {
   const uint32_t per = h < LT / 2 ? (uint32_t)h : LT / 2;
   LN(kn_oa_miller, nb * 4 * h, A, V, K, nb, h, per, F);
   return h / per;
 }
-void g1_mul(const g1_aff *P, int bc, const fe *k, uint64_t n, g1_aff *out, hipStream_t st) {
-  if (n) LN(kn_g1_mul, n, P, bc, k, n, out);
+void g1_mul(const g1_aff *P, int bc, const fe *k, uint64_t n, g1_aff *out, void *tab, hipStream_t st) {
+  if (n) LNT(kn_g1_mul, n, P, bc, k, n, out, tab);
 }
-void g2_mul(const g2_aff *P, int bc, const fe *k, uint64_t n, g2_aff *out, hipStream_t st) {
-  if (n) LN(kn_g2_mul, 2 * n, P, bc, k, n, out);
+void g2_mul(const g2_aff *P, int bc, const fe *k, uint64_t n, g2_aff *out, void *tab, hipStream_t st) {
+  if (n) LNT(kn_g2_mul, 2 * n, P, bc, k, n, out, tab);
 }
-void hyper_terms(const S2Job *J, uint32_t G, uint64_t K, const g1_aff *ek, uint64_t M, uint32_t lM, g1_jac *S, hipStream_t st) {
-  LN(kn_hyper_terms, G * lM * (M / 2), J, G, K, ek, M, lM, S);
+void hyper_terms(const S2Job *J, uint32_t G, uint64_t K, const g1_aff *ek, uint64_t M, uint32_t lM, g1_jac *S, void *tab, hipStream_t st) {
+  LNT(kn_hyper_terms, G * lM * (M / 2), J, G, K, ek, M, lM, S, tab);
 }
-void d_leaves(const S2Job *J, uint32_t G, uint64_t K, hipStream_t st) { LN(kn_d_leaves, G * K, J, G, K); }
+void d_leaves(const S2Job *J, uint32_t G, uint64_t K, void *tab, hipStream_t st) { LNT(kn_d_leaves, G * K, J, G, K, tab); }
 }  // namespace kn

@@ -945,18 +945,15 @@ void kzg_terms_split(const g2_aff *h, const g2_aff *hm, const fe *Qc, uint64_t K
 void g2_dbl_mults(const g2_aff *Q, uint64_t seg, uint64_t segstride, uint64_t n, g2_aff *M, hipStream_t st) {
   if (n) LAUNCH(ks_g2_dbl_mults, dim3((unsigned)(3 * n)), dim3(SLP_T), 0, Q, seg, segstride, n, M);
 }
-// Multiplications up to which the engine takes them, a workgroup each: on G1 0.63 ms at 128 points and
-// 1.4 at 2048, when the chip is full; single lanes take 0.9 to 1.1 ms up to 65536 (k_lane.hip).
-static constexpr uint64_t MUL_MAX = 2048;
-void g1_mul(const g1_aff *P, const fe *k, uint64_t n, g1_aff *out, hipStream_t st) {
-  if (n > MUL_MAX) kn::g1_mul(P, 0, k, n, out, st);
+void g1_mul(const g1_aff *P, const fe *k, uint64_t n, g1_aff *out, void *tab, hipStream_t st) {
+  if (n > MUL_MAX) kn::g1_mul(P, 0, k, n, out, tab, st);
   else if (n) LAUNCH(ks_g1_mul, dim3((unsigned)n), dim3(SLP_T), 0, P, k, n, out);
 }
 void mults(const fp12 *X, const fe *kx, uint64_t n3, fp12 *outx, const g2_aff *Q, const fe *kq, uint64_t n2, g2_aff *outq,
-           const g1_aff *P, const fe *kp, uint64_t n1, g1_aff *outp, hipStream_t st) {
+           const g1_aff *P, const fe *kp, uint64_t n1, g1_aff *outp, void *tab, hipStream_t st) {
   const bool many1 = n1 > MUL_MAX, many2 = n2 > MUL_MAX;
-  if (many1) kn::g1_mul(P, 0, kp, n1, outp, st);
-  if (many2) kn::g2_mul(Q, 1, kq, n2, outq, st);
+  if (many1) kn::g1_mul(P, 0, kp, n1, outp, tab, st);
+  if (many2) kn::g2_mul(Q, 1, kq, n2, outq, tab, st);
   const uint64_t m1 = many1 ? 0 : n1, m2 = many2 ? 0 : n2;
   if (n3 + m2 + m1)
     LAUNCH(ks_mults, dim3((unsigned)(n3 + m2 + m1)), dim3(SLP_T), 0, X, kx, n3, outx, Q, kq, m2, outq, P, kp, m1, outp);

@@ -134,28 +134,39 @@ void diag_field(int which, int op, const void *a, const void *b, uint64_t n, voi
 // one lane per element (k_lane.hip): the direct rounds with points enough to fill the device, and
 // multiplications that no chain waits for
 namespace kn {
+// The lanes' tables: a slot of `tab` for each of a launch's workgroups of 64 lanes, at most 2048 (two
+// wavefronts for each of 1024 SIMDs; 220 MB).  Launches that may run at the same time need memory of their own.
+static constexpr uint64_t TABLE_SLOTS = 2048, TABLE_SLOT_BYTES = 107520;
+inline uint64_t table_slots(uint64_t lanes) { return (lanes + 63) / 64 < TABLE_SLOTS ? (lanes + 63) / 64 : TABLE_SLOTS; }
+inline uint64_t table_bytes(uint64_t lanes) { return table_slots(lanes) * TABLE_SLOT_BYTES; }
+// Multiplications from which a launch is given to lanes.  A lane's chain is the longest (G1 0.9 to 1.1
+// ms, a G2 fold on two lanes 1.5, whatever the number up to a wavefront for each SIMD), but it does the least
+// work for it: the engine's workgroup for each takes 0.4 ms (G1) to 0.85 (a fold) for a few, and
+// 1.5 ms for 8192 terms, with the whole chip.  With the line at 1024 an open-all of 2^10 entries, b = 1,
+// took 9.4 ms against 8.75, one of 2^17, b = 34, 16.5 against 16.8.
+static constexpr uint64_t LANE_MIN = 4096;
+// whether a direct round of nb batches folds on single lanes (else ks::oa_fold)
+inline bool fold_lanes(uint64_t nb, uint64_t h) { return nb * h >= LANE_MIN; }
 // G1 terms of a direct round, homogeneous, into S[(2 k + side) (K / 2) + i]: the terms or the sums of
 // some consecutive ones; returns how many per batch and side
-uint64_t oa_g1terms(const g1_aff *A, const fe *B, uint64_t K, uint64_t nb, uint64_t h, g1_jac *S, hipStream_t st);
+uint64_t oa_g1terms(const g1_aff *A, const fe *B, uint64_t K, uint64_t nb, uint64_t h, g1_jac *S, void *tab, hipStream_t st);
 // G1 terms of the next round (oa_terms.hpp), homogeneous; returns how many consecutive ones are summed
-uint64_t oa_g1terms_next(const g1_aff *A, const fe *B, uint64_t K, uint64_t nb, uint64_t q, g1_jac *S1, hipStream_t st);
-// whether a direct round of nb batches folds on single lanes (else ks::oa_fold)
-bool fold_lanes(uint64_t nb, uint64_t h);
+uint64_t oa_g1terms_next(const g1_aff *A, const fe *B, uint64_t K, uint64_t nb, uint64_t q, g1_jac *S1, void *tab, hipStream_t st);
 void oa_fold_g1(const g1_aff *Ain, const fe *Bin, g1_aff *Aout, fe *Bout, const fe *Xinv, const glv::Dec *dec, uint64_t K,
-                uint64_t nb, uint64_t h, uint32_t j, uint32_t lK, hipStream_t st);
+                uint64_t nb, uint64_t h, uint32_t j, uint32_t lK, void *tab, hipStream_t st);
 void oa_fold_g2(const g2_aff *Vin, g2_aff *Vout, const fe *Xinv, uint64_t K, uint64_t nb, uint64_t h, uint32_t j, uint32_t lK,
-                hipStream_t st);
+                void *tab, hipStream_t st);
 // Miller values of a direct round, or the products of some consecutive ones, at the start of each batch
 // and side (stride K / 2); returns how many per batch and side, the length of the F_p12 tree that follows
 uint64_t oa_miller(const g1_aff *A, const g2_aff *V, uint64_t K, uint64_t nb, uint64_t h, fp12 *F, hipStream_t st);
-// out[i] = k_i P_i, or k_i P_0 with bc
-void g1_mul(const g1_aff *P, int bc, const fe *k, uint64_t n, g1_aff *out, hipStream_t st);
-void g2_mul(const g2_aff *P, int bc, const fe *k, uint64_t n, g2_aff *out, hipStream_t st);
+// out[i] = k_i P_i, or k_i P_0 with bc (G2: two lanes each)
+void g1_mul(const g1_aff *P, int bc, const fe *k, uint64_t n, g1_aff *out, void *tab, hipStream_t st);
+void g2_mul(const g2_aff *P, int bc, const fe *k, uint64_t n, g2_aff *out, void *tab, hipStream_t st);
 // HyperEval terms of every job's g* (the root row of its y-tree): level d of job x at
 // S + (d G + x) M / 2, so the M / 2 terms of a level of all jobs are contiguous
-void hyper_terms(const S2Job *J, uint32_t G, uint64_t K, const g1_aff *ek, uint64_t M, uint32_t lM, g1_jac *S, hipStream_t st);
+void hyper_terms(const S2Job *J, uint32_t G, uint64_t K, const g1_aff *ek, uint64_t M, uint32_t lM, g1_jac *S, void *tab, hipStream_t st);
 // D_j = rho_j C_j, the D-tree's leaves of every job
-void d_leaves(const S2Job *J, uint32_t G, uint64_t K, hipStream_t st);
+void d_leaves(const S2Job *J, uint32_t G, uint64_t K, void *tab, hipStream_t st);
 }  // namespace kn
 
 // the engine (k_slp.hip): a workgroup of two wavefronts per pairing / product / element (of four per final
@@ -176,11 +187,20 @@ void g1_hom_to_aff(const g1_jac *in, uint64_t stride, uint64_t n, g1_aff *out0, 
 void g2_hom_to_aff(const g2_jac *in, uint64_t stride, uint64_t n, g2_aff *out, uint64_t ostride, hipStream_t st);
 // G1 terms of a direct round on the engine (layout as kn::oa_g1terms, one each)
 void oa_g1terms(const g1_aff *A, const fe *B, uint64_t K, uint64_t nb, uint64_t h, g1_jac *S, hipStream_t st);
-// out[i] = k_i P_i
-void g1_mul(const g1_aff *P, const fe *k, uint64_t n, g1_aff *out, hipStream_t st);
-// powers outx[i] = X[i]^{kx_i} in F_p12 (n3), multiples outq[i] = kq_i Q (n2) and outp[i] = kp_i P[i] (n1)
+// Multiplications up to which the engine takes them, a workgroup each: on G1 0.63 ms at 128 points and
+// 1.4 at 2048, when the chip is full; single lanes take 0.9 to 1.1 ms up to 65536 (k_lane.hip).
+static constexpr uint64_t MUL_MAX = 2048;
+// the lanes' tables for n1 multiplications on G1 and n2 on G2, one launch after the other
+inline uint64_t mul_table_bytes(uint64_t n1, uint64_t n2 = 0) {
+  const uint64_t a = n1 > MUL_MAX ? n1 : 0, b = n2 > MUL_MAX ? 2 * n2 : 0;
+  return kn::table_bytes(a > b ? a : b);
+}
+// out[i] = k_i P_i (tab: mul_table_bytes(n))
+void g1_mul(const g1_aff *P, const fe *k, uint64_t n, g1_aff *out, void *tab, hipStream_t st);
+// powers outx[i] = X[i]^{kx_i} in F_p12 (n3), multiples outq[i] = kq_i Q (n2) and outp[i] = kp_i P[i] (n1;
+// tab: mul_table_bytes(n1, n2))
 void mults(const fp12 *X, const fe *kx, uint64_t n3, fp12 *outx, const g2_aff *Q, const fe *kq, uint64_t n2, g2_aff *outq,
-           const g1_aff *P, const fe *kp, uint64_t n1, g1_aff *outp, hipStream_t st);
+           const g1_aff *P, const fe *kp, uint64_t n1, g1_aff *outp, void *tab, hipStream_t st);
 // fused round kernels: G1 + G2 fold; Miller loops + G1 terms of the next round (oa_terms.hpp);
 // final exponentiations of two strided lists
 void oa_fold(const g1_aff *Ain, const fe *Bin, g1_aff *Aout, fe *Bout, const g2_aff *Vin, g2_aff *Vout, const fe *X,

@@ -334,31 +334,35 @@ template <class L> HD __forceinline__ jac<typename L::O> to_jac(const pt<L> &p) 
 }
 
 // ---------------------------------------------------------------- scalar multiplication
-// k P on G1 with the split k = k_0 + k_1 lam (glv.hpp): the table of d_0 B_0 + d_1 B_1, d_j < 4, in
-// scratch memory, two doublings and at most one addition per two bits
-HD __forceinline__ pt<G1> mul_lane(const g1_aff &P, const glv::Dec &d) {
+// k P on G1 with the split k = k_0 + k_1 lam (glv.hpp): the table of d_0 B_0 + d_1 B_1, d_j < 4, two
+// doublings and at most one addition per two bits.  The table's 15 points are in the caller's
+// memory: T.put(e, point), T.get<G1>(e), 0 < e < 16.
+template <class Tab> HD __forceinline__ pt<G1> mul_lane(const g1_aff &P, const glv::Dec &d, const Tab &T) {
   if (aff_is_inf(P) || d.nbits == 0) return identity<G1>();
-  pt<G1> T[16];
   const fl x = in_small(P.x), y = in_small(P.y), x1 = mul(x, in(fe_const(bn::GLV_BETA))), one = small_one();
   const fl y0 = d.neg & 1 ? neg(y) : y, y1 = d.neg & 2 ? neg(y) : y;
 #pragma unroll 1
   for (int s = 1; s <= 4; s *= 4) {  // the multiples of B_0, of B_1
     const fl &bx = s == 1 ? x : x1, &by = s == 1 ? y0 : y1;
-    T[s] = {bx, by, one};
-    T[2 * s] = madd<G1>(T[s], bx, by);
-    T[3 * s] = madd<G1>(T[2 * s], bx, by);
+    pt<G1> t = {bx, by, one};
+    T.put(s, t);
+#pragma unroll 1
+    for (int m = 2; m <= 3; m++) {
+      t = madd<G1>(t, bx, by);
+      T.put(m * s, t);
+    }
   }
 #pragma unroll 1
   for (int e = 5; e < 16; e++)
-    if (e & 3) T[e] = add<G1>(T[e & 12], T[e & 3]);
+    if (e & 3) T.put(e, add<G1>(T.template get<G1>(e & 12), T.template get<G1>(e & 3)));
   const int n = (int)(d.nbits + 1) / 2;
-  pt<G1> acc = T[glv::digit2(d, (uint32_t)(n - 1))];
+  pt<G1> acc = T.template get<G1>((int)glv::digit2(d, (uint32_t)(n - 1)));
 #pragma unroll 1
   for (int w = n - 2; w >= 0; w--) {
 #pragma unroll 1
     for (int i = 0; i < 2; i++) acc = dbl<G1>(acc);
     const uint32_t dg = glv::digit2(d, (uint32_t)w);
-    if (dg) acc = add<G1>(acc, T[dg]);
+    if (dg) acc = add<G1>(acc, T.template get<G1>((int)dg));
   }
   return acc;
 }

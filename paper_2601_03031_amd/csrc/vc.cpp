@@ -450,6 +450,7 @@ VC_API int vc_setup(uint32_t log_n, const uint8_t seed[32], int device, vc_param
   Carve t;
   size_t o_seed = t.take<uint8_t>(32), o_s = t.take<fe>(lM + 1), o_beta = t.take<fe>(1);
   size_t o_w = t.take<fe>(2 * M - 1), o_pw = t.take<fe>(2 * K - 1);
+  size_t o_tab = t.take<uint8_t>(kn::table_bytes(std::max(2 * M - 1, 2 * (2 * K - 1))));  // the lanes' tables
   int rc = ensure_ws(ex, t.off);
   if (rc) { vc_params_free(pp); return rc; }
   hipStream_t st = nullptr;
@@ -457,13 +458,14 @@ VC_API int vc_setup(uint32_t log_n, const uint8_t seed[32], int device, vc_param
   hipError_t e = hipMemcpy(at<uint8_t>(ws, o_seed), seed, 32, hipMemcpyHostToDevice);
   if (e != hipSuccess) { vc_params_free(pp); return hip_fail(e, "vc_setup"); }
   fe *s = at<fe>(ws, o_s), *beta = at<fe>(ws, o_beta), *w = at<fe>(ws, o_w), *pw = at<fe>(ws, o_pw);
+  void *tab = at<void>(ws, o_tab);
   kl::trapdoor(at<uint8_t>(ws, o_seed), pp->lM, s, beta, st);
   kl::ek_weights(pp->lM, s, w, 2 * M - 1, st);
-  kn::g1_mul(pp->g1gen, 1, w, 2 * M - 1, pp->ek, st);
-  kn::g2_mul(pp->g2gen, 1, s, lM, pp->vk, st);
+  kn::g1_mul(pp->g1gen, 1, w, 2 * M - 1, pp->ek, tab, st);
+  kn::g2_mul(pp->g2gen, 1, s, lM, pp->vk, tab, st);
   kl::pow_table(beta, pw, 2 * K - 1, st);
-  kn::g2_mul(pp->g2gen, 1, pw, 2 * K - 1, pp->h, st);
-  kn::g1_mul(pp->g1gen, 1, beta, 1, pp->g1beta, st);
+  kn::g2_mul(pp->g2gen, 1, pw, 2 * K - 1, pp->h, tab, st);
+  kn::g1_mul(pp->g1gen, 1, beta, 1, pp->g1beta, tab, st);
   params_tables(pp, st);
   e = hipGetLastError();
   if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -1091,6 +1093,14 @@ static int open_all_group(const vc_params *cpp, const vc_commitment *const *cms,
   // (multiples of whole arrays, one set per round parity; the G1 terms split likewise use them)
   size_t o_FM1 = t.take<g1_aff>(2 * 6 * nsplit), o_FM2 = t.take<g2_aff>(2 * 6 * nsplit);
   size_t o_FJ1 = t.take<g1_jac>(4 * nsplit), o_FJ2 = t.take<g2_jac>(4 * nsplit), o_GJ = t.take<g1_jac>(16 * nsplit);
+  // the lanes' tables: of the G1 side (and of C_F's terms, before it), of the terms taken ahead, of the G2
+  // folds and of Step 2 or the PST proof, whose launches run side by side
+  const uint64_t m_dir = nb * K >= kn::LANE_MIN ? nb * K : 0, m_next = ahead ? 8 * nb * (K >> j0) : 0;
+  const uint64_t m_f2 = !ahead && kn::fold_lanes(nb, K / 2) ? nb * K : 0;
+  const uint64_t m_s2 = with2 * std::max<uint64_t>(G * K, G * lM * (M / 2));
+  size_t o_T1 = t.take<uint8_t>(std::max(kn::table_bytes(m_dir), ks::mul_table_bytes(ev * K))),
+         o_T1n = t.take<uint8_t>(m_next >= kn::LANE_MIN ? kn::table_bytes(m_next) : 0), o_T2 = t.take<uint8_t>(kn::table_bytes(m_f2)),
+         o_TS = t.take<uint8_t>(std::max(kn::table_bytes(m_s2), ks::mul_table_bytes(ev * (M - 1))));
   const uint64_t c_dir = 2 * nb * tree_counters(K / 2), c_u = 2 * nb * tree_counters(K / 2),
                  c_xy = 4 * nb * tree_counters(K / 4);
   const uint64_t c_kzg = nb * tree_counters(kzg_len);
@@ -1148,6 +1158,7 @@ static int open_all_group(const vc_params *cpp, const vc_commitment *const *cms,
   fe *B = at<fe>(ws, o_B);
   fp12 *F = at<fp12>(ws, o_F);
   g1_jac *S = at<g1_jac>(ws, o_S);
+  void *T1 = at<void>(ws, o_T1), *T1n = at<void>(ws, o_T1n), *T2 = at<void>(ws, o_T2), *TS = at<void>(ws, o_TS);
   uint32_t *Hq = at<uint32_t>(ws, o_Hq), *sigma = at<uint32_t>(ws, o_sig);
   fe *Xinv = at<fe>(ws, o_Xi), *Q = at<fe>(ws, o_Q), *z = at<fe>(ws, o_z);
   g2_jac *S2 = at<g2_jac>(ws, o_S2);
@@ -1214,9 +1225,9 @@ static int open_all_group(const vc_params *cpp, const vc_commitment *const *cms,
     for (uint64_t s = N / 2; s >= 1; s /= 2) kl::merkle_level(J, G, s, st);
     kl::rho(J, G, K, st);
     kl::ytree(J, G, M, K, lK, st);
-    kn::d_leaves(J, G, K, st);
+    kn::d_leaves(J, G, K, TS, st);
     for (uint32_t h = 1; h <= lK; h++) klw::dlevel(J, G, K, h, st);
-    kn::hyper_terms(J, G, K, pp->ek, M, lM, HS, st);
+    kn::hyper_terms(J, G, K, pp->ek, M, lM, HS, TS, st);
     for (uint32_t d = 0; d < lM; d++) {
       // level d of every job: G 2^d segments of M / 2^{d+1} terms, contiguous
       uint64_t half = M >> (d + 1);
@@ -1281,7 +1292,7 @@ static int open_all_group(const vc_params *cpp, const vc_commitment *const *cms,
     CK(hipMemcpyAsync(at<void>(ws, o_rle), eval_r, 32ull * pp->L, hipMemcpyHostToDevice, st));
     kl::ev_point(at<uint8_t>(ws, o_rle), pp->L, er, err, st);
     kl::ev_eq(er, lM, lK, K, eT, st);
-    ks::g1_mul(Cj, eT, K, at<g1_aff>(ws, o_pK), st);
+    ks::g1_mul(Cj, eT, K, at<g1_aff>(ws, o_pK), T1, st);
     kl::ev_sum(at<g1_aff>(ws, o_pK), K, at<g1_aff>(bm, pr->o_CF), st);
     kl::ev_r0(C, er, pp->L, at<g1_aff>(bm, pr->o_CF), eT, K, B, st);
   } else {
@@ -1300,7 +1311,7 @@ static int open_all_group(const vc_params *cpp, const vc_commitment *const *cms,
       uint64_t half = 1ull << (k - 1);
       kl::ev_pst_step(eg, half, er + (k - 1), eq + (half - 1), s1);
     }
-    ks::g1_mul(pp->ek, eq, M - 1, at<g1_aff>(ws, o_pW), s1);
+    ks::g1_mul(pp->ek, eq, M - 1, at<g1_aff>(ws, o_pW), TS, s1);
     kl::ev_finish(at<g1_aff>(ws, o_pW), lM, eg, at<g1_aff>(bm, pr->o_We), at<fe>(bm, pr->o_yv), s1);
     return VC_OK;
   };
@@ -1331,7 +1342,7 @@ static int open_all_group(const vc_params *cpp, const vc_commitment *const *cms,
     if (split_round(jn - 1))
       ks::oa_g1terms_split(Ab[src], Bb[src], FM1[(jn - 1) & 1], K, nb, q, GJ, cnt_g1s, PS[par], sq);
     else
-      per = kn::oa_g1terms_next(Ab[src], Bb[src], K, nb, q, PS[par], sq);
+      per = kn::oa_g1terms_next(Ab[src], Bb[src], K, nb, q, PS[par], T1n, sq);
     ks::g1_tree(PS[par], 2 * nb, 2 * q, 2 * q / per, cnt_gu[par], sq);
     ks::g1_tree(PS[par] + nb * 4 * q, 4 * nb, q, q / per, cnt_gxy[par], sq);
     ks::g1_finish(PS[par], nb, q, PU1[par], PX1[par], PX1m[par], sq);
@@ -1341,7 +1352,7 @@ static int open_all_group(const vc_params *cpp, const vc_commitment *const *cms,
     const uint64_t h = K >> j;
     const int cur = (j - 1) & 1, nxt = j & 1;
     if (!ahead || j < j0) {
-      ks::g1_tree(S, 2 * nb, K / 2, kn::oa_g1terms(Ab[cur], Bb[cur], K, nb, h, S, sg), cnt_g1dir, sg);
+      ks::g1_tree(S, 2 * nb, K / 2, kn::oa_g1terms(Ab[cur], Bb[cur], K, nb, h, S, T1, sg), cnt_g1dir, sg);
       ks::g1_hom_to_aff(S, K / 2, 2 * nb, Lg1 + (j - 1), Rg1 + (j - 1), lK, sg);
       if (int rc2 = ev_mark(ex, 3, sg)) return rc2;
       // round 1 pairs the same A = aux with the same v in every batch of a job: its G_T
@@ -1415,9 +1426,9 @@ static int open_all_group(const vc_params *cpp, const vc_commitment *const *cms,
       if (int rc2 = stream_wait(ex, 4, st, sg)) return rc2;
       if (kn::fold_lanes(nb, h)) {
         kl::glv_dec(X, nb, j, lK, gdec, sg);
-        kn::oa_fold_g1(Ab[cur], Bb[cur], Ab[nxt], Bb[nxt], Xinv, gdec, K, nb, h, j, lK, sg);
+        kn::oa_fold_g1(Ab[cur], Bb[cur], Ab[nxt], Bb[nxt], Xinv, gdec, K, nb, h, j, lK, T1, sg);
         if (int rc2 = stream_wait(ex, 5, st, sf)) return rc2;
-        kn::oa_fold_g2(Vb[cur], Vb[nxt], Xinv, K, nb, h, j, lK, sf);
+        kn::oa_fold_g2(Vb[cur], Vb[nxt], Xinv, K, nb, h, j, lK, T2, sf);
         if (int rc2 = stream_wait(ex, 12, sf, st)) return rc2;
       } else {
         ks::oa_fold(Ab[cur], Bb[cur], Ab[nxt], Bb[nxt], Vb[cur], Vb[nxt], X, Xinv, K, nb, h, j, lK, sg);
@@ -2135,7 +2146,8 @@ static int verify_many(const vc_params *pp, const uint8_t *Cb, uint32_t b, uint3
          o_fzg2 = c.take<g2_aff>(n), o_gtb = c.take<fp12>(2 * n * lK), o_gtp = c.take<fp12>(2 * n * lK),
          o_gto = c.take<fp12>(n * (2 * lK + 1)), o_Cg1 = c.take<g1_aff>(n), o_bA = c.take<g1_aff>(n),
          o_pp = c.take<g1_aff>(n * npair), o_pq = c.take<g2_aff>(n * npair), o_F = c.take<fp12>(n * npair),
-         o_E = c.take<fp12>(3 * n), o_G = c.take<fp12>(3 * n), o_fl = c.take<int>(n);
+         o_E = c.take<fp12>(3 * n), o_G = c.take<fp12>(3 * n), o_fl = c.take<int>(n),
+         o_tab = c.take<uint8_t>(ks::mul_table_bytes((uint64_t)n * nmul, n));
   // the three product trees below run one after another and share one counter area
   const uint64_t tc = tree_counters(npair > 2 * lK + 1 ? npair : 2 * lK + 1);
   if (int rc = ensure_cnt(ex, n * tc, st)) return rc;
@@ -2179,7 +2191,8 @@ static int verify_many(const vc_params *pp, const uint8_t *Cb, uint32_t b, uint3
     kv::decode(cs, n, tmax, lK, lM, st);
     kv::transcript(cs, n, st);
     ks::mults(at<fp12>(d, o_gtb), at<fe>(d, o_gts), 2 * n * lK, at<fp12>(d, o_gtp), pp->g2gen, at<fe>(d, o_fz), n,
-              at<g2_aff>(d, o_fzg2), at<g1_aff>(d, o_mb), at<fe>(d, o_ms), (uint64_t)n * nmul, at<g1_aff>(d, o_mo), st);
+              at<g2_aff>(d, o_fzg2), at<g1_aff>(d, o_mb), at<fe>(d, o_ms), (uint64_t)n * nmul, at<g1_aff>(d, o_mo),
+              at<void>(d, o_tab), st);
     kv::assemble(cs, n, st);
     ks::f12_reduce(at<fp12>(d, o_gto), n, 2 * lK + 1, 2 * lK + 1, ex->cnt, st);
     ks::miller(at<g1_aff>(d, o_pp), 1, at<g2_aff>(d, o_pq), 1, (uint64_t)n * npair, F, st);
@@ -2292,7 +2305,8 @@ VC_API int vc_verify_eval(const vc_params *pp, const uint8_t C[384], const uint8
          o_g2o = w.take<g2_aff>(1 + lM), o_gts = w.take<fe>(2 * l), o_gtb = w.take<fp12>(2 * l),
          o_gtp = w.take<fp12>(2 * l), o_gto = w.take<fp12>(2 * l + 1), o_pp = w.take<g1_aff>(npair),
          o_pq = w.take<g2_aff>(npair), o_F = w.take<fp12>(npair), o_E = w.take<fp12>(3), o_Cg1 = w.take<g1_aff>(1),
-         o_bA = w.take<g1_aff>(1), o_fl = w.take<int>(1), o_ctx = w.take<VCtx>(1), o_G = w.take<fp12>(3);
+         o_bA = w.take<g1_aff>(1), o_fl = w.take<int>(1), o_ctx = w.take<VCtx>(1), o_G = w.take<fp12>(3),
+         o_tab = w.take<uint8_t>(ks::mul_table_bytes(nmul, 1 + lM));
   if (int rc = ensure_cnt(ex, tree_counters(npair > 2 * l + 1 ? npair : 2 * l + 1), st)) return rc;
   void *d = nullptr;
   CK(hipMalloc(&d, w.off));
@@ -2325,7 +2339,7 @@ VC_API int vc_verify_eval(const vc_params *pp, const uint8_t C[384], const uint8
     kve::decode(c, st);
     kl::ev_eq(c.r, lM, l, K, c.T, st);
     kve::transcript(c, st);
-    ks::mults(c.gtb, c.gts, 2 * l, c.gtp, pp->g2gen, c.g2s, 1 + lM, c.g2o, c.mb, c.ms, nmul, c.mo, st);
+    ks::mults(c.gtb, c.gts, 2 * l, c.gtp, pp->g2gen, c.g2s, 1 + lM, c.g2o, c.mb, c.ms, nmul, c.mo, at<void>(d, o_tab), st);
     kve::assemble(c, st);
     ks::f12_reduce(c.gto, 1, 2 * l + 1, 2 * l + 1, ex->cnt, st);
     ks::miller(c.pp, 1, c.pq, 1, npair, F, st);
@@ -2537,7 +2551,8 @@ VC_API int vc_verify_all(const vc_params *pp, const uint8_t C[384], uint32_t b, 
          o_oc = w.take<uint32_t>(1), o_row = w.take<fe>(K), o_col = w.take<fe>(M), o_sy = w.take<fe>(1);
   const uint64_t T = 3 * K + 2 * M - 3;
   size_t o_bases = w.take<g1_aff>(T), o_scal = w.take<fe>(T), o_prod = w.take<g1_aff>(T), o_pp = w.take<g1_aff>(y.lM + 1),
-         o_pq = w.take<g2_aff>(y.lM + 1), o_F = w.take<fp12>(y.lM + 1), o_E = w.take<fp12>(1), o_fl = w.take<int>(1);
+         o_pq = w.take<g2_aff>(y.lM + 1), o_F = w.take<fp12>(y.lM + 1), o_E = w.take<fp12>(1), o_fl = w.take<int>(1),
+         o_tab = w.take<uint8_t>(ks::mul_table_bytes(T));
   if (int rc = ensure_cnt(ex, tree_counters(y.lM + 1), st)) return rc;
   void *d = nullptr;
   CK(hipMalloc(&d, w.off));
@@ -2564,7 +2579,7 @@ VC_API int vc_verify_all(const vc_params *pp, const uint8_t C[384], uint32_t b, 
   kva::proof(c, st);
   kva::sums(c, st);
   kva::terms(c, st);
-  ks::g1_mul(c.bases, c.scal, T, c.prod, st);
+  ks::g1_mul(c.bases, c.scal, T, c.prod, at<void>(d, o_tab), st);
   kva::segsum(c, st);
   ks::miller(c.pp, 1, c.pq, 1, y.lM + 1, F, st);
   ks::f12_reduce(F, 1, y.lM + 1, y.lM + 1, ex->cnt, st);
