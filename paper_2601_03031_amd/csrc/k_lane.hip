@@ -385,7 +385,11 @@ __device__ __forceinline__ void to_aff_pair(const pt<G2pair> &t, fe &x, fe &y) {
   x = lane::out(G2pair::mul(t.X, zi));
   y = lane::out(G2pair::mul(t.Y, zi));
 }
-__device__ __forceinline__ bool both(bool c) { return c && __builtin_amdgcn_mov_dpp((int)c, 0xB1, 0xF, 0xF, true); }
+// c in both lanes of a pair (the other lane's is read whatever this one's is: both are active then)
+__device__ __forceinline__ bool both(bool c) {
+  const int o = __builtin_amdgcn_mov_dpp((int)c, 0xB1, 0xF, 0xF, true);
+  return (int)c & o;
+}
 
 struct point {
   fl X, Y, Z;  // homogeneous
@@ -480,8 +484,8 @@ __global__ void __launch_bounds__(LT) kn_oa_miller(const g1_aff *A, const g2_aff
   const fe *Q = reinterpret_cast<const fe *>(V + (side ? k * K + h + i : k * K + i));
   const fe qx = Q[p], qy = Q[2 + p];
   // the identity in either place: 1
-  const bool qz = fe_is_zero(qx) && fe_is_zero(qy);
-  const bool none = aff_is_inf(P) || both(qz);
+  const bool qz = both(fe_is_zero(qx) && fe_is_zero(qy));
+  const bool none = aff_is_inf(P) || qz;
   const fl xP = lane::in_small(P.x), yP = lane::in_small(P.y), x = lane::in_small(qx), y = lane::in_small(qy);
   fl one = lane::small_one(), zero = {};
   one = pick(p, zero, one);
