@@ -50,3 +50,43 @@ def test_identity_commitments(vc, rows):
         assert pr.export(w) == oop.export(w), w
     for i in (0, 3 * M + 1, 64 * M, N - 1):
         assert vc.vc_proof_get(pr, i) == oop.proof(i), i
+
+
+def same_step1(vc, pp, got, ref):
+    for k in range((pp.K + ref.b - 1) // ref.b):
+        for w in ("fc_x", "fc_rounds", "fc_tail"):
+            assert got.export(w, k) == ref.export(w, k), (w, k)
+
+
+@pytest.mark.parametrize("L,b,bound", [(8, 16, 4096), (10, 3, 4096), (12, 1, 4096), (14, 4, 4096), (16, 256, 4096), (16, 128, None), (18, 128, None)])
+def test_rounds_ahead_equal_direct_rounds(vc, L, b, bound):
+    """Rounds taken ahead (a caller's bound of 4096 pairs, or None: the default rule, which takes them ahead
+    at these sizes) give the same bytes as direct rounds (a bound of 0).  (12, 1) and (14, 4) go
+    direct first and then ahead; their first terms ahead are 4096, sums of 8 and of 16 by lanes, and those of
+    (18, 128) sums of 64; (16, 128) has 1024, on the engine."""
+    print("rounds ahead L=%d b=%d bound=%s" % (L, b, bound), flush=True)
+    pp = vc.vc_setup(L, SEED, 0)
+    cm = vc.vc_commit(pp, I.device_entries(1 << L, 180 + L), 256)
+    direct, other = vc.vc_exec_create(0, 6), vc.vc_exec_create(0, 6)
+    direct.set_ahead(0)
+    if bound is not None:
+        other.set_ahead(bound)
+    ref = vc.vc_open_all_ex(pp, cm, b, direct)
+    got = vc.vc_open_all_ex(pp, cm, b, other)
+    same_step1(vc, pp, got, ref)
+    for w in ("merkle", "rho", "D", "W"):
+        assert got.export(w) == ref.export(w), w
+    for i in (0, pp.N // 2 + 1, pp.N - 1):
+        assert vc.vc_proof_get(got, i) == vc.vc_proof_get(ref, i), i
+
+
+def test_blocks_in_turn(vc):
+    """2^18 entries, b = 1: the terms and G2 folds of round 1 have 262144 lanes, twice as many as the launch's
+    workgroups, and the G1 folds 131072, as many: every proof verifies."""
+    L, b = 18, 1
+    print("blocks in turn L=%d" % L, flush=True)
+    pp = vc.vc_setup(L, SEED, 0)
+    m = I.device_entries(1 << L, 188)
+    cm = vc.vc_commit(pp, m, 256)
+    proofs = vc.vc_proofs_serialize(vc.vc_open_all(pp, cm, b))
+    assert vc.vc_verify_all(pp, cm.C, b, m, proofs, bytes(range(32))) == (1, pp.K)
