@@ -6,8 +6,10 @@
 // 741 of them bring g to 0 and f to +-1 for 256-bit inputs.  The steps of a batch depend on the
 // low 30 bits of f and g alone; their product, a 2 x 2 matrix t / 2^30 with row sums |u| + |v| <=
 // 2^30, is then applied to f and g (exactly) and, modulo m, to d and e with f = d x, g = e x.
-// A run of zero bits of g is one shift, and up to 6 bits of g are cancelled at a time by adding a
-// multiple of f (as many as delta lets the steps go on without a swap).
+// The steps fall into three kinds.  With delta at or below 0 the next 1 - delta of them swap nothing,
+// whatever g's bits are: together they take g to (g + w f) / 2^n, w = -g / f mod 2^n, n = 1 - delta, in one go.
+// With delta above 0 an even g is halved, and an odd one swaps: (f, g) -> (g, -f), -delta is below 0, and the step is the
+// first of those without a swap.
 // Numbers are 9 signed limbs of 30 bits, the lower 8 in [0, 2^30).  d and e are not reduced on the
 // way: with the multiple of m taken in [-2^29, 2^29) each batch adds at most m / 2 to them.
 #pragma once
@@ -36,34 +38,46 @@ __host__ __device__ constexpr int32_t limb30(const uint32_t *x, int i) {
   return (int32_t)(v & MASK);
 }
 
-// 30 steps from the low bits of f (odd) and g; eta = -delta
-__host__ __device__ __forceinline__ Mat batch(int32_t &eta, uint32_t f, uint32_t g) {
-  uint32_t u = 1, v = 0, q = 0, r = 1;
+// the low bits of f or g within a batch, and its coefficients of the f and g that the batch began with
+// (times 2 for each step so far)
+struct Low {
+  uint32_t x, f, g;
+};
+
+// w with x + w f = 0 mod 2^n, for odd f and 0 < n < 32.  f is its own inverse mod 8 (odd squares are 1
+// there), and Newton's step for 1 / f doubles the bits that are right.
+__host__ __device__ __forceinline__ uint32_t cancelling(uint32_t x, uint32_t f, int n) {
+  uint32_t inv = f;
+  for (int right = 3; right < n; right *= 2) inv *= 2 - f * inv;
+  return (0u - x * inv) & ((1u << n) - 1);
+}
+
+// 30 steps from the low bits of f (odd) and g
+__host__ __device__ __forceinline__ Mat batch(int32_t &delta, uint32_t flow, uint32_t glow) {
+  Low f = {flow, 1, 0}, g = {glow, 0, 1};
   int left = 30;
   for (;;) {
-    const int z = __builtin_ctz(g | (0xffffffffu << left));
-    g >>= z;
-    u <<= z;
-    v <<= z;
-    eta -= z;
-    left -= z;
-    if (left == 0) break;
-    if (eta < 0) {
-      uint32_t t;
-      t = f; f = g; g = 0u - t;
-      t = u; u = q; q = 0u - t;
-      t = v; v = r; r = 0u - t;
-      eta = -eta;
+    if (delta <= 0) {
+      const int n = 1 - delta < left ? 1 - delta : left;
+      const uint32_t w = cancelling(g.x, f.x, n);
+      g = {(g.x + w * f.x) >> n, g.f + w * f.f, g.g + w * f.g};
+      f.f <<= n;
+      f.g <<= n;
+      delta += n;
+      left -= n;
     }
-    // w = -g / f mod 2^k: f (f^2 - 2) = -1 / f mod 2^6, as f^2 = 1 mod 8
-    int k = eta + 1 < left ? eta + 1 : left;
-    k = k < 6 ? k : 6;
-    const uint32_t w = (g * f * (f * f - 2)) & ((1u << k) - 1);
-    g += f * w;
-    q += u * w;
-    r += v * w;
+    const int even = __builtin_ctz(g.x | 1u << left);  // (at most the steps that are left)
+    g.x >>= even;
+    f.f <<= even;
+    f.g <<= even;
+    delta += even;
+    left -= even;
+    if (left == 0) return {(int32_t)f.f, (int32_t)f.g, (int32_t)g.f, (int32_t)g.g};
+    const Low was = f;
+    f = g;
+    g = {0u - was.x, 0u - was.f, 0u - was.g};
+    delta = -delta;
   }
-  return {(int32_t)u, (int32_t)v, (int32_t)q, (int32_t)r};
 }
 
 // o = (a x + b y + k m) / 2^30, with k (masked by kmask) the multiple that makes the low limb zero.
@@ -120,7 +134,7 @@ template <class F> __host__ __device__ __forceinline__ void finish(const int32_t
 
 // x^{-1} mod m of the integer 0 < x < m, one lane by itself
 template <class F> __host__ __device__ __forceinline__ void inverse(const uint32_t *x, uint32_t *out) {
-  int32_t f[NL], g[NL], d[NL], e[NL], eta = -1;
+  int32_t f[NL], g[NL], d[NL], e[NL], delta = 1;
 #pragma unroll
   for (int i = 0; i < NL; i++) {
     f[i] = limb30(F::M, i);
@@ -133,7 +147,7 @@ template <class F> __host__ __device__ __forceinline__ void inverse(const uint32
 #pragma unroll
     for (int i = 0; i < NL; i++) any |= g[i];
     if (any == 0) break;
-    const Mat t = batch(eta, (uint32_t)f[0], (uint32_t)g[0]);
+    const Mat t = batch(delta, (uint32_t)f[0], (uint32_t)g[0]);
     int32_t n0[NL], n1[NL];
     row<F>(f, g, t.u, t.v, 0, n0);
     row<F>(f, g, t.q, t.r, 0, n1);
@@ -155,7 +169,7 @@ template <class F> __host__ __device__ __forceinline__ void inverse(const uint32
 template <class F> __device__ __forceinline__ void inverse_uniform(const uint32_t *x, uint32_t *out) {
   const int p = threadIdx.x & 3;
   const int32_t kmask = p & 2 ? -1 : 0;
-  int32_t own[NL], eta = -1;
+  int32_t own[NL], delta = 1;
 #pragma unroll
   for (int i = 0; i < NL; i++) own[i] = p == 0 ? limb30(F::M, i) : p == 1 ? limb30(x, i) : p == 3 ? (i == 0) : 0;
 #pragma unroll 1
@@ -167,7 +181,7 @@ template <class F> __device__ __forceinline__ void inverse_uniform(const uint32_
       for (int i = 0; i < NL; i++) any |= own[i];
       if (__builtin_amdgcn_readlane(any, 1) == 0) break;
     }
-    const Mat t = batch(eta, f0, g0);
+    const Mat t = batch(delta, f0, g0);
     int32_t other[NL], o[NL];
 #pragma unroll
     for (int i = 0; i < NL; i++) other[i] = __builtin_amdgcn_mov_dpp(own[i], 0xB1, 0xF, 0xF, true);  // lane ^ 1

@@ -1003,3 +1003,10 @@ API void hc_proof_grid(uint64_t N, uint32_t *xy) {
   xy[0] = g.x;
   xy[1] = g.y;
 }
+
+// a batch of 30 division steps: delta, the low words of f (odd) and g -> the matrix u, v, q, r and delta after it
+API void hc_divsteps_batch(int32_t delta, uint32_t f, uint32_t g, int32_t *out) {
+  const divsteps::Mat t = divsteps::batch(delta, f, g);
+  out[0] = t.u; out[1] = t.v; out[2] = t.q; out[3] = t.r;
+  out[4] = delta;
+}

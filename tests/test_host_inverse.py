@@ -48,3 +48,28 @@ def test_pow_fixed(hc, which, mod):
             o = C.create_string_buffer(32)
             hc.hc_pow_fixed(which, O.be32(x), O.be32(e), o)
             assert int.from_bytes(o.raw, "big") == pow(x, e, mod), (x, e)
+
+
+def division_steps(n, delta, f, g):
+    """n division steps by their definition: 2^n times the matrix that takes f and g to theirs, and delta"""
+    u, v, q, r = 1, 0, 0, 1
+    for _ in range(n):
+        if delta > 0 and g & 1:
+            delta, f, g, u, v, q, r = 1 - delta, g, (g - f) // 2, 2 * q, 2 * r, q - u, r - v
+        else:
+            b = g & 1
+            delta, g, u, v, q, r = 1 + delta, (g + b * f) // 2, 2 * u, 2 * v, q + b * u, r + b * v
+    return [u, v, q, r], delta
+
+
+def test_batch(hc):
+    """A batch's matrix and delta are those of 30 single steps: every small delta, runs without a swap as
+    long as the batch and longer, g zero, even or all ones."""
+    rng = random.Random(920)
+    out = (C.c_int32 * 5)()
+    deltas = list(range(-40, 41)) + [1] * 200
+    for delta in deltas:
+        for g in (0, 1, 2, 1 << 29, 1 << 30, 0xffffffff, 0x3fffffff, rng.getrandbits(32), rng.getrandbits(32) << 7 & 0xffffffff):
+            f = rng.getrandbits(32) | 1
+            hc.hc_divsteps_batch(C.c_int32(delta), C.c_uint32(f), C.c_uint32(g), out)
+            assert (list(out[:4]), out[4]) == division_steps(30, delta, f, g), (delta, f, g)
