@@ -315,7 +315,7 @@ template <class F> NOINL fe f_pow(const fe &a, const uint32_t *e) {
 }
 
 // the same by sliding windows of up to 4 bits, on loose limbs from start to end (factor 2^{261}: 32 a
-// is below 2^5 m, its square's reduction below 8 m, all later values below 2 m): 253 squarings and 59
+// is below 2^5 m, its square's reduction below 8 m, all later values below 2.4 m): 253 squarings and 59
 // products of the 8 odd powers for a square root's exponent, a third of the time of f_pow.  e is
 // not zero and the same in every lane.
 template <class F> DEV fe f_pow_fixed(const fe &a, const uint32_t *e) {

@@ -9,7 +9,7 @@
 #include "pairing.hpp"
 #include "hash.hpp"
 #include "slp.hpp"
-#include "lane29.hpp"
+#include "lane_models.hpp"
 #include "gls.hpp"
 #include "g2mul.hpp"
 #include "gtpow.hpp"
@@ -904,17 +904,11 @@ template <class L, class A> static A lane_sum(const A *p, int n, int m) {
     if (!aff_is_inf(p[i])) s[i >= m] = lane::madd<L>(s[i >= m], L::in(p[i].x), L::in(p[i].y));
   return jac_to_aff(lane::to_jac<L>(lane::add<L>(s[0], s[1])));
 }
-// a table of the one-lane multiplications
-struct HostTable {
-  lane::pt<lane::G1> *t;
-  template <class L> void put(int e, const lane::pt<L> &v) const { t[e] = v; }
-  template <class L> lane::pt<L> get(int e) const { return t[e]; }
-};
 // k P by the one-lane multiplication
 API int hc_lane_mul(const uint8_t *Pb, const uint8_t *kb, uint8_t *out) {
   const fe k = rd_raw(kb);
   lane::pt<lane::G1> tab[16];
-  wrg1(out, lane::to_aff<lane::G1>(lane::mul_lane(rdg1(Pb), glv::decompose(k.l), HostTable{tab})));
+  wrg1(out, lane::to_aff<lane::G1>(lane::mul_lane(rdg1(Pb), glv::decompose(k.l), lane::Kept<lane::pt<lane::G1>>{tab})));
   return 0;
 }
 API int hc_lane_sum(int grp, const uint8_t *pts, int n, int m, uint8_t *out) {
@@ -1009,4 +1003,198 @@ API void hc_divsteps_batch(int32_t delta, uint32_t f, uint32_t g, int32_t *out) 
   const divsteps::Mat t = divsteps::batch(delta, f, g);
   out[0] = t.u; out[1] = t.v; out[2] = t.q; out[3] = t.r;
   out[4] = delta;
+}
+
+// ---------------------------------------------------------------- two lanes a point, a pairing
+typedef lane::Both<lane::fl> Pair;
+typedef lane::G2pairOf<Pair> G2lanes;
+static Pair pair_in(const fp2 &x) { return {{lane::in_small(x.c0), lane::in_small(x.c1)}}; }
+static fp2 pair_out(const Pair &x) { return {lane::out(x.l[0]), lane::out(x.l[1])}; }
+static bool is_inf2(const g2_aff &q) { return aff_is_inf(q); }
+
+// k Q + A on G2 by a pair of lanes (A the identity: left out)
+API int hc_pair_mul(const uint8_t *Qb, const uint8_t *kb, const uint8_t *Ab, uint8_t *out) {
+  const fe k = rd_raw(kb);
+  const g2_aff Q = rdg2(Qb), A = rdg2(Ab);
+  lane::pt<G2lanes> tab[16];
+  lane::pt<G2lanes> t = lane::mul_pair(pair_in(Q.x), pair_in(Q.y), is_inf2(Q), gls::decompose(k.l), lane::Kept<lane::pt<G2lanes>>{tab});
+  if (!is_inf2(A)) t = lane::madd<G2lanes>(t, pair_in(A.x), pair_in(A.y));
+  const fp2 z = pair_out(t.Z);
+  if (f2_is_zero(z)) {
+    wrg2(out, aff_inf<OpsG2>());
+    return 0;
+  }
+  const fp2 zi = f2_inv(z);
+  const Pair zl = {{lane::in(zi.c0), lane::in(zi.c1)}};
+  wrg2(out, {pair_out(G2lanes::mul(t.X, zl)), pair_out(G2lanes::mul(t.Y, zl))});
+  return 0;
+}
+// the product of n Miller values by pairs of lanes (before the final exponentiation)
+API int hc_pair_miller(const uint8_t *Pb, const uint8_t *Qb, int n, uint8_t *out) {
+  lane::twelve<Pair> f;
+  for (int i = 0; i < n; i++) {
+    const g1_aff P = rdg1(Pb + 64 * i);
+    const g2_aff Q = rdg2(Qb + 128 * i);
+    const lane::fl x = lane::in_small(P.x), y = lane::in_small(P.y);
+    const lane::twelve<Pair> g = lane::miller_pair(lane::Lanes{}, Pair{{x, x}}, Pair{{y, y}}, pair_in(Q.x), pair_in(Q.y));
+    f = i ? lane::mul12(lane::Lanes{}, f, g) : g;
+  }
+  fp12 o;
+  fe *w = reinterpret_cast<fe *>(&o);
+  for (int q = 0; q < 6; q++)
+    for (int p = 0; p < 2; p++) w[2 * q + p] = lane::out((q < 3 ? f.a.c[q] : f.b.c[q - 3]).l[p]);
+  wr12(out, o);
+  return 0;
+}
+
+// ---------------------------------------------------------------- bounds of the lane kernels' limbs and values
+// Runs the kernels' formulas on bounds; w: how near the worst column, limb, argument of `reduce` come to
+// what they may be (1), the largest value packed, plus p (2), and the largest coordinate of a point.  Returns whether sums of any length stay within
+// the bounds found (the others' steps are run one by one).
+namespace {
+using lane::Bnd;
+template <class L> struct Bounds {
+  typedef lane::pt<L> pt;
+  // grows acc by step until that adds less than EPS, widens it a little and looks whether step keeps within
+  template <class F> static bool closed(pt &acc, F step) {
+    for (int i = 0; i < 200; i++) acc = lane::join(acc, step(acc));
+    const pt wide = widened(acc);
+    acc = wide;
+    return within(step(wide), wide);
+  }
+  static Bnd widen(const Bnd &a) { return {a.u * (1 + 1e-6), a.v * (1 + 1e-6)}; }
+  static lane::over2<Bnd> widen(const lane::over2<Bnd> &a) { return {widen(a.c0), widen(a.c1)}; }
+  static lane::Both<Bnd> widen(const lane::Both<Bnd> &a) { return {{widen(a.l[0]), widen(a.l[1])}}; }
+  static pt widened(const pt &a) { return {widen(a.X), widen(a.Y), widen(a.Z)}; }
+  static bool le(const Bnd &a, const Bnd &b) { return a.u <= b.u && a.v <= b.v; }
+  static bool le(const lane::over2<Bnd> &a, const lane::over2<Bnd> &b) { return le(a.c0, b.c0) && le(a.c1, b.c1); }
+  static bool le(const lane::Both<Bnd> &a, const lane::Both<Bnd> &b) { return le(a.l[0], b.l[0]) && le(a.l[1], b.l[1]); }
+  static bool within(const pt &a, const pt &b) { return le(a.X, b.X) && le(a.Y, b.Y) && le(a.Z, b.Z); }
+};
+double widest;
+void largest(const Bnd &a) { widest = std::fmax(widest, a.v); }
+void largest(const lane::over2<Bnd> &a) { largest(a.c0); largest(a.c1); }
+void largest(const lane::Both<Bnd> &a) { largest(a.l[0]); largest(a.l[1]); }
+template <class L> void largest(const lane::pt<L> &t) { largest(t.X); largest(t.Y); largest(t.Z); }
+void pack(const lane::over2<Bnd> &a) { pack(a.c0); pack(a.c1); }
+void pack(const lane::Both<Bnd> &a) { pack(a.l[0]); pack(a.l[1]); }
+// what follows: packed as it is, to Jacobian form, to affine form (z: a packed inverse)
+template <class L> void results(const lane::pt<L> &t, const typename L::T &z) {
+  largest(t);
+  pack(t.X); pack(t.Y); pack(t.Z);
+  pack(L::mul(t.X, t.Z)); pack(L::mul(L::mul(t.Y, t.Z), t.Z));
+  pack(L::mul(t.X, z)); pack(L::mul(t.Y, z));
+}
+// a multi-scalar multiplication: mixed additions of packed points, then sums of sums
+template <class L> bool msm_bounds(const typename L::T &a) {
+  typedef lane::pt<L> pt;
+  pt acc = lane::identity<L>();
+  const bool ok = Bounds<L>::closed(acc, [&](const pt &t) { return lane::join(lane::madd<L>(t, a, a), lane::add<L>(t, t)); });
+  results<L>(acc, a);
+  return ok;
+}
+}  // namespace
+
+API int hc_lane_bounds(int which, double *w) {
+  lane::bounds::worst = {};
+  widest = 0;
+  const Bnd in = lane::packed(), one = lane::const29<Bnd>(bn::P_ONE29), small = lane::mul(in, one);
+  bool ok = true;
+  if (which == 0) {
+    ok = msm_bounds<lane::G1of<Bnd>>(in);
+  } else if (which == 1) {
+    ok = msm_bounds<lane::G2of<Bnd>>({in, in});
+  } else if (which == 2) {
+    // a multiplication, a packed point added (the folds), sums of up to 64 (the terms)
+    typedef lane::G1of<Bnd> L;
+    glv::Dec d;
+    memset(&d, 0xff, sizeof d);
+    d.nbits = 128;
+    lane::pt<L> tab = {}, t = lane::mul_table(small, small, lane::mul(small, in), one, d, lane::Joined<lane::pt<L>>{&tab});
+    results<L>(lane::madd<L>(t, in, in), in);
+    for (int i = 0; i < 6; i++) t = lane::join(t, lane::add<L>(t, t));
+    results<L>(t, in);
+  } else if (which == 3) {
+    typedef lane::Both<Bnd> V;
+    typedef lane::G2pairOf<V> L;
+    gls::Dec d;
+    memset(&d, 0xff, sizeof d);
+    d.nbits = 96;
+    const V s = {{small, small}};
+    lane::pt<L> tab = {}, t = lane::mul_pair(s, s, false, d, lane::Joined<lane::pt<L>>{&tab});
+    t = lane::join(t, lane::madd<L>(t, s, s));
+    largest(t);
+    pack(t.Z);
+    pack(L::mul(t.X, V{{in, in}}));
+    pack(L::mul(t.Y, V{{in, in}}));
+  } else {
+    typedef lane::Both<Bnd> V;
+    const V s = {{small, small}};
+    lane::twelve<V> f = lane::miller_pair(lane::Lanes{}, s, s, s, s);
+    for (int i = 0; i < 5; i++) f = lane::mul12(lane::Lanes{}, f, f);
+    for (int q = 0; q < 3; q++) {
+      pack(f.a.c[q]);
+      pack(f.b.c[q]);
+    }
+  }
+  const lane::bounds::Worst &b = lane::bounds::worst;
+  w[0] = b.column; w[1] = b.limb; w[2] = b.reduced; w[3] = b.packed; w[4] = widest;
+  return ok;
+}
+
+// sum_n a_n b_n 2^{-261}, six products of 9 limbs each; k a + b less its quotient by p
+API void hc_lane_dot6(const int32_t *a, const int32_t *b, int32_t *o) {
+  lane::fl x[6], y[6];
+  const lane::fl *px[6], *py[6];
+  for (int n = 0; n < 6; n++) {
+    x[n] = lane::const29<lane::fl>(a + 9 * n);
+    y[n] = lane::const29<lane::fl>(b + 9 * n);
+    px[n] = &x[n];
+    py[n] = &y[n];
+  }
+  const lane::fl r = lane::dot6(px, py);
+  memcpy(o, r.l, sizeof r.l);
+}
+API void hc_lane_reduce(const int32_t *a, int k, const int32_t *b, int32_t *o) {
+  const lane::fl r = lane::reduce(lane::const29<lane::fl>(a), k, lane::const29<lane::fl>(b));
+  memcpy(o, r.l, sizeof r.l);
+}
+// the canonical residue of an engine slot's limbs, and of the sum of four
+API void hc_canon29(const int32_t *l, uint8_t *out) {
+  slp::f29 x = {};
+  for (int j = 0; j < 9; j++) x.l[j] = (uint32_t)l[j];
+  wr<FpP>(out, slp::from29(slp::canon29(x)));
+}
+API void hc_red29(const int64_t *c, int32_t *o) {
+  const slp::f29 r = slp::red29(c);
+  for (int j = 0; j < 9; j++) o[j] = (int32_t)r.l[j];
+}
+
+// operations of program prog (0 .. 8: the group laws' that write the accumulator) that write a slot of T
+// and are neither products nor copies of 0 or 1; -1 for another number
+API int hc_sums_into_T(int prog) {
+  static const int g1[] = {slp::PROG_G1_DBL2, slp::PROG_G1_DBL2_ADD, slp::PROG_G1_MADD, slp::PROG_G1_ADD},
+                   g2[] = {slp::PROG_G2_DBL, slp::PROG_G2_DBL_ADD, slp::PROG_G2_MADD, slp::PROG_G2_ADD, slp::PROG_G2_LOAD};
+  if (prog < 0 || prog >= 9) return -1;
+  const bool two = prog >= 4;
+  const int first = two ? slp::G2_T_0_0_0 : slp::G1_T_0_0, n = two ? g2m::NT : g1m::NT;
+  const slp::Call c = slp::call(two ? g2[prog - 4] : g1[prog]);
+  int sums = 0;
+  for (int v = 0; v < 4; v++)
+    for (uint32_t d = c.d[v]; d; d = slp::blk_word(slp::OPS, d, 0, 1))
+      for (int i = 0; i < slp::blk_ops(d); i++) {
+        const uint32_t head = slp::blk_word(slp::OPS, d, 2 * i, 0);
+        const int dst = (int)(slp::term_addr(head, c.rel) / 48);
+        if (dst < first || dst >= first + n || slp::term_coef(head) == 1) continue;
+        int terms = 0, consts = 0;  // (a copy of the constant 0 or 1, the first two)
+        for (int h = 0; h < 2; h++)
+          for (int t = 0; t < slp::blk_terms(d); t++) {
+            const uint32_t w = slp::blk_word(slp::OPS, d, 2 * i + h, 2 + t);
+            const int src = (int)(slp::term_addr(w, c.rel) / 48), base = two ? slp::G2_CBASE : slp::G1_CBASE;
+            terms += slp::term_coef(w) != 0;
+            consts += slp::term_coef(w) == 1 && (src == base || src == base + 1);
+          }
+        if (terms != 1 || consts != 1) sums++;
+      }
+  return sums;
 }

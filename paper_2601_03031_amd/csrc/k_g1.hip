@@ -3,7 +3,7 @@
 // points went through scratch memory)
 #define VC_INLINE_HELPERS 1
 #include "kcommon.hpp"
-#include "lane29.hpp"
+#include "lane_group.hpp"
 
 #define MSM_MAXE 8192
 #define MSM_G2_MAXE 8192  // S nwin for the G2 MSM (with its 256 Jacobian G2 points, 48 KB, 82 KB of LDS)

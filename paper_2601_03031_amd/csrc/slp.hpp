@@ -54,13 +54,13 @@ __host__ __device__ __forceinline__ fe from29(const f29 &x) {
   return r;
 }
 
-// Values in slots are signed and "almost reduced": |x| < 1.2 p, limbs 0..7 signed and below
-// 2^29 + 2^23 in magnitude ("loose"), the top limb signed.  Only kernel outputs are made
-// canonical.  So no offset is carried through the sums, a negation is the negated limbs, and
-// the carries of a sum are taken once, all columns side by side.
+// Values in slots are signed and "almost reduced": |x| < 1.2 p, limbs 0..7 signed and within 2^30 +
+// 2^18 ("loose": a sum's slot adds two reduced halves limb by limb, each in [-2^17, 2^29 + 2^17]), the top
+// limb signed.  Only kernel outputs are made canonical.  So no offset is carried through the sums, a
+// negation is the negated limbs, and the carries of a sum are taken once, all columns side by side.
 //
 // red29: V = sum c_j 2^{29 j} minus its rounded quotient by p.  The coefficient magnitudes of
-// a sum add up to less than 2^15, so every column is below 2^45 (V below 2^16 p).  The
+// a sum add up to less than 2^15, so every column is below 2^45 + 2^33 (V below 2^16 p).  The
 // quotient is estimated in single precision from the top column: the columns below it move V / p
 // by less than 0.021, the dropped low bits by 2^-13, the roundings by less than 0.01 for
 // quotients below 2^16.  The sum with 1.5 2^23 rounds it to the nearest integer, so
@@ -98,7 +98,8 @@ __host__ __device__ __forceinline__ f29 norm29(const f29 &x) {
   return o;
 }
 
-// x + y (limbs 0..7 in [0, 2^29) again), and -x limb by limb (limbs are signed)
+// x + y (limbs 0..7 in [0, 2^29) again) for slots that products write, the constants 0 and 1, and sums of
+// such; -x limb by limb (limbs are signed)
 __host__ __device__ __forceinline__ f29 add29(const f29 &x, const f29 &y) {
   f29 o;
 #pragma unroll
@@ -113,7 +114,8 @@ __host__ __device__ __forceinline__ f29 neg29(const f29 &x) {
 }
 
 // canonical residue of an almost-reduced value or a sum of up to four products (in (-2p, 5p)):
-// x + 2p lies in (0, 7p), and 4p, 2p and p are taken off where they fit
+// x + 2p lies in (0, 7p), and 4p, 2p and p are taken off where they fit.  Limbs of x within 2^30 + 2^18:
+// those of 2p are below 0.89 2^30, and the sums below 2^31
 __host__ __device__ __forceinline__ f29 canon29(const f29 &x) {
   f29 y = x;
 #pragma unroll
@@ -145,8 +147,8 @@ __host__ __device__ inline bool zero29(const f29 &x) {
 
 // Montgomery product with radix 2^29 over 9 limbs: a b 2^{-261} mod p for almost-reduced a and
 // b, result in (-0.01 p, 1.01 p) with limbs 0..7 in [0, 2^29).  Products go into signed 64-bit
-// columns without carries (each column stays below 2^62.5); the reduction clears one column at
-// a time.  The order is fixed row by row: a multiply-add that needs the one before it issues
+// columns without carries (the factors are reductions, limbs below 2^29 + 2^17, and each column
+// stays below 2^62.5); the reduction clears one column at a time.  The order is fixed row by row: a multiply-add that needs the one before it issues
 // after 8 cycles instead of 4, and left to itself the compiler sums each column in one
 // dependent chain to save registers (1512 cycles a product against 930 in this order).
 __host__ __device__ __forceinline__ f29 mont29(const f29 &a, const f29 &b) {
