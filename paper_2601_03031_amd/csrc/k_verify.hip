@@ -722,8 +722,7 @@ __global__ void __launch_bounds__(64) kva_rho(VACtx c) {
 __global__ void __launch_bounds__(256) kva_same(VACtx c) {
   const PLayout &y = c.y;
   __shared__ int diff;
-  uint64_t i = blockIdx.x;
-  if (i >= y.N) return;
+  const uint64_t i = proof_id();
   const int t = threadIdx.x;
   if (t == 0) diff = 0;
   __syncthreads();
@@ -919,7 +918,10 @@ void serialize(const PSCtx &c, hipStream_t st) {
 void decode(const VACtx &c, hipStream_t st) { L1(kva_decode, 3 * c.y.K + c.y.M + 9, c); }
 void roots(const VACtx &c, hipStream_t st) { L1(kva_roots, c.y.N, c); }
 void rho(const VACtx &c, hipStream_t st) { LAUNCH(kva_rho, dim3((unsigned)((c.y.K + 63) / 64)), dim3(64), 0, c); }
-void same(const VACtx &c, hipStream_t st) { LAUNCH(kva_same, dim3((unsigned)c.y.N), dim3(256), 0, c); }
+void same(const VACtx &c, hipStream_t st) {
+  const ProofGrid g = proof_grid(c.y.N);
+  LAUNCH(kva_same, dim3(g.x, g.y), dim3(256), 0, c);
+}
 void proof(const VACtx &c, hipStream_t st) { L1(kva_proof, c.y.N, c); }
 void sums(const VACtx &c, hipStream_t st) { LAUNCH(kva_sums, dim3((unsigned)(c.y.K + c.y.M + 1)), dim3(256), 0, c); }
 void terms(const VACtx &c, hipStream_t st) { L1(kva_terms, nterms(c), c); }
