@@ -13,7 +13,6 @@
 #include "field.hpp"
 #include "tower.hpp"
 #include "curve.hpp"
-#include "pairing.hpp"
 #include "hash.hpp"
 #include "kernels.h"
 

@@ -1,6 +1,7 @@
 // Optimal ate pairing on BN254: Miller loop over 6u+2 with homogeneous projective
 // coordinates for the twist point T (x = X/Z, y = Y/Z), followed by the two
-// Frobenius lines, and the final exponentiation of tower.hpp.
+// Frobenius lines, and the final exponentiation of tower.hpp.  The host checks compare the
+// engine's programs with it and count its products; no kernel includes it.
 //
 // Line values are taken at P = (xP, yP) in G1 through the untwisted points
 // psi(x, y) = (x w^2, y w^3); a line with slope lambda*w through psi(T) evaluates to
