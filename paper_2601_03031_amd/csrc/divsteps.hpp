@@ -6,10 +6,10 @@
 // 741 of them bring g to 0 and f to +-1 for 256-bit inputs.  The steps of a batch depend on the
 // low 30 bits of f and g alone; their product, a 2 x 2 matrix t / 2^30 with row sums |u| + |v| <=
 // 2^30, is then applied to f and g (exactly) and, modulo m, to d and e with f = d x, g = e x.
-// The steps fall into three kinds.  With delta at or below 0 the next 1 - delta of them swap nothing,
-// whatever g's bits are: together they take g to (g + w f) / 2^n, w = -g / f mod 2^n, n = 1 - delta, in one go.
-// With delta above 0 an even g is halved, and an odd one swaps: (f, g) -> (g, -f), -delta is below 0, and the step is the
-// first of those without a swap.
+// With delta at or below 0 the next 1 - delta steps swap nothing, whatever g's bits are: together they add
+// w f to g, w = -g / f mod 2^n, n = 1 - delta, and halve n times.  After them delta is above 0; then an even g is halved,
+// and an odd one swaps.  A swap's (f, g) -> (g, -f) and the run without one that follows it, of 1 + delta steps, are one
+// combination, g -> w g - f with w = f / g mod 2^(1 + delta), and its halvings one shift with those of the even g's.
 // Numbers are 9 signed limbs of 30 bits, the lower 8 in [0, 2^30).  d and e are not reduced on the
 // way: with the multiple of m taken in [-2^29, 2^29) each batch adds at most m / 2 to them.
 #pragma once
@@ -44,38 +44,34 @@ struct Low {
   uint32_t x, f, g;
 };
 
-// w with x + w f = 0 mod 2^n, for odd f and 0 < n < 32.  f is its own inverse mod 8 (odd squares are 1
-// there), and Newton's step for 1 / f doubles the bits that are right.
-__host__ __device__ __forceinline__ uint32_t cancelling(uint32_t x, uint32_t f, int n) {
-  uint32_t inv = f;
-  for (int right = 3; right < n; right *= 2) inv *= 2 - f * inv;
-  return (0u - x * inv) & ((1u << n) - 1);
+// x / f mod 2^n, for odd f and 0 < n < 32.  f is its own inverse mod 8 (odd squares are 1 there), and Newton's
+// step for 1 / f doubles the bits that are right.
+__host__ __device__ __forceinline__ uint32_t quotient(uint32_t x, uint32_t f, int n) {
+  uint32_t inv = f * (2 - f * f);
+  for (int right = 6; right < n; right *= 2) inv *= 2 - f * inv;
+  return x * inv & ((1u << n) - 1);
 }
 
 // 30 steps from the low bits of f (odd) and g
 __host__ __device__ __forceinline__ Mat batch(int32_t &delta, uint32_t flow, uint32_t glow) {
   Low f = {flow, 1, 0}, g = {glow, 0, 1};
   int left = 30;
+  if (delta <= 0) {  // the rest of a run that the batch before began
+    const uint32_t w = quotient(0u - g.x, f.x, 1 - delta < left ? 1 - delta : left);
+    g = {g.x + w * f.x, w * f.f, 1 + w * f.g};
+  }
   for (;;) {
-    if (delta <= 0) {
-      const int n = 1 - delta < left ? 1 - delta : left;
-      const uint32_t w = cancelling(g.x, f.x, n);
-      g = {(g.x + w * f.x) >> n, g.f + w * f.f, g.g + w * f.g};
-      f.f <<= n;
-      f.g <<= n;
-      delta += n;
-      left -= n;
-    }
-    const int even = __builtin_ctz(g.x | 1u << left);  // (at most the steps that are left)
-    g.x >>= even;
-    f.f <<= even;
-    f.g <<= even;
-    delta += even;
-    left -= even;
+    const int halved = __builtin_ctz(g.x | 1u << left);  // (at most the steps that are left)
+    g.x >>= halved;
+    f.f <<= halved;
+    f.g <<= halved;
+    delta += halved;
+    left -= halved;
     if (left == 0) return {(int32_t)f.f, (int32_t)f.g, (int32_t)g.f, (int32_t)g.g};
+    const uint32_t w = quotient(f.x, g.x, 1 + delta < left ? 1 + delta : left);
     const Low was = f;
     f = g;
-    g = {0u - was.x, 0u - was.f, 0u - was.g};
+    g = {w * f.x - was.x, w * f.f - was.f, w * f.g - was.g};
     delta = -delta;
   }
 }
