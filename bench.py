@@ -34,13 +34,17 @@ sys.path.insert(0, ROOT)
 METRIC = "all-N-proofs time (ms) at N=2^16,b=log²N and N=2^20; MSM points/s"
 PEAK_MAD_TOPS = 256 * 64 * 2.4e9 / 2 / 1e12   # v_mad_u64_u32 issues at half rate: 19.66 T multiply-adds/s
 PEAK_HBM_GBS = 8000.0
-MADS_PER_FMUL = 136                        # 8x32-bit CIOS: 64 + 64 products + 8 reduction words
+MADS_PER_FMUL = 136                        # the price of a field multiplication: an 8x32-bit CIOS product
+                                           # (64 + 64 + 8; the kernels' own, on 9x29-bit limbs, have 81 + 81)
 AHEAD_MAX_PAIRS = 4096                     # the library's switch to next-round terms (batches x K)
 AHEAD_FEW_PAIRS, AHEAD_FEW_BATCHES = 1024, 4
 # HBM bytes per launch from rocprofv3 FETCH_SIZE / WRITE_SIZE, scaled by a reference copy
-# (profiles/ks_final_exp2_n16_b256_hbm_counters.md); valid for the kernel build it was taken on
-TRAFFIC_BYTES = {"ks_final_exp2": round((417.0 * 2.000 + 14.2 * 1.000) * 1024),
-                 "ks_oa_pterms": round((827.6 * 2.000 + 127.0 * 1.000) * 1024)}
+# (profiles/ks_final_exp2_n16_b256_hbm_counters.md): of the programs those kernels run now
+TRAFFIC_BYTES = {"ks_final_exp2": round((4600.9 * 2.000 + 2.2 * 1.000) * 1024),
+                 "ks_oa_pterms": round((7445.6 * 2.000 + 910.5 * 1.000) * 1024)}
+# additions of the reduction of a block's buckets: with 128 buckets the two sums of each (128), the suffix
+# sums (7 x 128 - 127) and their sum (127); with 256 places the suffix sums (8 x 256 - 255) and their sum (255)
+REDUCE_128, REDUCE_256 = 128 + 769 + 127, 1793 + 255
 FOLD_SPLIT_MAX = 256                       # folds of at most this many pairs run split in four parts
 DIRECT_MIN = 512                           # rounds of more pairs than this run direct in the ahead mode
 KZG_SPLIT_MAX = 8192                       # KZG proofs of at most this many split jobs run split
@@ -150,34 +154,61 @@ def method_work(L, b, limbs, c):
             "commit": msm + fc_commit, "by_kernel": {k: v for k, v in by_kernel.items() if v}}
 
 
+def msm_work(limbs, K, M):
+    """What the library's commit MSM executes: nonzero digits (mixed additions) and the additions of its
+    blocks' reductions.  Entries of 256 bits take signed digits (a byte of the entry plus 128 in every
+    byte, less 128) into 128 buckets with two sums each, 32-bit ones bytes into 255 buckets; a block sums
+    up to 8 slices of a row (a power of two that leaves 1024 blocks) before it reduces them."""
+    import numpy as np
+    limbs = np.ascontiguousarray(limbs)
+    full = int(limbs[:, 1:].max()) != 0
+    S = min(M, 8192 // (32 if full else 4))
+    nslice = -(-M // S)
+    g = 1
+    while g < 8 and nslice % (2 * g) == 0 and K * nslice // (2 * g) >= 1024:
+        g *= 2
+    if not full:
+        return int(np.count_nonzero(limbs.view(np.uint8))), K * nslice // g * REDUCE_256
+    add, carry, nz = np.uint64(0x8080808080808080), np.zeros(len(limbs), dtype=np.uint64), 0
+    for q in range(4):
+        t = limbs[:, q] + add
+        c = t < add
+        t = t + carry
+        carry = (c | (t < carry)).astype(np.uint64)
+        nz += int(np.count_nonzero(t.view(np.uint8) != 128))
+    return nz, K * nslice // g * REDUCE_128
+
+
 def work_model(L, b, limbs, costs):
     """Algorithmic field multiplications per kernel over one step (commit + open-all)."""
-    import numpy as np
     lK, lM = L // 2, L - L // 2
     K, M, N = 1 << lK, 1 << lM, 1 << L
     nb = (K + b - 1) // b
     rounds = [K >> j for j in range(1, lK + 1)]
-    nz_digits = int(np.count_nonzero(np.ascontiguousarray(limbs).view(np.uint8)))
-    S = min(M, 8192 // (4 if int(limbs[:, 1:].max()) == 0 else 32))
-    blocks = K * ((M + S - 1) // S)
+    digits, adds = msm_work(limbs, K, M)
     g1_fold = costs["e_g1_mul"] + costs["e_g1_madd"] + costs["e_g1_to_aff"]
     g2_fold = costs["e_g2_mul"] + costs["e_g2_madd"] + costs["e_g2_to_aff"]
     nq = 2 * K - 2
     w = {
-        "k_msm_slices<lane::G1>": nz_digits * costs["g1_madd"] + blocks * 2048 * costs["g1_add"],
+        "k_msm_slices<lane::G1>": digits * costs["g1_madd"] + adds * costs["g1_add"],
         "ks_miller": K * costs["e_miller"],
         "kn_hyper_terms": lM * (M // 2) * costs["g1_mul"],
     }
     # KZG proof: with few terms, split multiplications; otherwise a G2 MSM over 8-bit windows
-    # of the fixed SRS points (about 255/256 of the (term, window) pairs have a nonzero digit;
-    # 2 x 255 additions per block of 32 bases); then the engine tree over the partial sums
+    # of the fixed SRS points (about 255/256 of the (term, window) pairs have a nonzero signed digit;
+    # slices of 32 bases, or of 256 where those give 512 blocks); then the engine tree over the
+    # partial sums
     if 4 * nb * nq <= KZG_SPLIT_MAX:
         w["ks_kzg_terms_split"] = 4 * nb * nq * costs["e_g2_part"]
         w["(ks_pt_tree<true, true>)"] = nb * (4 * nq - 1) * costs["e_g2_add"]
     else:
-        kzg_blocks = nb * (-(-nq // 32))
-        w["k_msm_slices<lane::G2>"] = (nb * nq * 32 * 255 // 256) * costs["g2_madd"] + kzg_blocks * 510 * costs["g2_add"]
-        w["(ks_pt_tree<true, false>)"] = (kzg_blocks - nb) * costs["e_g2_add"]
+        slices = -(-nq // (256 if nb * -(-nq // 256) >= 512 else 32))
+        group = 1
+        while group < 8 and slices % (2 * group) == 0 and nb * slices // (2 * group) >= 1024:
+            group *= 2
+        w["k_msm_slices<lane::G2>"] = ((nb * nq * 32 * 255 // 256) * costs["g2_madd"]
+                                       + nb * slices // group * REDUCE_128 * costs["g2_add"])
+        w["(ks_pt_tree<true, false>)"] = nb * (slices - 1) * costs["e_g2_add"]
     if lK >= 2 and takes_ahead(nb, K):
         # rounds j < j0 direct (the device is full), rounds j >= j0 from terms of the arrays of
         # round j - 1 (q = K >> j)
@@ -307,7 +338,7 @@ def run_workload(V, torch, L, b, bits, seed, steps, warmup, profile="all"):
 # (executors, streams per executor, jobs per fused group[, ahead threshold]) of the batched-jobs
 # runs: group 1 is one job per executor (vc_open_all_batch), larger groups fuse the jobs of one
 # size; a threshold set on the executors overrides the library's choice (0: every Step 1 round
-# direct; 4096: terms taken one round ahead up to 4096 batch-index pairs, the one-job default;
+# direct; 4096: terms taken one round ahead up to 4096 batch-index pairs, whatever their number of batches;
 # fused groups sharing the device run direct unless one is set)
 BATCH_SETUPS = ((8, 2, 1), (16, 1, 1), (16, 1, 1, 0), (16, 1, 64), (16, 1, 64, 4096), (8, 2, 64))
 
