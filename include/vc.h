@@ -19,11 +19,11 @@
  *  - Device pointers are borrowed for the duration of the call and must be device
  *    memory on the params' device.  `stream` is a hipStream_t (NULL = default
  *    stream); work is ordered on it and every call is synchronous on return.
- *    vc_open_all also runs work on five side streams of the params' default executor
- *    (joined to `stream` before it returns); they overlap only if the process has at
- *    least six hardware queues (environment GPU_MAX_HW_QUEUES, read by HIP at its first
- *    device use; the Python package raises it to 16), otherwise they share queues and run
- *    partly in sequence, with the same results.
+ *    vc_open_all also runs work on the four streams of the params' default executor
+ *    (joined to `stream` before it returns).  Streams that share a hardware queue run partly
+ *    in sequence, with the same results: HIP gives a process four (environment
+ *    GPU_MAX_HW_QUEUES, read at its first device use), for which the default executor's
+ *    streams are laid out; the Python package raises them to 16, on which all overlap.
  *  - Handles (vc_params, vc_commitment, vc_proofs, vc_exec, vc_server) own their device
  *    memory and are released with the matching *_free, in any order (each keeps its own
  *    device id; a release reports nothing and leaves no HIP error behind).  A commitment
@@ -52,7 +52,7 @@ extern "C" {
 #define VC_ECHALLENGE (-5) /* a Fiat-Shamir challenge was zero (probability ~2^-254) */
 
 /* Largest log2 N: at N = 2^30 an open-all with b = log^2 N, its entries and commitment hold
- * about 212 GB of device memory (measured; the entries, their copy in the commitment, the
+ * about 215 GB of device memory (measured; the entries, their copy in the commitment, the
  * Merkle tree and the y-tree dominate, about 192 N bytes), which fits the 288 GB of one
  * MI355X; 2^31 does not.  Per-element thread indices stay below 2^32 up to this size. */
 #define VC_MAX_LOG_N 30
@@ -140,8 +140,8 @@ int vc_tune_load(const char *path);
 int vc_open_all(const vc_params *pp, const vc_commitment *cm, uint32_t b, void *stream, vc_proofs **out);
 
 /* Executor: the streams, events, workspace and reduction counters that vc_commit,
- * vc_open_all and vc_verify use.  Every vc_params holds a default one (six streams), so calls
- * on the same params must not overlap; calls that run at the same time need executors of
+ * vc_open_all and vc_verify use.  Every vc_params holds a default one (four streams, shared by
+ * the six roles below as suits four hardware queues), so calls on the same params must not overlap; calls that run at the same time need executors of
  * their own.  nstreams in [1, 6]: the executor's own stream plus the five side streams of an
  * open-all mapped onto nstreams streams in turn.  Six give one job the most overlap; with
  * many jobs at once fewer streams per job (1 or 2) keep the jobs from sharing hardware
@@ -161,11 +161,14 @@ void vc_exec_free(vc_exec *ex);
  * (then the chain runs eagerly).  vc_exec_graph_stats: stats[0] captures, stats[1] replays. */
 int vc_exec_set_graphs(vc_exec *ex, int on);
 
-/* Step 1 scheduling of open-alls on executor ex (§3 Eq. (folding), Protocol 1 Step 1): their
- * rounds take the next round's terms one round ahead (shorter dependent chain, about four times
- * the Miller loops) while batches x K <= max_pairs, and run direct (the paper's order) above
- * it; the default is 4096.  0 makes every round direct.  Results are the same either way; the
- * footprint reported by vc_open_all_footprint assumes the default. */
+/* Step 1 scheduling of open-alls on executor ex (§3 Eq. (folding), Protocol 1 Step 1): rounds
+ * take the next round's terms one round ahead (shorter dependent chain, about four times the
+ * Miller loops) or run direct (the paper's order).  An executor that was never set takes them
+ * ahead while batches x K <= 4096 and there are at most 4 batches or batches x K <= 1024.  A
+ * bound set here is the only condition: ahead while batches x K <= max_pairs, so that 4096 is
+ * not the default schedule and 0 makes every round direct.  Results are the same either way;
+ * the footprint reported by vc_open_all_footprint is that of the default, and an open-all that
+ * takes terms ahead where the default does not needs more. */
 int vc_exec_set_ahead(vc_exec *ex, uint64_t max_pairs);
 int vc_exec_graph_stats(const vc_exec *ex, uint64_t stats[2]);
 
@@ -201,8 +204,10 @@ int vc_open_all_grouped(uint32_t n, const vc_params *const *pps, const vc_commit
                         const uint32_t *bs, uint32_t max_group, uint32_t nexec, vc_exec *const *exs,
                         vc_proofs **outs);
 
-/* Device bytes one vc_open_all of (pp, b) holds while it runs: proof bundle, workspace and
- * reduction counters (the bundle stays with the returned proofs).  Host-only: nothing is
+/* Device bytes one vc_open_all of (pp, b) holds while it runs: proof bundle, workspace (with the
+ * tables of its scalar multiplications) and reduction counters (the bundle stays with the
+ * returned proofs).  Beside them the runtime keeps 0.2 GB a hardware queue for the kernels'
+ * registers saved around calls, until the process ends.  Host-only: nothing is
  * allocated or launched.  VC_EINVAL for b outside [1, K]. */
 int vc_open_all_footprint(const vc_params *pp, uint32_t b, uint64_t *bytes);
 

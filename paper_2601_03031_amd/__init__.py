@@ -297,7 +297,8 @@ class Exec(_Handle):
         _check(lib().vc_exec_set_graphs(self.ptr, 1 if on else 0), "vc_exec_set_graphs")
 
     def set_ahead(self, max_pairs: int) -> None:
-        """Take Step 1's terms one round ahead while batches x K <= max_pairs (0: never)."""
+        """Take Step 1's terms one round ahead while batches x K <= max_pairs (0: never).  An executor
+        that was never set does so up to 4096 pairs in at most 4 batches, or 1024 pairs."""
         _check(lib().vc_exec_set_ahead(self.ptr, max_pairs), "vc_exec_set_ahead")
 
     def graph_stats(self) -> tuple:

@@ -6,7 +6,7 @@
 #include "lane_group.hpp"
 
 #define MSM_MAXE 8192
-#define MSM_G2_MAXE 8192  // S nwin for the G2 MSM (with its 256 Jacobian G2 points, 48 KB, 82 KB of LDS)
+#define MSM_G2_MAXE 8192  // S nwin for the G2 MSM (64 KB of LDS: its 256 points 54 KB, the digits 8 KB)
 
 // weights of the Lagrange keys at every level: node n = 2^k - 1 + c holds eq_k(c; s)
 __global__ void __launch_bounds__(TPB) k_ek_weights(uint32_t lM, const fe *s, fe *w, uint64_t n_total) {
@@ -122,13 +122,13 @@ __global__ void __launch_bounds__(TPB) k_check_curve(const aff<O> *p, uint64_t n
 
 // Batched MSM with shared bases: C_j = sum_a m[jM+a] ek[a] (canonical scalars).  Block
 // (j, slice) handles bases [slice*S, (slice+1)*S); every (base, window) pair with a nonzero
-// 8-bit digit is counting-sorted by digit in LDS, thread d sums bucket d over the
-// precomputed table points 2^{8w} ek[a], and the block reduces sum_d d B_d with a suffix
+// 8-bit digit is counting-sorted by digit in LDS, a thread (two with signed digits) sums a bucket over
+// the precomputed table points 2^{8w} ek[a], and the block reduces sum_d d B_d with a suffix
 // scan.  S nwin <= MSM_MAXE (G1), MSM_G2_MAXE (G2).  (A tree over bucket ranges that merges
 // (S, W) pairs with doublings does a quarter of the scan's additions but measured slower:
 // with one block per CU at N = 2^16 the block's latency sets the time, and its doubling
-// chains are longer than the scan's eight steps.)  Bound by the issue of its products: the
-// complete additions on one-lane limbs (lane29.hpp) take 1024 rows of 1024 bases in 3.7 ms, Jacobian
+// chains are longer than the scan's seven or eight steps.)  Bound by the issue of its products: the
+// complete additions on one-lane limbs (lane_group.hpp) take 1024 rows of 1024 bases in 3.7 ms, Jacobian
 // ones on packed elements took 6.5.  A block takes g consecutive slices of a row (g divides their
 // number): blk = (j nslice + slice) / g, and leaves their sum in the first one's place.
 template <class L>

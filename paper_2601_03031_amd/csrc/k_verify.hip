@@ -6,7 +6,7 @@
 //   kv_assemble    point sums and the pairs of the three pairing checks
 //   kv_compare     the final equalities
 // Scalar multiplications, G_T exponentiations, Miller loops and final exponentiations
-// run in the shared kernels (wide layout and engine).
+// run in the shared kernels (the engine's, and single lanes' for more than 2048 multiplications).
 #include "kcommon.hpp"
 #include "verify.h"
 

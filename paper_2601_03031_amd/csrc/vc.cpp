@@ -176,8 +176,10 @@ struct vc_params {
 // Step 1 takes the next round's terms ahead (oa_terms.hpp) when the batches leave the device mostly
 // idle: at most AHEAD_MAX_PAIRS (batch, index) pairs per round, and few batches or few pairs.  Beyond
 // that the doubled Miller-loop count and the three times as many final exponentiations of that scheme
-// cost more than the shorter chain saves (ms direct / ahead; batches x K: 32 x 32 8.1 / 8.5, 16 x 64 10.4 / 9.6,
-// 4 x 256 13.5 / 11.7, 3 x 1024 18.9 / 18.0; 32 x 64 9.6 / 11.1, 8 x 256 12.4 / 13.2, 64 x 64 13.3 / 16.0).
+// cost more than the shorter chain saves (ms direct / ahead; batches x K: 16 x 32 7.9 / 6.4, 16 x 64 10.3 /
+// 9.3, 4 x 256 11.8 / 11.1, 3 x 1024 18.9 / 16.9; 32 x 64 10.4 / 11.3, 8 x 256 12.2 / 13.2, 64 x 64 12.0 / 15.3).
+// What decides is the number of batches, for which the pairs stand in here: 32 x 32, at the line,
+// goes ahead though it is the faster direct (7.9 / 9.3).
 static constexpr uint64_t AHEAD_MAX_PAIRS = 4096, AHEAD_FEW_PAIRS = 1024, AHEAD_FEW_BATCHES = 4;
 // in the ahead mode, rounds of more than this many pairs (batches x h) still run direct: the
 // device is full there and the terms taken ahead (twice the Miller loops) cost more than the
@@ -191,7 +193,7 @@ static constexpr uint64_t FOLD_SPLIT_MAX = 256;
 static constexpr uint64_t LANE_MILLER_MIN = 4096;
 // bases per block of the KZG proof's G2 MSM (times 32 windows: at most 8192 digits): long
 // slices when the MSMs of all batches give at least KZG_LONG_MIN_BLOCKS blocks (the bucket
-// reduction, about 2300 G2 additions per block, is then spread over eight times the digits),
+// reduction, 1024 G2 additions per block, is then spread over eight times the digits),
 // short ones otherwise (more blocks, shorter chains, for few batches)
 static constexpr uint32_t KZG_S = 32, KZG_S_LONG = 256;
 static constexpr uint64_t KZG_LONG_MIN_BLOCKS = 512;
@@ -353,14 +355,15 @@ VC_API int vc_exec_create(int device, uint32_t nstreams, vc_exec **out) {
 
 // The default executor of a params has four streams beside the caller's: Step 2, the folds, the
 // pairing side of the terms of both parities, their G1 side.  HIP maps streams onto 4 hardware
-// queues by default, and roles that share a queue wait for one another's events: with six
-// streams, one of them idle and the rest shared by creation order, an open-all at 2^16, b = 256
-// took 18.0 ms on 4 queues against 11.1 on 16; with these four 12.2 and 10.9 (2^17, b = 34:
-// 27.3 and 19.5 against 20.4 and 19.5; 2^10, b = 1: 17.2 and 12.0 against 12.8 and 11.8).  The
-// order is the best of all maps of the five roles onto 3 to 5 streams on 4 queues, and within
-// noise of the best on 16.  The folds' stream is the one that shares a queue with the caller's
-// there; where all rounds run direct it would hold up the chain (2^16, b = 1: 107 ms against 87),
-// so the G1 side then takes the stream that the terms' G1 side leaves free.
+// queues by default, and roles that share a queue wait for one another's events.  The figures are
+// those on which the map was chosen, of a build whose kernels took longer (2^16, b = 256 is 8.6 ms
+// now, b = 1 33): with six streams, one of them idle and the rest shared by creation order, an
+// open-all at 2^16, b = 256 took 18.0 ms on 4 queues against 11.1 on 16; with these four 12.2 and
+// 10.9 (2^17, b = 34: 27.3 and 19.5 against 20.4 and 19.5; 2^10, b = 1: 17.2 and 12.0 against 12.8
+// and 11.8).  The order is the best of all maps of the five roles onto 3 to 5 streams on 4 queues,
+// and within noise of the best on 16.  The folds' stream is the one that shares a queue with the
+// caller's there; where all rounds run direct it would hold up the chain (2^16, b = 1: 107 ms
+// against 87), so the G1 side then takes the stream that the terms' G1 side leaves free.
 static const uint8_t DEFAULT_ROLES[5] = {1, 3, 0, 0, 2};
 
 static const uint32_t NWIN = 32;  // 8-bit windows of a 256-bit scalar

@@ -47,8 +47,8 @@ def same_proofs(V, pp, a, b_, idx):
 
 
 def test_batch_matches_single_jobs_and_oracle(vc):
-    # (L, b, seed): rounds taken ahead (most), direct then ahead (2^12, b=1), all direct
-    # (2^14, b=2), ragged last batches, two jobs on one params, more jobs than executors
+    # (L, b, seed): rounds taken ahead (most), all direct (2^12, b=1 and 2^14, b=2), ragged
+    # last batches, two jobs on one params, more jobs than executors
     spec = [(4, 1, 11), (6, 8, 12), (10, 3, 13), (5, 3, 14), (12, 36, 15), (6, 2, 16), (10, 20, 17),
             (12, 1, 18), (14, 2, 19)]
     params = {}

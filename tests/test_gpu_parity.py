@@ -233,7 +233,8 @@ def test_zero_challenge_is_reported(vc, L, b):
 def test_direct_rounds_equal_rounds_ahead(vc, L, b):
     """Step 1 with every round direct (an executor with vc_exec_set_ahead(0): the paper's
     order) gives the same bytes as the default schedule, which takes terms one round ahead
-    at these sizes (Eq. (folding): the lookahead only regroups the same pairings)."""
+    at these sizes but (12, 1), direct by default (Eq. (folding): the lookahead only regroups
+    the same pairings; test_gpu_lanes.py has schedules that go direct first and then ahead)."""
     say("direct rounds: L=%d b=%d" % (L, b))
     pp = vc.vc_setup(L, SEED, 0)
     N = 1 << L

@@ -24,7 +24,7 @@ def vc():
 @pytest.mark.parametrize("L,b", [(14, 2), (14, 1)])
 def test_verify_products(vc, L, b):
     """One check of every batch: 64 (20 products each, 1280) and 128 batches (19 each, 2432), the
-    multiplications on the engine and in the wide kernel.  The proofs verify; a byte changed in a
+    multiplications on the engine and on single lanes (from 2049 on).  The proofs verify; a byte changed in a
     round's point of one batch (an invalid encoding or another point) does not."""
     print("verify_all L=%d b=%d" % (L, b), flush=True)
     limbs = I.entries(1 << L, 77 + b, 256)
