@@ -356,8 +356,8 @@ VC_API int vc_exec_create(int device, uint32_t nstreams, vc_exec **out) {
 // The default executor of a params has four streams beside the caller's: Step 2, the folds, the
 // pairing side of the terms of both parities, their G1 side.  HIP maps streams onto 4 hardware
 // queues by default, and roles that share a queue wait for one another's events.  The figures are
-// those on which the map was chosen, of a build whose kernels took longer (2^16, b = 256 is 8.6 ms
-// now, b = 1 33): with six streams, one of them idle and the rest shared by creation order, an
+// those on which the map was chosen, when the kernels took longer (2^16, b = 256 is 8.6 ms now, b = 1
+// 33): with six streams, one of them idle and the rest shared by creation order, an
 // open-all at 2^16, b = 256 took 18.0 ms on 4 queues against 11.1 on 16; with these four 12.2 and
 // 10.9 (2^17, b = 34: 27.3 and 19.5 against 20.4 and 19.5; 2^10, b = 1: 17.2 and 12.0 against 12.8
 // and 11.8).  The order is the best of all maps of the five roles onto 3 to 5 streams on 4 queues,

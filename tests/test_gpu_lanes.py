@@ -53,7 +53,7 @@ def test_identity_commitments(vc, rows):
 
 
 def same_step1(vc, pp, got, ref):
-    for k in range((pp.K + ref.b - 1) // ref.b):
+    for k in range((pp.K + got.b - 1) // got.b):
         for w in ("fc_x", "fc_rounds", "fc_tail"):
             assert got.export(w, k) == ref.export(w, k), (w, k)
 
@@ -90,3 +90,24 @@ def test_blocks_in_turn(vc):
     cm = vc.vc_commit(pp, m, 256)
     proofs = vc.vc_proofs_serialize(vc.vc_open_all(pp, cm, b))
     assert vc.vc_verify_all(pp, cm.C, b, m, proofs, bytes(range(32))) == (1, pp.K)
+
+
+@pytest.mark.parametrize("L,b", [(12, 1), (14, 2), (14, 3)])
+def test_direct_rounds_at_the_lines(vc, L, b):
+    """Direct rounds at the lines where lanes take over from the engine (4096): (12, 1) has 4096 terms in round 1
+    and 2048 folds, (14, 2) 8192 terms, 4096 folds and, in round 2, 4096 terms; (14, 3) has 43 batches, 5504 and
+    2752 terms and 2752 folds, blocks that hold parts of two batches.  Every array of Step 1 as the oracle's."""
+    print("direct rounds L=%d b=%d" % (L, b), flush=True)
+    limbs = I.entries(1 << L, 200 + 10 * L + b, 256)
+    ocm = O.Commitment(O.Params(L, SEED), I.limbs_to_bytes(limbs))
+    oop = O.Opening(ocm, b)
+    print("  oracle done", flush=True)
+    pp = vc.vc_setup(L, SEED, 0)
+    cm = vc.vc_commit(pp, to_device(limbs), 256)
+    ex = vc.vc_exec_create(0, 6)
+    ex.set_ahead(0)
+    pr = vc.vc_open_all_ex(pp, cm, b, ex)
+    assert oop.nb == -(-pp.K // b)
+    same_step1(vc, pp, pr, oop)
+    for i in (0, pp.N - 1):
+        assert vc.vc_proof_get(pr, i) == oop.proof(i), i
